@@ -6,8 +6,8 @@
 // distinct neighbours chosen by Floyd's algorithm (Bentley & Floyd, 1987),
 // draw m from word m mod 4 of Philox(v, round, m / 4, PSI).  Products and sums
 // are FP64 (the FP32 entries are exact in FP64), so the decision Psi < mu is
-// taken in FP64.  One wave scores one node: the subset is drawn by lane 0
-// into LDS, then 64 lanes span the embedding dimension.
+// taken in FP64.  One wave scores one node: each lane draws one pick of the
+// subset, then 64 lanes span the embedding dimension.
 //
 // The next active set keeps the scored nodes with Psi < mu, in their order
 // (a sorted list stays sorted), by an order-preserving compaction.
@@ -16,18 +16,24 @@
 
 #include "common.h"
 #include "scan.h"
+#include "wave.h"
 
 namespace felog {
 
 constexpr int kWavesPerBlock = 4;
+constexpr int kNbrs = 4;   // neighbours scored at a time
 
-__device__ __forceinline__ double wave_sum_d(double x)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-    return x;
-}
-
+// One wave per scored node.  Lane s draws pick s of the subset (its own
+// Philox word; Floyd's test against the earlier picks is one ballot per pick)
+// and reads its neighbour's id, so the ids cost two loads for all neighbours
+// together.  Rows are then read kNbrs at a time, all in flight before the
+// first is used, and the 2 kNbrs sums (dot and squared norm of each) are
+// reduced together: each halving step of the butterfly also halves the number
+// of values, so eight sums take 36 vector instructions instead of 8 x 18, and
+// the lanes end with different neighbours' sums, whose square root and
+// division they evaluate at the same time.  Bound by the row reads: R-MAT 2^20
+// at d = 128, k_s = 10, every node scored, 1.94 -> 0.61 ms (one row at a time,
+// reduced by ds_bpermute, before), 3.6 GB of rows at 5.8 TB/s.
 template <int VPL>
 __global__ __launch_bounds__(256) void psi_kernel(
     const float* __restrict__ tin, const int64_t* __restrict__ indptr,
@@ -36,78 +42,90 @@ __global__ __launch_bounds__(256) void psi_kernel(
     uint8_t* keep /* nullable */)
 {
     constexpr int D = 64 * VPL;
-    __shared__ int32_t picks[kWavesPerBlock][64];
     const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    // block-uniform trip count, so the block barrier below is reached by all waves
-    for (int64_t base = (int64_t)blockIdx.x * kWavesPerBlock; base < count;
-         base += (int64_t)gridDim.x * kWavesPerBlock) {
-        const int64_t i = base + wv;
-        const bool live = i < count;
-        const int32_t v = live ? (nodes ? nodes[i] : (int32_t)i) : 0;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int64_t i = (int64_t)blockIdx.x * kWavesPerBlock + wv; i < count;
+         i += (int64_t)gridDim.x * kWavesPerBlock) {
+        const int32_t v = nodes ? nodes[i] : (int32_t)i;
         const int64_t lo = indptr[v];
-        const int64_t deg = live ? indptr[v + 1] - lo : 0;
-        int m = 0;
-        if (deg > 0) {
-            if (deg <= k_s) {
-                m = (int)deg;
-                if (lane < m) picks[wv][lane] = lane;
-            } else {
-                m = k_s;
-                if (lane == 0) {
-                    Rand4 r{};
-                    for (int s = 0; s < k_s; ++s) {
-                        const int64_t j = deg - k_s + s;   // Floyd: j runs over deg-k .. deg-1
-                        if ((s & 3) == 0)
-                            r = philox4x32((uint32_t)v, round, (uint32_t)(s >> 2), kTagPsi, seed);
-                        const uint32_t x = (s & 3) == 0 ? r.v[0] : (s & 3) == 1 ? r.v[1]
-                                           : (s & 3) == 2 ? r.v[2] : r.v[3];
-                        int32_t t = (int32_t)scale32(x, (uint32_t)(j + 1));   // uniform in [0, j]
-                        bool seen = false;
-                        for (int q = 0; q < s; ++q) seen |= picks[wv][q] == t;
-                        picks[wv][s] = seen ? (int32_t)j : t;
-                    }
-                }
+        const int64_t deg = indptr[v + 1] - lo;
+        if (deg == 0) {
+            if (lane == 0) {
+                psi[i] = __longlong_as_double(0x7FF8000000000000ll);   // NaN
+                if (keep) keep[i] = 0;
+            }
+            continue;
+        }
+        double a[VPL];
+#pragma unroll
+        for (int e = 0; e < VPL; ++e) a[e] = (double)tin[(int64_t)v * D + e * 64 + lane];
+        int32_t pick = lane;
+        const int m = deg <= k_s ? (int)deg : k_s;
+        if (deg > k_s) {
+            // Floyd: j runs over deg - k_s .. deg - 1, t uniform in [0, j]
+            const int32_t j = (int32_t)(deg - k_s) + lane;
+            const Rand4 r = philox4x32((uint32_t)v, round, (uint32_t)(lane >> 2), kTagPsi, seed);
+            const uint32_t x = (lane & 3) == 0 ? r.v[0] : (lane & 3) == 1 ? r.v[1]
+                               : (lane & 3) == 2 ? r.v[2] : r.v[3];
+            pick = (int32_t)scale32(x, (uint32_t)j + 1u);
+            for (int s = 1; s < k_s; ++s) {
+                const int32_t t = __builtin_amdgcn_readlane(pick, s);
+                const bool seen = __ballot(lane < s && pick == t) != 0;
+                if (seen && lane == s) pick = j;
             }
         }
-        __syncthreads();
-        if (live) {
-            if (deg == 0) {
-                if (lane == 0) {
-                    psi[i] = __longlong_as_double(0x7FF8000000000000ll);   // NaN
-                    if (keep) keep[i] = 0;
-                }
-            } else {
-                double a[VPL];
-                double na = 0.0;
+        const int32_t nbr = lane < m ? indices[lo + pick] : 0;
+        double na = 0.0;
+#pragma unroll
+        for (int e = 0; e < VPL; ++e) na = fma(a[e], a[e], na);
+        na = wave_total(na);
+        const double rna = sqrt(na);
+        double acc = 0.0;
+        for (int s0 = 0; s0 < m; s0 += kNbrs) {
+            float b[kNbrs][VPL];
+#pragma unroll
+            for (int q = 0; q < kNbrs; ++q) {
+                const int32_t u = __builtin_amdgcn_readlane(nbr, min(s0 + q, m - 1));
+#pragma unroll
+                for (int e = 0; e < VPL; ++e) b[q][e] = tin[(int64_t)u * D + e * 64 + lane];
+            }
+            // sums 0 .. 3: dots, 4 .. 7: squared norms
+            double x[2 * kNbrs];
+#pragma unroll
+            for (int q = 0; q < kNbrs; ++q) {
+                double dot = 0.0, nb = 0.0;
 #pragma unroll
                 for (int e = 0; e < VPL; ++e) {
-                    a[e] = (double)tin[(int64_t)v * D + e * 64 + lane];
-                    na += a[e] * a[e];
+                    const double y = (double)b[q][e];
+                    dot = fma(a[e], y, dot);
+                    nb = fma(y, y, nb);
                 }
-                na = wave_sum_d(na);
-                double acc = 0.0;
-                for (int s = 0; s < m; ++s) {
-                    const int32_t u = indices[lo + picks[wv][s]];
-                    double dot = 0.0, nb = 0.0;
-#pragma unroll
-                    for (int e = 0; e < VPL; ++e) {
-                        double b = (double)tin[(int64_t)u * D + e * 64 + lane];
-                        dot += a[e] * b;
-                        nb += b * b;
-                    }
-                    dot = wave_sum_d(dot);
-                    nb = wave_sum_d(nb);
-                    acc += (na == 0.0 || nb == 0.0) ? 0.0 : dot / (sqrt(na) * sqrt(nb));
-                }
-                const double p = acc / (double)m;
-                if (lane == 0) {
-                    psi[i] = p;
-                    if (keep) keep[i] = p < mu ? 1 : 0;
-                }
+                x[q] = dot;
+                x[kNbrs + q] = nb;
             }
+            // lane l ends with the sum of index 4 bit5 + 2 bit4 + bit3 of l
+#pragma unroll
+            for (int q = 0; q < 4; ++q) x[q] = pair_sums<32>(x[q], x[q + 4]);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) x[q] = pair_sums<16>(x[q], x[q + 2]);
+            double y = pair_sums<8>(x[0], x[1]);
+            y = xor_sum<4>(y);
+            y = xor_sum<2>(y);
+            y = xor_sum<1>(y);
+            // dots are in lanes 0 .. 31, the norms of the same neighbours 32 lanes up
+            const auto l = __builtin_amdgcn_permlane32_swap(lo32(y), lo32(y), false, false);
+            const auto h = __builtin_amdgcn_permlane32_swap(hi32(y), hi32(y), false, false);
+            const double dot = make_f64(l[0], h[0]), nb = make_f64(l[1], h[1]);
+            const double cosv = (na == 0.0 || nb == 0.0) ? 0.0 : dot / (rna * sqrt(nb));
+#pragma unroll
+            for (int q = 0; q < kNbrs; ++q)
+                if (s0 + q < m) acc += read_lane(cosv, 8 * q);
         }
-        __syncthreads();
+        const double p = acc / (double)m;
+        if (lane == 0) {
+            psi[i] = p;
+            if (keep) keep[i] = p < mu ? 1 : 0;
+        }
     }
 }
 
