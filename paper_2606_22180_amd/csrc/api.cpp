@@ -478,6 +478,28 @@ felog_status felog_walks_info(const felog_walks* w, int64_t* n_walks, int32_t* l
     });
 }
 
+// Device block a corpus is turned through when read, and the smallest read
+// (ints) and block (walks) for which that is used: below 16 KB the block's
+// allocation costs more than turning on the host, and blocks of few walks
+// would make many small copies.
+constexpr int64_t kTurnBytes = (int64_t)256 << 20;
+constexpr int64_t kTurnMinInts = 4096;
+constexpr int64_t kTurnMinWalks = 1024;
+
+// Allocates unless the card has no room (the budget is the caller's to check).
+static bool try_alloc(DevBuf& b, Ctx* c, size_t bytes)
+{
+    try {
+        b.alloc(c, bytes);
+        return true;
+    } catch (const Error& e) {
+        if (e.code != FELOG_ENOMEM) throw;
+        (void)hipGetLastError();
+        clear_error();
+        return false;
+    }
+}
+
 felog_status felog_walks_read_range(const felog_walks* w, int64_t first, int64_t count,
                                     int32_t* walks, int64_t cap)
 {
@@ -492,8 +514,26 @@ felog_status felog_walks_read_range(const felog_walks* w, int64_t first, int64_t
         FELOG_REQUIRE(cap >= total, "buffer holds %lld ints, need %lld", (long long)cap,
                       (long long)total);
         Ctx* c = w->g->ctx;
-        // Device layout is step-major [L][W]: one strided copy of the L rows'
-        // column range, then a transpose to walk-major on the host.
+        // Device layout is step-major [L][W]; walk-major is turned on the
+        // device, a block of walks at a time, and copied out as one run.
+        // Small reads, and contexts whose budget or card has no room for the
+        // block, turn on the host instead.
+        const int64_t row_bytes = sizeof(int32_t) * (int64_t)w->L;
+        int64_t room = kTurnBytes;
+        if (c->budget) room = std::min<int64_t>(room, (int64_t)(c->budget - std::min(c->budget, c->in_use)));
+        const int64_t block = std::min<int64_t>(count, room / row_bytes);
+        DevBuf rows;
+        if (total > kTurnMinInts && block >= std::min<int64_t>(count, kTurnMinWalks) &&
+            try_alloc(rows, c, (size_t)(block * row_bytes))) {
+            for (int64_t c0 = 0; c0 < count; c0 += block) {
+                const int64_t nc = std::min(block, count - c0);
+                launch_walk_rows(*w, first + c0, nc, rows.as<int32_t>(), c->stream);
+                FELOG_HIP(hipMemcpyAsync(walks + c0 * w->L, rows.ptr, (size_t)(nc * row_bytes),
+                                         hipMemcpyDeviceToHost, c->stream));
+            }
+            c->sync();
+            return;
+        }
         std::vector<int32_t> tmp(total);
         FELOG_HIP(hipMemcpy2DAsync(tmp.data(), sizeof(int32_t) * count,
                                    w->data.as<int32_t>() + first, sizeof(int32_t) * w->W,

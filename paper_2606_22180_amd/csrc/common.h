@@ -269,6 +269,8 @@ void launch_walks(Walks& w, const felog_walk_params& p, const Active* starts, in
 void launch_walk_columns(Walks& w, const felog_walk_params& p, const Active* starts,
                          int64_t n_starts, int64_t col0, int64_t ncols, hipStream_t s,
                          unsigned long long* d_capped);
+// columns [col0, col0 + ncols) as walk-major rows of L ints in device memory
+void launch_walk_rows(const Walks& w, int64_t col0, int64_t ncols, int32_t* rows, hipStream_t s);
 void launch_valid_columns(Walks& w, int64_t chunk);
 // the same columns and counts from the start list, before the walks exist
 void plan_valid_columns(Walks& w, const Active* starts, int64_t n_starts, int64_t chunk);

@@ -349,6 +349,42 @@ void launch_walks(Walks& w, const felog_walk_params& p, const Active* starts, in
 }
 
 // --------------------------------------------------------------------------
+// Columns [col0, col0 + ncols) of a step-major corpus as walk-major rows of L.
+// A block turns a tile of 64 walks by 64 steps through LDS, so that both the
+// reads (64 walks of a step) and the writes (64 steps of a walk) are runs of
+// 256 bytes; rows of 65 words keep the column reads off each other's banks.
+// It costs microseconds beside the copy to the host that follows; turning the
+// rows on the host instead took 40 ms for 300,007 walks of 80 (generated and
+// read: 54.4 -> 15.5 ms).
+// --------------------------------------------------------------------------
+constexpr int kTurn = 64;
+
+__global__ __launch_bounds__(256) void walk_rows_kernel(const int32_t* __restrict__ walks,
+                                                        int64_t W, int32_t L, int64_t col0,
+                                                        int64_t ncols, int32_t* __restrict__ rows)
+{
+    __shared__ int32_t tile[kTurn][kTurn + 1];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t c0 = (int64_t)blockIdx.x * kTurn;
+    const int32_t t0 = (int32_t)blockIdx.y * kTurn;
+    for (int t = wv; t < kTurn; t += 4)
+        if (t0 + t < L && c0 + lane < ncols)
+            tile[t][lane] = walks[(int64_t)(t0 + t) * W + col0 + c0 + lane];
+    __syncthreads();
+    for (int c = wv; c < kTurn; c += 4)
+        if (c0 + c < ncols && t0 + lane < L)
+            rows[(c0 + c) * L + t0 + lane] = tile[lane][c];
+}
+
+void launch_walk_rows(const Walks& w, int64_t col0, int64_t ncols, int32_t* rows, hipStream_t s)
+{
+    const dim3 grid((uint32_t)((ncols + kTurn - 1) / kTurn), (uint32_t)((w.L + kTurn - 1) / kTurn));
+    hipLaunchKernelGGL(walk_rows_kernel, grid, dim3(256), 0, s, w.data.as<int32_t>(), w.W, w.L,
+                       col0, ncols, rows);
+    FELOG_HIP(hipGetLastError());
+}
+
+// --------------------------------------------------------------------------
 // Columns whose walk yields pairs (two or more nodes), and their count per
 // chunk of `chunk` consecutive walks.
 // --------------------------------------------------------------------------
