@@ -8,11 +8,11 @@
 //
 //   plan    one workgroup per minibatch, many minibatches per launch.  It
 //           draws the minibatch's node ids (walk reads, noise draws), sorts
-//           its touches by (table, row, touch) with a bitonic network in LDS
-//           and lists the rows' segments.  Sorting by touch index within a
-//           row is pair order (pair, then slot), so no atomics and no
-//           per-row counters are needed.  Plans depend only on the walks and
-//           the noise table, never on the embeddings.
+//           its touches by (table, row) with a stable radix sort in LDS and
+//           lists the rows' segments.  Touches of a row keep touch order,
+//           which is pair order (pair, then slot), so no global atomics and
+//           no per-row counters are needed.  Plans depend only on the walks
+//           and the noise table, never on the embeddings.
 //   update  one persistent cooperative launch for those minibatches.  Per
 //           minibatch: the forward (gathers, FP64 dots, sigma, coefficients;
 //           each out-touch's coefficient at its sorted position; the context
@@ -59,8 +59,8 @@ struct MbDesc {
 };
 static_assert(sizeof(MbDesc) == 32, "descriptor layout shared by host and device");
 
-constexpr int kPlanThreads = 512;
-constexpr int kPlanMaxTouches = kSmallMaxTouches;   // touches a plan sorts in LDS (64 KB of keys)
+constexpr int kPlanThreads = 1024;
+constexpr int kPlanMaxTouches = kSmallMaxTouches;   // touches a plan sorts in LDS
 constexpr int32_t kPosMask = (1 << 30) - 1;
 constexpr int32_t kSingleBit = 1 << 30;  // row touched once in the minibatch: the forward updates it
 constexpr uint32_t kSpinLimit = 1u << 22;  // polls before a barrier wait gives up (seconds)
@@ -78,6 +78,7 @@ struct PlanArgs {
     int32_t window;
     uint64_t seed;
     NoiseTable noise;
+    int32_t row_bits;              // n < 2^row_bits, at most 31
     const MbDesc* desc;            // [minibatches of the launch]
     int32_t tmax;                  // touch slots per minibatch, P (K + 2)
     int2* tinfo;                   // [mb][tmax]: (row, sorted position | kSingleBit), -1 skipped
@@ -96,33 +97,92 @@ struct PlanBatch {
     int32_t njobs;
 };
 
-// Exclusive scan of one value per thread over the workgroup; *total gets the sum.
-__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* tmp, uint32_t* total)
+constexpr int kPlanWaves = kPlanThreads / 64;
+constexpr int kPlanRounds = kPlanMaxTouches / kPlanThreads;   // most touches per thread
+constexpr int kPlanBins = 256;                                // 8 key bits per sorting pass
+
+// Sorts the workgroup's touches by the low `bits` of key, stably: pass by
+// pass over 8 bits, every touch's new position is the number of touches
+// before it in (digit, position) order.  Wave w holds positions
+// [w R 64, (w + 1) R 64), one per lane and round, so counting a wave's rounds
+// in turn keeps their order: a round finds each lane's peers of equal digit
+// with eight ballots, and its first peer adds their number to the wave's bin.
+// A bitonic network over the same 8,192 touches took 91 dependent passes
+// through LDS (196 us of a one-minibatch plan).
+__device__ __forceinline__ void sort_touches(uint32_t (&key)[kPlanRounds],
+                                             uint32_t (&touch)[kPlanRounds], int R, int bits,
+                                             uint32_t* skey, uint16_t* stouch,
+                                             uint16_t (*bins)[kPlanBins], uint32_t* wave_sum)
 {
-    constexpr int NW = kPlanThreads / 64;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    uint32_t x = v;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned long long lt = (1ull << lane) - 1ull;
+    for (int shift = 0; shift < bits; shift += 8) {
+        for (int b = lane; b < kPlanBins; b += 64) bins[w][b] = 0;
+        uint32_t rank[kPlanRounds];   // touches of the same digit before this one in the wave
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t y = __shfl_up(x, off);
-        if (lane >= off) x += y;
-    }
-    if (lane == 63) tmp[w] = x;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t run = 0;
-        for (int i = 0; i < NW; ++i) {
-            const uint32_t c = tmp[i];
-            tmp[i] = run;
-            run += c;
+        for (int r = 0; r < kPlanRounds; ++r) {
+            rank[r] = 0;
+            if (r < R) {
+                const uint32_t d = (key[r] >> shift) & (kPlanBins - 1);
+                unsigned long long peers = ~0ull;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const bool set = (d >> i) & 1u;
+                    const unsigned long long m = __ballot(set);
+                    peers &= set ? m : ~m;
+                }
+                const uint32_t before = bins[w][d];
+                const uint32_t mine = (uint32_t)__popcll(peers & lt);
+                rank[r] = before + mine;
+                __builtin_amdgcn_wave_barrier();
+                if (mine == 0) bins[w][d] = (uint16_t)(before + (uint32_t)__popcll(peers));
+                __builtin_amdgcn_wave_barrier();
+            }
         }
-        tmp[NW] = run;
+        __syncthreads();
+        // thread b < 256: bin b's touches over the waves, then an exclusive scan over the bins
+        uint32_t total = 0;
+        if (threadIdx.x < kPlanBins) {
+#pragma unroll
+            for (int i = 0; i < kPlanWaves; ++i) {
+                const uint32_t c = bins[i][threadIdx.x];
+                bins[i][threadIdx.x] = (uint16_t)total;
+                total += c;
+            }
+        }
+        uint32_t incl = total;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t y = __shfl_up(incl, off);
+            if (lane >= off) incl += y;
+        }
+        if (threadIdx.x < kPlanBins && lane == 63) wave_sum[w] = incl;
+        __syncthreads();
+        if (threadIdx.x < kPlanBins) {
+            uint32_t base = incl - total;
+            for (int i = 0; i < w; ++i) base += wave_sum[i];
+#pragma unroll
+            for (int i = 0; i < kPlanWaves; ++i)
+                bins[i][threadIdx.x] = (uint16_t)(bins[i][threadIdx.x] + base);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kPlanRounds; ++r)
+            if (r < R) {
+                const uint32_t at = bins[w][(key[r] >> shift) & (kPlanBins - 1)] + rank[r];
+                skey[at] = key[r];
+                stouch[at] = (uint16_t)touch[r];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kPlanRounds; ++r)
+            if (r < R) {
+                const int at = (w * R + r) * 64 + lane;
+                key[r] = skey[at];
+                touch[r] = stouch[at];
+            }
     }
-    __syncthreads();
-    const uint32_t excl = tmp[w] + x - v;
-    *total = tmp[NW];
-    __syncthreads();
-    return excl;
 }
 
 template <int K>
@@ -133,29 +193,30 @@ __global__ __launch_bounds__(kPlanThreads) void sgns_plan_kernel(PlanBatch pb)
     while (jb + 1 < pb.njobs && (int32_t)blockIdx.x >= pb.start[jb + 1]) ++jb;
     const PlanArgs& a = pb.job[jb];
     const uint32_t lb = blockIdx.x - (uint32_t)pb.start[jb];   // minibatch within the job's group
-    __shared__ unsigned long long keys[kPlanMaxTouches];
-    // segment starts (step 3); before that, the pairs' centres (step 1)
-    __shared__ __align__(16) uint16_t seg_first[kPlanMaxTouches + 1];
-    __shared__ uint32_t tmp[kPlanThreads / 64 + 1];
-    __shared__ uint32_t counts[3];     // in rows, out rows touched once, applied in segments
+    __shared__ uint32_t skey[kPlanMaxTouches + 1];
+    __shared__ uint16_t stouch[kPlanMaxTouches];
+    __shared__ uint16_t bins[kPlanWaves][kPlanBins];
+    __shared__ uint16_t seg_lo[kPlanMaxTouches / 2], seg_hi[kPlanMaxTouches / 2];
+    __shared__ uint32_t wave_sum[kPlanWaves], wave_end[kPlanWaves];
+    __shared__ uint32_t counts[4];   // segments, in rows, out rows touched once, applied in segments
     const MbDesc d = a.desc[lb];
-    const uint32_t nt = d.npairs * T;
-    uint32_t N = 64;
-    while (N < nt) N <<= 1;                 // nt <= kPlanMaxTouches (checked on the host)
+    const uint32_t nt = d.npairs * T;       // nt <= kPlanMaxTouches (checked on the host)
+    const int R = (int)((nt + kPlanThreads - 1) / kPlanThreads);
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int2* tinfo = a.tinfo + (int64_t)lb * a.tmax;
     int4* segs = a.segs + (int64_t)lb * a.tmax;
     int32_t* spair = a.spair + (int64_t)lb * a.tmax;
     const int32_t* vcols = a.vcols + d.vcol_base;
-    if (threadIdx.x < 3) counts[threadIdx.x] = 0;
+    const uint32_t none = (2u << a.row_bits) - 1u;   // above every real key
+    if (threadIdx.x < 4) counts[threadIdx.x] = 0;
 
-    // 1. each touch's row and sort key (table << 62 | row << 16 | touch).  A
-    //    pair's walk reads are made once: its context and centre first (one
-    //    thread per pair), then the negatives (one thread per negative),
-    //    which read the centre from LDS; every thread's loads are independent
-    //    of its earlier items', so they overlap.
-    for (uint32_t t = threadIdx.x; t < N; t += kPlanThreads) keys[t] = ~0ull;
-    __syncthreads();
-    int32_t* ctr_of = reinterpret_cast<int32_t*>(seg_first);   // [P] centres, until step 3
+    // 1. each touch's key, table << row_bits | row.  One thread per pair: its
+    //    walk reads and its negatives' guide entries are in flight together
+    //    (negative k of a pair: Philox(walk id, (j << 8) | slot, NEG | k / 2),
+    //    words 2 (k mod 2) and 2 (k mod 2) + 1), then the cumulative weights.
+    for (uint32_t t = nt + threadIdx.x; t < (uint32_t)R * kPlanThreads; t += kPlanThreads)
+        skey[t] = none;
     for (uint32_t p = threadIdx.x; p < d.npairs; p += kPlanThreads) {
         const uint32_t gq = d.first_pair + p;
         const uint32_t sidx = gq / d.Wv;
@@ -166,112 +227,129 @@ __global__ __launch_bounds__(kPlanThreads) void sgns_plan_kernel(PlanBatch pb)
         const int32_t off = s < a.window ? s - a.window : s - a.window + 1;
         const int32_t ctr = a.walks[(int64_t)j * a.W + col];
         const int32_t ctx = a.walks[(int64_t)(j + off) * a.W + col];
-        ctr_of[p] = ctr;
-        keys[p * T] = ((unsigned long long)ctx << 16) | (p * T);
-        keys[p * T + 1] = (1ull << 62) | ((unsigned long long)ctr << 16) | (p * T + 1);
-    }
-    __syncthreads();
-    for (uint32_t e = threadIdx.x; e < d.npairs * K; e += kPlanThreads) {
-        // negative k of pair p: Philox(walk id, (j << 8) | slot, NEG | k / 2), words
-        // 2 (k mod 2) and 2 (k mod 2) + 1
-        const uint32_t p = e / K, k = e - p * K;
-        const uint32_t gq = d.first_pair + p;
-        const uint32_t sidx = gq / d.Wv;
-        const uint32_t rank = gq - sidx * d.Wv;
-        const int32_t js = a.slices[sidx];
-        const int64_t wid = a.id_base + vcols[rank];
-        const Rand4 x = philox4x32((uint32_t)wid, (uint32_t)(wid >> 32), (uint32_t)js,
-                                   kTagNeg | (k >> 1), a.seed);
-        const uint32_t lo = (k & 1) ? x.v[2] : x.v[0];
-        const uint32_t hi = (k & 1) ? x.v[3] : x.v[1];
-        const int32_t neg = noise_draw(a.noise, ((uint64_t)hi << 32) | lo);
-        const uint32_t t = p * T + 2 + k;
-        if (neg != ctr_of[p])
-            keys[t] = (1ull << 62) | ((unsigned long long)neg << 16) | t;
-        else
-            tinfo[t] = make_int2(-1, -1);   // a negative equal to the centre is skipped
-    }
-    __syncthreads();
-
-    // 2. bitonic sort, ascending
-    for (uint32_t k = 2; k <= N; k <<= 1)
-        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-            for (uint32_t i = threadIdx.x; i < N; i += kPlanThreads) {
-                const uint32_t l = i ^ j;
-                if (l > i) {
-                    const unsigned long long x = keys[i], y = keys[l];
-                    if ((x > y) == ((i & k) == 0)) {
-                        keys[i] = y;
-                        keys[l] = x;
-                    }
-                }
+        const int64_t wid = a.id_base + col;
+        uint64_t u[K];
+        int32_t neg[K];
+        Rand4 x{};
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if ((k & 1) == 0)
+                x = philox4x32((uint32_t)wid, (uint32_t)(wid >> 32), (uint32_t)js,
+                               kTagNeg | (uint32_t)(k >> 1), a.seed);
+            u[k] = ((uint64_t)((k & 1) ? x.v[3] : x.v[1]) << 32) | ((k & 1) ? x.v[2] : x.v[0]);
+            neg[k] = a.noise.guide[u[k] >> (64 - a.noise.bits)];
+            u[k] = __umul64hi(u[k], a.noise.total);
+        }
+        uint64_t c[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) c[k] = a.noise.cdf[neg[k] + 1];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (c[k] <= u[k]) {
+                ++neg[k];
+                while (a.noise.cdf[neg[k] + 1] <= u[k]) ++neg[k];
             }
-            __syncthreads();
         }
-
-    // 3. segments: a position starts one where (table, row) changes; each
-    //    thread takes a contiguous run of positions
-    const uint32_t per = (N + kPlanThreads - 1) / kPlanThreads;
-    const uint32_t lo = min(N, threadIdx.x * per), hi = min(N, lo + per);
-    uint32_t nstart = 0, nvalid = 0;
-    for (uint32_t i = lo; i < hi; ++i) {
-        const unsigned long long x = keys[i];
-        if (x == ~0ull) continue;
-        ++nvalid;
-        if (i == 0 || (keys[i - 1] >> 16) != (x >> 16)) ++nstart;
-    }
-    uint32_t nseg, nv;
-    uint32_t s = block_scan(nstart, tmp, &nseg);
-    block_scan(nvalid, tmp, &nv);
-    for (uint32_t i = lo; i < hi; ++i) {
-        const unsigned long long x = keys[i];
-        if (x != ~0ull && (i == 0 || (keys[i - 1] >> 16) != (x >> 16))) seg_first[s++] = (uint16_t)i;
-    }
-    if (threadIdx.x == 0) seg_first[nseg] = (uint16_t)nv;
-    __syncthreads();
-
-    // 4. per segment: length; segments of two or more touches go to the
-    //    apply list (in segments first: they sort first), rows touched once
-    //    are updated by the forward; every touch's sorted position
-    const uint32_t sper = (nseg + kPlanThreads - 1) / kPlanThreads;
-    const uint32_t s_lo = min(nseg, threadIdx.x * sper), s_hi = min(nseg, s_lo + sper);
-    uint32_t napply = 0, nin = 0, nin_apply = 0, nsingle = 0;
-    for (uint32_t q = s_lo; q < s_hi; ++q) {
-        const uint32_t f = seg_first[q], len = seg_first[q + 1] - f;
-        const bool out = (keys[f] >> 62) != 0;
-        napply += len > 1 ? 1u : 0u;
-        nin += out ? 0u : 1u;
-        nin_apply += (!out && len > 1) ? 1u : 0u;
-        nsingle += (out && len == 1) ? 1u : 0u;
-    }
-    uint32_t n_apply;
-    uint32_t slot = block_scan(napply, tmp, &n_apply);
-    atomicAdd(&counts[0], nin);
-    atomicAdd(&counts[1], nsingle);
-    atomicAdd(&counts[2], nin_apply);
-    for (uint32_t q = s_lo; q < s_hi; ++q) {
-        const uint32_t f = seg_first[q], len = seg_first[q + 1] - f;
-        const unsigned long long x = keys[f];
-        const int32_t out = (int32_t)(x >> 62);
-        const int32_t row = (int32_t)((x >> 16) & 0x7FFFFFFFull);
-        const bool single = len == 1;
-        if (!single) segs[slot++] = make_int4(row, (int32_t)f, (int32_t)len, out);
-        for (uint32_t i = f; i < f + len; ++i) {
-            const uint32_t t = (uint32_t)(keys[i] & 0xFFFF);
-            tinfo[t] = make_int2(row, (int32_t)i | (single ? kSingleBit : 0));
-            spair[i] = (int32_t)(t / T);
+        skey[p * T] = (uint32_t)ctx;
+        skey[p * T + 1] = (1u << a.row_bits) | (uint32_t)ctr;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const bool skip = neg[k] == ctr;   // a negative equal to the centre is skipped
+            skey[p * T + 2 + k] = skip ? none : (1u << a.row_bits) | (uint32_t)neg[k];
+            if (skip) tinfo[p * T + 2 + k] = make_int2(-1, -1);
         }
     }
     __syncthreads();
+
+    // 2. sort by (table, row), touches of a row in touch (pair, then slot) order
+    uint32_t key[kPlanRounds], touch[kPlanRounds];
+#pragma unroll
+    for (int r = 0; r < kPlanRounds; ++r) {
+        key[r] = none;
+        touch[r] = 0;
+        if (r < R) {
+            touch[r] = (uint32_t)((w * R + r) * 64 + lane);
+            key[r] = skey[touch[r]];
+        }
+    }
+    __syncthreads();
+    sort_touches(key, touch, R, a.row_bits + 1, skey, stouch, bins, wave_sum);
+
+    // 3. a position is its row's first or last where its neighbour's key
+    //    differs.  Rows touched once are updated by the forward; the k-th
+    //    first and the k-th last position of the others bound segment k.
+    //    In-table rows sort first.
+    if (threadIdx.x == 0) skey[(uint32_t)R * kPlanThreads] = none;
+    __syncthreads();
+    const unsigned long long lt = (1ull << lane) - 1ull;
+    uint32_t nfirst = 0, nlast = 0, c_seg = 0, c_in = 0, c_single = 0, c_inap = 0;
+    uint32_t bits_first = 0, bits_last = 0;   // per round: this lane starts / ends a segment
+#pragma unroll
+    for (int r = 0; r < kPlanRounds; ++r)
+        if (r < R) {
+            const int i = (w * R + r) * 64 + lane;
+            const bool real = key[r] != none;
+            const bool first = real && (i == 0 || skey[i - 1] != key[r]);
+            const bool last = real && skey[i + 1] != key[r];
+            const bool out = (key[r] >> a.row_bits) != 0;
+            if (real) {
+                const uint32_t t = touch[r];
+                const int32_t row = (int32_t)(key[r] & ((1u << a.row_bits) - 1u));
+                tinfo[t] = make_int2(row, i | (first && last ? kSingleBit : 0));
+                spair[i] = (int32_t)(t / T);
+            }
+            c_seg += first ? 1u : 0u;
+            c_in += first && !out ? 1u : 0u;
+            c_single += first && last && out ? 1u : 0u;
+            c_inap += first && !last && !out ? 1u : 0u;
+            const bool f = first && !last, l = last && !first;
+            bits_first |= (f ? 1u : 0u) << r;
+            bits_last |= (l ? 1u : 0u) << r;
+            nfirst += (uint32_t)__popcll(__ballot(f));
+            nlast += (uint32_t)__popcll(__ballot(l));
+        }
+    if (c_seg) atomicAdd(&counts[0], c_seg);
+    if (c_in) atomicAdd(&counts[1], c_in);
+    if (c_single) atomicAdd(&counts[2], c_single);
+    if (c_inap) atomicAdd(&counts[3], c_inap);
+    if (lane == 0) {
+        wave_sum[w] = nfirst;
+        wave_end[w] = nlast;
+    }
+    __syncthreads();
+    uint32_t at_first = 0, at_last = 0, n_apply = 0;
+#pragma unroll
+    for (int i = 0; i < kPlanWaves; ++i) {
+        at_first += i < w ? wave_sum[i] : 0u;
+        at_last += i < w ? wave_end[i] : 0u;
+        n_apply += wave_sum[i];
+    }
+#pragma unroll
+    for (int r = 0; r < kPlanRounds; ++r)
+        if (r < R) {
+            const uint16_t i = (uint16_t)((w * R + r) * 64 + lane);
+            const bool f = (bits_first >> r) & 1u, l = (bits_last >> r) & 1u;
+            const unsigned long long mf = __ballot(f), ml = __ballot(l);
+            if (f) seg_lo[at_first + (uint32_t)__popcll(mf & lt)] = i;
+            if (l) seg_hi[at_last + (uint32_t)__popcll(ml & lt)] = i;
+            at_first += (uint32_t)__popcll(mf);
+            at_last += (uint32_t)__popcll(ml);
+        }
+    __syncthreads();
+    for (uint32_t q = threadIdx.x; q < n_apply; q += kPlanThreads) {
+        const uint32_t f = seg_lo[q], x = skey[f];
+        segs[q] = make_int4((int32_t)(x & ((1u << a.row_bits) - 1u)), (int32_t)f,
+                            (int32_t)(seg_hi[q] - f + 1u), (int32_t)(x >> a.row_bits));
+    }
     if (threadIdx.x == 0) {
         uint32_t* m = a.meta + (int64_t)lb * 4;
         m[0] = n_apply;
-        m[1] = counts[2];
-        m[2] = nseg - counts[0];
-        m[3] = counts[1];
-        atomicAdd(&a.row_totals[0], (unsigned long long)counts[0]);
-        atomicAdd(&a.row_totals[1], (unsigned long long)(nseg - counts[0]));
-        atomicAdd(&a.row_totals[2], (unsigned long long)counts[1]);
+        m[1] = counts[3];
+        m[2] = counts[0] - counts[1];
+        m[3] = counts[2];
+        atomicAdd(&a.row_totals[0], (unsigned long long)counts[1]);
+        atomicAdd(&a.row_totals[1], (unsigned long long)(counts[0] - counts[1]));
+        atomicAdd(&a.row_totals[2], (unsigned long long)counts[2]);
     }
 }
 
@@ -757,6 +835,8 @@ static PlanArgs plan_args(Model& m, Walks& w, const felog_train_params& p,
     pa.seed = p.seed;
     pa.noise = NoiseTable{m.cdf.as<uint64_t>(), m.guide.as<int32_t>(), m.total_weight,
                           m.guide_bits};
+    pa.row_bits = 1;
+    while (((int64_t)1 << pa.row_bits) <= m.g->n) ++pa.row_bits;
     pa.tmax = tmax;
     pa.tinfo = m.sm_tinfo.as<int2>();
     pa.segs = m.sm_segs.as<int4>();

@@ -77,3 +77,47 @@ def test_read_walks_within_a_budget(fl, orc):
         W2 = fl.Walks.generate(G2, r=1, L=L, seed=3)
         assert np.array_equal(W2.read(), orc.walks_uniform(g, np.arange(n), 1, L, 3))
         assert c.bytes_in_use() == held
+
+
+def _two_paths(fl, g, *, dim, K, P, first, count, r=2, L=12, window=3):
+    """Tables and counts of the same minibatches on both update paths."""
+    out = []
+    for path in (0, 1):
+        c = fl.Context(0)
+        c.set_sgns_path(path)
+        G = fl.Graph.from_csr(c, g.indptr, g.indices)
+        W = fl.Walks.generate(G, r=r, L=L, seed=4)
+        M = fl.Model.create(G, dim=dim, seed=6)
+        rng = np.random.default_rng(7)
+        for which in (fl.TABLE_IN, fl.TABLE_OUT):
+            M.write(which, rng.normal(0, 0.2, (g.n, dim)).astype(np.float32))
+        st = M.train_steps(W, fl.train_params(window=window, negatives=K, minibatch_pairs=P,
+                                              seed=9), first, count)
+        assert st.path == 1 - path
+        out.append((M.read(fl.TABLE_IN), M.read(fl.TABLE_OUT), st.loss, st.pairs, st.rows_in,
+                    st.rows_out, st.rows_out_single))
+    return out
+
+
+# touches around a round of the plan's sort (1,024) and at its largest (8,192);
+# node counts around a power of two, the largest row keys of a digit and below
+@pytest.mark.parametrize("P,K,n", [(1, 1, 3), (341, 1, 255), (342, 1, 256), (146, 5, 257),
+                                   (147, 5, 1000), (1024, 6, 1023), (1170, 5, 1024),
+                                   (2730, 1, 65535), (372, 20, 65536), (1024, 6, 65537)])
+def test_plan_sizes(fl, orc, P, K, n):
+    rng = np.random.default_rng(n)
+    e = np.stack([rng.integers(0, n, 4 * n), rng.integers(0, n, 4 * n)], 1)
+    e = np.concatenate([np.sort(e[e[:, 0] != e[:, 1]], 1), [[0, n - 1]]])
+    g = synth.csr_from_edges(n, np.unique(e, axis=0))
+    a, b = _two_paths(fl, g, dim=128, K=K, P=P, first=3 if n > 100 else 0, count=3)
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+    assert a[3:] == b[3:] and abs(a[2] - b[2]) <= 1e-12 * abs(b[2])
+
+
+def test_plan_one_hub(fl):
+    """Every context or centre is one node: segments of hundreds of touches,
+    and negatives that are skipped as often as drawn."""
+    n = 64
+    g = synth.csr_from_edges(n, np.array([(0, i) for i in range(1, n)], np.int64))
+    a, b = _two_paths(fl, g, dim=64, K=5, P=1024, first=0, count=2, r=20)
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]) and a[3:] == b[3:]
