@@ -22,7 +22,7 @@
 //            touches and one per kChunk touches of the rows with more.  No
 //            atomics: same-address device atomics serialise at about one per
 //            12 ns on this part.
-//   forward  one group of 16 lanes (d = 64) or 32 (d >= 128) per pair: gather
+//   forward  one wave per pair, two pairs at d = 64 (sgns_forward.h): gather
 //            in[ctx], out[ctr], out[neg_1..K]; K+1 dots, sigma and the
 //            coefficients g in FP64 over the FP32 entries; writes (g_k, ctx)
 //            and the touch's pair-order key at the out-row's segment
@@ -43,14 +43,15 @@
 // delta) is bounded by lr 2^15 in magnitude and rounded once to a multiple
 // of 2^(e - 35), e = floor(log2 lr); in FP64, sums of such multiples below
 // lr 2^17 carry no rounding error in any order.
-// Lanes own elements 4 (gl + 16 i) .. +3 of a row, so each row access is a
-// coalesced 256-byte transaction per i.
+// In the apply, lanes own elements 4 (gl + 16 i) .. +3 of a row, so each row
+// access is a coalesced 256-byte transaction per i.
 #include <algorithm>
 #include <cmath>
 
 #include "common.h"
 #include "noise.h"
 #include "sgns_device.h"
+#include "sgns_forward.h"
 
 namespace felog {
 
@@ -388,19 +389,23 @@ struct FwdArgs {
     float* cap_out;          // capture != NULL: single-touch out-row deltas to cap_out[slot][d]
 };
 
-// One pair per group of LPP lanes, 64 / LPP pairs at a time.  With FP64
-// dots and coefficients the kernel needs 164 registers at d = 128, K = 5
-// (three waves per SIMD).
-template <int D, int K>
+// A wave takes its ppw pairs one step (sgns_forward.h) at a time.  CAP: the
+// deltas of the out rows touched once are captured, not applied.  Bound by the
+// random row reads and the rows, deltas and entries written: 65,536 pairs on
+// R-MAT 2^20 (d = 128, K = 5) 87 -> 62 us, about 330 MB at 5.3 TB/s.  Before, a
+// half wave per pair needed 164 registers (three waves per SIMD) and each dot
+// five ds_bpermute steps.  One step holds 74 registers (six waves); two steps
+// per batch share more arithmetic and were no faster (62 - 65 us).
+template <int D, int K, bool CAP>
 __global__ __launch_bounds__(256) void sgns_forward_kernel(FwdArgs a)
 {
-    constexpr int LPP = fwd_lanes_per_pair<D, K>();   // lanes per pair
-    constexpr int G = 64 / LPP;               // pairs in flight per wave
-    constexpr int V4 = D / (4 * LPP);         // float4s per lane and row
-    constexpr int T = K + 2;                  // touches per pair
+    constexpr int S = 1;
+    using Batch = FwdBatch<D, K, S, kStream>;
+    constexpr int T = K + 2, H = Batch::H, L = Batch::L, V = Batch::V;
     const int lane = threadIdx.x & 63;
-    const int grp = lane / LPP, gl = lane % LPP;
-    const uint32_t gwave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    const uint32_t gl = lane & (L - 1);
+    const uint32_t gwave = blockIdx.x * (blockDim.x >> 6) +
+                           (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t q0 = gwave * (uint32_t)a.ppw;
     if (q0 >= a.npairs) return;
     const int np = (int)min((uint32_t)a.ppw, a.npairs - q0);
@@ -409,7 +414,7 @@ __global__ __launch_bounds__(256) void sgns_forward_kernel(FwdArgs a)
     //      its position in its row's segment, or, for an out row touched once
     //      in the minibatch, the row's list slot (and a bit in `single`)
     int32_t m_row = -1;
-    uint32_t m_pos = 0;
+    int32_t m_pos = 0;
     bool m_single = false;
     if (lane < np * T) {
         const uint32_t t = q0 * T + lane;
@@ -419,103 +424,63 @@ __global__ __launch_bounds__(256) void sgns_forward_kernel(FwdArgs a)
         if (m_row >= 0) {
             const int32_t off = (in ? a.off_in : a.off_out)[m_row];
             m_single = off < 0;
-            m_pos = m_single ? (uint32_t)(-1 - off) : (uint32_t)off + rk;
+            m_pos = m_single ? -1 - off : off + (int32_t)rk;
         }
     }
     const unsigned long long single = __ballot(m_single);
 
+    const double lr = (double)a.lr;
     double lacc = 0.0;
-    for (int base = 0; base < np; base += G) {
-        const int p = base + grp;
-        const bool live = p < np;
-        const uint32_t q = q0 + (uint32_t)p;   // pair index within the minibatch
-        const int src = (live ? p : 0) * T;
-        const int32_t ctx = __shfl(m_row, src);
-        const uint32_t pos_in = __shfl(m_pos, src);
-        int32_t t[K + 1];
-#pragma unroll
-        for (int k = 0; k <= K; ++k) t[k] = __shfl(m_row, src + 1 + k);
-        // out position of touch k = gl (and, with 16 lanes, k = gl + 16)
-        const uint32_t my_pos = __shfl(m_pos, src + 1 + (gl <= K ? gl : 0));
-        uint32_t my_pos_hi = 0;
-        if (LPP == 16 && K >= 16) my_pos_hi = __shfl(m_pos, src + 1 + (gl + 16 <= K ? gl + 16 : 0));
-
-        float4 vin[V4];
-        float4 vo[K + 1][V4];
-        const float4* ri = row4<D>(a.tin, live ? ctx : 0);
-#pragma unroll
-        for (int i = 0; i < V4; ++i) vin[i] = ri[i * LPP + gl];
-#pragma unroll
-        for (int k = 0; k <= K; ++k) {
-            const bool ok = live && t[k] >= 0;
-            const float4* ro = row4<D>(a.tout, ok ? t[k] : 0);
-#pragma unroll
-            for (int i = 0; i < V4; ++i)
-                vo[k][i] = ok ? ro[i * LPP + gl] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int base = 0; base < np; base += S * H) {
+        Batch bt;
+        bt.load(a.tin, a.tout, m_row, base, np);
+        bt.coefficients(m_row, base, np, lr, lacc);
+        // the lane that evaluated a touch writes its entry
+        {
+            const int32_t pos = __shfl(m_pos, bt.touch);
+            const int pr = bt.touch / T;
+            const int32_t ctx = __shfl(m_row, pr * T);
+            if (bt.mine && !((single >> bt.touch) & 1ull))
+                store_nt(&a.ent_out[pos],
+                         pack_entry(bt.g, ctx, (q0 + (uint32_t)pr) * (K + 1) +
+                                                   (uint32_t)(bt.touch - pr * T - 1)));
         }
-        // dots, sigma and coefficients in FP64 over the FP32 entries; lane
-        // k mod LPP of the group takes touch k's loss term, -log sigma(s0) for
-        // the centre and -log sigma(-s_k) for a negative
-        const double lr = (double)a.lr;
-        double g[K + 1];
-        coefficients<K, LPP, V4>(vin, vo, t, lr, live, gl, grp, g, lacc);
-
-        // lane j of the group writes the entry of touch k = j (and j + 16)
 #pragma unroll
-        for (int h = 0; h < (K + LPP) / LPP; ++h) {
-            const int k = gl + h * LPP;
-            double gk = g[0];
-            int32_t tk = t[0];
+        for (int b = 0; b < S; ++b) {
+            const int p = base + b * H + (H == 2 ? lane >> 5 : 0);
+            const bool live = p < np;
+            const int src = (live ? p : 0) * T;
+            double gk[K + 1];
 #pragma unroll
-            for (int j = 1; j <= K; ++j)
-                if (k == j) {
-                    gk = g[j];
-                    tk = t[j];
-                }
-            if (k <= K && live && tk >= 0 && !((single >> (src + 1 + k)) & 1ull)) {
-                const uint32_t pos = h == 0 ? my_pos : my_pos_hi;
-                store_nt(&a.ent_out[pos], pack_entry(gk, ctx, q * (K + 1) + (uint32_t)k));
-            }
-        }
-        // out rows touched once: row + g in[ctx] in FP64, rounded once (or the
-        // delta alone, when capturing)
+            for (int k = 0; k <= K; ++k) gk[k] = bt.coef(b, k);
+            // out rows touched once: row + g in[ctx] in FP64, rounded once (or
+            // the delta alone, when capturing)
 #pragma unroll
-        for (int k = 0; k <= K; ++k) {
-            uint32_t slot = 0;
-            if (a.cap_out) slot = __shfl(m_pos, src + 1 + k);   // uniform branch
-            if (live && t[k] >= 0 && ((single >> (src + 1 + k)) & 1ull)) {
-                float4* dst = reinterpret_cast<float4*>(
-                    a.cap_out ? a.cap_out + (int64_t)slot * D : a.tout + (int64_t)t[k] * D);
+            for (int k = 0; k <= K; ++k) {
+                int32_t slot = 0;
+                if constexpr (CAP) slot = __shfl(m_pos, src + 1 + k);
+                if (live && bt.row[b][k] >= 0 && ((single >> (src + 1 + k)) & 1ull)) {
+                    f2* dst = reinterpret_cast<f2*>(CAP ? a.cap_out + (int64_t)slot * D
+                                                        : a.tout + (int64_t)bt.row[b][k] * D);
 #pragma unroll
-                for (int i = 0; i < V4; ++i) {
-                    const float4 base = a.cap_out ? make_float4(0.0f, 0.0f, 0.0f, 0.0f) : vo[k][i];
-                    const float4 d = make_float4(
-                        (float)fma(g[k], (double)vin[i].x, (double)base.x),
-                        (float)fma(g[k], (double)vin[i].y, (double)base.y),
-                        (float)fma(g[k], (double)vin[i].z, (double)base.z),
-                        (float)fma(g[k], (double)vin[i].w, (double)base.w));
-                    store_nt(&dst[i * LPP + gl], d);
+                    for (int i = 0; i < V; ++i)
+                        store_row2<kStream>(row_at(dst, i * L + gl),
+                                            bt.out_row(b, i, gk[k],
+                                                       CAP ? f2{0.0f, 0.0f} : bt.vo[b][k][i]));
                 }
             }
-        }
-        if (live) {
-            if (gl == 0) store_nt(&a.key_in[pos_in], q);
-            float4* dp = reinterpret_cast<float4*>(a.dinp + (int64_t)pos_in * D);
+            const int32_t pos_in = __shfl(m_pos, src);
+            if (live) {
+                if (gl == 0) store_nt(&a.key_in[pos_in], q0 + (uint32_t)p);
+                f2* dp = reinterpret_cast<f2*>(a.dinp + (int64_t)pos_in * D);
+                f2 o[V];
+                bt.in_delta(b, gk, o);
 #pragma unroll
-            for (int i = 0; i < V4; ++i) {
-                double ax = 0.0, ay = 0.0, az = 0.0, aw = 0.0;
-#pragma unroll
-                for (int k = 0; k <= K; ++k) {
-                    ax = fma(g[k], (double)vo[k][i].x, ax);
-                    ay = fma(g[k], (double)vo[k][i].y, ay);
-                    az = fma(g[k], (double)vo[k][i].z, az);
-                    aw = fma(g[k], (double)vo[k][i].w, aw);
-                }
-                store_nt(&dp[i * LPP + gl], make_float4((float)ax, (float)ay, (float)az, (float)aw));
+                for (int i = 0; i < V; ++i) store_row2<kStream>(row_at(dp, i * L + gl), o[i]);
             }
         }
     }
-    lacc = wave_sum_f64(lacc);
+    lacc = wave_total(lacc);
     if (lane == 0) a.loss_part[gwave] += lacc;
 }
 
@@ -943,7 +908,10 @@ static void launch_train_t(Model& m, MinibatchBufs& mb, FwdArgs fa, const Miniba
     fa.off_out = mb.off_out.as<int32_t>();
     fa.cap_out = cap_out;
     if (ev) FELOG_HIP(hipEventRecord(ev[0], s));
-    hipLaunchKernelGGL((sgns_forward_kernel<D, K>), dim3(ml.fwd_blocks), dim3(256), 0, s, fa);
+    if (cap_out)
+        hipLaunchKernelGGL((sgns_forward_kernel<D, K, true>), dim3(ml.fwd_blocks), dim3(256), 0, s, fa);
+    else
+        hipLaunchKernelGGL((sgns_forward_kernel<D, K, false>), dim3(ml.fwd_blocks), dim3(256), 0, s, fa);
     if (ev) FELOG_HIP(hipEventRecord(ev[1], s));
     if (fwd_done) FELOG_HIP(hipEventRecord(fwd_done, s));
     double* part_in = m.partial.as<double>();
@@ -1117,11 +1085,12 @@ void train_minibatches(Model& m, const Walks& wc, const felog_train_params& p, i
         m.partial.alloc(&c, sizeof(double) * (m.split_rows_in + max_split_chunks(touches_out)) *
                                 m.dim);
     }
-    // pairs per forward wave: 4 (more, shorter waves) ran 1.4 us per minibatch
-    // faster than 8 at 65,536 pairs, d = 128, K = 5
-    const int ppw_max = std::max(1, std::min(4, 64 / (K + 2)));
-    const int ppw = (int)std::min<int64_t>(ppw_max,
-                                           std::max<int64_t>(1, P / ((int64_t)c.num_cus * 32)));
+    // pairs per forward wave: two steps (at 65,536 pairs, d = 128, K = 5 one
+    // step ran 71 us, two to four 63; at 5,000 pairs, d = 256, K = 7 one step
+    // 18.1, two 17.4, four 20.2), one where two would leave fewer than eight
+    // waves per compute unit
+    const int side = m.dim == 64 ? 2 : 1;
+    const int ppw = P >= (int64_t)2 * side * c.num_cus * 8 ? std::min(64 / (K + 2), 2 * side) : side;
     const int64_t waves = (P + ppw - 1) / ppw;
     const int64_t blocks = (waves + 3) / 4;
     DevBuf loss_part;

@@ -37,30 +37,64 @@ constexpr int kMetaWords = 16;            // per minibatch parity
 // multiple of 2^(k-52); taking c off again is exact.
 __device__ __forceinline__ double on_grid(double t, double c) { return __dsub_rn(__dadd_rn(t, c), c); }
 
-__device__ __forceinline__ double wave_sum_f64(double x)
+// sigma(x), sigma(-x) (FP64) and log(1 + exp(-|x|)) (FP32, relative error
+// about 1e-7) from one exponential E = exp(-|x|): sigma of the argument with
+// the sign of x is 1 / (1 + E), the other E / (1 + E), both to full FP64
+// precision, and the logarithm is 2 atanh(E / (2 + E)).  Against exp, a
+// division, expf and log1pf of the math library (and 1 - sigma, which cancels)
+// this is a third of the vector instructions of the evaluation.
+struct SigmaTerms {
+    double pos, neg;   // sigma(x), sigma(-x)
+    float l1p;
+};
+__device__ __forceinline__ SigmaTerms sigma_terms(double x)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-    return x;
-}
-
-// sigma(x) = 1 / (1 + exp(-x)) in FP64, without clipping (Eq. (2)).
-__device__ __forceinline__ double sigmoid_d(double x) { return 1.0 / (1.0 + exp(-x)); }
-
-// -log sigma(x) = log(1 + exp(-x)), without overflow.  A loss term is
-// evaluated in FP32 from the FP64 dot (relative error ~1e-7 per term) and the
-// terms are summed in FP64.
-__device__ __forceinline__ float neg_log_sigmoid(float x)
-{
-    return fmaxf(-x, 0.0f) + log1pf(expf(-fabsf(x)));
-}
-
-__device__ __forceinline__ double dot4d(float4 a, float4 b, double acc)
-{
-    acc = fma((double)a.x, (double)b.x, acc);
-    acc = fma((double)a.y, (double)b.y, acc);
-    acc = fma((double)a.z, (double)b.z, acc);
-    return fma((double)a.w, (double)b.w, acc);
+    // E: argument -a = n log 2 + r, |r| <= log(2) / 2, Taylor series of exp(r) to
+    // r^13 / 13! (the next term is below 2^-57).  exp(-800) is 0 in FP64; NaN stays.
+    double a = fabs(x);
+    a = a > 800.0 ? 800.0 : a;
+    const double n = rint(a * -1.4426950408889634);
+    double r = fma(n, -0.6931471805599453, -a);
+    r = fma(n, -2.3190468138462996e-17, r);
+    double p = 1.6059043836821613e-10;
+    p = fma(p, r, 2.08767569878681e-9);
+    p = fma(p, r, 2.505210838544172e-8);
+    p = fma(p, r, 2.755731922398589e-7);
+    p = fma(p, r, 2.7557319223985893e-6);
+    p = fma(p, r, 2.48015873015873e-5);
+    p = fma(p, r, 1.984126984126984e-4);
+    p = fma(p, r, 1.388888888888889e-3);
+    p = fma(p, r, 8.333333333333333e-3);
+    p = fma(p, r, 4.1666666666666664e-2);
+    p = fma(p, r, 1.6666666666666666e-1);
+    p = fma(p, r, 0.5);
+    p = fma(p, r, 1.0);
+    p = fma(p, r, 1.0);
+    const double E = ldexp(p, (int)n);
+    // 1 / (1 + E), 1 + E in [1, 2]: two Newton steps on the hardware reciprocal
+    const double d = 1.0 + E;
+    double q = __builtin_amdgcn_rcp(d);
+    q = fma(q, fma(-d, q, 1.0), q);
+    q = fma(q, fma(-d, q, 1.0), q);
+    const double Eq = E * q;
+    SigmaTerms t;
+    t.pos = x < 0.0 ? Eq : q;
+    t.neg = x < 0.0 ? q : Eq;
+    // 2 atanh(s) = 2 s (1 + z / 3 + z^2 / 5 + ..), z = s^2 <= 1 / 9
+    const float e = (float)E, w = 2.0f + e;
+    float u = __builtin_amdgcn_rcpf(w);
+    u = fmaf(u, fmaf(-w, u, 1.0f), u);
+    const float s = e * u, z = s * s;
+    float l = 1.0f / 17.0f;
+    l = fmaf(l, z, 1.0f / 15.0f);
+    l = fmaf(l, z, 1.0f / 13.0f);
+    l = fmaf(l, z, 1.0f / 11.0f);
+    l = fmaf(l, z, 1.0f / 9.0f);
+    l = fmaf(l, z, 1.0f / 7.0f);
+    l = fmaf(l, z, 1.0f / 5.0f);
+    l = fmaf(l, z, 1.0f / 3.0f);
+    t.l1p = 2.0f * fmaf(l * z, s, s);
+    return t;
 }
 
 // The FP64 coefficient g and the pair-order key of an out-touch, with the
@@ -80,105 +114,6 @@ template <int D>
 __device__ __forceinline__ const float4* row4(const float* base, int64_t row)
 {
     return reinterpret_cast<const float4*>(base + row * D);
-}
-
-// The apply's row slots past a segment's end: zeros, with no load issued.
-// Pointing those loads at row 0 instead made every short segment of the
-// minibatch read the same line, which queued in one L2 channel (about 1 us
-// per minibatch of the persistent update on R-MAT 2^20).
-template <int D, int NV>
-__device__ __forceinline__ void load_row_if(float4 (&x)[NV], const float* base, int32_t row,
-                                            bool ok, int lane16)
-{
-#pragma unroll
-    for (int i = 0; i < NV; ++i) x[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (ok) {
-        const float4* r = row4<D>(base, row);
-#pragma unroll
-        for (int i = 0; i < NV; ++i) x[i] = r[i * 16 + lane16];
-    }
-}
-
-__device__ __forceinline__ float dot4(float4 a, float4 b, float acc)
-{
-    acc = fmaf(a.x, b.x, acc);
-    acc = fmaf(a.y, b.y, acc);
-    acc = fmaf(a.z, b.z, acc);
-    return fmaf(a.w, b.w, acc);
-}
-
-// Sum over the L lanes of a lane group (L = 16 or 32).
-template <int L>
-__device__ __forceinline__ float group_sum(float x)
-{
-    if (L > 16) x += __shfl_xor(x, 16);
-    x += __shfl_xor(x, 8);
-    x += __shfl_xor(x, 4);
-    x += __shfl_xor(x, 2);
-    x += __shfl_xor(x, 1);
-    return x;
-}
-
-// Lanes per pair in the forward: 16 at d = 64, 32 from d = 128.  With FP64
-// dots and coefficients, 16 lanes at d = 128 needed 228 registers (two waves
-// per SIMD); 32 lanes need 164 (three), and the forward at P = 65,536 on
-// R-MAT 2^20 went from 103.9 to 91.9 us.
-template <int D, int K>
-constexpr int fwd_lanes_per_pair() { return D <= 64 ? 16 : 32; }
-
-template <int L>
-__device__ __forceinline__ double group_sum_d(double x);
-
-// The pair's coefficients g[0..K] (Eq. (2) gradient weights, FP64):
-// g0 = lr (1 - sigma(s0)), gk = -lr sigma(sk), 0 for a skipped negative,
-// from FP64 dots over the group's LPP lanes.  Lane j of the group evaluates
-// sigma and the loss term of touch j (and j + LPP), so each lane runs one
-// FP64 exponential instead of K + 1; the coefficients are then broadcast.
-// The loss term, -log sigma(s0) or -log sigma(-sk), is FP32 from the FP64
-// dot, added to lacc in FP64.
-template <int K, int LPP, int V4>
-__device__ __forceinline__ void coefficients(const float4 (&vin)[V4], const float4 (&vo)[K + 1][V4],
-                                             const int32_t (&t)[K + 1], double lr, bool live,
-                                             int gl, int grp, double (&g)[K + 1], double& lacc)
-{
-    double dot[K + 1];
-#pragma unroll
-    for (int k = 0; k <= K; ++k) {
-        double acc = 0.0;
-#pragma unroll
-        for (int i = 0; i < V4; ++i) acc = dot4d(vin[i], vo[k][i], acc);
-        dot[k] = group_sum_d<LPP>(acc);
-    }
-    constexpr int H = (K + LPP) / LPP;   // touches per lane
-    double mine[H];
-#pragma unroll
-    for (int h = 0; h < H; ++h) {
-        const int k = gl + h * LPP;
-        double dk = dot[0];
-        bool ok = true;
-#pragma unroll
-        for (int j = 1; j <= K; ++j)
-            if (k == j) {
-                dk = dot[j];
-                ok = t[j] >= 0;
-            }
-        const double sg = sigmoid_d(dk);
-        mine[h] = k == 0 ? lr * (1.0 - sg) : (ok ? -lr * sg : 0.0);
-        if (k <= K && live && ok) lacc += (double)neg_log_sigmoid((float)(k == 0 ? dk : -dk));
-    }
-#pragma unroll
-    for (int k = 0; k <= K; ++k) g[k] = __shfl(mine[k / LPP], grp * LPP + k % LPP);
-}
-
-template <int L>
-__device__ __forceinline__ double group_sum_d(double x)
-{
-    if (L > 16) x += __shfl_xor(x, 16);
-    x += __shfl_xor(x, 8);
-    x += __shfl_xor(x, 4);
-    x += __shfl_xor(x, 2);
-    x += __shfl_xor(x, 1);
-    return x;
 }
 
 // The row's current values (zero when capturing), read before the delta is

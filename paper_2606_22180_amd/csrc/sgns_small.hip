@@ -28,13 +28,22 @@
 // terms rounded onto the exact-sum grid, every stored value is rounded once.
 // The two paths therefore give bit-identical tables.
 //
+// The workgroups exchange rows, coefficients, deltas and context copies
+// through agent-scope relaxed accesses of 8 bytes instead of release and
+// acquire fences, which write back and invalidate each XCD's whole L2 at every
+// barrier (the rows are read once per minibatch, so the L2 held little of use).
+// With the forward of sgns_forward.h, per minibatch of 1,024 pairs: R-MAT 2^20,
+// d = 128, 17.3 -> 11.5 us (forward phase 7.4 -> 4.0 us, first barrier 3.3 ->
+// 1.6); 1,000 nodes, d = 64, 18.8 -> 12.1.  A minibatch is two dependent trips
+// to memory, the arithmetic between them and two barriers.
+//
 // The grid barrier is a flag per workgroup: each workgroup stores its barrier
 // count to a flag on its own 128-byte line, and the first wave of every
-// workgroup watches all the flags (one lane per flag).  On MI355X (512
-// threads per workgroup) this measured 1.7 us at 32 workgroups, 2.2 at 64 and
-// 3.4 at 128; workgroup 0 gathering the flags and raising a go flag that the
-// others wait for took 2.0-3.1 / 2.5 / 3.5 us, and one shared atomic counter,
-// whose same-address atomics serialise, 3.4 / 3.4 / 4.9 us.  Every wait is
+// workgroup watches all the flags (one lane per flag).  Workgroup 0 gathering
+// the flags and raising a go flag, and one shared atomic counter, whose
+// same-address atomics serialise, were slower.  Workgroups and us per
+// minibatch (R-MAT 2^20 / 1,000 nodes): 32 15.2 / 16.5, 64 11.9 / 12.6,
+// 96 12.7 / 13.3, 128 12.8 / 13.5.  Every wait is
 // bounded: one that exceeds kSpinLimit polls raises an abort flag that every
 // workgroup checks, so every wave leaves the kernel, and the host reports the
 // failure.
@@ -45,6 +54,7 @@
 #include "common.h"
 #include "noise.h"
 #include "sgns_device.h"
+#include "sgns_forward.h"
 
 namespace felog {
 
@@ -405,68 +415,228 @@ __device__ __forceinline__ bool wait_at_least(const uint32_t* p, uint32_t target
     return true;
 }
 
-// Grid barrier with release/acquire at agent scope.  Returns false when the
-// launch is aborting (a wait exceeded its bound somewhere).
+// Grid barrier.  What the workgroups exchange (table rows, coefficients,
+// deltas, context copies) goes through agent-scope relaxed atomics, which no
+// cache holds back, so a barrier needs only that every wave's accesses have
+// completed before its workgroup's flag is raised.  A release and an acquire
+// fence at agent scope write back and invalidate the whole L2 instead.
+// Returns false when the launch is aborting (a wait exceeded its bound).
 __device__ __forceinline__ bool grid_sync(const UpdArgs& a, uint32_t& epoch,
                                           unsigned long long* arrive)
 {
     __shared__ int s_ok;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (arrive) *arrive = wall_clock64();   // every wave of the workgroup is here
     ++epoch;
-    if (threadIdx.x == 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    if (threadIdx.x == 0)
         __hip_atomic_store(&a.flags[kFlagStride * (1 + blockIdx.x)], epoch, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
-    }
     // every workgroup's first wave watches every flag (lane l the flags of
-    // workgroups l, l + 64, ...), then acquires for the workgroup
+    // workgroups l, l + 64, ...)
     if (threadIdx.x < 64) {
         bool ok = true;
         for (uint32_t b = threadIdx.x; b < gridDim.x; b += 64)
             ok = ok && wait_at_least(&a.flags[kFlagStride * (1 + b)], epoch, a.abort);
         const bool all_ok = __all(ok);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        if (threadIdx.x == 0)
-            s_ok = all_ok &&
-                   !__hip_atomic_load(a.abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0) s_ok = all_ok;
     }
     __syncthreads();
+    asm volatile("" ::: "memory");
     return s_ok != 0;
 }
+
+// Touch l of the pairs [q0, q0 + S H) of minibatch m, or -1.
+template <int K>
+__device__ __forceinline__ int2 touch_of(const UpdJob& J, int m, uint32_t np, uint32_t q0,
+                                         uint32_t pairs)
+{
+    const int lane = threadIdx.x & 63;
+    if (q0 < np && lane < (int)min(pairs, np - q0) * (K + 2))
+        return J.tinfo[(int64_t)m * J.tmax + (int64_t)q0 * (K + 2) + lane];
+    return make_int2(-1, -1);
+}
+
+// Forward of one batch of pairs of minibatch m, from pair q0; `touch` is
+// touch_of those pairs.
+template <int D, int K, int S, RowAccess A>
+__device__ __forceinline__ void forward_pairs(const UpdJob& J, uint32_t npairs, uint32_t q0,
+                                              int2 touch, double lr, double& lacc)
+{
+    using Batch = FwdBatch<D, K, S, A>;
+    constexpr int T = K + 2, H = Batch::H, L = Batch::L, V = Batch::V;
+    const int lane = threadIdx.x & 63;
+    const uint32_t gl = lane & (L - 1);
+    const int np = (int)min((uint32_t)(S * H), npairs - q0);
+    const int32_t m_row = touch.x, m_code = touch.y;
+    const unsigned long long single = __ballot(m_code >= 0 && (m_code & kSingleBit));
+    const unsigned long long shared = __ballot(m_code >= 0 && !(m_code & kSingleBit));
+    Batch bt;
+    bt.load(J.tin, J.tout, m_row, 0, np);
+    bt.coefficients(m_row, 0, np, lr, lacc);
+    {
+        // coefficients of the out-touches (not of the rows touched once)
+        const int32_t code = __shfl(m_code, bt.touch);
+        if (bt.mine && !(code & kSingleBit)) {
+            double* gp = &J.gpos[code & kPosMask];
+            if constexpr (A == kAgent)
+                __hip_atomic_store(gp, bt.g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else
+                *gp = bt.g;
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < S; ++b) {
+        const int p = b * H + (H == 2 ? lane >> 5 : 0);
+        const bool live = p < np;
+        const int src = (live ? p : 0) * T;
+        double gk[K + 1];
+#pragma unroll
+        for (int k = 0; k <= K; ++k) gk[k] = bt.coef(b, k);
+        // out rows touched once: row + g in[ctx] in FP64, rounded once
+#pragma unroll
+        for (int k = 0; k <= K; ++k) {
+            if (live && bt.row[b][k] >= 0 && ((single >> (src + 1 + k)) & 1ull)) {
+                f2* dst = reinterpret_cast<f2*>(J.tout + (int64_t)bt.row[b][k] * D);
+#pragma unroll
+                for (int i = 0; i < V; ++i)
+                    store_row2<A>(row_at(dst, i * L + gl), bt.out_row(b, i, gk[k], bt.vo[b][k][i]));
+            }
+        }
+        const int32_t pos_in = __shfl(m_code, src) & kPosMask;
+        if (live) {
+            // the context copy is read by the apply of the pair's out rows
+            // touched more than once; an in row touched once is updated here
+            // (its delta rounded to FP32 first, as the apply rounds the stored
+            // delta), others store the delta
+            const bool need_ctx = ((shared >> (src + 1)) & ((1ull << (K + 1)) - 1ull)) != 0;
+            const bool in_single = (single >> src) & 1ull;
+            f2 o[V];
+            bt.in_delta(b, gk, o);
+            if (need_ctx) {
+                f2* cc = reinterpret_cast<f2*>(J.ctxc + (int64_t)(q0 + (uint32_t)p) * D);
+#pragma unroll
+                for (int i = 0; i < V; ++i) store_row2<A>(row_at(cc, i * L + gl), bt.vin[b][i]);
+            }
+            f2* dp = reinterpret_cast<f2*>(in_single ? J.tin + (int64_t)bt.ctx[b] * D
+                                                     : J.dinp + (int64_t)pos_in * D);
+#pragma unroll
+            for (int i = 0; i < V; ++i) {
+                f2 v = o[i];
+                if (in_single)
+                    v = f2{(float)((double)bt.vin[b][i].x + (double)o[i].x),
+                           (float)((double)bt.vin[b][i].y + (double)o[i].y)};
+                store_row2<A>(row_at(dp, i * L + gl), v);
+            }
+        }
+    }
+}
+
+// Adds the sum of a segment's terms to its row: one 16-lane group.  pair0: the
+// pair of each of the first 16 touches (out segments).  A whole wave per
+// segment, with all 16 touches in flight, was slower (the apply 1.1 -> 3.2 us
+// per workgroup on R-MAT 2^20, 2.9 -> 9.6 on 1,000 nodes).
+template <int D, RowAccess A>
+__device__ __forceinline__ void apply_segment(const UpdJob& J, const int32_t* sp, int4 seg,
+                                              bool out, int32_t pair0, double gc)
+{
+    constexpr int V = D / 32;        // float2s per lane and row
+    constexpr int kRows = 4;         // rows in flight
+    const int lane = threadIdx.x & 63;
+    const int g0 = lane & 48, l16 = lane & 15;
+    const int32_t row = seg.x, start = seg.y, len = seg.z;
+    f2* const table = reinterpret_cast<f2*>((out ? J.tout : J.tin) + (int64_t)row * D);
+    const float* const srcb = out ? J.ctxc : J.dinp;
+    f2 cur[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) cur[i] = load_row2<A>(table + i * 16 + l16);
+    double acc[2 * V];
+#pragma unroll
+    for (int e = 0; e < 2 * V; ++e) acc[e] = 0.0;
+    const bool exact = len > kChunk;
+    // touches in batches of 16, one descriptor per lane
+    for (int32_t b0 = 0; b0 < len; b0 += 16) {
+        const int32_t nb = min(16, len - b0);
+        // out rows: the touch's coefficient and its pair's context copy; in
+        // rows: the pair's delta at the touch's position
+        double my_g = 1.0;
+        int32_t my_src = start + b0 + l16;
+        if (out && l16 < nb) {
+            const double* gp = &J.gpos[start + b0 + l16];
+            if constexpr (A == kAgent)
+                my_g = __hip_atomic_load(gp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else
+                my_g = *gp;
+            my_src = b0 == 0 ? pair0 : sp[start + b0 + l16];
+        }
+        for (int32_t i0 = 0; i0 < nb; i0 += kRows) {
+            double gg[kRows];
+            f2 x[kRows][V];
+            // no load is issued for slots past the segment's end: pointing them
+            // at row 0 made every short segment read the same line, which
+            // queued in one memory channel
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                const bool ok = i0 + u < nb;
+                const int32_t rr = __shfl(my_src, g0 + min(i0 + u, 15));
+                const f2* rp = reinterpret_cast<const f2*>(srcb + (int64_t)rr * D);
+#pragma unroll
+                for (int i = 0; i < V; ++i) x[u][i] = f2{0.0f, 0.0f};
+                if (ok) {
+#pragma unroll
+                    for (int i = 0; i < V; ++i) x[u][i] = load_row2<A>(rp + i * 16 + l16);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) gg[u] = __shfl(my_g, g0 + min(i0 + u, 15));
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                if (i0 + u >= nb) break;
+#pragma unroll
+                for (int i = 0; i < V; ++i) {
+                    if (exact) {
+                        // order-free: each term rounded onto the grid, sums exact
+                        acc[2 * i] += on_grid(gg[u] * (double)x[u][i].x, gc);
+                        acc[2 * i + 1] += on_grid(gg[u] * (double)x[u][i].y, gc);
+                    } else {
+                        // in rows: g = 1, and 1 * x + acc is exactly x + acc
+                        acc[2 * i] = fma(gg[u], (double)x[u][i].x, acc[2 * i]);
+                        acc[2 * i + 1] = fma(gg[u], (double)x[u][i].y, acc[2 * i + 1]);
+                    }
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+        store_row2<A>(table + i * 16 + l16, f2{(float)((double)cur[i].x + acc[2 * i]),
+                                               (float)((double)cur[i].y + acc[2 * i + 1])});
+}
+
+// Steps of pairs per forward batch of the persistent update: two pairs per
+// wave, so that 1,024 pairs occupy every wave of the 64 workgroups.
+template <int D, int K>
+constexpr int upd_steps() { return D == 64 || fwd_max_steps(D, K) < 2 ? 1 : 2; }
 
 template <int D, int K>
 __global__ __launch_bounds__(kUpdThreads) void sgns_small_update_kernel(UpdArgs a)
 {
-    // lanes per pair in the forward: 32 at d >= 128, so that the 1,024 pairs of
-    // a minibatch occupy every wave of the 64 workgroups (16 lanes left half
-    // of them idle: 10.2 -> 6.8 us for the forward on R-MAT 2^20, K = 5)
-    constexpr int LPP = D >= 128 ? 32 : 16;
-    constexpr int G = 64 / LPP;                         // pairs in flight per wave
-    constexpr int V4 = D / (4 * LPP);                   // float4s per lane and row
-    constexpr int T = K + 2;
-    constexpr int AV4 = D / 64;                         // float4s per lane and row (apply)
-    constexpr int kRows = 4;                            // rows in flight per apply group
+    constexpr int S = upd_steps<D, K>();
+    constexpr uint32_t G = S * FwdShape<D, K>::kHalves;   // pairs per wave at a time
     const int lane = threadIdx.x & 63;
-    const int grp = lane / LPP, gl = lane % LPP;
     const int g16 = lane >> 4, l16 = lane & 15;
     const uint32_t nw = gridDim.x * (blockDim.x >> 6);
-    const uint32_t gw = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    const uint32_t gw = blockIdx.x * (blockDim.x >> 6) +
+                        (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint32_t epoch = a.epoch0;
     double lacc = 0.0;
     // plan data of job 0's next phase, loaded a phase ahead: this lane's touch
-    // of the wave's first pair group (forward) and the group's first segment
-    // with the pair of each of its first 16 positions (apply)
+    // of the wave's first batch (forward) and the group's first segment with
+    // the pair of each of its first 16 positions (apply)
     const UpdJob& J0 = a.job[0];
-    auto first_touch = [&](int mm) -> int2 {
-        const uint32_t npm = J0.desc[mm].npairs, q0 = gw * G;
-        if (q0 < npm && lane < (int)min((uint32_t)G, npm - q0) * T)
-            return J0.tinfo[(int64_t)mm * J0.tmax + (int64_t)q0 * T + lane];
-        return make_int2(-1, -1);
-    };
-    int2 pf_touch = J0.nmb > 0 ? first_touch(0) : make_int2(-1, -1);
+    int2 pf_touch = J0.nmb > 0 ? touch_of<K>(J0, 0, J0.desc[0].npairs, gw * G, G)
+                               : make_int2(-1, -1);
     const uint32_t sidx0 = gw * 4 + (uint32_t)g16;
-
     // phase clocks (thread 0 of each workgroup, when asked for), kept in LDS:
     // [0..3] ticks of the phases summed over the launch's minibatches (added
     // to the totals once at the end), [4] phase start, [5] barrier arrival,
@@ -488,127 +658,20 @@ __global__ __launch_bounds__(kUpdThreads) void sgns_small_update_kernel(UpdArgs 
         for (int j = 0; j < a.njobs; ++j) {
             const UpdJob& J = a.job[j];
             if (m >= J.nmb) continue;
-            const MbDesc dsc = J.desc[m];
-            const int2* ti = J.tinfo + (int64_t)m * J.tmax;
-            const uint32_t np = dsc.npairs;
-            const double lr = (double)dsc.lr;
-            for (uint32_t q0 = gw * G; q0 < np; q0 += nw * G) {
-                const int npw = (int)min((uint32_t)G, np - q0);
-                int32_t m_row = -1, m_code = -1;
-                if (j == 0 && q0 == gw * G) {
-                    m_row = pf_touch.x;
-                    m_code = pf_touch.y;
-                } else if (lane < npw * T) {
-                    const int2 x = ti[(int64_t)q0 * T + lane];
-                    m_row = x.x;
-                    m_code = x.y;
-                }
-                const unsigned long long single = __ballot(m_code >= 0 && (m_code & kSingleBit));
-                const int p = grp;
-                const bool live = p < npw;
-                const uint32_t q = q0 + (uint32_t)p;
-                const int src = (live ? p : 0) * T;
-                const int32_t ctx = __shfl(m_row, src);
-                const int32_t pos_in = __shfl(m_code, src) & kPosMask;
-                int32_t t[K + 1];
-#pragma unroll
-                for (int k = 0; k <= K; ++k) t[k] = __shfl(m_row, src + 1 + k);
-                const int32_t my_code = __shfl(m_code, src + 1 + (gl <= K ? gl : 0));
-                int32_t my_code_hi = 0;
-                if (LPP == 16 && K >= 16) my_code_hi = __shfl(m_code, src + 1 + (gl + 16 <= K ? gl + 16 : 0));
-
-                float4 vin[V4];
-                float4 vo[K + 1][V4];
-                const float4* ri = reinterpret_cast<const float4*>(J.tin + (int64_t)(live ? ctx : 0) * D);
-#pragma unroll
-                for (int i = 0; i < V4; ++i) vin[i] = ri[i * LPP + gl];
-#pragma unroll
-                for (int k = 0; k <= K; ++k) {
-                    const bool ok = live && t[k] >= 0;
-                    const float4* ro = reinterpret_cast<const float4*>(J.tout + (int64_t)(ok ? t[k] : 0) * D);
-#pragma unroll
-                    for (int i = 0; i < V4; ++i)
-                        vo[k][i] = ok ? ro[i * LPP + gl] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                }
-                double g[K + 1];
-                coefficients<K, LPP, V4>(vin, vo, t, lr, live, gl, grp, g, lacc);
-                // entries of the out-touches (not the rows touched once)
-#pragma unroll
-                for (int h = 0; h < (K + LPP) / LPP; ++h) {
-                    const int k = gl + h * LPP;
-                    double gk = g[0];
-                    int32_t tk = t[0];
-#pragma unroll
-                    for (int jj = 1; jj <= K; ++jj)
-                        if (k == jj) {
-                            gk = g[jj];
-                            tk = t[jj];
-                        }
-                    if (k <= K && live && tk >= 0 && !((single >> (src + 1 + k)) & 1ull)) {
-                        const int32_t code = h == 0 ? my_code : my_code_hi;
-                        J.gpos[code & kPosMask] = gk;
-                    }
-                }
-                // out rows touched once: row + g in[ctx] in FP64, rounded once
-#pragma unroll
-                for (int k = 0; k <= K; ++k) {
-                    if (live && t[k] >= 0 && ((single >> (src + 1 + k)) & 1ull)) {
-                        float4* dst = reinterpret_cast<float4*>(J.tout + (int64_t)t[k] * D);
-#pragma unroll
-                        for (int i = 0; i < V4; ++i) {
-                            const float4 b = vo[k][i];
-                            dst[i * LPP + gl] = make_float4((float)fma(g[k], (double)vin[i].x, (double)b.x),
-                                                            (float)fma(g[k], (double)vin[i].y, (double)b.y),
-                                                            (float)fma(g[k], (double)vin[i].z, (double)b.z),
-                                                            (float)fma(g[k], (double)vin[i].w, (double)b.w));
-                        }
-                    }
-                }
-                if (live) {
-                    // the context copy is read by the apply of the pair's out
-                    // rows touched more than once; an in row touched once is
-                    // updated here (its delta rounded to FP32 first, as the
-                    // apply rounds the stored delta), others store the delta
-                    bool need_ctx = false;
-#pragma unroll
-                    for (int k = 0; k <= K; ++k)
-                        need_ctx = need_ctx || (t[k] >= 0 && !((single >> (src + 1 + k)) & 1ull));
-                    const bool in_single = (single >> src) & 1ull;
-                    float4* cc = reinterpret_cast<float4*>(J.ctxc + (int64_t)q * D);
-                    float4* dp = in_single ? reinterpret_cast<float4*>(J.tin + (int64_t)ctx * D)
-                                           : reinterpret_cast<float4*>(J.dinp + (int64_t)pos_in * D);
-#pragma unroll
-                    for (int i = 0; i < V4; ++i) {
-                        if (need_ctx) cc[i * LPP + gl] = vin[i];
-                        double ax = 0.0, ay = 0.0, az = 0.0, aw = 0.0;
-#pragma unroll
-                        for (int k = 0; k <= K; ++k) {
-                            ax = fma(g[k], (double)vo[k][i].x, ax);
-                            ay = fma(g[k], (double)vo[k][i].y, ay);
-                            az = fma(g[k], (double)vo[k][i].z, az);
-                            aw = fma(g[k], (double)vo[k][i].w, aw);
-                        }
-                        float4 dv = make_float4((float)ax, (float)ay, (float)az, (float)aw);
-                        if (in_single)
-                            dv = make_float4((float)((double)vin[i].x + (double)dv.x),
-                                             (float)((double)vin[i].y + (double)dv.y),
-                                             (float)((double)vin[i].z + (double)dv.z),
-                                             (float)((double)vin[i].w + (double)dv.w));
-                        dp[i * LPP + gl] = dv;
-                    }
-                }
-            }
+            const uint32_t np = J.desc[m].npairs;
+            const double lr = (double)J.desc[m].lr;
+            for (uint32_t q0 = gw * G; q0 < np; q0 += nw * G)
+                forward_pairs<D, K, S, kAgent>(
+                    J, np, q0,
+                    j == 0 && q0 == gw * G ? pf_touch : touch_of<K>(J, m, np, q0, G), lr, lacc);
             if (a.njobs > 1) {
                 // each job's loss terms to its own partials
-                const double l = wave_sum_f64(lacc);
+                const double l = wave_total(lacc);
                 if (lane == 0) J.loss_part[gw] += l;
                 lacc = 0.0;
             }
         }
-        if (m < J0.nmb) {
-            const uint32_t nseg0 = J0.meta[(int64_t)m * 4];
-            if (sidx0 < nseg0 && l16 < pf_seg.z) pf_pair = J0.spair[(int64_t)m * J0.tmax + pf_seg.y + l16];
-        }
+        if (pf_seg.z > l16) pf_pair = J0.spair[(int64_t)m * J0.tmax + pf_seg.y + l16];
         if (!grid_sync(a, epoch, clk ? &s_clk[5] : nullptr)) break;
         if (clk) {
             s_clk[6] = wall_clock64();
@@ -617,84 +680,21 @@ __global__ __launch_bounds__(kUpdThreads) void sgns_small_update_kernel(UpdArgs 
         }
 
         // ---- apply: one 16-lane group per segment, in and out rows together
-        if (m + 1 < J0.nmb) pf_touch = first_touch(m + 1);
+        if (m + 1 < J0.nmb) pf_touch = touch_of<K>(J0, m + 1, J0.desc[m + 1].npairs, gw * G, G);
         for (int j = 0; j < a.njobs; ++j) {
             const UpdJob& J = a.job[j];
             if (m >= J.nmb) continue;
-            const MbDesc dsc = J.desc[m];
             const int32_t* sp = J.spair + (int64_t)m * J.tmax;
             const uint32_t nseg = J.meta[(int64_t)m * 4], nin = J.meta[(int64_t)m * 4 + 1];
             const int4* sg = J.segs + (int64_t)m * J.tmax;
-            const double gc = dsc.grid_c;
+            const double gc = J.desc[m].grid_c;
             for (uint32_t sidx = sidx0; sidx < nseg; sidx += nw * 4) {
-                const bool first_seg = j == 0 && sidx == sidx0;
-                const int4 sd = first_seg ? pf_seg : sg[sidx];
+                const bool ahead = j == 0 && sidx == sidx0;
+                const int4 sd = ahead ? pf_seg : sg[sidx];
                 const bool out = sidx >= nin;
-                const int32_t row = sd.x, start = sd.y, len = sd.z;
-                float* table = out ? J.tout : J.tin;
-                const float* srcb = out ? J.ctxc : J.dinp;
-                float4 cur[AV4];
-                const float4* r4 = reinterpret_cast<const float4*>(table + (int64_t)row * D);
-#pragma unroll
-                for (int i = 0; i < AV4; ++i) cur[i] = r4[i * 16 + l16];
-                double acc[D / 16];
-#pragma unroll
-                for (int e = 0; e < D / 16; ++e) acc[e] = 0.0;
-                const bool exact = len > kChunk;
-                // touches in batches of 16, one descriptor per lane
-                for (int32_t b0 = 0; b0 < len; b0 += 16) {
-                    const int32_t nb = min(16, len - b0);
-                    // out rows: the touch's coefficient and its pair's context
-                    // copy; in rows: the pair's delta at the touch's position
-                    double my_g = 1.0;
-                    int32_t my_src = start + b0 + l16;
-                    if (out && l16 < nb) {
-                        my_g = J.gpos[start + b0 + l16];
-                        my_src = (first_seg && b0 == 0) ? pf_pair : sp[start + b0 + l16];
-                    }
-                    for (int32_t i0 = 0; i0 < nb; i0 += kRows) {
-                        double gg[kRows];
-                        float4 x[kRows][AV4];
-#pragma unroll
-                        for (int u = 0; u < kRows; ++u) {
-                            const bool ok = i0 + u < nb;
-                            const int32_t idx = min(i0 + u, 15);
-                            gg[u] = __shfl(my_g, (g16 << 4) + idx);
-                            const int32_t rr = __shfl(my_src, (g16 << 4) + idx);
-                            load_row_if<D, AV4>(x[u], srcb, rr, ok, l16);
-                            if (!ok) gg[u] = 0.0;
-                        }
-#pragma unroll
-                        for (int u = 0; u < kRows; ++u) {
-                            if (i0 + u >= nb) break;
-#pragma unroll
-                            for (int i = 0; i < AV4; ++i) {
-                                if (exact) {
-                                    // order-free: each term rounded onto the grid, sums exact
-                                    acc[4 * i + 0] += on_grid(gg[u] * (double)x[u][i].x, gc);
-                                    acc[4 * i + 1] += on_grid(gg[u] * (double)x[u][i].y, gc);
-                                    acc[4 * i + 2] += on_grid(gg[u] * (double)x[u][i].z, gc);
-                                    acc[4 * i + 3] += on_grid(gg[u] * (double)x[u][i].w, gc);
-                                } else {
-                                    // in rows: g = 1, and 1 * x + acc is exactly x + acc
-                                    acc[4 * i + 0] = fma(gg[u], (double)x[u][i].x, acc[4 * i + 0]);
-                                    acc[4 * i + 1] = fma(gg[u], (double)x[u][i].y, acc[4 * i + 1]);
-                                    acc[4 * i + 2] = fma(gg[u], (double)x[u][i].z, acc[4 * i + 2]);
-                                    acc[4 * i + 3] = fma(gg[u], (double)x[u][i].w, acc[4 * i + 3]);
-                                }
-                            }
-                        }
-                    }
-                }
-                float4* d4 = reinterpret_cast<float4*>(table + (int64_t)row * D);
-#pragma unroll
-                for (int i = 0; i < AV4; ++i) {
-                    const float4 c = cur[i];
-                    d4[i * 16 + l16] = make_float4((float)((double)c.x + acc[4 * i + 0]),
-                                                   (float)((double)c.y + acc[4 * i + 1]),
-                                                   (float)((double)c.z + acc[4 * i + 2]),
-                                                   (float)((double)c.w + acc[4 * i + 3]));
-                }
+                int32_t pair = pf_pair;
+                if (!ahead) pair = out && l16 < sd.z ? sp[sd.y + l16] : 0;
+                apply_segment<D, kAgent>(J, sp, sd, out, pair, gc);
             }
         }
         if (!grid_sync(a, epoch, clk ? &s_clk[5] : nullptr)) break;
@@ -706,7 +706,7 @@ __global__ __launch_bounds__(kUpdThreads) void sgns_small_update_kernel(UpdArgs 
     if (clk)
         for (int i = 0; i < 4; ++i) atomicAdd(&a.clocks[i], s_clk[i]);
     if (a.njobs == 1) {
-        lacc = wave_sum_f64(lacc);
+        lacc = wave_total(lacc);
         if (lane == 0) J0.loss_part[gw] += lacc;
     }
 }

@@ -121,3 +121,36 @@ def test_plan_one_hub(fl):
     g = synth.csr_from_edges(n, np.array([(0, i) for i in range(1, n)], np.int64))
     a, b = _two_paths(fl, g, dim=64, K=5, P=1024, first=0, count=2, r=20)
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]) and a[3:] == b[3:]
+
+
+# odd pair counts at d = 64, where a wave holds two pairs side by side and the
+# last of an odd number stands alone; many negatives equal their centre
+@pytest.mark.parametrize("P", [1, 3, 255, 257])
+@pytest.mark.parametrize("K", [1, 9, 15, 20])
+def test_forward_odd_pairs_d64(fl, orc, K, P):
+    n = 40
+    e = np.array([(i, j) for i in range(n) for j in range(i + 1, min(n, i + 6))], np.int64)
+    g = synth.csr_from_edges(n, e)
+    c = fl.Context(0)
+    c.set_sgns_path(1)
+    G = fl.Graph.from_csr(c, g.indptr, g.indices)
+    W = fl.Walks.generate(G, r=8, L=12, seed=4)
+    M = fl.Model.create(G, dim=64, seed=6)
+    rng = np.random.default_rng(K)
+    tab = [rng.normal(0, 0.2, (n, 64)).astype(np.float32) for _ in range(2)]
+    for which in (0, 1):
+        M.write(which, tab[which])
+    walks = orc.walks_uniform(g, np.arange(n), 8, 12, 4)
+    cdf = orc.neg_cdf(g.degrees().astype(np.uint64))
+    prm = fl.train_params(window=3, negatives=K, minibatch_pairs=P, seed=9, lr_start=0.02,
+                          lr_end=0.02)
+    for b in (2, 3, 4):
+        mb = orc.minibatch_pairs(walks, 3, P, b)
+        ref = orc.sgns_step(tab[0], tab[1], mb.ctx, mb.ctr, orc.draw_negatives(mb, 0, K, 9, cdf),
+                            float(np.float32(0.02)), apply=False)
+        ri, di, ro, do, _ = M.train_delta(W, prm, b)
+        for rows, d, rrows, rd in ((ri, di, ref.rows_in, ref.d_in), (ro, do, ref.rows_out, ref.d_out)):
+            assert np.array_equal(np.sort(rows), np.sort(rrows))
+            d, rd = d[np.argsort(rows)], rd[np.argsort(rrows)]
+            err = np.linalg.norm(d.astype(np.float64) - rd, axis=1)
+            assert (err <= 1e-5 * np.linalg.norm(rd, axis=1) + 1e-12).all()
