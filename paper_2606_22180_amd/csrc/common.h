@@ -299,6 +299,11 @@ bool small_path_applies(const Model& m, const felog_train_params& p);
 void train_minibatches_small(Model& m, Walks& w, const felog_train_params& p,
                              const TrainSchedule& sch, const int32_t* d_slices, int64_t first_mb,
                              int64_t end, felog_train_stats* stats);
+// Planned launches of the same minibatches (two per minibatch); false when
+// they do not apply or their plans find no room.
+bool train_minibatches_planned(Model& m, Walks& w, const felog_train_params& p,
+                               const TrainSchedule& sch, const int32_t* d_slices,
+                               int64_t first_mb, int64_t end, felog_train_stats* stats);
 void launch_loss_reduce(const double* part, int64_t n, double* out, hipStream_t s);
 int64_t small_minibatches_per_launch();
 // touches per minibatch, P (K + 2), up to which the persistent update applies

@@ -1046,15 +1046,19 @@ void train_minibatches(Model& m, const Walks& wc, const felog_train_params& p, i
         return;
     }
 
-    if (apply && small_path_applies(m, p)) {
+    if (apply && P * (K + 2) <= 2 * kSmallMaxTouches) {
         std::vector<int32_t> sl = make_slices(w.L, p.window);
         DevBuf slices;
         slices.alloc(&c, sizeof(int32_t) * std::max<size_t>(sl.size(), 1));
         if (!sl.empty())
             FELOG_HIP(hipMemcpyAsync(slices.ptr, sl.data(), sizeof(int32_t) * sl.size(),
                                      hipMemcpyHostToDevice, c.stream));
-        train_minibatches_small(m, w, p, sch, slices.as<int32_t>(), first_mb, end, stats);
-        return;
+        if (small_path_applies(m, p)) {
+            train_minibatches_small(m, w, p, sch, slices.as<int32_t>(), first_mb, end, stats);
+            return;
+        }
+        if (train_minibatches_planned(m, w, p, sch, slices.as<int32_t>(), first_mb, end, stats))
+            return;
     }
 
     // scratch sized for this minibatch size

@@ -32,10 +32,12 @@
 // through agent-scope relaxed accesses of 8 bytes instead of release and
 // acquire fences, which write back and invalidate each XCD's whole L2 at every
 // barrier (the rows are read once per minibatch, so the L2 held little of use).
-// With the forward of sgns_forward.h, per minibatch of 1,024 pairs: R-MAT 2^20,
-// d = 128, 17.3 -> 11.5 us (forward phase 7.4 -> 4.0 us, first barrier 3.3 ->
-// 1.6); 1,000 nodes, d = 64, 18.8 -> 12.1.  A minibatch is two dependent trips
-// to memory, the arithmetic between them and two barriers.
+// With the forward of sgns_forward.h, and hubs' segments shared by a workgroup,
+// per minibatch of 1,024 pairs: R-MAT 2^20, d = 128, 17.3 -> 10.7 us (forward
+// phase 4.0, first barrier 1.6, apply 1.1, second barrier 3.3: it waits for the
+// workgroups that have segments); 1,000 nodes, d = 64, 18.8 -> 10.1.  A
+// minibatch is two dependent trips to memory, the arithmetic between them and
+// two barriers.
 //
 // The grid barrier is a flag per workgroup: each workgroup stores its barrier
 // count to a flag on its own 128-byte line, and the first wave of every
@@ -70,7 +72,9 @@ struct MbDesc {
 static_assert(sizeof(MbDesc) == 32, "descriptor layout shared by host and device");
 
 constexpr int kPlanThreads = 1024;
-constexpr int kPlanMaxTouches = kSmallMaxTouches;   // touches a plan sorts in LDS
+// touches a plan sorts in LDS: the persistent update's most, and twice that
+// (136 KB of LDS) for planned launches
+constexpr int kPlanMaxTouches = 2 * kSmallMaxTouches;
 constexpr int32_t kPosMask = (1 << 30) - 1;
 constexpr int32_t kSingleBit = 1 << 30;  // row touched once in the minibatch: the forward updates it
 constexpr uint32_t kSpinLimit = 1u << 22;  // polls before a barrier wait gives up (seconds)
@@ -89,15 +93,38 @@ struct PlanArgs {
     uint64_t seed;
     NoiseTable noise;
     int32_t row_bits;              // n < 2^row_bits, at most 31
-    const MbDesc* desc;            // [minibatches of the launch]
+    const MbDesc* desc;            // [minibatches of the launch], or NULL: consecutive
+                                   // minibatches of `pairs` pairs of one chunk, from `first`
+    MbDesc first;
+    uint32_t pairs, chunk_pairs;
     int32_t tmax;                  // touch slots per minibatch, P (K + 2)
     int2* tinfo;                   // [mb][tmax]: (row, sorted position | kSingleBit), -1 skipped
-    int4* segs;                    // [mb][tmax]: (row, first position, touches, table)
-    int32_t* spair;                // [mb][tmax]: pair of each sorted position
-    uint32_t* meta;                // [mb][4]: applied segments, applied in segments,
+    int2* segs;                    // [mb][tmax / 2]: pack_seg of each segment, those of at
+                                   // most kChunk touches from the front, the others from the
+                                   // back
+    uint16_t* spair;               // [mb][tmax]: pair of each sorted position
+    uint32_t* meta;                // [mb][4]: segments of at most kChunk touches, longer ones,
                                    // out rows, out rows touched once
     unsigned long long* row_totals;// [3]: in rows, out rows, out rows touched once
 };
+
+// A segment: its row, and its first position (14 bits), its touches less one
+// (14 bits) and its table in one word.
+static_assert(kPlanMaxTouches <= 16384, "positions and touches of a segment take 14 bits");
+__device__ __forceinline__ int2 pack_seg(int32_t row, uint32_t start, uint32_t len, uint32_t out)
+{
+    return make_int2(row, (int32_t)(start | ((len - 1u) << 14) | (out << 28)));
+}
+struct Seg {
+    int32_t row, start, len;   // len 0: none
+    bool out;
+};
+constexpr int32_t kNoSeg = -1;
+__device__ __forceinline__ Seg unpack_seg(int2 s)
+{
+    if (s.x == kNoSeg) return Seg{0, 0, 0, false};
+    return Seg{s.x, s.y & 16383, ((s.y >> 14) & 16383) + 1, (s.y >> 28) != 0};
+}
 
 // Plans of one launch: workgroups [start[j], start[j + 1]) plan the
 // minibatches of job j (one model and corpus per job).
@@ -108,7 +135,6 @@ struct PlanBatch {
 };
 
 constexpr int kPlanWaves = kPlanThreads / 64;
-constexpr int kPlanRounds = kPlanMaxTouches / kPlanThreads;   // most touches per thread
 constexpr int kPlanBins = 256;                                // 8 key bits per sorting pass
 
 // Sorts the workgroup's touches by the low `bits` of key, stably: pass by
@@ -119,6 +145,7 @@ constexpr int kPlanBins = 256;                                // 8 key bits per 
 // with eight ballots, and its first peer adds their number to the wave's bin.
 // A bitonic network over the same 8,192 touches took 91 dependent passes
 // through LDS (196 us of a one-minibatch plan).
+template <int kPlanRounds>
 __device__ __forceinline__ void sort_touches(uint32_t (&key)[kPlanRounds],
                                              uint32_t (&touch)[kPlanRounds], int R, int bits,
                                              uint32_t* skey, uint16_t* stouch,
@@ -128,6 +155,9 @@ __device__ __forceinline__ void sort_touches(uint32_t (&key)[kPlanRounds],
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const unsigned long long lt = (1ull << lane) - 1ull;
     for (int shift = 0; shift < bits; shift += 8) {
+        // (opaque, so that the rounds' addresses are not all kept across passes)
+        uint32_t at0 = (uint32_t)(w * R * 64 + lane);
+        asm volatile("" : "+v"(at0));
         for (int b = lane; b < kPlanBins; b += 64) bins[w][b] = 0;
         uint32_t rank[kPlanRounds];   // touches of the same digit before this one in the wave
 #pragma unroll
@@ -149,6 +179,7 @@ __device__ __forceinline__ void sort_touches(uint32_t (&key)[kPlanRounds],
                 if (mine == 0) bins[w][d] = (uint16_t)(before + (uint32_t)__popcll(peers));
                 __builtin_amdgcn_wave_barrier();
             }
+            __builtin_amdgcn_sched_barrier(0);   // one round's ballots live at a time
         }
         __syncthreads();
         // thread b < 256: bin b's touches over the waves, then an exclusive scan over the bins
@@ -188,38 +219,48 @@ __device__ __forceinline__ void sort_touches(uint32_t (&key)[kPlanRounds],
 #pragma unroll
         for (int r = 0; r < kPlanRounds; ++r)
             if (r < R) {
-                const int at = (w * R + r) * 64 + lane;
-                key[r] = skey[at];
-                touch[r] = stouch[at];
+                key[r] = skey[at0 + 64 * r];
+                touch[r] = stouch[at0 + 64 * r];
             }
     }
 }
 
-template <int K>
+template <int K, int MAXT>
 __global__ __launch_bounds__(kPlanThreads) void sgns_plan_kernel(PlanBatch pb)
 {
     constexpr int T = K + 2;
+    constexpr int kPlanRounds = MAXT / kPlanThreads;   // most touches per thread
     int jb = 0;
     while (jb + 1 < pb.njobs && (int32_t)blockIdx.x >= pb.start[jb + 1]) ++jb;
     const PlanArgs& a = pb.job[jb];
     const uint32_t lb = blockIdx.x - (uint32_t)pb.start[jb];   // minibatch within the job's group
-    __shared__ uint32_t skey[kPlanMaxTouches + 1];
-    __shared__ uint16_t stouch[kPlanMaxTouches];
+    __shared__ uint32_t skey[MAXT + 1];
+    __shared__ uint16_t stouch[MAXT];
     __shared__ uint16_t bins[kPlanWaves][kPlanBins];
-    __shared__ uint16_t seg_lo[kPlanMaxTouches / 2], seg_hi[kPlanMaxTouches / 2];
+    __shared__ uint16_t seg_lo[MAXT / 2], seg_hi[MAXT / 2];
     __shared__ uint32_t wave_sum[kPlanWaves], wave_end[kPlanWaves];
-    __shared__ uint32_t counts[4];   // segments, in rows, out rows touched once, applied in segments
-    const MbDesc d = a.desc[lb];
-    const uint32_t nt = d.npairs * T;       // nt <= kPlanMaxTouches (checked on the host)
-    const int R = (int)((nt + kPlanThreads - 1) / kPlanThreads);
+    __shared__ uint32_t counts[5];   // rows, in rows, out rows touched once, segments of at most
+                                     // kChunk touches, longer ones
+    MbDesc d = a.first;
+    if (a.desc) {
+        d = a.desc[lb];
+    } else {
+        d.first_pair += lb * a.pairs;
+        d.npairs = min(a.pairs, a.chunk_pairs - d.first_pair);
+    }
+    const uint32_t nt = d.npairs * T;       // nt <= MAXT (checked on the host)
+    // rounds: as many as the minibatch needs, or all (with 16 conditional rounds
+    // the arrays below do not stay in registers)
+    const int R = MAXT > kSmallMaxTouches ? kPlanRounds
+                                          : (int)((nt + kPlanThreads - 1) / kPlanThreads);
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int2* tinfo = a.tinfo + (int64_t)lb * a.tmax;
-    int4* segs = a.segs + (int64_t)lb * a.tmax;
-    int32_t* spair = a.spair + (int64_t)lb * a.tmax;
+    int2* segs = a.segs + (int64_t)lb * (a.tmax / 2);
+    uint16_t* spair = a.spair + (int64_t)lb * a.tmax;
     const int32_t* vcols = a.vcols + d.vcol_base;
     const uint32_t none = (2u << a.row_bits) - 1u;   // above every real key
-    if (threadIdx.x < 4) counts[threadIdx.x] = 0;
+    if (threadIdx.x < 5) counts[threadIdx.x] = 0;
 
     // 1. each touch's key, table << row_bits | row.  One thread per pair: its
     //    walk reads and its negatives' guide entries are in flight together
@@ -292,7 +333,7 @@ __global__ __launch_bounds__(kPlanThreads) void sgns_plan_kernel(PlanBatch pb)
     if (threadIdx.x == 0) skey[(uint32_t)R * kPlanThreads] = none;
     __syncthreads();
     const unsigned long long lt = (1ull << lane) - 1ull;
-    uint32_t nfirst = 0, nlast = 0, c_seg = 0, c_in = 0, c_single = 0, c_inap = 0;
+    uint32_t nfirst = 0, nlast = 0, c_seg = 0, c_in = 0, c_single = 0;
     uint32_t bits_first = 0, bits_last = 0;   // per round: this lane starts / ends a segment
 #pragma unroll
     for (int r = 0; r < kPlanRounds; ++r)
@@ -306,12 +347,11 @@ __global__ __launch_bounds__(kPlanThreads) void sgns_plan_kernel(PlanBatch pb)
                 const uint32_t t = touch[r];
                 const int32_t row = (int32_t)(key[r] & ((1u << a.row_bits) - 1u));
                 tinfo[t] = make_int2(row, i | (first && last ? kSingleBit : 0));
-                spair[i] = (int32_t)(t / T);
+                spair[i] = (uint16_t)(t / T);
             }
             c_seg += first ? 1u : 0u;
             c_in += first && !out ? 1u : 0u;
             c_single += first && last && out ? 1u : 0u;
-            c_inap += first && !last && !out ? 1u : 0u;
             const bool f = first && !last, l = last && !first;
             bits_first |= (f ? 1u : 0u) << r;
             bits_last |= (l ? 1u : 0u) << r;
@@ -321,7 +361,6 @@ __global__ __launch_bounds__(kPlanThreads) void sgns_plan_kernel(PlanBatch pb)
     if (c_seg) atomicAdd(&counts[0], c_seg);
     if (c_in) atomicAdd(&counts[1], c_in);
     if (c_single) atomicAdd(&counts[2], c_single);
-    if (c_inap) atomicAdd(&counts[3], c_inap);
     if (lane == 0) {
         wave_sum[w] = nfirst;
         wave_end[w] = nlast;
@@ -346,15 +385,19 @@ __global__ __launch_bounds__(kPlanThreads) void sgns_plan_kernel(PlanBatch pb)
             at_last += (uint32_t)__popcll(ml);
         }
     __syncthreads();
+    // (the order of the lists does not matter: no two segments share a row)
     for (uint32_t q = threadIdx.x; q < n_apply; q += kPlanThreads) {
-        const uint32_t f = seg_lo[q], x = skey[f];
-        segs[q] = make_int4((int32_t)(x & ((1u << a.row_bits) - 1u)), (int32_t)f,
-                            (int32_t)(seg_hi[q] - f + 1u), (int32_t)(x >> a.row_bits));
+        const uint32_t f = seg_lo[q], x = skey[f], len = seg_hi[q] - f + 1u;
+        const bool is_long = len > (uint32_t)kChunk;
+        const uint32_t at = atomicAdd(&counts[is_long ? 4 : 3], 1u);
+        segs[is_long ? (uint32_t)(a.tmax / 2) - 1u - at : at] =
+            pack_seg((int32_t)(x & ((1u << a.row_bits) - 1u)), f, len, x >> a.row_bits);
     }
+    __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t* m = a.meta + (int64_t)lb * 4;
-        m[0] = n_apply;
-        m[1] = counts[3];
+        m[0] = counts[3];
+        m[1] = counts[4];
         m[2] = counts[0] - counts[1];
         m[3] = counts[2];
         atomicAdd(&a.row_totals[0], (unsigned long long)counts[1]);
@@ -370,9 +413,9 @@ struct UpdJob {
     float* tout;
     const MbDesc* desc;            // [nmb]
     const int2* tinfo;             // [nmb][tmax]
-    const int4* segs;              // [nmb][tmax]
+    const int2* segs;              // [nmb][tmax / 2]
     const uint32_t* meta;          // [nmb][4]
-    const int32_t* spair;          // [nmb][tmax]: pair of each sorted position
+    const uint16_t* spair;         // [nmb][tmax]: pair of each sorted position
     double* gpos;                  // [tmax]: FP64 coefficient of each out-touch, by position
     float* dinp;                   // [P][D]: each pair's in-row delta, by sorted position
     float* ctxc;                   // [P][D]: each pair's context row at the minibatch start
@@ -532,85 +575,177 @@ __device__ __forceinline__ void forward_pairs(const UpdJob& J, uint32_t npairs, 
     }
 }
 
-// Adds the sum of a segment's terms to its row: one 16-lane group.  pair0: the
-// pair of each of the first 16 touches (out segments).  A whole wave per
-// segment, with all 16 touches in flight, was slower (the apply 1.1 -> 3.2 us
-// per workgroup on R-MAT 2^20, 2.9 -> 9.6 on 1,000 nodes).
-template <int D, RowAccess A>
-__device__ __forceinline__ void apply_segment(const UpdJob& J, const int32_t* sp, int4 seg,
-                                              bool out, int32_t pair0, double gc)
+// Rows in flight per 16-lane group of an apply: 8 of up to 16 float2s per lane.
+template <int D>
+constexpr int apply_rows() { return D == 256 ? 4 : 8; }
+
+// Coefficient of the out-touch at a sorted position.
+template <RowAccess A>
+__device__ __forceinline__ double load_coef(const double* p)
+{
+    if constexpr (A == kAgent)
+        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+        return *p;
+}
+
+// Adds to acc the terms of touches [i0, i0 + R) of a 16-lane group's nb.
+// g, src: in lane l of the group, touch l's coefficient and source row (out
+// rows: its pair's context copy; in rows: 1 and the pair's delta).  No load is
+// issued for slots past nb: pointing them at row 0 made every short segment
+// read the same line, which queued in one memory channel.
+template <int D, RowAccess A, int R, bool EXACT>
+__device__ __forceinline__ void add_terms(const float* srcb, double g, int32_t src, int32_t i0,
+                                          int32_t nb, double gc, double (&acc)[D / 16])
 {
     constexpr int V = D / 32;        // float2s per lane and row
-    constexpr int kRows = 4;         // rows in flight
-    const int lane = threadIdx.x & 63;
-    const int g0 = lane & 48, l16 = lane & 15;
-    const int32_t row = seg.x, start = seg.y, len = seg.z;
-    f2* const table = reinterpret_cast<f2*>((out ? J.tout : J.tin) + (int64_t)row * D);
-    const float* const srcb = out ? J.ctxc : J.dinp;
-    f2 cur[V];
+    const int g0 = threadIdx.x & 48, l16 = threadIdx.x & 15;
+    f2 x[R][V];
 #pragma unroll
-    for (int i = 0; i < V; ++i) cur[i] = load_row2<A>(table + i * 16 + l16);
-    double acc[2 * V];
+    for (int u = 0; u < R; ++u) {
+        const int32_t rr = __shfl(src, g0 + min(i0 + u, 15));
+        const f2* rp = reinterpret_cast<const f2*>(srcb + (int64_t)rr * D);
 #pragma unroll
-    for (int e = 0; e < 2 * V; ++e) acc[e] = 0.0;
-    const bool exact = len > kChunk;
-    // touches in batches of 16, one descriptor per lane
-    for (int32_t b0 = 0; b0 < len; b0 += 16) {
-        const int32_t nb = min(16, len - b0);
-        // out rows: the touch's coefficient and its pair's context copy; in
-        // rows: the pair's delta at the touch's position
-        double my_g = 1.0;
-        int32_t my_src = start + b0 + l16;
-        if (out && l16 < nb) {
-            const double* gp = &J.gpos[start + b0 + l16];
-            if constexpr (A == kAgent)
-                my_g = __hip_atomic_load(gp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            else
-                my_g = *gp;
-            my_src = b0 == 0 ? pair0 : sp[start + b0 + l16];
+        for (int i = 0; i < V; ++i) x[u][i] = f2{0.0f, 0.0f};
+        if (i0 + u < nb) {
+#pragma unroll
+            for (int i = 0; i < V; ++i) x[u][i] = load_row2<A>(rp + i * 16 + l16);
         }
-        for (int32_t i0 = 0; i0 < nb; i0 += kRows) {
-            double gg[kRows];
-            f2 x[kRows][V];
-            // no load is issued for slots past the segment's end: pointing them
-            // at row 0 made every short segment read the same line, which
-            // queued in one memory channel
+    }
+    double gg[R];
 #pragma unroll
-            for (int u = 0; u < kRows; ++u) {
-                const bool ok = i0 + u < nb;
-                const int32_t rr = __shfl(my_src, g0 + min(i0 + u, 15));
-                const f2* rp = reinterpret_cast<const f2*>(srcb + (int64_t)rr * D);
+    for (int u = 0; u < R; ++u) gg[u] = __shfl(g, g0 + min(i0 + u, 15));
 #pragma unroll
-                for (int i = 0; i < V; ++i) x[u][i] = f2{0.0f, 0.0f};
-                if (ok) {
+    for (int u = 0; u < R; ++u) {
+        if (i0 + u >= nb) break;
 #pragma unroll
-                    for (int i = 0; i < V; ++i) x[u][i] = load_row2<A>(rp + i * 16 + l16);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kRows; ++u) gg[u] = __shfl(my_g, g0 + min(i0 + u, 15));
-#pragma unroll
-            for (int u = 0; u < kRows; ++u) {
-                if (i0 + u >= nb) break;
-#pragma unroll
-                for (int i = 0; i < V; ++i) {
-                    if (exact) {
-                        // order-free: each term rounded onto the grid, sums exact
-                        acc[2 * i] += on_grid(gg[u] * (double)x[u][i].x, gc);
-                        acc[2 * i + 1] += on_grid(gg[u] * (double)x[u][i].y, gc);
-                    } else {
-                        // in rows: g = 1, and 1 * x + acc is exactly x + acc
-                        acc[2 * i] = fma(gg[u], (double)x[u][i].x, acc[2 * i]);
-                        acc[2 * i + 1] = fma(gg[u], (double)x[u][i].y, acc[2 * i + 1]);
-                    }
-                }
+        for (int i = 0; i < V; ++i) {
+            if (EXACT) {
+                // order-free: each term rounded onto the grid, sums exact
+                acc[2 * i] += on_grid(gg[u] * (double)x[u][i].x, gc);
+                acc[2 * i + 1] += on_grid(gg[u] * (double)x[u][i].y, gc);
+            } else {
+                // in rows: g = 1, and 1 * x + acc is exactly x + acc
+                acc[2 * i] = fma(gg[u], (double)x[u][i].x, acc[2 * i]);
+                acc[2 * i + 1] = fma(gg[u], (double)x[u][i].y, acc[2 * i + 1]);
             }
         }
     }
+}
+
+// Adds a segment's terms, in touch order, to its row: one 16-lane group, at
+// most kChunk touches (none: len 0).  pair0: in lane l, the pair of touch l
+// (out segments).  A whole wave per segment, with all 16 touches in flight,
+// was slower (the apply 1.1 -> 3.2 us per workgroup on R-MAT 2^20, 2.9 -> 9.6
+// on 1,000 nodes).
+template <int D, RowAccess A>
+__device__ __forceinline__ void apply_short(const UpdJob& J, const Seg& seg, int32_t pair0)
+{
+    constexpr int V = D / 32, R = apply_rows<D>();
+    if (seg.len == 0) return;        // whole groups leave
+    const int l16 = threadIdx.x & 15;
+    f2* const table = reinterpret_cast<f2*>((seg.out ? J.tout : J.tin) + (int64_t)seg.row * D);
+    f2 cur[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) cur[i] = load_row2<A>(table + i * 16 + l16);
+    const double g = seg.out && l16 < seg.len ? load_coef<A>(&J.gpos[seg.start + l16]) : 1.0;
+    const int32_t src = seg.out ? pair0 : seg.start + l16;
+    double acc[2 * V];
+#pragma unroll
+    for (int e = 0; e < 2 * V; ++e) acc[e] = 0.0;
+    for (int32_t i0 = 0; i0 < seg.len; i0 += R)
+        add_terms<D, A, R, false>(seg.out ? J.ctxc : J.dinp, g, src, i0, seg.len, 0.0, acc);
 #pragma unroll
     for (int i = 0; i < V; ++i)
         store_row2<A>(table + i * 16 + l16, f2{(float)((double)cur[i].x + acc[2 * i]),
                                                (float)((double)cur[i].y + acc[2 * i + 1])});
+}
+
+// A segment of more than kChunk touches: the whole workgroup, whose 16-lane
+// groups take 16 touches each in turn.  The terms are rounded onto the
+// exact-sum grid, so the groups' sums add up in any order.  A hub's segment
+// (hundreds of touches of a 1,024-pair minibatch on a power-law graph of 700
+// nodes) took one group 20 us.  part: NW D doubles of LDS.
+template <int D, RowAccess A, int NW>
+__device__ __forceinline__ void apply_long(const UpdJob& J, const uint16_t* sp, const Seg& seg,
+                                           double gc, double* part)
+{
+    constexpr int V = D / 32, R = apply_rows<D>();
+    const int lane = threadIdx.x & 63, l16 = lane & 15;
+    f2* const table = reinterpret_cast<f2*>((seg.out ? J.tout : J.tin) + (int64_t)seg.row * D);
+    f2 cur = f2{0.0f, 0.0f};
+    if (threadIdx.x < D / 2) cur = load_row2<A>(table + threadIdx.x);
+    double acc[2 * V];
+#pragma unroll
+    for (int e = 0; e < 2 * V; ++e) acc[e] = 0.0;
+    for (int32_t b0 = (int32_t)(threadIdx.x >> 4) * 16; b0 < seg.len; b0 += NW * 64) {
+        const int32_t nb = min(16, seg.len - b0), at = seg.start + b0 + l16;
+        double g = 1.0;
+        int32_t src = at;
+        if (seg.out && l16 < nb) {
+            g = load_coef<A>(&J.gpos[at]);
+            src = sp[at];
+        }
+        for (int32_t i0 = 0; i0 < nb; i0 += R)
+            add_terms<D, A, R, true>(seg.out ? J.ctxc : J.dinp, g, src, i0, nb, gc, acc);
+    }
+#pragma unroll
+    for (int e = 0; e < 2 * V; ++e) acc[e] = xor_sum<32>(xor_sum<16>(acc[e]));
+    double* mine = part + (threadIdx.x >> 6) * D;
+    if (lane < 16)
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            mine[2 * (i * 16 + l16)] = acc[2 * i];
+            mine[2 * (i * 16 + l16) + 1] = acc[2 * i + 1];
+        }
+    __syncthreads();
+    if (threadIdx.x < D / 2) {
+        double x = 0.0, y = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            x += part[w * D + 2 * threadIdx.x];
+            y += part[w * D + 2 * threadIdx.x + 1];
+        }
+        store_row2<A>(table + threadIdx.x, f2{(float)((double)cur.x + x), (float)((double)cur.y + y)});
+    }
+    __syncthreads();
+}
+
+// Item `item` of minibatch m's apply: a long segment, or one short segment
+// per 16-lane group.  Items [0, n_long) are the long ones.
+template <int NW>
+__device__ __forceinline__ int2 short_seg(const UpdJob& J, int m, uint32_t item)
+{
+    const uint32_t nshort = J.meta[(int64_t)m * 4], nlong = J.meta[(int64_t)m * 4 + 1];
+    const uint32_t q = (item - nlong) * (NW * 4) + (threadIdx.x >> 4);
+    return item >= nlong && q < nshort ? J.segs[(int64_t)m * (J.tmax / 2) + q] : make_int2(kNoSeg, 0);
+}
+__device__ __forceinline__ int32_t short_pair(const UpdJob& J, int m, const Seg& sd)
+{
+    const int l16 = threadIdx.x & 15;
+    return sd.out && l16 < sd.len ? J.spair[(int64_t)m * J.tmax + sd.start + l16] : 0;
+}
+
+// Every item of minibatch m from `first` on.  ahead, pair0: short_seg and
+// short_pair of the first item.
+template <int D, RowAccess A, int NW>
+__device__ __forceinline__ void apply_items(const UpdJob& J, int m, uint32_t first, uint32_t stride,
+                                            int2 ahead, int32_t pair0, double gc, double* part)
+{
+    const uint32_t nshort = J.meta[(int64_t)m * 4], nlong = J.meta[(int64_t)m * 4 + 1];
+    const uint32_t items = nlong + (nshort + NW * 4 - 1) / (NW * 4);
+    for (uint32_t item = first; item < items; item += stride) {
+        if (item < nlong) {
+            const Seg sd = unpack_seg(J.segs[(int64_t)m * (J.tmax / 2) + (J.tmax / 2) - 1 - item]);
+            apply_long<D, A, NW>(J, J.spair + (int64_t)m * J.tmax, sd, gc, part);
+            continue;
+        }
+        if (item != first) {
+            ahead = short_seg<NW>(J, m, item);
+            pair0 = short_pair(J, m, unpack_seg(ahead));
+        }
+        apply_short<D, A>(J, unpack_seg(ahead), pair0);
+    }
 }
 
 // Steps of pairs per forward batch of the persistent update: two pairs per
@@ -623,8 +758,9 @@ __global__ __launch_bounds__(kUpdThreads) void sgns_small_update_kernel(UpdArgs 
 {
     constexpr int S = upd_steps<D, K>();
     constexpr uint32_t G = S * FwdShape<D, K>::kHalves;   // pairs per wave at a time
+    constexpr int NW = kUpdThreads / 64;
+    __shared__ double part[NW * D];
     const int lane = threadIdx.x & 63;
-    const int g16 = lane >> 4, l16 = lane & 15;
     const uint32_t nw = gridDim.x * (blockDim.x >> 6);
     const uint32_t gw = blockIdx.x * (blockDim.x >> 6) +
                         (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -636,7 +772,6 @@ __global__ __launch_bounds__(kUpdThreads) void sgns_small_update_kernel(UpdArgs 
     const UpdJob& J0 = a.job[0];
     int2 pf_touch = J0.nmb > 0 ? touch_of<K>(J0, 0, J0.desc[0].npairs, gw * G, G)
                                : make_int2(-1, -1);
-    const uint32_t sidx0 = gw * 4 + (uint32_t)g16;
     // phase clocks (thread 0 of each workgroup, when asked for), kept in LDS:
     // [0..3] ticks of the phases summed over the launch's minibatches (added
     // to the totals once at the end), [4] phase start, [5] barrier arrival,
@@ -647,11 +782,10 @@ __global__ __launch_bounds__(kUpdThreads) void sgns_small_update_kernel(UpdArgs 
         for (int i = 0; i < 4; ++i) s_clk[i] = 0;
     for (int m = 0; m < a.nmb_max; ++m) {
         if (clk) s_clk[4] = wall_clock64();
-        int4 pf_seg = make_int4(0, 0, 0, 0);
+        int2 pf_seg = make_int2(kNoSeg, 0);
         int32_t pf_pair = 0;
         if (m < J0.nmb) {
-            const uint32_t nseg0 = J0.meta[(int64_t)m * 4];
-            if (sidx0 < nseg0) pf_seg = J0.segs[(int64_t)m * J0.tmax + sidx0];
+            pf_seg = short_seg<NW>(J0, m, blockIdx.x);
         }
 
         // ---- forward of every job's minibatch m: G pairs per wave at a time
@@ -671,7 +805,7 @@ __global__ __launch_bounds__(kUpdThreads) void sgns_small_update_kernel(UpdArgs 
                 lacc = 0.0;
             }
         }
-        if (pf_seg.z > l16) pf_pair = J0.spair[(int64_t)m * J0.tmax + pf_seg.y + l16];
+        pf_pair = short_pair(J0, m, unpack_seg(pf_seg));
         if (!grid_sync(a, epoch, clk ? &s_clk[5] : nullptr)) break;
         if (clk) {
             s_clk[6] = wall_clock64();
@@ -679,23 +813,19 @@ __global__ __launch_bounds__(kUpdThreads) void sgns_small_update_kernel(UpdArgs 
             s_clk[1] += s_clk[6] - s_clk[5];
         }
 
-        // ---- apply: one 16-lane group per segment, in and out rows together
+        // ---- apply: in and out rows together
         if (m + 1 < J0.nmb) pf_touch = touch_of<K>(J0, m + 1, J0.desc[m + 1].npairs, gw * G, G);
         for (int j = 0; j < a.njobs; ++j) {
             const UpdJob& J = a.job[j];
             if (m >= J.nmb) continue;
-            const int32_t* sp = J.spair + (int64_t)m * J.tmax;
-            const uint32_t nseg = J.meta[(int64_t)m * 4], nin = J.meta[(int64_t)m * 4 + 1];
-            const int4* sg = J.segs + (int64_t)m * J.tmax;
-            const double gc = J.desc[m].grid_c;
-            for (uint32_t sidx = sidx0; sidx < nseg; sidx += nw * 4) {
-                const bool ahead = j == 0 && sidx == sidx0;
-                const int4 sd = ahead ? pf_seg : sg[sidx];
-                const bool out = sidx >= nin;
-                int32_t pair = pf_pair;
-                if (!ahead) pair = out && l16 < sd.z ? sp[sd.y + l16] : 0;
-                apply_segment<D, kAgent>(J, sp, sd, out, pair, gc);
+            int2 seg = pf_seg;
+            int32_t pair = pf_pair;
+            if (j > 0) {
+                seg = short_seg<NW>(J, m, blockIdx.x);
+                pair = short_pair(J, m, unpack_seg(seg));
             }
+            apply_items<D, kAgent, NW>(J, m, blockIdx.x, gridDim.x, seg, pair, J.desc[m].grid_c,
+                                       part);
         }
         if (!grid_sync(a, epoch, clk ? &s_clk[5] : nullptr)) break;
         if (clk) {
@@ -709,6 +839,38 @@ __global__ __launch_bounds__(kUpdThreads) void sgns_small_update_kernel(UpdArgs 
         lacc = wave_total(lacc);
         if (lane == 0) J0.loss_part[gw] += lacc;
     }
+}
+
+// ------------------------------------------------- planned launches
+// One minibatch's forward and apply as launches of their own, for callers that
+// want no persistent launch (update path 1, serving jobs on streams of their
+// own): two launches per minibatch with the plans of many made ahead, where
+// ids, two scan passes, forward and two applies were six.  Jobs of 700 to
+// 1,400 nodes (d = 64, K = 5, P = 1,024 and 2,048, one stream): 37 -> 14 us per
+// minibatch, of which plans of ten minibatches per launch are 3 to 5.5.  Taken
+// up to the 16,384 touches a plan sorts in LDS.
+template <int D, int K>
+__global__ __launch_bounds__(256) void sgns_planned_forward_kernel(UpdJob J, int32_t m,
+                                                                   uint32_t npairs, float lr)
+{
+    constexpr uint32_t H = FwdShape<D, K>::kHalves;
+    const uint32_t gw = blockIdx.x * 4 + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t q0 = gw * H;
+    if (q0 >= npairs) return;
+    double lacc = 0.0;
+    forward_pairs<D, K, 1, kPlain>(J, npairs, q0, touch_of<K>(J, m, npairs, q0, H), (double)lr,
+                                   lacc);
+    lacc = wave_total(lacc);
+    if ((threadIdx.x & 63) == 0) J.loss_part[gw] += lacc;
+}
+
+template <int D>
+__global__ __launch_bounds__(256) void sgns_planned_apply_kernel(UpdJob J, int32_t m, double gc)
+{
+    __shared__ double part[4 * D];
+    const int2 seg = short_seg<4>(J, m, blockIdx.x);
+    apply_items<D, kPlain, 4>(J, m, blockIdx.x, gridDim.x, seg, short_pair(J, m, unpack_seg(seg)),
+                              gc, part);
 }
 
 __global__ void zero_words_kernel(uint32_t* p, int32_t n)
@@ -731,7 +893,7 @@ static bool small_touches_fit_wave(int d, int K)
 bool small_path_applies(const Model& m, const felog_train_params& p)
 {
     return m.precision == FELOG_PREC_FP32 && m.ctx->sgns_path == 0 &&
-           p.minibatch_pairs * (p.negatives + 2) <= kPlanMaxTouches && p.negatives <= 20 &&
+           p.minibatch_pairs * (p.negatives + 2) <= kSmallMaxTouches && p.negatives <= 20 &&
            small_touches_fit_wave(m.dim, p.negatives);
 }
 
@@ -780,10 +942,16 @@ static void* update_kernel(int D, int K)
 
 static void launch_plan(int K, int nblocks, const PlanBatch& pb, hipStream_t s)
 {
+    const bool wide = pb.job[0].tmax > kSmallMaxTouches;   // one job per such launch
     switch (K) {
 #define FELOG_CASE(k)                                                                          \
     case k:                                                                                    \
-        hipLaunchKernelGGL((sgns_plan_kernel<k>), dim3(nblocks), dim3(kPlanThreads), 0, s, pb); \
+        if (wide)                                                                              \
+            hipLaunchKernelGGL((sgns_plan_kernel<k, kPlanMaxTouches>), dim3(nblocks),          \
+                               dim3(kPlanThreads), 0, s, pb);                                  \
+        else                                                                                   \
+            hipLaunchKernelGGL((sgns_plan_kernel<k, kSmallMaxTouches>), dim3(nblocks),         \
+                               dim3(kPlanThreads), 0, s, pb);                                  \
         break;
         FELOG_CASE(1) FELOG_CASE(2) FELOG_CASE(3) FELOG_CASE(4) FELOG_CASE(5) FELOG_CASE(6)
         FELOG_CASE(7) FELOG_CASE(8) FELOG_CASE(9) FELOG_CASE(10) FELOG_CASE(11) FELOG_CASE(12)
@@ -795,30 +963,48 @@ static void launch_plan(int K, int nblocks, const PlanBatch& pb, hipStream_t s)
     FELOG_HIP(hipGetLastError());
 }
 
-// Model-owned buffers of the persistent path, grown on demand: two sets of
-// plan buffers for 64 minibatches (the plans of launch group i + 1 are
+// Model-owned buffers of the planned paths, grown on demand: plans of `plans`
+// minibatches (two sets of a launch group: the plans of group i + 1 are
 // written while the update of group i reads set i mod 2), the out-touch
 // coefficients, and each pair's in-row delta and context copy.
-static void small_buffers(Model& m, int64_t P, int32_t tmax)
+static void small_buffers(Model& m, int64_t P, int32_t tmax, int64_t plans)
 {
     Ctx& c = *m.ctx;
-    const int64_t G = small_minibatches_per_launch();
     const int D = m.dim;
-    if (m.sm_tmax < tmax || m.sm_G < 2 * G) {
-        m.sm_tmax = std::max<int64_t>(m.sm_tmax, tmax);
-        m.sm_G = std::max<int64_t>(m.sm_G, 2 * G);
-        m.sm_tinfo.alloc(&c, sizeof(int2) * m.sm_tmax * m.sm_G);
-        m.sm_segs.alloc(&c, sizeof(int4) * m.sm_tmax * m.sm_G);
-        m.sm_meta.alloc(&c, sizeof(uint32_t) * 4 * m.sm_G);
-        m.sm_spair.alloc(&c, sizeof(int32_t) * m.sm_tmax * m.sm_G);
-        m.sm_gpos.alloc(&c, sizeof(double) * m.sm_tmax);
+    if (m.sm_tmax < tmax || m.sm_G < plans) {
+        const int64_t t = std::max<int64_t>(m.sm_tmax, tmax), g = std::max<int64_t>(m.sm_G, plans);
+        m.sm_tmax = m.sm_G = 0;   // an allocation that fails leaves no stale capacity
+        m.sm_tinfo.alloc(&c, sizeof(int2) * t * g);
+        m.sm_segs.alloc(&c, sizeof(int2) * (t / 2) * g);
+        m.sm_meta.alloc(&c, sizeof(uint32_t) * 4 * g);
+        m.sm_spair.alloc(&c, sizeof(uint16_t) * t * g);
+        m.sm_gpos.alloc(&c, sizeof(double) * t);
+        m.sm_tmax = t;
+        m.sm_G = g;
     }
     if (m.sm_pairs < P || m.sm_dim != D) {
-        m.sm_pairs = std::max<int64_t>(m.sm_pairs, P);
+        const int64_t n = std::max<int64_t>(m.sm_pairs, P);
+        m.sm_pairs = 0;
+        m.sm_dinp.alloc(&c, sizeof(float) * n * D);
+        m.sm_ctxc.alloc(&c, sizeof(float) * n * D);
+        m.sm_pairs = n;
         m.sm_dim = D;
-        m.sm_dinp.alloc(&c, sizeof(float) * m.sm_pairs * D);
-        m.sm_ctxc.alloc(&c, sizeof(float) * m.sm_pairs * D);
     }
+}
+
+static void release_small_buffers(Model& m)
+{
+    for (DevBuf* b : {&m.sm_tinfo, &m.sm_segs, &m.sm_meta, &m.sm_spair, &m.sm_gpos, &m.sm_dinp,
+                      &m.sm_ctxc})
+        b->release();
+    m.sm_tmax = m.sm_G = m.sm_pairs = 0;
+}
+
+// Bytes of one minibatch's plan, and of what a call holds beside its plans.
+static uint64_t plan_bytes(int64_t T) { return (uint64_t)(8 + 4 + 2) * T + 16; }
+static uint64_t planned_fixed_bytes(int64_t P, int K, int d)
+{
+    return 8 * (uint64_t)(P * (K + 2)) + 2 * 4 * (uint64_t)P * d + 8 * ((uint64_t)P + 1);
 }
 
 // Plan arguments of a training call (plan set 0; the caller offsets them).
@@ -839,8 +1025,8 @@ static PlanArgs plan_args(Model& m, Walks& w, const felog_train_params& p,
     while (((int64_t)1 << pa.row_bits) <= m.g->n) ++pa.row_bits;
     pa.tmax = tmax;
     pa.tinfo = m.sm_tinfo.as<int2>();
-    pa.segs = m.sm_segs.as<int4>();
-    pa.spair = m.sm_spair.as<int32_t>();
+    pa.segs = m.sm_segs.as<int2>();
+    pa.spair = m.sm_spair.as<uint16_t>();
     pa.meta = m.sm_meta.as<uint32_t>();
     pa.row_totals = m.row_totals.as<unsigned long long>();
     return pa;
@@ -928,7 +1114,7 @@ static PlanArgs group_plan(const SmallJob& j, int64_t b)
     PlanArgs pl = j.pa;
     pl.desc = j.ddesc.as<MbDesc>() + b;
     pl.tinfo = j.pa.tinfo + set * G * j.tmax;
-    pl.segs = j.pa.segs + set * G * j.tmax;
+    pl.segs = j.pa.segs + set * G * (j.tmax / 2);
     pl.spair = j.pa.spair + set * G * j.tmax;
     pl.meta = j.pa.meta + set * G * 4;
     return pl;
@@ -957,7 +1143,7 @@ static void plan_next_group(SmallJob& j)
 bool small_job_fits(const Model& m, const felog_train_params& p)
 {
     return m.precision == FELOG_PREC_FP32 && p.negatives <= 20 &&
-           p.minibatch_pairs * (p.negatives + 2) <= kPlanMaxTouches &&
+           p.minibatch_pairs * (p.negatives + 2) <= kSmallMaxTouches &&
            (m.dim == 64 || m.dim == 128 || m.dim == 256) && small_touches_fit_wave(m.dim, p.negatives);
 }
 
@@ -975,7 +1161,7 @@ SmallJobPtr small_job_begin(Model& m, Walks& w, const felog_train_params& p, int
     j->tmax = (int32_t)(p.minibatch_pairs * (p.negatives + 2));
     j->end = j->sch.B;
     j->nwaves = nblocks * (kUpdThreads / 64);
-    small_buffers(m, p.minibatch_pairs, j->tmax);
+    small_buffers(m, p.minibatch_pairs, j->tmax, 2 * small_minibatches_per_launch());
     const std::vector<int32_t> sl = train_slices(w.L, p.window);
     j->slices.alloc(&c, sizeof(int32_t) * std::max<size_t>(sl.size(), 1));
     if (!sl.empty())
@@ -1108,7 +1294,7 @@ void train_minibatches_small(Model& m, Walks& w, const felog_train_params& p,
     const int D = m.dim;
     const int64_t P = p.minibatch_pairs;
     const int32_t tmax = (int32_t)(P * (K + 2));
-    FELOG_REQUIRE(tmax <= kPlanMaxTouches, "minibatch of %lld pairs is too large for the "
+    FELOG_REQUIRE(tmax <= kSmallMaxTouches, "minibatch of %lld pairs is too large for the "
                   "small-minibatch update", (long long)P);
     FELOG_REQUIRE(D == 64 || D == 128 || D == 256, "dim %d not supported", D);
     const int64_t G = small_minibatches_per_launch();
@@ -1116,7 +1302,7 @@ void train_minibatches_small(Model& m, Walks& w, const felog_train_params& p,
     const int nblocks = small_update_blocks(c, D, K);
     const int nwaves = nblocks * (kUpdThreads / 64);
 
-    small_buffers(m, P, tmax);
+    small_buffers(m, P, tmax, 2 * G);
     // control words: barrier flags (an unused line, then one per workgroup,
     // each on its own 128-byte line), the abort flag on the next line, then
     // the loss partials, one per wave, and the four phase-clock sums
@@ -1199,7 +1385,7 @@ void train_minibatches_small(Model& m, Walks& w, const felog_train_params& p,
         PlanArgs pl = pa;
         pl.desc = ddesc.as<MbDesc>() + (g0 - first_mb);
         pl.tinfo = pa.tinfo + (int64_t)set * G * tmax;
-        pl.segs = pa.segs + (int64_t)set * G * tmax;
+        pl.segs = pa.segs + (int64_t)set * G * (tmax / 2);
         pl.spair = pa.spair + (int64_t)set * G * tmax;
         pl.meta = pa.meta + (int64_t)set * G * 4;
         PlanBatch pb{};
@@ -1278,6 +1464,244 @@ void train_minibatches_small(Model& m, Walks& w, const felog_train_params& p,
                 stats->us_phase[i] = khz > 0 ? (double)ticks[i] / per : 0.0;
         }
     }
+}
+
+// ---------------------------------------------------- planned launches, host
+template <int D>
+static void launch_planned_forward_d(int K, const UpdJob& J, int32_t m, uint32_t np, float lr,
+                                     hipStream_t s)
+{
+    const uint32_t per_block = 4 * (D == 64 ? 2 : 1);   // pairs
+    const dim3 grid((np + per_block - 1) / per_block);
+    switch (K) {
+#define FELOG_CASE(k)                                                                            \
+    case k:                                                                                      \
+        hipLaunchKernelGGL((sgns_planned_forward_kernel<D, k>), grid, dim3(256), 0, s, J, m, np, lr); \
+        break;
+        FELOG_CASE(1) FELOG_CASE(2) FELOG_CASE(3) FELOG_CASE(4) FELOG_CASE(5) FELOG_CASE(6)
+        FELOG_CASE(7) FELOG_CASE(8) FELOG_CASE(9) FELOG_CASE(10) FELOG_CASE(11) FELOG_CASE(12)
+        FELOG_CASE(13) FELOG_CASE(14) FELOG_CASE(15) FELOG_CASE(16) FELOG_CASE(17)
+        FELOG_CASE(18) FELOG_CASE(19) FELOG_CASE(20)
+#undef FELOG_CASE
+        default: fail(FELOG_EUNSUPPORTED, "negatives = %d not supported", K);
+    }
+}
+
+// Trains [first_mb, end) with planned launches; false (nothing done) when the
+// minibatches are too large for a plan or the context's budget or the card
+// has no room for the plans of one.
+bool train_minibatches_planned(Model& m, Walks& w, const felog_train_params& p,
+                               const TrainSchedule& sch, const int32_t* d_slices,
+                               int64_t first_mb, int64_t end, felog_train_stats* stats)
+{
+    Ctx& c = *m.ctx;
+    const int K = p.negatives, D = m.dim;
+    const int64_t P = p.minibatch_pairs;
+    if (m.precision != FELOG_PREC_FP32 || K > 20 || P * (K + 2) > kPlanMaxTouches) return false;
+    const int32_t tmax = (int32_t)(P * (K + 2));
+    const int64_t B = std::max<int64_t>(1, end - first_mb);
+    // launch groups: one set of plans when everything is on one stream
+    const int64_t sets = c.single_stream ? 1 : 2;
+    int64_t G = std::min<int64_t>(small_minibatches_per_launch(), B);
+    if (c.budget) {
+        uint64_t held = 0;   // plan buffers of earlier calls, which a larger set replaces
+        for (const DevBuf* b : {&m.sm_tinfo, &m.sm_segs, &m.sm_meta, &m.sm_spair, &m.sm_gpos,
+                                &m.sm_dinp, &m.sm_ctxc})
+            held += b->bytes;
+        const uint64_t room = c.budget + held - std::min(c.budget + held, c.in_use);
+        const uint64_t fixed = planned_fixed_bytes(P, K, D) + 4096;
+        if (room < fixed + sets * plan_bytes(tmax)) return false;
+        G = std::min<int64_t>(G, (int64_t)((room - fixed) / (sets * plan_bytes(tmax))));
+        if (m.sm_tmax < tmax || m.sm_G < sets * G || m.sm_pairs < P) release_small_buffers(m);
+    }
+    const int64_t side = D == 64 ? 2 : 1;
+    const int64_t nwaves = (P + side - 1) / side;
+    DevBuf loss_part;
+    try {
+        small_buffers(m, P, tmax, sets * G);
+        loss_part.alloc(&c, sizeof(double) * nwaves);
+    } catch (const Error& e) {
+        if (e.code != FELOG_ENOMEM) throw;
+        (void)hipGetLastError();
+        clear_error();
+        release_small_buffers(m);
+        return false;
+    }
+    int64_t pairs = 0;
+    const std::vector<MbDesc> desc = mb_descs(w, p, sch, first_mb, end, G, nullptr, &pairs);
+    // launch groups: up to G consecutive minibatches of one chunk
+    struct Group {
+        int64_t first, end;
+        size_t chunk;
+    };
+    std::vector<Group> groups;
+    {
+        size_t chunk = 0;
+        for (int64_t b = first_mb; b < end;) {
+            while (chunk + 1 < sch.chunk_first_mb.size() && sch.chunk_first_mb[chunk + 1] <= b) ++chunk;
+            int64_t e = std::min(end, b + G);
+            if (chunk + 1 < sch.chunk_first_mb.size())
+                e = std::min<int64_t>(e, sch.chunk_first_mb[chunk + 1]);
+            groups.push_back(Group{b, e, chunk});
+            b = e;
+        }
+    }
+    FELOG_HIP(hipMemsetAsync(loss_part.ptr, 0, loss_part.bytes, c.stream));
+    FELOG_HIP(hipMemsetAsync(m.row_totals.ptr, 0, sizeof(uint64_t) * 3, c.stream));
+    const PlanArgs pa = plan_args(m, w, p, d_slices, tmax);
+    UpdJob uj{};
+    uj.tin = m.tin.as<float>();
+    uj.tout = m.tout.as<float>();
+    uj.tmax = tmax;
+    uj.gpos = m.sm_gpos.as<double>();
+    uj.dinp = m.sm_dinp.as<float>();
+    uj.ctxc = m.sm_ctxc.as<float>();
+    uj.loss_part = loss_part.as<double>();
+    // a segment has two touches or more, and each table row at most one segment
+    const int64_t segs = std::min<int64_t>(tmax / 2 + 1, 2 * (int64_t)m.g->n);
+    const int64_t items = (segs + 15) / 16 + std::min<int64_t>(tmax / kChunk, segs);
+    const dim3 agrid((uint32_t)std::min<int64_t>(items, (int64_t)c.num_cus));
+
+    // plans of group i + 1 on the second stream beside group i, as in the
+    // persistent path (pipe_ev: [0] start, [1 + set] plan done, [3 + set]
+    // group done)
+    c.ensure_aux();
+    hipStream_t ps = c.aux;
+    FELOG_HIP(hipEventRecord(c.pipe_ev[0], c.stream));
+    if (ps != c.stream) FELOG_HIP(hipStreamWaitEvent(ps, c.pipe_ev[0], 0));
+    size_t gated = 0;
+    // sampled timing: per timed minibatch [0, 1] around its group's plan
+    // launch (one launch for the group's minibatches, each timed one counts
+    // its share), [2] before its forward, [3] after it, [5] after its apply
+    const int every = c.timing_every;
+    const size_t pool = c.timing_pool.size() / kTimingEvents;
+    size_t next_slot = 0, used_slots = 0;
+    int64_t timed = 0;
+    double ms_prep = 0.0, ms_fwd = 0.0, ms_apply = 0.0;
+    std::vector<double> slot_share(pool, 0.0);   // 1 / minibatches of the group, by slot
+    std::vector<hipEvent_t> plan_ev;             // two per group that has a timed minibatch
+    struct PlanEvents {
+        std::vector<hipEvent_t>& v;
+        ~PlanEvents()
+        {
+            for (hipEvent_t e : v) (void)hipEventDestroy(e);
+        }
+    } plan_ev_guard{plan_ev};
+    std::vector<size_t> slot_plan(pool, 0);
+    auto harvest = [&](size_t slot) {
+        hipEvent_t* e = &c.timing_pool[kTimingEvents * slot];
+        FELOG_HIP(hipEventSynchronize(e[5]));
+        float a0 = 0.0f, f = 0.0f, ap = 0.0f;
+        FELOG_HIP(hipEventElapsedTime(&a0, plan_ev[slot_plan[slot]], plan_ev[slot_plan[slot] + 1]));
+        FELOG_HIP(hipEventElapsedTime(&f, e[2], e[3]));
+        FELOG_HIP(hipEventElapsedTime(&ap, e[3], e[5]));
+        ms_prep += a0 * slot_share[slot];
+        ms_fwd += f;
+        ms_apply += ap;
+        ++timed;
+    };
+    FELOG_HIP(hipEventRecord(c.ev0, c.stream));
+    auto plan_group = [&](size_t li) {
+        const Group& gr = groups[li];
+        const int64_t set = (int64_t)li % sets;
+        const int nmb = (int)(gr.end - gr.first);
+        if (ps != c.stream && li >= 2) FELOG_HIP(hipStreamWaitEvent(ps, c.pipe_ev[3 + set], 0));
+        while (gated <= gr.chunk && gated < w.chunk_ready.size())
+            FELOG_HIP(hipStreamWaitEvent(ps, w.chunk_ready[gated++], 0));
+        PlanBatch pb{};
+        pb.job[0] = pa;
+        pb.job[0].first = desc[(size_t)(gr.first - first_mb)];
+        pb.job[0].pairs = (uint32_t)P;
+        pb.job[0].chunk_pairs = (uint32_t)sch.chunk_pairs[gr.chunk];
+        pb.job[0].tinfo += set * G * tmax;
+        pb.job[0].segs += set * G * (tmax / 2);
+        pb.job[0].spair += set * G * tmax;
+        pb.job[0].meta += set * G * 4;
+        pb.start[1] = nmb;
+        pb.njobs = 1;
+        if (every > 0) {
+            hipEvent_t e[2] = {nullptr, nullptr};
+            for (hipEvent_t& x : e) {
+                FELOG_HIP(hipEventCreate(&x));
+                plan_ev.push_back(x);
+            }
+            FELOG_HIP(hipEventRecord(e[0], ps));
+            launch_plan(K, nmb, pb, ps);
+            FELOG_HIP(hipEventRecord(e[1], ps));
+        } else {
+            launch_plan(K, nmb, pb, ps);
+        }
+        FELOG_HIP(hipEventRecord(c.pipe_ev[1 + set], ps));
+    };
+    if (!groups.empty()) plan_group(0);
+    for (size_t li = 0; li < groups.size(); ++li) {
+        const int64_t set = (int64_t)li % sets, g0 = groups[li].first, g1 = groups[li].end;
+        if (sets == 2 && li + 1 < groups.size()) plan_group(li + 1);
+        if (ps != c.stream) FELOG_HIP(hipStreamWaitEvent(c.stream, c.pipe_ev[1 + set], 0));
+        UpdJob J = uj;
+        J.tinfo = pa.tinfo + set * G * tmax;
+        J.segs = pa.segs + set * G * (tmax / 2);
+        J.spair = pa.spair + set * G * tmax;
+        J.meta = pa.meta + set * G * 4;
+        for (int64_t b = g0; b < g1; ++b) {
+            const MbDesc& d = desc[(size_t)(b - first_mb)];
+            const int32_t mm = (int32_t)(b - g0);
+            hipEvent_t* e = nullptr;
+            if (every > 0 && pool > 0 && (b - first_mb) % every == 0) {
+                if (used_slots == pool) harvest(next_slot);
+                else ++used_slots;
+                e = &c.timing_pool[kTimingEvents * next_slot];
+                slot_share[next_slot] = 1.0 / (double)(g1 - g0);
+                slot_plan[next_slot] = 2 * li;
+                next_slot = (next_slot + 1) % pool;
+            }
+            if (e) FELOG_HIP(hipEventRecord(e[2], c.stream));
+            if (D == 64) launch_planned_forward_d<64>(K, J, mm, d.npairs, d.lr, c.stream);
+            else if (D == 128) launch_planned_forward_d<128>(K, J, mm, d.npairs, d.lr, c.stream);
+            else launch_planned_forward_d<256>(K, J, mm, d.npairs, d.lr, c.stream);
+            if (e) FELOG_HIP(hipEventRecord(e[3], c.stream));
+            if (D == 64)
+                hipLaunchKernelGGL(sgns_planned_apply_kernel<64>, agrid, dim3(256), 0, c.stream, J, mm, d.grid_c);
+            else if (D == 128)
+                hipLaunchKernelGGL(sgns_planned_apply_kernel<128>, agrid, dim3(256), 0, c.stream, J, mm, d.grid_c);
+            else
+                hipLaunchKernelGGL(sgns_planned_apply_kernel<256>, agrid, dim3(256), 0, c.stream, J, mm, d.grid_c);
+            if (e) FELOG_HIP(hipEventRecord(e[5], c.stream));
+        }
+        FELOG_HIP(hipGetLastError());
+        FELOG_HIP(hipEventRecord(c.pipe_ev[3 + set], c.stream));
+        if (sets == 1 && li + 1 < groups.size()) plan_group(li + 1);
+    }
+    launch_loss_reduce(loss_part.as<double>(), nwaves, m.loss_out.as<double>(), c.stream);
+    FELOG_HIP(hipGetLastError());
+    FELOG_HIP(hipEventRecord(c.ev1, c.stream));
+    double loss = 0.0;
+    unsigned long long rows[3] = {0, 0, 0};
+    FELOG_HIP(hipMemcpyAsync(&loss, m.loss_out.ptr, sizeof loss, hipMemcpyDeviceToHost, c.stream));
+    FELOG_HIP(hipMemcpyAsync(rows, m.row_totals.ptr, sizeof rows, hipMemcpyDeviceToHost, c.stream));
+    c.sync();
+    if (ps != c.stream) FELOG_HIP(hipStreamSynchronize(ps));
+    for (size_t k = 0; k < used_slots; ++k) harvest((next_slot + pool - used_slots + k) % pool);
+    float ms = 0.0f;
+    FELOG_HIP(hipEventElapsedTime(&ms, c.ev0, c.ev1));
+    if (stats) {
+        *stats = felog_train_stats{};
+        stats->minibatches = end - first_mb;
+        stats->pairs = pairs;
+        stats->minibatches_total = sch.B;
+        stats->loss = loss;
+        stats->ms = ms;
+        stats->rows_in = (int64_t)rows[0];
+        stats->rows_out = (int64_t)rows[1];
+        stats->rows_out_single = (int64_t)rows[2];
+        stats->timed_launches = timed;
+        stats->timed_minibatches = timed;
+        stats->ms_forward = ms_fwd;
+        stats->ms_apply = ms_apply;
+        stats->ms_apply_first = ms_apply;
+        stats->ms_prep = ms_prep;
+    }
+    return true;
 }
 
 }  // namespace felog

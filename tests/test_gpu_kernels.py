@@ -93,25 +93,48 @@ def _two_paths(fl, g, *, dim, K, P, first, count, r=2, L=12, window=3):
             M.write(which, rng.normal(0, 0.2, (g.n, dim)).astype(np.float32))
         st = M.train_steps(W, fl.train_params(window=window, negatives=K, minibatch_pairs=P,
                                               seed=9), first, count)
-        assert st.path == 1 - path
+        assert st.path == (1 - path if P * (K + 2) <= 8192 else 0)
         out.append((M.read(fl.TABLE_IN), M.read(fl.TABLE_OUT), st.loss, st.pairs, st.rows_in,
                     st.rows_out, st.rows_out_single))
     return out
 
 
-# touches around a round of the plan's sort (1,024) and at its largest (8,192);
-# node counts around a power of two, the largest row keys of a digit and below
+# touches around a round of the plan's sort (1,024) and at the largest of its
+# two sizes (8,192 and 16,384, the second of planned launches only); node
+# counts around a power of two, the largest row keys of a digit and below
 @pytest.mark.parametrize("P,K,n", [(1, 1, 3), (341, 1, 255), (342, 1, 256), (146, 5, 257),
                                    (147, 5, 1000), (1024, 6, 1023), (1170, 5, 1024),
-                                   (2730, 1, 65535), (372, 20, 65536), (1024, 6, 65537)])
+                                   (2730, 1, 65535), (372, 20, 65536), (1024, 6, 65537),
+                                   (1171, 5, 1200), (2340, 5, 3000), (5461, 1, 4097),
+                                   (744, 20, 800)])
 def test_plan_sizes(fl, orc, P, K, n):
     rng = np.random.default_rng(n)
     e = np.stack([rng.integers(0, n, 4 * n), rng.integers(0, n, 4 * n)], 1)
     e = np.concatenate([np.sort(e[e[:, 0] != e[:, 1]], 1), [[0, n - 1]]])
     g = synth.csr_from_edges(n, np.unique(e, axis=0))
-    a, b = _two_paths(fl, g, dim=128, K=K, P=P, first=3 if n > 100 else 0, count=3)
+    first = 3 if n > 100 else 0
+    a, b = _two_paths(fl, g, dim=128, K=K, P=P, first=first, count=3)
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
     assert a[3:] == b[3:] and abs(a[2] - b[2]) <= 1e-12 * abs(b[2])
+    # the oracle's minibatches one after another: each stored entry within the
+    # per-row bar of the deltas plus one FP32 spacing per minibatch
+    rng = np.random.default_rng(7)
+    tab = [rng.normal(0, 0.2, (n, 128)).astype(np.float32) for _ in range(2)]
+    walks = orc.walks_uniform(g, np.arange(n), 2, 12, 4)
+    cdf = orc.neg_cdf(g.degrees().astype(np.uint64))
+    prm = fl.train_params(window=3, negatives=K, minibatch_pairs=P, seed=9)
+    slices = sum(1 for j in range(12) for o in range(-3, 4) if o and 0 <= j + o < 12)
+    B = -(-2 * int((g.degrees() > 0).sum()) * slices // P)
+    moved = [np.zeros(n), np.zeros(n)]
+    for i in range(first, min(first + 3, B)):
+        mb = orc.minibatch_pairs(walks, 3, P, i)
+        d = orc.sgns_step(tab[0], tab[1], mb.ctx, mb.ctr, orc.draw_negatives(mb, 0, K, 9, cdf),
+                          orc.lr_at(i, B, prm.lr_start, prm.lr_end))
+        moved[0][d.rows_in] += np.linalg.norm(d.d_in, axis=1)
+        moved[1][d.rows_out] += np.linalg.norm(d.d_out, axis=1)
+    for got, ref, mv in zip(a[:2], tab, moved):
+        assert (np.abs(got.astype(np.float64) - ref) <=
+                1e-5 * mv[:, None] + 3 * np.spacing(np.abs(ref)) + 1e-12).all()
 
 
 def test_plan_one_hub(fl):
@@ -154,3 +177,38 @@ def test_forward_odd_pairs_d64(fl, orc, K, P):
             d, rd = d[np.argsort(rows)], rd[np.argsort(rrows)]
             err = np.linalg.norm(d.astype(np.float64) - rd, axis=1)
             assert (err <= 1e-5 * np.linalg.norm(rd, axis=1) + 1e-12).all()
+
+
+@pytest.mark.parametrize("P,K", [(200, 5), (2000, 5)])
+def test_launches_within_a_budget(fl, P, K):
+    """Per-minibatch launches under shrinking budgets: fewer plans per launch,
+    then none (the ids of each minibatch instead), then ENOMEM; every call that
+    succeeds gives the same tables."""
+    n = 300
+    rng = np.random.default_rng(1)
+    e = np.sort(np.stack([rng.integers(0, n, 2000), rng.integers(0, n, 2000)], 1), 1)
+    g = synth.csr_from_edges(n, np.unique(e[e[:, 0] != e[:, 1]], axis=0))
+    prm = fl.train_params(window=3, negatives=K, minibatch_pairs=P, seed=9)
+
+    def train(budget):
+        c = fl.Context(0, hbm_budget=budget)
+        c.set_sgns_path(1)
+        c.set_single_stream(True)
+        G = fl.Graph.from_csr(c, g.indptr, g.indices)
+        W = fl.Walks.generate(G, r=4, L=12, seed=4)
+        M = fl.Model.create(G, dim=64, seed=6)
+        held = c.bytes_in_use()
+        M.train_steps(W, prm, 0, 30)
+        return M.read(fl.TABLE_IN), M.read(fl.TABLE_OUT), held
+
+    ref = train(0)
+    done = 0
+    for spare in (64 << 20, 4 << 20, 1500000, 900000, 500000, 250000, 100000, 20000):
+        try:
+            got = train(ref[2] + spare)
+        except fl.FelogError as err:
+            assert err.status == fl.FELOG_ENOMEM
+            continue
+        done += 1
+        assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1])
+    assert done >= 2
