@@ -60,7 +60,7 @@ struct DevBuf {
     template <class T> T* as() const { return static_cast<T*>(ptr); }
 };
 
-constexpr int kIdSets = 3;   // minibatch id buffer sets: ids run kIdSets - 1 minibatches ahead
+constexpr int kIdSets = 3;   // fewest minibatch id buffer sets a model holds
 constexpr int kScanSpanMin = 512;   // fewest touches a block of the SGNS scan passes takes
 constexpr int kTimingEvents = 6;   // events per timed minibatch
 
@@ -152,8 +152,8 @@ struct Packed {
     DevBuf buf;                     // the bytes
 };
 
-// Buffers of one minibatch's ids and destination sort; kIdSets sets let the
-// ids of the next kIdSets - 1 minibatches be computed while one trains.
+// Buffers of minibatches' ids and destination sorts, id set after id set: the
+// ids of later minibatches are computed while one trains.
 struct MinibatchBufs {
     DevBuf cnt_in, cnt_out;       // uint32 [n]: touches of each row (0 between minibatches)
     DevBuf off_in, off_out;       // int32 [n]: first entry of each touched row's segment
@@ -184,7 +184,9 @@ struct Model {
     bool counters_dirty = false;  // row counters of the id sets may be non-zero
     int64_t cap_pairs = 0;
     int32_t cap_K = 0;
-    MinibatchBufs mb[kIdSets];    // by minibatch index mod kIdSets: ids and sort of one minibatch
+    int id_sets = 0;              // id sets with counters and offsets (at least kIdSets)
+    int id_sets_cap = 0;          // id sets of the other arrays, for cap_pairs and cap_K
+    MinibatchBufs mb;
     DevBuf ent_out;               // int4 [P(K+1)]: (FP64 g, ctx, pair-order key) of each
                                   // out-touch, by row segment
     DevBuf key_in;                // uint32 [P]: pair of each in-row segment position
@@ -192,7 +194,7 @@ struct Model {
                                   // rounded once), by row segment
     DevBuf partial;               // double [chunks of split rows][d]: each chunk's exact sums
     int64_t split_rows_in = 0;    // partial rows reserved for the in-table; the out-table's follow
-    DevBuf meta;                  // uint32 [kIdSets][16]: list lengths and counts, by id set
+    DevBuf meta;                  // uint32 [id_sets][16]: list lengths and counts, by id set
     DevBuf loss_out;              // double [1]
     DevBuf row_totals;            // uint64 [3]: summed touched-list lengths (in, out) and
                                   // out rows touched once

@@ -55,20 +55,37 @@
 
 namespace felog {
 
+// A launch group: the ids and sorts of up to kIdGroupMax minibatches in one
+// launch of each pass (minibatch i in the blocks with blockIdx.y = i, in id
+// set set0 + i).  One minibatch's passes are a few dependent loads per thread
+// over a few thousand blocks at most, and its launches and the events between
+// the two streams cost as much again.
+constexpr int kIdGroupMax = 8;
+struct GroupMb {
+    int64_t vcol_base;     // offset of the minibatch's chunk in valid_cols
+    uint32_t Wv;           // valid columns of the chunk
+    uint32_t first_pair;   // first pair of the minibatch in its chunk
+    uint32_t npairs;
+};
+// Elements per id set of each array of MinibatchBufs.
+struct SetStrides {
+    int64_t n, touches, in, out, split_in, split_out, mrows_in, mrows_out, scan_blocks;
+};
+
 // ------------------------------------------------------------------- prep
 struct PrepArgs {
     const int32_t* __restrict__ walks;   // step-major [L][W]
     int64_t W;
-    const int32_t* __restrict__ vcols;   // valid columns of this chunk
-    uint32_t Wv;
+    const int32_t* __restrict__ vcols;
     const int32_t* __restrict__ slices;  // (j << 8) | slot
-    uint32_t first_pair;
-    uint32_t npairs;
+    GroupMb g[kIdGroupMax];
+    int32_t set0;
+    SetStrides st;
     int64_t id_base;
     int32_t window;
     uint64_t seed;
     NoiseTable noise;
-    uint32_t* cnt_in;
+    uint32_t* cnt_in;        // (these four by id set)
     uint32_t* cnt_out;
     int32_t* touch_row;      // [P][K+2]: context, centre, negatives (-1: negative == centre)
     uint32_t* touch_pos;     // [P][K+2]: rank of the touch within its row
@@ -79,16 +96,23 @@ struct PrepArgs {
 template <int K>
 __global__ __launch_bounds__(256) void sgns_prep_kernel(PrepArgs a)
 {
-    const uint32_t nt = a.npairs * (K + 2);
+    const GroupMb mb = a.g[blockIdx.y];
+    const int64_t set = a.set0 + (int32_t)blockIdx.y;
+    const int32_t* vcols = a.vcols + mb.vcol_base;
+    uint32_t* const cnt_in = a.cnt_in + set * a.st.n;
+    uint32_t* const cnt_out = a.cnt_out + set * a.st.n;
+    int32_t* const touch_row = a.touch_row + set * a.st.touches;
+    uint32_t* const touch_pos = a.touch_pos + set * a.st.touches;
+    const uint32_t nt = mb.npairs * (K + 2);
     for (uint32_t t = blockIdx.x * 256 + threadIdx.x; t < nt; t += gridDim.x * 256) {
         int32_t row = -1;
         bool out = false;
         const uint32_t p = t / (K + 2), r = t - p * (K + 2);
-        const uint32_t gq = a.first_pair + p;
-        const uint32_t sidx = gq / a.Wv;
-        const uint32_t rank = gq - sidx * a.Wv;
+        const uint32_t gq = mb.first_pair + p;
+        const uint32_t sidx = gq / mb.Wv;
+        const uint32_t rank = gq - sidx * mb.Wv;
         const int32_t js = a.slices[sidx];
-        const int32_t col = a.vcols[rank];
+        const int32_t col = vcols[rank];
         const int32_t j = js >> 8, s = js & 255;
         const int32_t ctr = a.walks[(int64_t)j * a.W + col];
         if (r == 0) {
@@ -110,8 +134,8 @@ __global__ __launch_bounds__(256) void sgns_prep_kernel(PrepArgs a)
             row = neg != ctr ? neg : -1;   // a negative equal to the centre is skipped
             out = true;
         }
-        a.touch_row[t] = row;
-        a.touch_pos[t] = row >= 0 ? atomicAdd((out ? a.cnt_out : a.cnt_in) + row, 1u) : 0u;
+        touch_row[t] = row;
+        touch_pos[t] = row >= 0 ? atomicAdd((out ? cnt_out : cnt_in) + row, 1u) : 0u;
     }
 }
 
@@ -132,11 +156,14 @@ constexpr int64_t kScanSmallPairs = 65536;
 static_assert(kScanT * kScanISmall == kScanSpanMin, "fewest items per scan block");
 
 struct ScanArgs {
+    uint32_t npairs[kIdGroupMax];
+    int32_t set0;
+    SetStrides st;
+    // by id set
     const int32_t* touch_row;
     const uint32_t* touch_pos;
     const uint32_t* cnt_in;
     uint32_t* cnt_out;
-    uint32_t n_in, n_out, nb_in;
     unsigned long long* part_ec;   // per block
     uint4* part_rm;                // per block: rows, split rows, chunks of split rows,
                                    // single-touch out rows
@@ -155,6 +182,41 @@ struct ScanArgs {
                                    // whole counter arrays are zeroed before the ids)
 };
 
+// The arguments of this block's minibatch, and its items and blocks: in-touches
+// in blocks [0, nb_in), out-touches in [nb_in, nb).
+struct ScanMb : ScanArgs {
+    uint32_t n_in, n_out, nb_in, nb;
+};
+template <int K>
+__device__ __forceinline__ ScanMb scan_mb(const ScanArgs& g, uint32_t span)
+{
+    ScanMb a;
+    static_cast<ScanArgs&>(a) = g;
+    const int64_t set = g.set0 + (int32_t)blockIdx.y;
+    a.n_in = g.npairs[blockIdx.y];
+    a.n_out = a.n_in * (K + 1);
+    a.nb_in = (a.n_in + span - 1) / span;
+    a.nb = a.nb_in + (a.n_out + span - 1) / span;
+    a.touch_row += set * g.st.touches;
+    a.touch_pos += set * g.st.touches;
+    a.cnt_in += set * g.st.n;
+    a.cnt_out += set * g.st.n;
+    a.part_ec += set * g.st.scan_blocks;
+    a.part_rm += set * g.st.scan_blocks;
+    a.list_in += set * g.st.in;
+    a.list_out += set * g.st.out;
+    a.off_in += set * g.st.n;
+    a.off_out += set * g.st.n;
+    a.chunks_in += set * g.st.in;
+    a.chunks_out += set * g.st.out;
+    a.split_in += set * g.st.split_in;
+    a.split_out += set * g.st.split_out;
+    a.mrows_in += set * g.st.mrows_in;
+    a.mrows_out += set * g.st.mrows_out;
+    a.meta += set * kMetaWords;
+    return a;
+}
+
 // Items base .. base + I - 1 of a table (n items): the row each one
 // lists (-1 if none) and the row's touch count.  BATCH issues the loads of
 // all the items before it uses any (indices past the end clamped, their
@@ -163,7 +225,7 @@ struct ScanArgs {
 // wait for the previous item, which leaves more bandwidth to the launches
 // that run beside the scan.
 template <int K, bool BATCH, int I>
-__device__ __forceinline__ void scan_items(const ScanArgs& a, bool out, uint32_t base, uint32_t n,
+__device__ __forceinline__ void scan_items(const ScanMb& a, bool out, uint32_t base, uint32_t n,
                                            int32_t (&rows)[I], uint32_t (&cs)[I])
 {
     const uint32_t* cnt = out ? a.cnt_out : a.cnt_in;
@@ -226,10 +288,12 @@ __device__ __forceinline__ unsigned long long pack_ec(uint32_t c, bool out)
 }
 
 template <int K, bool BATCH, int I>
-__global__ __launch_bounds__(256) void sgns_scan_partials(ScanArgs a)
+__global__ __launch_bounds__(256) void sgns_scan_partials(ScanArgs g)
 {
     __shared__ unsigned long long s_ec[kScanT];
     __shared__ uint4 s_rm[kScanT];
+    const ScanMb a = scan_mb<K>(g, kScanT * I);
+    if (blockIdx.x >= a.nb) return;
     const bool out = blockIdx.x >= a.nb_in;
     const uint32_t nb = out ? blockIdx.x - a.nb_in : blockIdx.x;
     const uint32_t n = out ? a.n_out : a.n_in;
@@ -263,10 +327,12 @@ __global__ __launch_bounds__(256) void sgns_scan_partials(ScanArgs a)
 }
 
 template <int K, bool BATCH, int I>
-__global__ __launch_bounds__(256) void sgns_scan_write(ScanArgs a)
+__global__ __launch_bounds__(256) void sgns_scan_write(ScanArgs g)
 {
     __shared__ unsigned long long s_ec[kScanT];
     __shared__ uint4 s_rm[kScanT];
+    const ScanMb a = scan_mb<K>(g, kScanT * I);
+    if (blockIdx.x >= a.nb) return;
     const bool out = blockIdx.x >= a.nb_in;
     const uint32_t b0 = out ? a.nb_in : 0u;   // first block of this table
     const uint32_t n = out ? a.n_out : a.n_in;
@@ -493,25 +559,39 @@ __global__ __launch_bounds__(256) void sgns_forward_kernel(FwdArgs a)
 // in pair order whatever the atomics did.  Chunks of the rows with more
 // touches (their membership follows the atomics' order) get exact sums
 // instead, which a merge adds in chunk order.
-// Sort (key, a, b) ascending over the 16 lanes of a group.
-__device__ __forceinline__ void sort16(uint32_t& key, double& va, int32_t& vb, int gl)
+// Sort (key, a, b) ascending over the 16 lanes of a group, of which the first
+// `most` hold keys (the others the largest key): the bitonic network's stages
+// up to that many lanes.  The keys carry their lane; the values move once, at
+// the end.
+__device__ __forceinline__ void sort16(uint32_t key, double& va, int32_t& vb, int gl, int most)
 {
-#pragma unroll
-    for (int k = 2; k <= 16; k <<= 1)
-#pragma unroll
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            const uint32_t pk = __shfl_xor(key, j);
-            const double pa = __shfl_xor(va, j);
-            const int32_t pb = __shfl_xor(vb, j);
-            const bool up = (gl & k) == 0;        // this pair of lanes sorts ascending
-            const bool low = (gl & j) == 0;       // this lane keeps the smaller key
-            const bool take = (low == up) ? pk < key : pk > key;
-            if (take) {
-                key = pk;
-                va = pa;
-                vb = pb;
-            }
-        }
+    uint32_t from = (uint32_t)gl;
+    auto stage = [&](uint32_t pk, uint32_t pf, int k, int j) {
+        const bool up = (gl & k) == 0;        // this pair of lanes sorts ascending
+        const bool low = (gl & j) == 0;       // this lane keeps the smaller key
+        const bool take = (low == up) ? pk < key : pk > key;
+        key = take ? pk : key;
+        from = take ? pf : from;
+    };
+    stage(from_xor<1>(key), from_xor<1>(from), 2, 1);
+    if (most > 2) {
+        stage(from_xor<2>(key), from_xor<2>(from), 4, 2);
+        stage(from_xor<1>(key), from_xor<1>(from), 4, 1);
+    }
+    if (most > 4) {
+        stage(from_xor<4>(key), from_xor<4>(from), 8, 4);
+        stage(from_xor<2>(key), from_xor<2>(from), 8, 2);
+        stage(from_xor<1>(key), from_xor<1>(from), 8, 1);
+    }
+    if (most > 8) {
+        stage(from_xor<8>(key), from_xor<8>(from), 16, 8);
+        stage(from_xor<4>(key), from_xor<4>(from), 16, 4);
+        stage(from_xor<2>(key), from_xor<2>(from), 16, 2);
+        stage(from_xor<1>(key), from_xor<1>(from), 16, 1);
+    }
+    const int lane = (int)((threadIdx.x & 48u) | from);
+    va = __shfl(va, lane);
+    vb = __shfl(vb, lane);
 }
 
 // Two launches per minibatch, each over a list of work items of three kinds:
@@ -672,8 +752,7 @@ __global__ __launch_bounds__(256) void sgns_apply_kernel(ApplyArgs a)
         // a row of at most kChunk touches: FP64 sum in pair order
         float4 cur[V4];
         get_row<D>(out ? a.tout : a.tin, out ? a.cap_out : a.cap_in, row, cur, gl);
-        uint32_t key = my_key;
-        sort16(key, my_g, my_src, gl);
+        sort16(my_key, my_g, my_src, gl, len);
         double acc[D / 16];
 #pragma unroll
         for (int e = 0; e < D / 16; ++e) acc[e] = 0.0;
@@ -785,22 +864,27 @@ int64_t count_minibatches(Walks& w, const felog_train_params& p, int64_t* total_
     return s.B;
 }
 
-void model_alloc_update_state(Model& m)
+// (Re)allocates the counters and offsets of `sets` id sets.
+static void alloc_id_counters(Model& m, int sets)
 {
     Ctx& c = *m.ctx;
     const int64_t n = m.g->n;
-    for (MinibatchBufs& b : m.mb) {
-        b.cnt_in.alloc(&c, sizeof(uint32_t) * n);
-        b.cnt_out.alloc(&c, sizeof(uint32_t) * n);
-        b.off_in.alloc(&c, sizeof(int32_t) * n);
-        b.off_out.alloc(&c, sizeof(int32_t) * n);
-        FELOG_HIP(hipMemsetAsync(b.cnt_in.ptr, 0, sizeof(uint32_t) * n, c.stream));
-        FELOG_HIP(hipMemsetAsync(b.cnt_out.ptr, 0, sizeof(uint32_t) * n, c.stream));
-    }
-    m.meta.alloc(&c, sizeof(uint32_t) * kIdSets * kMetaWords);
+    MinibatchBufs& b = m.mb;
+    m.id_sets = 0;
+    for (DevBuf* x : {&b.cnt_in, &b.cnt_out, &b.off_in, &b.off_out, &m.meta}) x->release();
+    for (DevBuf* x : {&b.cnt_in, &b.cnt_out, &b.off_in, &b.off_out})
+        x->alloc(&c, sizeof(uint32_t) * n * sets);
+    m.meta.alloc(&c, sizeof(uint32_t) * sets * kMetaWords);
+    m.id_sets = sets;
+    m.counters_dirty = true;
+}
+
+void model_alloc_update_state(Model& m)
+{
+    Ctx& c = *m.ctx;
+    alloc_id_counters(m, kIdSets);
     m.row_totals.alloc(&c, sizeof(uint64_t) * 3);
     m.loss_out.alloc(&c, sizeof(double));
-    FELOG_HIP(hipMemsetAsync(m.meta.ptr, 0, m.meta.bytes, c.stream));
 }
 
 // Rows split over chunks have more than kChunk touches, so at most
@@ -810,6 +894,8 @@ static int64_t max_split_rows(int64_t touches) { return touches / (kChunk + 1) +
 
 // Largest minibatch whose launches all go to the training stream.
 constexpr int64_t kOneStreamPairs = 2048;
+// Touches of a launch group of ids.
+constexpr int64_t kIdGroupTouches = (int64_t)1 << 21;
 // Zero the row counters whole when n <= this many times the minibatch's touches.
 constexpr int64_t kZeroWholeRatio = 8;
 static int64_t max_split_chunks(int64_t touches) { return touches / 8 + 1; }
@@ -818,36 +904,53 @@ static int64_t max_split_chunks(int64_t touches) { return touches / 8 + 1; }
 struct MinibatchLaunch {
     uint32_t npairs;
     int dim, K;
-    uint32_t prep_blocks, fwd_blocks, nb_in, nb_out, reduce_blocks;
-    int scan_i;           // scan items per thread (kScanISmall or kScanILarge)
+    int set;              // id set
+    SetStrides st;
+    uint32_t fwd_blocks, reduce_blocks;
     int64_t split_in;     // partial-sum rows reserved for the in-table (the out-table's follow)
     double grid_c;        // exact-sum grid constant of this minibatch's learning rate
-    bool one_stream;      // ids on the training stream (on the critical path)
-    bool zero_whole;      // zero the row counters whole before the ids (else reset rows)
+    bool zero_whole;      // the row counters are zeroed whole before the ids (else reset rows)
 };
 
-// Zeroes a[0, n) and b[0, n): 16-byte stores, then the tails.
+// Launch values of a group's ids.
+struct IdGroup {
+    int K, set0, count;
+    uint32_t npairs[kIdGroupMax];
+    uint32_t prep_blocks, scan_blocks;   // of the largest minibatch
+    int scan_i;           // scan items per thread (kScanISmall or kScanILarge)
+    bool one_stream;      // ids on the training stream (on the critical path)
+    bool zero_whole;
+    SetStrides st;
+};
+
+// Zeroes a[0, n) and b[0, n) from element `off`: 16-byte stores, then the tails.
 __global__ __launch_bounds__(256) void zero_counters_kernel(uint32_t* a, uint32_t* b, int64_t n)
 {
-    const int64_t n4 = n / 4;
+    const int64_t head = min(n, (int64_t)((16 - (reinterpret_cast<uintptr_t>(a) & 15)) & 15) / 4);
+    const int64_t n4 = (n - head) / 4, tail = n - head - 4 * n4;
     const int64_t stride = (int64_t)gridDim.x * 256;
     const uint4 z = make_uint4(0u, 0u, 0u, 0u);
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < 2 * n4; i += stride) {
-        uint4* p = reinterpret_cast<uint4*>(i < n4 ? a : b);
+        uint4* p = reinterpret_cast<uint4*>((i < n4 ? a : b) + head);
         p[i < n4 ? i : i - n4] = z;
     }
-    if (blockIdx.x == 0 && threadIdx.x < (int)(n - 4 * n4)) {
-        a[4 * n4 + threadIdx.x] = 0u;
-        b[4 * n4 + threadIdx.x] = 0u;
+    if (blockIdx.x == 0 && threadIdx.x < 8) {
+        const int t = threadIdx.x & 3;
+        uint32_t* p = threadIdx.x < 4 ? a : b;
+        if (t < head) p[t] = 0u;
+        if (t < tail) p[head + 4 * n4 + t] = 0u;
     }
 }
 
-static void zero_counters(MinibatchBufs& mb, hipStream_t s)
+// Zeroes the counters of id sets [set0, set0 + count).
+static void zero_counters(Model& m, int set0, int count, hipStream_t s)
 {
-    const int64_t n = (int64_t)(mb.cnt_in.bytes / sizeof(uint32_t));
-    const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((n / 2 + 255) / 256, 512));
+    const int64_t n = m.g->n, total = n * count;
+    const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((total / 2 + 255) / 256, 512));
+    // both arrays come from an allocator and have the same offset from 16 bytes
     hipLaunchKernelGGL(zero_counters_kernel, dim3(blocks), dim3(256), 0, s,
-                       mb.cnt_in.as<uint32_t>(), mb.cnt_out.as<uint32_t>(), n);
+                       m.mb.cnt_in.as<uint32_t>() + set0 * n, m.mb.cnt_out.as<uint32_t>() + set0 * n,
+                       total);
 }
 
 // When the ids run on a second stream and the table is not much larger than
@@ -855,57 +958,74 @@ static void zero_counters(MinibatchBufs& mb, hipStream_t s)
 // minibatch's ids (two streaming writes of n words beside the training
 // launches) instead of with one scattered write per touched row on the
 // training stream; otherwise the rows are reset as they are done.
-// Ids, ranks and the destination sort of one minibatch (reads only the walks
-// and the noise table, so it may run ahead of the training of earlier ones).
+// Ids, ranks and the destination sort of a group (reads only the walks and
+// the noise table, so it may run ahead of the training of earlier ones).
 template <int K>
-static void launch_ids_t(MinibatchBufs& mb, PrepArgs pa, const MinibatchLaunch& ml,
-                         uint32_t* meta, hipStream_t s)
+static void launch_ids_t(Model& m, PrepArgs pa, const IdGroup& ig, hipStream_t s)
 {
-    if (ml.zero_whole) zero_counters(mb, s);
+    MinibatchBufs& mb = m.mb;
+    if (ig.zero_whole) zero_counters(m, ig.set0, ig.count, s);
+    pa.set0 = ig.set0;
+    pa.st = ig.st;
     pa.cnt_in = mb.cnt_in.as<uint32_t>();
     pa.cnt_out = mb.cnt_out.as<uint32_t>();
     pa.touch_row = mb.touch_row.as<int32_t>();
     pa.touch_pos = mb.touch_pos.as<uint32_t>();
-    hipLaunchKernelGGL((sgns_prep_kernel<K>), dim3(ml.prep_blocks), dim3(256), 0, s, pa);
-    const uint32_t nb = ml.nb_in + ml.nb_out;
-    uint4* part_rm = mb.partials.as<uint4>();
-    unsigned long long* part_ec = reinterpret_cast<unsigned long long*>(part_rm + nb);
-    ScanArgs sa{pa.touch_row, pa.touch_pos, pa.cnt_in, pa.cnt_out, ml.npairs,
-                ml.npairs * (uint32_t)(K + 1), ml.nb_in, part_ec, part_rm,
-                mb.list_in.as<int32_t>(), mb.list_out.as<int32_t>(), mb.off_in.as<int32_t>(),
-                mb.off_out.as<int32_t>(), mb.chunks_in.as<int4>(), mb.chunks_out.as<int4>(),
-                mb.split_in.as<int4>(), mb.split_out.as<int4>(), mb.mrows_in.as<int4>(),
-                mb.mrows_out.as<int4>(), meta, ml.zero_whole ? 0 : 1};
-    const bool small = ml.scan_i == kScanISmall;
-    if (ml.one_stream && small) {
-        hipLaunchKernelGGL((sgns_scan_partials<K, true, kScanISmall>), dim3(nb), dim3(256), 0, s, sa);
-        hipLaunchKernelGGL((sgns_scan_write<K, true, kScanISmall>), dim3(nb), dim3(256), 0, s, sa);
-    } else if (ml.one_stream) {
-        hipLaunchKernelGGL((sgns_scan_partials<K, true, kScanILarge>), dim3(nb), dim3(256), 0, s, sa);
-        hipLaunchKernelGGL((sgns_scan_write<K, true, kScanILarge>), dim3(nb), dim3(256), 0, s, sa);
+    hipLaunchKernelGGL((sgns_prep_kernel<K>), dim3(ig.prep_blocks, ig.count), dim3(256), 0, s, pa);
+    ScanArgs sa{};
+    for (int i = 0; i < ig.count; ++i) sa.npairs[i] = ig.npairs[i];
+    sa.set0 = ig.set0;
+    sa.st = ig.st;
+    sa.touch_row = pa.touch_row;
+    sa.touch_pos = pa.touch_pos;
+    sa.cnt_in = pa.cnt_in;
+    sa.cnt_out = pa.cnt_out;
+    sa.part_rm = mb.partials.as<uint4>();
+    sa.part_ec = reinterpret_cast<unsigned long long*>(sa.part_rm + m.id_sets_cap * ig.st.scan_blocks);
+    sa.list_in = mb.list_in.as<int32_t>();
+    sa.list_out = mb.list_out.as<int32_t>();
+    sa.off_in = mb.off_in.as<int32_t>();
+    sa.off_out = mb.off_out.as<int32_t>();
+    sa.chunks_in = mb.chunks_in.as<int4>();
+    sa.chunks_out = mb.chunks_out.as<int4>();
+    sa.split_in = mb.split_in.as<int4>();
+    sa.split_out = mb.split_out.as<int4>();
+    sa.mrows_in = mb.mrows_in.as<int4>();
+    sa.mrows_out = mb.mrows_out.as<int4>();
+    sa.meta = m.meta.as<uint32_t>();
+    sa.reset = ig.zero_whole ? 0 : 1;
+    const bool small = ig.scan_i == kScanISmall;
+    const dim3 grid(ig.scan_blocks, ig.count), block(256);
+    if (ig.one_stream && small) {
+        hipLaunchKernelGGL((sgns_scan_partials<K, true, kScanISmall>), grid, block, 0, s, sa);
+        hipLaunchKernelGGL((sgns_scan_write<K, true, kScanISmall>), grid, block, 0, s, sa);
+    } else if (ig.one_stream) {
+        hipLaunchKernelGGL((sgns_scan_partials<K, true, kScanILarge>), grid, block, 0, s, sa);
+        hipLaunchKernelGGL((sgns_scan_write<K, true, kScanILarge>), grid, block, 0, s, sa);
     } else if (small) {
-        hipLaunchKernelGGL((sgns_scan_partials<K, false, kScanISmall>), dim3(nb), dim3(256), 0, s, sa);
-        hipLaunchKernelGGL((sgns_scan_write<K, false, kScanISmall>), dim3(nb), dim3(256), 0, s, sa);
+        hipLaunchKernelGGL((sgns_scan_partials<K, false, kScanISmall>), grid, block, 0, s, sa);
+        hipLaunchKernelGGL((sgns_scan_write<K, false, kScanISmall>), grid, block, 0, s, sa);
     } else {
-        hipLaunchKernelGGL((sgns_scan_partials<K, false, kScanILarge>), dim3(nb), dim3(256), 0, s, sa);
-        hipLaunchKernelGGL((sgns_scan_write<K, false, kScanILarge>), dim3(nb), dim3(256), 0, s, sa);
+        hipLaunchKernelGGL((sgns_scan_partials<K, false, kScanILarge>), grid, block, 0, s, sa);
+        hipLaunchKernelGGL((sgns_scan_write<K, false, kScanILarge>), grid, block, 0, s, sa);
     }
     FELOG_HIP(hipGetLastError());
 }
 
 // Forward and the two apply launches of one minibatch whose ids are ready.
 // ev (optional): [0] recorded before the forward, [1] after it, [2] after the
-// first apply launch, [3] at the end;
-// fwd_done (optional) is recorded after the forward.
+// first apply launch, [3] at the end.
 template <int D, int K>
-static void launch_train_t(Model& m, MinibatchBufs& mb, FwdArgs fa, const MinibatchLaunch& ml,
-                           uint32_t* meta, float* cap_in, float* cap_out, hipStream_t s,
-                           hipEvent_t* ev, hipEvent_t fwd_done)
+static void launch_train_t(Model& m, FwdArgs fa, const MinibatchLaunch& ml, float* cap_in,
+                           float* cap_out, hipStream_t s, hipEvent_t* ev)
 {
-    fa.touch_row = mb.touch_row.as<int32_t>();
-    fa.touch_pos = mb.touch_pos.as<uint32_t>();
-    fa.off_in = mb.off_in.as<int32_t>();
-    fa.off_out = mb.off_out.as<int32_t>();
+    const MinibatchBufs& mb = m.mb;
+    const SetStrides& st = ml.st;
+    const int64_t set = ml.set;
+    fa.touch_row = mb.touch_row.as<int32_t>() + set * st.touches;
+    fa.touch_pos = mb.touch_pos.as<uint32_t>() + set * st.touches;
+    fa.off_in = mb.off_in.as<int32_t>() + set * st.n;
+    fa.off_out = mb.off_out.as<int32_t>() + set * st.n;
     fa.cap_out = cap_out;
     if (ev) FELOG_HIP(hipEventRecord(ev[0], s));
     if (cap_out)
@@ -913,17 +1033,30 @@ static void launch_train_t(Model& m, MinibatchBufs& mb, FwdArgs fa, const Miniba
     else
         hipLaunchKernelGGL((sgns_forward_kernel<D, K, false>), dim3(ml.fwd_blocks), dim3(256), 0, s, fa);
     if (ev) FELOG_HIP(hipEventRecord(ev[1], s));
-    if (fwd_done) FELOG_HIP(hipEventRecord(fwd_done, s));
     double* part_in = m.partial.as<double>();
     double* part_out = part_in + ml.split_in * D;
-    ApplyArgs aa{m.tin.as<float>(),       m.tout.as<float>(),      fa.ent_out,
-                 fa.dinp,                 fa.key_in,
-                 mb.chunks_in.as<int4>(), mb.chunks_out.as<int4>(), mb.split_in.as<int4>(),
-                 mb.split_out.as<int4>(), mb.mrows_in.as<int4>(),  mb.mrows_out.as<int4>(),
-                 part_in,                 part_out,                mb.cnt_in.as<uint32_t>(),
-                 mb.cnt_out.as<uint32_t>(), meta,                  cap_in,
-                 cap_out,                 m.row_totals.as<unsigned long long>(), ml.grid_c,
-                 ml.zero_whole ? 0 : 1};
+    ApplyArgs aa{};
+    aa.tin = m.tin.as<float>();
+    aa.tout = m.tout.as<float>();
+    aa.ent_out = fa.ent_out;
+    aa.dinp = fa.dinp;
+    aa.key_in = fa.key_in;
+    aa.chunks_in = mb.chunks_in.as<int4>() + set * st.in;
+    aa.chunks_out = mb.chunks_out.as<int4>() + set * st.out;
+    aa.split_in = mb.split_in.as<int4>() + set * st.split_in;
+    aa.split_out = mb.split_out.as<int4>() + set * st.split_out;
+    aa.mrows_in = mb.mrows_in.as<int4>() + set * st.mrows_in;
+    aa.mrows_out = mb.mrows_out.as<int4>() + set * st.mrows_out;
+    aa.partial_in = part_in;
+    aa.partial_out = part_out;
+    aa.cnt_in = mb.cnt_in.as<uint32_t>() + set * st.n;
+    aa.cnt_out = mb.cnt_out.as<uint32_t>() + set * st.n;
+    aa.meta = m.meta.as<uint32_t>() + set * kMetaWords;
+    aa.cap_in = cap_in;
+    aa.cap_out = cap_out;
+    aa.row_totals = m.row_totals.as<unsigned long long>();
+    aa.grid_c = ml.grid_c;
+    aa.reset = ml.zero_whole ? 0 : 1;
     hipLaunchKernelGGL((sgns_apply_kernel<D, 0>), dim3(ml.reduce_blocks), dim3(256), 0, s, aa);
     if (ev) FELOG_HIP(hipEventRecord(ev[2], s));
     hipLaunchKernelGGL((sgns_apply_kernel<D, 1>), dim3(ml.reduce_blocks), dim3(256), 0, s, aa);
@@ -935,29 +1068,27 @@ static void launch_train_t(Model& m, MinibatchBufs& mb, FwdArgs fa, const Miniba
     X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) \
     X(16) X(17) X(18) X(19) X(20)
 
-static void launch_ids(MinibatchBufs& mb, const PrepArgs& pa, const MinibatchLaunch& ml,
-                       uint32_t* meta, hipStream_t s)
+static void launch_ids(Model& m, const PrepArgs& pa, const IdGroup& ig, hipStream_t s)
 {
-    switch (ml.K) {
-#define FELOG_CASE(k)                                  \
-    case k:                                            \
-        launch_ids_t<k>(mb, pa, ml, meta, s);          \
+    switch (ig.K) {
+#define FELOG_CASE(k)                   \
+    case k:                             \
+        launch_ids_t<k>(m, pa, ig, s);  \
         break;
         FELOG_FOR_K(FELOG_CASE)
 #undef FELOG_CASE
-        default: fail(FELOG_EUNSUPPORTED, "negatives = %d not supported", ml.K);
+        default: fail(FELOG_EUNSUPPORTED, "negatives = %d not supported", ig.K);
     }
 }
 
 template <int D>
-static void launch_train_d(Model& m, MinibatchBufs& mb, const FwdArgs& fa,
-                           const MinibatchLaunch& ml, uint32_t* meta, float* ci, float* co,
-                           hipStream_t s, hipEvent_t* ev, hipEvent_t fd)
+static void launch_train_d(Model& m, const FwdArgs& fa, const MinibatchLaunch& ml, float* ci,
+                           float* co, hipStream_t s, hipEvent_t* ev)
 {
     switch (ml.K) {
-#define FELOG_CASE(k)                                                      \
-    case k:                                                                \
-        launch_train_t<D, k>(m, mb, fa, ml, meta, ci, co, s, ev, fd);      \
+#define FELOG_CASE(k)                                    \
+    case k:                                              \
+        launch_train_t<D, k>(m, fa, ml, ci, co, s, ev);  \
         break;
         FELOG_FOR_K(FELOG_CASE)
 #undef FELOG_CASE
@@ -965,13 +1096,109 @@ static void launch_train_d(Model& m, MinibatchBufs& mb, const FwdArgs& fa,
     }
 }
 
-static void launch_train(Model& m, MinibatchBufs& mb, const FwdArgs& fa,
-                         const MinibatchLaunch& ml, uint32_t* meta, float* ci, float* co,
-                         hipStream_t s, hipEvent_t* ev, hipEvent_t fd = nullptr)
+static void launch_train(Model& m, const FwdArgs& fa, const MinibatchLaunch& ml, float* ci,
+                         float* co, hipStream_t s, hipEvent_t* ev)
 {
-    if (ml.dim == 64) launch_train_d<64>(m, mb, fa, ml, meta, ci, co, s, ev, fd);
-    else if (ml.dim == 128) launch_train_d<128>(m, mb, fa, ml, meta, ci, co, s, ev, fd);
-    else launch_train_d<256>(m, mb, fa, ml, meta, ci, co, s, ev, fd);
+    if (ml.dim == 64) launch_train_d<64>(m, fa, ml, ci, co, s, ev);
+    else if (ml.dim == 128) launch_train_d<128>(m, fa, ml, ci, co, s, ev);
+    else launch_train_d<256>(m, fa, ml, ci, co, s, ev);
+}
+
+// Elements per id set for minibatches of up to P pairs and K negatives.
+static SetStrides set_strides(int64_t n, int64_t P, int64_t K)
+{
+    const int64_t touches_out = P * (K + 1);
+    SetStrides st{};
+    st.n = n;
+    st.touches = P * (K + 2);
+    st.in = P;
+    st.out = touches_out;
+    st.split_in = max_split_chunks(P);
+    st.split_out = max_split_chunks(touches_out);
+    st.mrows_in = max_split_rows(P);
+    st.mrows_out = max_split_rows(touches_out);
+    st.scan_blocks = (P + kScanSpanMin - 1) / kScanSpanMin +
+                     (touches_out + kScanSpanMin - 1) / kScanSpanMin;
+    return st;
+}
+
+// Bytes of one id set, without its counters and offsets, and of those.
+static uint64_t id_set_bytes(const SetStrides& st)
+{
+    return 8 * (uint64_t)st.touches + (4 + 16) * (uint64_t)(st.in + st.out) +
+           16 * (uint64_t)(st.split_in + st.split_out + st.mrows_in + st.mrows_out) +
+           24 * (uint64_t)st.scan_blocks;
+}
+static uint64_t id_counter_bytes(int64_t n) { return 16 * (uint64_t)n + 4 * kMetaWords; }
+
+// The model's scratch for minibatches of P pairs and K negatives with at least
+// kIdSets id sets, and as many as `want` when the budget and the card have
+// room; returns the id sets there are.
+static int ensure_id_buffers(Model& m, int64_t P, int K, int want)
+{
+    Ctx& c = *m.ctx;
+    const int64_t n = m.g->n;
+    const int64_t cp = std::max<int64_t>(m.cap_pairs, P);
+    const int ck = std::max(m.cap_K, K);
+    const SetStrides st = set_strides(n, cp, ck);
+    MinibatchBufs& b = m.mb;
+    DevBuf* const per_set[] = {&b.touch_row, &b.touch_pos, &b.list_in,  &b.list_out, &b.chunks_in,
+                               &b.chunks_out, &b.split_in, &b.split_out, &b.mrows_in, &b.mrows_out,
+                               &b.partials};
+    auto alloc_sets = [&](int sets) {
+        m.id_sets_cap = 0;
+        for (DevBuf* x : per_set) x->release();
+        const int64_t k = sets;
+        b.touch_row.alloc(&c, sizeof(int32_t) * k * st.touches);
+        b.touch_pos.alloc(&c, sizeof(uint32_t) * k * st.touches);
+        b.list_in.alloc(&c, sizeof(int32_t) * k * st.in);
+        b.list_out.alloc(&c, sizeof(int32_t) * k * st.out);
+        b.chunks_in.alloc(&c, sizeof(int4) * k * st.in);
+        b.chunks_out.alloc(&c, sizeof(int4) * k * st.out);
+        b.split_in.alloc(&c, sizeof(int4) * k * st.split_in);
+        b.split_out.alloc(&c, sizeof(int4) * k * st.split_out);
+        b.mrows_in.alloc(&c, sizeof(int4) * k * st.mrows_in);
+        b.mrows_out.alloc(&c, sizeof(int4) * k * st.mrows_out);
+        b.partials.alloc(&c, (sizeof(uint4) + sizeof(unsigned long long)) * k * st.scan_blocks);
+        m.id_sets_cap = sets;
+    };
+    if (m.cap_pairs < P || m.cap_K < K) {
+        const int64_t touches_out = cp * (ck + 1);
+        m.cap_pairs = 0;   // an allocation that fails leaves no stale capacity
+        m.cap_K = 0;
+        m.id_sets_cap = 0;
+        for (DevBuf* x : per_set) x->release();
+        m.ent_out.alloc(&c, sizeof(int4) * touches_out);
+        m.dinp.alloc(&c, sizeof(float) * cp * m.dim);
+        m.key_in.alloc(&c, sizeof(uint32_t) * cp);
+        m.split_rows_in = st.split_in;
+        m.partial.alloc(&c, sizeof(double) * (st.split_in + st.split_out) * m.dim);
+        m.cap_pairs = cp;
+        m.cap_K = ck;
+    }
+    const int have = std::min(m.id_sets, m.id_sets_cap);
+    if (have >= std::max(want, (int)kIdSets)) return have;
+    int sets = std::max(want, (int)kIdSets);
+    if (c.budget) {
+        uint64_t held = 0;
+        for (DevBuf* x : per_set) held += x->bytes;
+        for (DevBuf* x : {&b.cnt_in, &b.cnt_out, &b.off_in, &b.off_out, &m.meta}) held += x->bytes;
+        const uint64_t room = c.budget + held - std::min(c.budget + held, c.in_use);
+        if ((id_set_bytes(st) + id_counter_bytes(n)) * (uint64_t)sets > room)
+            sets = std::max(kIdSets, m.id_sets_cap);
+    }
+    try {
+        if (m.id_sets < sets) alloc_id_counters(m, sets);
+        if (m.id_sets_cap < sets) alloc_sets(sets);
+    } catch (const Error& e) {
+        if (e.code != FELOG_ENOMEM || sets == kIdSets) throw;
+        (void)hipGetLastError();
+        clear_error();
+        for (DevBuf* x : per_set) x->release();
+        if (m.id_sets != kIdSets) alloc_id_counters(m, kIdSets);
+        alloc_sets(kIdSets);
+    }
+    return std::min(m.id_sets, m.id_sets_cap);
 }
 
 void train_minibatches(Model& m, const Walks& wc, const felog_train_params& p, int64_t first_mb,
@@ -1061,34 +1288,18 @@ void train_minibatches(Model& m, const Walks& wc, const felog_train_params& p, i
             return;
     }
 
-    // scratch sized for this minibatch size
-    if (m.cap_pairs < P || m.cap_K < K) {
-        m.cap_pairs = std::max<int64_t>(m.cap_pairs, P);
-        m.cap_K = std::max(m.cap_K, K);
-        const int64_t cp = m.cap_pairs, ck = m.cap_K;
-        const int64_t touches_out = cp * (ck + 1);
-        const int64_t nbmax = (cp + kScanSpanMin - 1) / kScanSpanMin +
-                              (touches_out + kScanSpanMin - 1) / kScanSpanMin;
-        for (MinibatchBufs& b : m.mb) {
-            b.touch_row.alloc(&c, sizeof(int32_t) * cp * (ck + 2));
-            b.touch_pos.alloc(&c, sizeof(uint32_t) * cp * (ck + 2));
-            b.list_in.alloc(&c, sizeof(int32_t) * cp);
-            b.list_out.alloc(&c, sizeof(int32_t) * touches_out);
-            b.chunks_in.alloc(&c, sizeof(int4) * cp);
-            b.chunks_out.alloc(&c, sizeof(int4) * touches_out);
-            b.split_in.alloc(&c, sizeof(int4) * max_split_chunks(cp));
-            b.split_out.alloc(&c, sizeof(int4) * max_split_chunks(touches_out));
-            b.mrows_in.alloc(&c, sizeof(int4) * max_split_rows(cp));
-            b.mrows_out.alloc(&c, sizeof(int4) * max_split_rows(touches_out));
-            b.partials.alloc(&c, (sizeof(uint4) + sizeof(unsigned long long)) * nbmax);
-        }
-        m.ent_out.alloc(&c, sizeof(int4) * touches_out);
-        m.dinp.alloc(&c, sizeof(float) * cp * m.dim);
-        m.key_in.alloc(&c, sizeof(uint32_t) * cp);
-        m.split_rows_in = max_split_chunks(cp);
-        m.partial.alloc(&c, sizeof(double) * (m.split_rows_in + max_split_chunks(touches_out)) *
-                                m.dim);
-    }
+    // Launch groups: the ids of up to eight minibatches together, about 2^21
+    // touches, in two rings of id sets; without the memory for them (or for a
+    // single minibatch) one by one in a ring of kIdSets.
+    const bool one_stream = P <= kOneStreamPairs;
+    int G = 1;
+    if (apply && !one_stream)
+        G = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)kIdGroupMax, end - first_mb,
+                                                         kIdGroupTouches / (P * (K + 2))}));
+    const int id_sets = ensure_id_buffers(m, P, K, G > 1 ? 2 * G : kIdSets);
+    if (G > 1 && id_sets < 2 * G) G = std::max(1, id_sets / 2);
+    const int rings = G > 1 ? 2 : kIdSets;
+    const SetStrides st = set_strides(m.g->n, m.cap_pairs, m.cap_K);
     // pairs per forward wave: two steps (at 65,536 pairs, d = 128, K = 5 one
     // step ran 71 us, two to four 63; at 5,000 pairs, d = 256, K = 7 one step
     // 18.1, two 17.4, four 20.2), one where two would leave fewer than eight
@@ -1112,6 +1323,7 @@ void train_minibatches(Model& m, const Walks& wc, const felog_train_params& p, i
     PrepArgs pa{};
     pa.walks = w.data.as<int32_t>();
     pa.W = w.W;
+    pa.vcols = w.valid_cols.as<int32_t>();
     pa.slices = slices.as<int32_t>();
     pa.id_base = w.id_base;
     pa.window = p.window;
@@ -1132,36 +1344,32 @@ void train_minibatches(Model& m, const Walks& wc, const felog_train_params& p, i
     // Small minibatches run everything on one stream: their launches are
     // chains of a few dependent loads each, and waiting on another stream's
     // events costs more than the overlap gains.
-    const bool one_stream = P <= kOneStreamPairs;
     const bool zero_whole = !one_stream && (int64_t)m.g->n <= kZeroWholeRatio * P * (K + 2);
     // minibatches that reset their rows expect zero counters and leave them
     // zero; the others zero them first and leave them dirty
     if (!zero_whole && m.counters_dirty) {
-        for (MinibatchBufs& b : m.mb) zero_counters(b, c.stream);
+        zero_counters(m, 0, m.id_sets, c.stream);
         m.counters_dirty = false;
     }
     if (zero_whole) m.counters_dirty = true;
     // the launch values of minibatch b
     size_t chunk = 0;
     size_t gated = 0;   // walk chunks [0, gated) are known to be written
-    auto frame = [&](int64_t b, MinibatchLaunch& ml, PrepArgs& a) {
+    auto frame = [&](int64_t b, int set, MinibatchLaunch& ml, GroupMb& mb) {
         while (chunk + 1 < sch.chunk_first_mb.size() && sch.chunk_first_mb[chunk + 1] <= b) ++chunk;
         const int64_t first = (b - sch.chunk_first_mb[chunk]) * P;
         const int64_t np = std::min<int64_t>(P, sch.chunk_pairs[chunk] - first);
-        a.vcols = w.valid_cols.as<int32_t>() + sch.chunk_valid_base[chunk];
-        a.Wv = (uint32_t)w.chunk_valid[chunk];
-        a.first_pair = (uint32_t)first;
-        a.npairs = (uint32_t)np;
+        mb.vcol_base = sch.chunk_valid_base[chunk];
+        mb.Wv = (uint32_t)w.chunk_valid[chunk];
+        mb.first_pair = (uint32_t)first;
+        mb.npairs = (uint32_t)np;
         ml = MinibatchLaunch{};
         ml.dim = m.dim;
         ml.K = K;
+        ml.set = set;
+        ml.st = st;
         ml.npairs = (uint32_t)np;
-        ml.prep_blocks = (uint32_t)std::min<int64_t>((int64_t)c.num_cus * 4, (np * (K + 2) + 255) / 256);
         ml.fwd_blocks = (uint32_t)(((np + ppw - 1) / ppw + 3) / 4);
-        ml.scan_i = P <= kScanSmallPairs ? kScanISmall : kScanILarge;
-        const int64_t span = (int64_t)kScanT * ml.scan_i;
-        ml.nb_in = (uint32_t)((np + span - 1) / span);
-        ml.nb_out = (uint32_t)((np * (K + 1) + span - 1) / span);
         // 16 blocks per CU (faster than 6, 8 or 32 at 65,536 pairs on 2^20 rows),
         // but no more than the items can use: at most one row per touch and per
         // table row, plus the chunks of split rows, 16 items per block at a time
@@ -1170,57 +1378,77 @@ void train_minibatches(Model& m, const Walks& wc, const felog_train_params& p, i
         ml.reduce_blocks = (uint32_t)std::max<int64_t>(
             1, std::min<int64_t>((int64_t)c.num_cus * 16, (items + 15) / 16));
         ml.split_in = m.split_rows_in;
-        ml.one_stream = one_stream;
         ml.zero_whole = zero_whole;
         const double lr = lr0 - (lr0 - lr1) * (double)b / (double)std::max<int64_t>(1, sch.B - 1);
         const float lr32 = (float)lr;
         ml.grid_c = lr32 > 0.0f ? std::ldexp(1.5, std::ilogb(lr32) + 17) : 1.5;
         return lr32;
     };
-    uint32_t* meta0 = m.meta.as<uint32_t>();
+    // the launch values of a group's ids from its minibatches'
+    auto finish_group = [&](IdGroup& ig, const PrepArgs& a, int set0, int count) {
+        ig.K = K;
+        ig.set0 = set0;
+        ig.count = count;
+        ig.one_stream = one_stream;
+        ig.zero_whole = zero_whole;
+        ig.st = st;
+        ig.scan_i = P <= kScanSmallPairs ? kScanISmall : kScanILarge;
+        const int64_t span = (int64_t)kScanT * ig.scan_i;
+        for (int i = 0; i < count; ++i) {
+            const int64_t np = a.g[i].npairs;
+            ig.npairs[i] = a.g[i].npairs;
+            ig.prep_blocks = std::max(ig.prep_blocks, (uint32_t)std::min<int64_t>(
+                (int64_t)c.num_cus * 4, (np * (K + 2) + 255) / 256));
+            ig.scan_blocks = std::max(ig.scan_blocks, (uint32_t)((np + span - 1) / span +
+                                                                 (np * (K + 1) + span - 1) / span));
+        }
+    };
     // stream s reads the walks of chunk ch next: wait until they are written
     auto gate = [&](hipStream_t s, size_t ch) {
         while (gated <= ch && gated < w.chunk_ready.size())
             FELOG_HIP(hipStreamWaitEvent(s, w.chunk_ready[gated++], 0));
     };
 
-    // sampled timing: [0] before the ids (on the id stream), [1] after them,
-    // [2] before the forward, [3] after it, [4] after the first apply launch,
+    // sampled timing: [0] before the group's ids (on the id stream) and [1] after
+    // them for the first timed minibatch of a group (each timed one counts its
+    // share), [2] before the forward, [3] after it, [4] after the first apply launch,
     // [5] after the second
     const int every = apply ? c.timing_every : 0;
     const size_t pool = c.timing_pool.size() / kTimingEvents;
     size_t next_slot = 0, used_slots = 0;
     int64_t timed = 0;
     double ms_prep = 0.0, ms_fwd = 0.0, ms_apply = 0.0, ms_apply_first = 0.0;
+    std::vector<double> ids_share(pool, 0.0);   // by slot: timed minibatches of its group per
+                                                // minibatch of it, 0 without id events
     auto harvest = [&](size_t slot) {
         hipEvent_t* e = &c.timing_pool[kTimingEvents * slot];
         FELOG_HIP(hipEventSynchronize(e[5]));
         float a0 = 0.0f, f = 0.0f, ap = 0.0f, ap0 = 0.0f;
-        FELOG_HIP(hipEventElapsedTime(&a0, e[0], e[1]));
+        if (ids_share[slot] > 0.0) FELOG_HIP(hipEventElapsedTime(&a0, e[0], e[1]));
         FELOG_HIP(hipEventElapsedTime(&f, e[2], e[3]));
         FELOG_HIP(hipEventElapsedTime(&ap, e[3], e[5]));
         FELOG_HIP(hipEventElapsedTime(&ap0, e[3], e[4]));
-        ms_prep += a0;
+        ms_prep += a0 * ids_share[slot];
         ms_fwd += f;
         ms_apply += ap;
         ms_apply_first += ap0;
         ++timed;
     };
-    hipEvent_t* slot_of[kIdSets] = {};   // timing events of the minibatch of each id set
-    auto take_slot = [&](int64_t b) -> hipEvent_t* {
-        if (!(every > 0 && pool > 0 && (b - first_mb) % every == 0)) return nullptr;
+    auto take_slot = [&](int64_t b) -> int {
+        if (!(every > 0 && pool > 0 && (b - first_mb) % every == 0)) return -1;
         if (used_slots == pool) harvest(next_slot);   // reuse the oldest slot
         else ++used_slots;
-        hipEvent_t* e = &c.timing_pool[kTimingEvents * next_slot];
+        const int slot = (int)next_slot;
+        ids_share[slot] = 0.0;
         next_slot = (next_slot + 1) % pool;
-        return e;
+        return slot;
     };
 
     int64_t pairs_done = 0;
     FELOG_HIP(hipEventRecord(c.ev0, c.stream));
     if (apply && end > first_mb) {
-        // ids of minibatches b + 1 and b + 2 on the second stream while b trains
-        // on the first (or all in order on the first, for small minibatches)
+        // ids of the next groups on the second stream while a group trains on the
+        // first (or all in order on the first, for small minibatches)
         hipStream_t ids_s = c.stream;
         if (!one_stream) {
             c.ensure_aux();
@@ -1228,68 +1456,79 @@ void train_minibatches(Model& m, const Walks& wc, const felog_train_params& p, i
             FELOG_HIP(hipEventRecord(c.pipe_ev[0], c.stream));
             FELOG_HIP(hipStreamWaitEvent(ids_s, c.pipe_ev[0], 0));
         }
-        MinibatchLaunch mls[kIdSets];
-        float lrs[kIdSets];
-        hipEvent_t* ready = c.pipe_ev + 1;               // [set] ids ready
-        hipEvent_t* freed = c.pipe_ev + 1 + kIdSets;     // [set] buffers free
-        hipEvent_t fwd_done = c.pipe_ev[1 + 2 * kIdSets];
-        auto issue_ids = [&](int64_t b) {
-            const int set = (int)(b % kIdSets);
-            PrepArgs a = pa;
-            lrs[set] = frame(b, mls[set], a);
-            gate(ids_s, chunk);
-            // the set's previous minibatch must be done with it
-            if (!one_stream && b >= first_mb + kIdSets)
-                FELOG_HIP(hipStreamWaitEvent(ids_s, freed[set], 0));
-            hipEvent_t* e = take_slot(b);
-            slot_of[set] = e;
-            if (e) FELOG_HIP(hipEventRecord(e[0], ids_s));
-            launch_ids(m.mb[set], a, mls[set], meta0 + kMetaWords * set, ids_s);
-            if (e) FELOG_HIP(hipEventRecord(e[1], ids_s));
-            if (!one_stream) FELOG_HIP(hipEventRecord(ready[set], ids_s));
+        struct Mb {
+            MinibatchLaunch ml;
+            float lr;
+            int slot;
         };
-        const int64_t ahead = kIdSets - 1;
-        for (int64_t k = 0; k < ahead && first_mb + k < end; ++k) issue_ids(first_mb + k);
-        for (int64_t b = first_mb; b < end; ++b) {
-            const int set = (int)(b % kIdSets);
-            const MinibatchLaunch ml = mls[set];
-            const float lr = lrs[set];
-            hipEvent_t* e = slot_of[set];
-            if (!one_stream) FELOG_HIP(hipStreamWaitEvent(c.stream, ready[set], 0));
-            FwdArgs f = fa;
-            f.lr = lr;
-            f.npairs = ml.npairs;
-            launch_train(m, m.mb[set], f, ml, meta0 + kMetaWords * set, nullptr, nullptr,
-                         c.stream, e ? e + 2 : nullptr, one_stream ? nullptr : fwd_done);
-            if (!one_stream) FELOG_HIP(hipEventRecord(freed[set], c.stream));
-            pairs_done += ml.npairs;
-            // later minibatches' ids run beside this one's apply launches and the
-            // next forward, not beside this forward
-            if (b + ahead < end) {
-                if (!one_stream) FELOG_HIP(hipStreamWaitEvent(ids_s, fwd_done, 0));
-                issue_ids(b + ahead);
+        Mb mbs[kIdSets][kIdGroupMax];
+        hipEvent_t* ready = c.pipe_ev + 1;               // [ring] ids ready
+        hipEvent_t* freed = c.pipe_ev + 1 + kIdSets;     // [ring] buffers free
+        const int64_t ngroups = (end - first_mb + G - 1) / G;
+        auto issue_ids = [&](int64_t gi) {
+            const int ring = (int)(gi % rings);
+            const int64_t b0 = first_mb + gi * G;
+            const int count = (int)(std::min<int64_t>(end, b0 + G) - b0);
+            PrepArgs a = pa;
+            int timed_here = 0, first_slot = -1;
+            for (int i = 0; i < count; ++i) {
+                Mb& x = mbs[ring][i];
+                x.lr = frame(b0 + i, ring * G + i, x.ml, a.g[i]);
+                gate(ids_s, chunk);
+                x.slot = take_slot(b0 + i);
+                if (x.slot >= 0 && timed_here++ == 0) first_slot = x.slot;
             }
+            IdGroup ig{};
+            finish_group(ig, a, ring * G, count);
+            // the ring's previous group must be done with its sets
+            if (!one_stream && gi >= rings) FELOG_HIP(hipStreamWaitEvent(ids_s, freed[ring], 0));
+            hipEvent_t* e = first_slot >= 0 ? &c.timing_pool[kTimingEvents * first_slot] : nullptr;
+            if (e) {
+                ids_share[first_slot] = (double)timed_here / count;
+                FELOG_HIP(hipEventRecord(e[0], ids_s));
+            }
+            launch_ids(m, a, ig, ids_s);
+            if (e) FELOG_HIP(hipEventRecord(e[1], ids_s));
+            if (!one_stream) FELOG_HIP(hipEventRecord(ready[ring], ids_s));
+        };
+        for (int64_t gi = 0; gi < rings - 1 && gi < ngroups; ++gi) issue_ids(gi);
+        for (int64_t gi = 0; gi < ngroups; ++gi) {
+            const int ring = (int)(gi % rings);
+            const int64_t b0 = first_mb + gi * G;
+            const int count = (int)(std::min<int64_t>(end, b0 + G) - b0);
+            // (into the sets of the group before this one)
+            if (gi + rings - 1 < ngroups) issue_ids(gi + rings - 1);
+            if (!one_stream) FELOG_HIP(hipStreamWaitEvent(c.stream, ready[ring], 0));
+            for (int i = 0; i < count; ++i) {
+                const Mb& x = mbs[ring][i];
+                hipEvent_t* e = x.slot >= 0 ? &c.timing_pool[kTimingEvents * x.slot] : nullptr;
+                FwdArgs f = fa;
+                f.lr = x.lr;
+                f.npairs = x.ml.npairs;
+                launch_train(m, f, x.ml, nullptr, nullptr, c.stream, e ? e + 2 : nullptr);
+                pairs_done += x.ml.npairs;
+            }
+            if (!one_stream) FELOG_HIP(hipEventRecord(freed[ring], c.stream));
         }
     } else if (!apply) {
         // capture: the deltas of one minibatch, by touched-list position, not applied
         const int64_t b = first_mb;
-        const int par = (int)(b % kIdSets);
         MinibatchLaunch ml;
         PrepArgs a = pa;
-        const float lr = frame(b, ml, a);
+        const float lr = frame(b, 0, ml, a.g[0]);
+        IdGroup ig{};
+        finish_group(ig, a, 0, 1);
         gate(c.stream, chunk);
-        uint32_t* meta = meta0 + kMetaWords * par;
         DevBuf vin, vout;
         vin.alloc(&c, sizeof(float) * (size_t)P * m.dim);
         vout.alloc(&c, sizeof(float) * (size_t)P * (K + 1) * m.dim);
         FELOG_HIP(hipMemsetAsync(vin.ptr, 0, vin.bytes, c.stream));
         FELOG_HIP(hipMemsetAsync(vout.ptr, 0, vout.bytes, c.stream));
-        launch_ids(m.mb[par], a, ml, meta, c.stream);
+        launch_ids(m, a, ig, c.stream);
         FwdArgs f = fa;
         f.lr = lr;
         f.npairs = ml.npairs;
-        launch_train(m, m.mb[par], f, ml, meta, vin.as<float>(), vout.as<float>(), c.stream,
-                     nullptr);
+        launch_train(m, f, ml, vin.as<float>(), vout.as<float>(), c.stream, nullptr);
         unsigned long long tot[2];
         FELOG_HIP(hipMemcpyAsync(tot, m.row_totals.ptr, sizeof tot, hipMemcpyDeviceToHost,
                                  c.stream));
@@ -1300,9 +1539,9 @@ void train_minibatches(Model& m, const Walks& wc, const felog_train_params& p, i
         FELOG_REQUIRE(ui <= cap_in && uo <= cap_out,
                       "capture buffers hold %lld / %lld rows, need %lld / %lld",
                       (long long)cap_in, (long long)cap_out, (long long)ui, (long long)uo);
-        FELOG_HIP(hipMemcpyAsync(rows_in, m.mb[par].list_in.ptr, sizeof(int32_t) * ui,
+        FELOG_HIP(hipMemcpyAsync(rows_in, m.mb.list_in.ptr, sizeof(int32_t) * ui,
                                  hipMemcpyDeviceToHost, c.stream));
-        FELOG_HIP(hipMemcpyAsync(rows_out, m.mb[par].list_out.ptr, sizeof(int32_t) * uo,
+        FELOG_HIP(hipMemcpyAsync(rows_out, m.mb.list_out.ptr, sizeof(int32_t) * uo,
                                  hipMemcpyDeviceToHost, c.stream));
         FELOG_HIP(hipMemcpyAsync(d_in_host, vin.ptr, sizeof(float) * ui * m.dim,
                                  hipMemcpyDeviceToHost, c.stream));
