@@ -629,12 +629,13 @@ template <int D, int PHASE>
 __global__ __launch_bounds__(256) void sgns_apply_kernel(ApplyArgs a)
 {
     constexpr int V4 = D / 64;
-    // rows in flight per group, rows of one chunk: fewer registers and more
-    // waves beat more loads per wave here (65,536 pairs on R-MAT 2^20, us per
-    // minibatch with 4 / 2 / 1 rows: d = 64 128.4 / 124.7 / 125.9, d = 128
-    // 193.9 / 184.6 / 180.2, d = 256 400.8 / 346.3 / 319.1)
-    constexpr int kRows = D >= 128 ? 1 : 2;
-    constexpr int kRowsS = 2;   // rows in flight per group, chunks of split rows
+    // rows in flight per group.  No load is issued for slots past the item's
+    // end: pointed at row 0, they all read one line, which queued in one memory
+    // channel (with 2 rows, us per minibatch before and after: 5,000 pairs,
+    // d = 256, K = 7 72.5 and 56, 65,536 pairs 162 and 157; Algorithm 1 at
+    // 16,384 pairs on 20,000 nodes 66.7 and 59.5 ms).  One row is slower there
+    // (58.5, 158.5, 62.7), four hold too many registers (58.6, 165.5, 62.2).
+    constexpr int kRows = 2;
     const int lane = threadIdx.x & 63;
     const int grp = lane >> 4, gl = lane & 15;
     const int g0 = grp << 4;
@@ -713,22 +714,24 @@ __global__ __launch_bounds__(256) void sgns_apply_kernel(ApplyArgs a)
 #pragma unroll
             for (int e = 0; e < D / 16; ++e) acc[e] = 0.0;
             const double gc = a.grid_c;
-            for (int32_t i0 = 0; i0 < len; i0 += kRowsS) {
-                double gg[kRowsS];
-                float4 x[kRowsS][V4];
+            for (int32_t i0 = 0; i0 < len; i0 += kRows) {
+                double gg[kRows];
+                float4 x[kRows][V4];
 #pragma unroll
-                for (int u = 0; u < kRowsS; ++u) {
+                for (int u = 0; u < kRows; ++u) {
                     const int32_t idx = min(i0 + u, kChunk - 1);
                     const bool ok = i0 + u < len;
                     gg[u] = ok ? __shfl(my_g, g0 + idx) : 0.0;
                     const int32_t rr = __shfl(my_src, g0 + idx);
-                    const float4* rp = row4<D>(src, ok ? rr : 0);
+                    const float4* rp = row4<D>(src, rr);
 #pragma unroll
-                    for (int i = 0; i < V4; ++i)
-                        x[u][i] = ok ? rp[i * 16 + gl] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    for (int i = 0; i < V4; ++i) x[u][i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    if (ok)
+#pragma unroll
+                        for (int i = 0; i < V4; ++i) x[u][i] = rp[i * 16 + gl];
                 }
 #pragma unroll
-                for (int u = 0; u < kRowsS; ++u) {
+                for (int u = 0; u < kRows; ++u) {
                     // each FP64 term g * x is rounded once more, onto the grid
                     const double gd = gg[u];
 #pragma unroll
@@ -765,10 +768,12 @@ __global__ __launch_bounds__(256) void sgns_apply_kernel(ApplyArgs a)
                 const bool ok = i0 + u < len;
                 gg[u] = __shfl(my_g, g0 + idx);
                 const int32_t rr = __shfl(my_src, g0 + idx);
-                const float4* rp = row4<D>(src, ok ? rr : 0);
+                const float4* rp = row4<D>(src, rr);
 #pragma unroll
-                for (int i = 0; i < V4; ++i)
-                    x[u][i] = ok ? rp[i * 16 + gl] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                for (int i = 0; i < V4; ++i) x[u][i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                if (ok)
+#pragma unroll
+                    for (int i = 0; i < V4; ++i) x[u][i] = rp[i * 16 + gl];
             }
 #pragma unroll
             for (int u = 0; u < kRows; ++u)
