@@ -265,12 +265,11 @@ __global__ __launch_bounds__(64 * kGatherRows) void bf16_gather_kernel(Bf16Args 
 // stores its partial sum as the touches' rows of delta part s; the apply
 // adds the parts in order.
 // Per chunk a wave computes the 32 x 16 score tile Y X^T (Y the streamed
-// rows, X the panel) as two 16x16 MFMA tiles, so that lane l holds the
-// scores of panel row l mod 16 against streamed rows 4 (l / 16) + j and
-// 16 + 4 (l / 16) + j (j < 4).  Those 8 G values are exactly an A operand of
-// the output contraction for panel row l mod 16 if the contraction's k index
-// runs over the chunk's streamed rows in that order (any order of k gives
-// the same sum's terms); the B operand takes the same rows from the
+// rows, X the panel) as two 16x16 MFMA tiles.  Row i of tile h is the chunk's
+// row 8 (i / 4) + 4 h + i mod 4, so that lane l receives the scores of panel
+// row l mod 16 against the 8 consecutive streamed rows 8 (l / 16) .. + 7: an A
+// operand of the output contraction for that panel row as it stands, and the
+// B operand is 16 consecutive bytes of each row of the
 // transposed copy Y^T.  So G goes from the score accumulators to the next
 // MFMA in registers.  The waves' partial outputs meet in LDS and are added
 // in wave order; every element's terms are then stored as the touches'
@@ -279,13 +278,14 @@ __global__ __launch_bounds__(64 * kGatherRows) void bf16_gather_kernel(Bf16Args 
 constexpr int kFusedWaves = 8;
 
 template <int D>
-__global__ __launch_bounds__(64 * kFusedWaves) void bf16_fused_kernel(Bf16Args a)
+__global__ __launch_bounds__(64 * kFusedWaves, D == 256 ? 2 : 4) void bf16_fused_kernel(Bf16Args a)
 {
     constexpr int KS = D / 32;   // k steps of a score tile
     constexpr int ET = D / 16;   // 16-wide output tiles
     __shared__ float part[kFusedWaves][16][D + 4];
     __shared__ double lred[kFusedWaves];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int li = lane & 15, q = lane >> 4;
     const uint32_t npb = a.P / 16;
     const uint32_t panels = npb + a.M / 16;
@@ -309,11 +309,12 @@ __global__ __launch_bounds__(64 * kFusedWaves) void bf16_fused_kernel(Bf16Args a
     const float wk = -a.lr * (float)a.K / (float)a.M;
     const double lw = (double)a.K / (double)a.M;
     double lacc = 0.0;
+    // chunks <= 2048 and nparts, a power of two, <= 32
     const uint32_t chunks = ny / 32;
-    const uint32_t nparts = kFusedWaves * a.split;
-    const uint32_t part_id = (sp * kFusedWaves + wv + panel) % nparts;
-    const uint32_t c0 = (uint32_t)((uint64_t)chunks * part_id / nparts);
-    const uint32_t c1 = (uint32_t)((uint64_t)chunks * (part_id + 1) / nparts);
+    const uint32_t nparts = kFusedWaves * a.split, lg = 31 - __clz(nparts);
+    const uint32_t part_id = (sp * kFusedWaves + wv + panel) & (nparts - 1);
+    const uint32_t c0 = (chunks * part_id) >> lg;
+    const uint32_t c1 = (chunks * (part_id + 1)) >> lg;
     for (uint32_t ch = c0; ch < c1; ++ch) {
         const uint32_t y0 = ch * 32;
         bf16x8 yf[2][KS];
@@ -321,11 +322,11 @@ __global__ __launch_bounds__(64 * kFusedWaves) void bf16_fused_kernel(Bf16Args a
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int s = 0; s < KS; ++s)
-                yf[h][s] = load8(Y + (int64_t)(y0 + 16 * h + li) * D + 32 * s + 8 * q);
+                yf[h][s] = load8(Y + (int64_t)(y0 + 8 * (li >> 2) + 4 * h + (li & 3)) * D + 32 * s + 8 * q);
         int4 ids2[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
-            ids2[h] = *reinterpret_cast<const int4*>(yid + y0 + 16 * h + 4 * q);
+            ids2[h] = *reinterpret_cast<const int4*>(yid + y0 + 8 * q + 4 * h);
         f32x4 sc[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -334,7 +335,16 @@ __global__ __launch_bounds__(64 * kFusedWaves) void bf16_fused_kernel(Bf16Args a
             for (int s = 0; s < KS; ++s)
                 sc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yf[h][s], xf[s], sc[h], 0, 0, 0);
         }
-        uint32_t gw[4];   // G as 8 BF16 values, streamed rows 4q + j then 16 + 4q + j
+        // B operands of the output contraction, asked for once the score operands
+        // are used up and in flight beside the sigmas (before the scores they
+        // would hold more than 128 VGPRs in all, which halves the resident
+        // blocks: measured slower)
+        bf16x8 bt[ET];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < ET; ++t) bt[t] = load8(Yt + (int64_t)(16 * t + li) * ny + y0 + 8 * q);
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t gw[4];   // G as 8 BF16 values, streamed rows 8q .. 8q + 7
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int32_t iv[4] = {ids2[h].x, ids2[h].y, ids2[h].z, ids2[h].w};
@@ -343,35 +353,23 @@ __global__ __launch_bounds__(64 * kFusedWaves) void bf16_fused_kernel(Bf16Args a
             for (int j = 0; j < 4; ++j) {
                 const float x = sc[h][j];
                 const int32_t sv = iv[j];
-                float g = 0.0f;
-                if (pv >= 0 && sv >= 0 && pv != sv) {
-                    float sig, l1p;
-                    sigma_fast(x, sig, l1p);
-                    g = wk * sig;
-                    // -(K/M) log sigma(-s) = (K/M) (max(s, 0) + log(1 + exp(-|s|)))
-                    if (isC) lacc += lw * (double)(fmaxf(x, 0.0f) + l1p);
-                }
-                gb[j] = bf16_rne(g);
+                // no branch: the terms that are dropped are few
+                const bool on = (pv >= 0) & (sv >= 0) & (pv != sv);
+                float sig, l1p;
+                sigma_fast(x, sig, l1p);
+                gb[j] = on ? bf16_rne(wk * sig) : 0u;
+                // -(K/M) log sigma(-s) = (K/M) (max(s, 0) + log(1 + exp(-|s|)))
+                if (isC) lacc += on ? (double)(fmaxf(x, 0.0f) + l1p) : 0.0;
             }
             gw[2 * h] = gb[0] | (gb[1] << 16);
             gw[2 * h + 1] = gb[2] | (gb[3] << 16);
         }
         const bf16x8 ga = __builtin_bit_cast(bf16x8, make_uint4(gw[0], gw[1], gw[2], gw[3]));
-        // B operands of the output contraction, loaded after the scores: with
-        // them in flight beside the score operands the kernel needs more than
-        // 128 VGPRs, which halves the resident blocks (measured slower)
 #pragma unroll
-        for (int t = 0; t < ET; ++t) {
-            uint2 bt[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-                bt[h] = *reinterpret_cast<const uint2*>(Yt + (int64_t)(16 * t + li) * ny + y0 +
-                                                        16 * h + 4 * q);
-            const bf16x8 b =
-                __builtin_bit_cast(bf16x8, make_uint4(bt[0].x, bt[0].y, bt[1].x, bt[1].y));
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ga, b, acc[t], 0, 0, 0);
-        }
+        for (int t = 0; t < ET; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ga, bt[t], acc[t], 0, 0, 0);
     }
+    lacc *= lw;
     // acc[t][j] is element (4q + j, 16 t + li) of the block's 16 x D output
 #pragma unroll
     for (int t = 0; t < ET; ++t)
@@ -389,26 +387,34 @@ __global__ __launch_bounds__(64 * kFusedWaves) void bf16_fused_kernel(Bf16Args a
         a.loss_part[a.P + a.M + sp * npb + panel] += l;
     }
     float* const dpart = a.delta + (size_t)sp * (2 * a.P + a.M) * D;
-    for (int i = threadIdx.x; i < 16 * D; i += 64 * kFusedWaves) {
-        const int row = i / D, e = i % D;
-        float v = part[0][row][e];
+    // four elements per thread
+    for (int i = threadIdx.x; i < 16 * D / 4; i += 64 * kFusedWaves) {
+        const int row = i / (D / 4), e = i % (D / 4) * 4;
+        f32x4 v = *reinterpret_cast<const f32x4*>(&part[0][row][e]);
 #pragma unroll
-        for (int w = 1; w < kFusedWaves; ++w) v += part[w][row][e];
+        for (int w = 1; w < kFusedWaves; ++w) v += *reinterpret_cast<const f32x4*>(&part[w][row][e]);
         const uint32_t r = x0 + row;
+        float* const dst = dpart + (int64_t)(isC ? r : 2 * a.P + r) * D + e;
         if (isC) {
             if (a.ids[r] < 0) continue;          // no pair in this row
             if (sp == 0) {                       // the positive terms go with part 0
                 const float g = a.g0[r];
-                const float o = bf16_to_f32(a.O[(int64_t)r * D + e]);
-                const float c = bf16_to_f32(a.C[(int64_t)r * D + e]);
-                dpart[(int64_t)r * D + e] = v + g * o;
-                dpart[(int64_t)(a.P + r) * D + e] = g * c;
-            } else {
-                dpart[(int64_t)r * D + e] = v;
+                const uint2 ob = *reinterpret_cast<const uint2*>(a.O + (int64_t)r * D + e);
+                const uint2 cb = *reinterpret_cast<const uint2*>(a.C + (int64_t)r * D + e);
+                const f32x4 o = {bf16_to_f32((uint16_t)ob.x), bf16_to_f32((uint16_t)(ob.x >> 16)),
+                                 bf16_to_f32((uint16_t)ob.y), bf16_to_f32((uint16_t)(ob.y >> 16))};
+                const f32x4 c = {bf16_to_f32((uint16_t)cb.x), bf16_to_f32((uint16_t)(cb.x >> 16)),
+                                 bf16_to_f32((uint16_t)cb.y), bf16_to_f32((uint16_t)(cb.y >> 16))};
+                f32x4 p;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    v[j] = v[j] + g * o[j];
+                    p[j] = g * c[j];
+                }
+                *reinterpret_cast<f32x4*>(dpart + (int64_t)(a.P + r) * D + e) = p;
             }
-        } else {
-            dpart[(int64_t)(2 * a.P + r) * D + e] = v;
         }
+        *reinterpret_cast<f32x4*>(dst) = v;
     }
 }
 
@@ -477,48 +483,85 @@ __global__ void bf16_keys_kernel(const int32_t* ids, uint32_t P, uint32_t M, uin
 // One wave per sorted position; the wave at the first position of a row sums
 // the terms of the row's touches in FP64, in sorted (touch) order and part
 // order within a touch (a centre's term has part 0 only), 64 keys at a time,
-// and adds the sum to the row with one rounding.
-template <int D>
+// and adds the sum to the row with one rounding.  The parts of kBfTouches
+// touches are in flight together.
+constexpr int kBfTouches = 4;
+
+template <int D, int SPLIT>
 __global__ __launch_bounds__(256) void bf16_apply_kernel(const uint32_t* skey,
                                                          const uint32_t* stouch, uint32_t nt,
-                                                         uint32_t rb, uint32_t P, uint32_t split,
+                                                         uint32_t rb, uint32_t P,
                                                          const float* delta, float* tin,
                                                          float* tout)
 {
+    typedef float fv __attribute__((ext_vector_type(D / 64)));
     constexpr int U = D / 64;
     const int lane = threadIdx.x & 63;
-    const uint32_t i = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const uint32_t i = blockIdx.x * 4 + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (i >= nt) return;
-    const uint32_t key = skey[i];
-    if (key == (uint32_t)((2ull << rb) - 1) || (i > 0 && skey[i - 1] == key)) return;
+    // the keys from i on (lane l: key i + l) and the touches that share the first's row
+    uint32_t mine_key = i + lane < nt ? skey[i + lane] : (uint32_t)((2ull << rb) - 1);
+    const uint32_t before = i > 0 ? skey[i - 1] : (uint32_t)((2ull << rb) - 1);
+    uint32_t mine = i + lane < nt ? stouch[i + lane] : 0u;
+    const uint32_t key = (uint32_t)__builtin_amdgcn_readfirstlane((int)mine_key);
+    if (key == (uint32_t)((2ull << rb) - 1) || before == key) return;
+    const uint32_t row = key & ((1u << rb) - 1);
+    fv* const x = reinterpret_cast<fv*>((key >> rb ? tout : tin) + (int64_t)row * D) + lane;
+    const fv cur = *x;
     double acc[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) acc[u] = 0.0;
-    for (uint32_t j0 = i;; j0 += 64) {
-        const uint32_t j = j0 + lane;
-        const bool same = j < nt && skey[j] == key;
-        const unsigned long long ends = __ballot(!same);
+    for (uint32_t j0 = i;;) {
+        const unsigned long long ends = __ballot(!(j0 + lane < nt && mine_key == key));
         const int len = ends ? __ffsll((long long)ends) - 1 : 64;
-        const uint32_t mine = same ? stouch[j] : 0u;
-#pragma unroll 4
-        for (int q = 0; q < len; ++q) {
-            const uint32_t t = __shfl(mine, q);
-            const uint32_t parts = (t >= P && t < 2 * P) ? 1u : split;
-            for (uint32_t s = 0; s < parts; ++s) {
-                const float* row = delta + ((size_t)s * nt + t) * D;
+        for (int q0 = 0; q0 < len; q0 += kBfTouches) {
+            fv v[kBfTouches][SPLIT];
+            bool centre[kBfTouches];
 #pragma unroll
-                for (int u = 0; u < U; ++u) acc[u] += (double)row[lane + 64 * u];
+            for (int q = 0; q < kBfTouches; ++q) {
+                if (q0 + q >= len) break;
+                const uint32_t t = (uint32_t)__builtin_amdgcn_readlane((int)mine, q0 + q);
+                centre[q] = t >= P && t < 2 * P;
+#pragma unroll
+                for (int s = 0; s < SPLIT; ++s)
+                    if (s == 0 || !centre[q])
+                        v[q][s] = reinterpret_cast<const fv*>(delta + ((size_t)s * nt + t) * D)[lane];
+            }
+#pragma unroll
+            for (int q = 0; q < kBfTouches; ++q) {
+                if (q0 + q >= len) break;
+#pragma unroll
+                for (int s = 0; s < SPLIT; ++s)
+                    if (s == 0 || !centre[q])
+#pragma unroll
+                        for (int u = 0; u < U; ++u) acc[u] += (double)v[q][s][u];
             }
         }
         if (len < 64) break;
+        j0 += 64;
+        mine_key = j0 + lane < nt ? skey[j0 + lane] : 0u;
+        mine = j0 + lane < nt ? stouch[j0 + lane] : 0u;
     }
-    const uint32_t row = key & ((1u << rb) - 1);
-    float* T = (key >> rb) ? tout : tin;
+    fv o;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        float* x = T + (int64_t)row * D + lane + 64 * u;
-        *x = (float)((double)*x + acc[u]);
-    }
+    for (int u = 0; u < U; ++u) o[u] = (float)((double)cur[u] + acc[u]);
+    *x = o;
+}
+
+template <int D>
+static void launch_bf16_apply(uint32_t split, dim3 grid, hipStream_t s, const uint32_t* skey,
+                              const uint32_t* stouch, uint32_t nt, uint32_t rb, uint32_t P,
+                              const float* delta, float* tin, float* tout)
+{
+    if (split == 1)
+        hipLaunchKernelGGL((bf16_apply_kernel<D, 1>), grid, dim3(256), 0, s, skey, stouch, nt, rb, P,
+                           delta, tin, tout);
+    else if (split == 2)
+        hipLaunchKernelGGL((bf16_apply_kernel<D, 2>), grid, dim3(256), 0, s, skey, stouch, nt, rb, P,
+                           delta, tin, tout);
+    else
+        hipLaunchKernelGGL((bf16_apply_kernel<D, 4>), grid, dim3(256), 0, s, skey, stouch, nt, rb, P,
+                           delta, tin, tout);
 }
 
 __global__ void bf16_from_master_kernel(const float* src, uint16_t* dst, int64_t count)
@@ -703,14 +746,11 @@ void train_minibatches_bf16(Model& m, Walks& w, const felog_train_params& p,
             hipLaunchKernelGGL(bf16_fused_kernel<256>, fgrid, fblock, 0, c.stream, a);
         }
         if (d == 64)
-            hipLaunchKernelGGL(bf16_apply_kernel<64>, agrid, dim3(256), 0, c.stream, skey, stouch,
-                               nt, rb, P, split, (const float*)a.delta, dst_in, dst_out);
+            launch_bf16_apply<64>(split, agrid, c.stream, skey, stouch, nt, rb, P, a.delta, dst_in, dst_out);
         else if (d == 128)
-            hipLaunchKernelGGL(bf16_apply_kernel<128>, agrid, dim3(256), 0, c.stream, skey, stouch,
-                               nt, rb, P, split, (const float*)a.delta, dst_in, dst_out);
+            launch_bf16_apply<128>(split, agrid, c.stream, skey, stouch, nt, rb, P, a.delta, dst_in, dst_out);
         else
-            hipLaunchKernelGGL(bf16_apply_kernel<256>, agrid, dim3(256), 0, c.stream, skey, stouch,
-                               nt, rb, P, split, (const float*)a.delta, dst_in, dst_out);
+            launch_bf16_apply<256>(split, agrid, c.stream, skey, stouch, nt, rb, P, a.delta, dst_in, dst_out);
         FELOG_HIP(hipGetLastError());
         pairs_done += np;
     }
