@@ -253,19 +253,17 @@ __global__ __launch_bounds__(64 * kGatherRows) void bf16_gather_kernel(Bf16Args 
 }
 
 // Scores and gradients in one launch, G never stored.  A block owns a panel
-// of 16 rows of one side and streams the other side in chunks of 32 rows:
-//   panels [0, P/16):       panel = 16 pairs,      streamed = negatives,
-//                           out = dC = G N  (16 x d)
-//   panels [P/16, +M/16):   panel = 16 negatives,  streamed = pairs,
-//                           out = dN = G^T C (16 x d)
+// of 32 rows (16 at d = 256) of one side and streams the other side in chunks of 32 rows:
+//   pair panels:      streamed = negatives, out = dC = G N   (rows x d)
+//   negative panels:  streamed = pairs,     out = dN = G^T C (rows x d)
 // Each panel has `split` blocks (block = s * panels + panel), so that small
 // minibatches still fill the chip; the chunks form 8 * split contiguous
 // parts, and wave w of block s takes part (8 s + w + panel) mod 8 split, so
 // that blocks of different panels read different chunks at a time.  Block s
 // stores its partial sum as the touches' rows of delta part s; the apply
 // adds the parts in order.
-// Per chunk a wave computes the 32 x 16 score tile Y X^T (Y the streamed
-// rows, X the panel) as two 16x16 MFMA tiles.  Row i of tile h is the chunk's
+// Per chunk and 16 panel rows a wave computes the 32 x 16 score tile Y X^T (Y
+// the streamed rows, X the panel) as two 16x16 MFMA tiles.  Row i of tile h is the chunk's
 // row 8 (i / 4) + 4 h + i mod 4, so that lane l receives the scores of panel
 // row l mod 16 against the 8 consecutive streamed rows 8 (l / 16) .. + 7: an A
 // operand of the output contraction for that panel row as it stands, and the
@@ -274,24 +272,36 @@ __global__ __launch_bounds__(64 * kGatherRows) void bf16_gather_kernel(Bf16Args 
 // MFMA in registers.  The waves' partial outputs meet in LDS and are added
 // in wave order; every element's terms are then stored as the touches'
 // rows of the delta buffer: dC + g0 O and g0 C for a pair, dN for a negative.
-// Pair blocks also sum the negative loss terms, one slot per block.
+// Pair blocks also sum the negative loss terms, one slot per block.  Bound by
+// the trips to L2 of a chunk's operands, not by MFMA: at P = M = 1,024, d = 128 a
+// wave has one chunk, and the launch went from 18.1 us (16-row panels, operands
+// of the output contraction in 8-byte pieces after the scores) to 15.5 with
+// 16-byte pieces and 13.6 with 32-row panels and every read of the chunk in
+// flight at once; minibatch 32.1 -> 23.7 us (d = 64 25 -> 19, d = 256 44 -> 31; P =
+// 4,096 123 -> 95 and, d = 256, 200 -> 143).
 constexpr int kFusedWaves = 8;
 
+// Rows of a panel: 32 in two tiles that share the streamed rows' reads; at d =
+// 256 the two tiles' outputs would not fit the registers.
 template <int D>
-__global__ __launch_bounds__(64 * kFusedWaves, D == 256 ? 2 : 4) void bf16_fused_kernel(Bf16Args a)
+constexpr int panel_rows() { return D == 256 ? 16 : 32; }
+
+template <int D>
+__global__ __launch_bounds__(64 * kFusedWaves, 2) void bf16_fused_kernel(Bf16Args a)
 {
+    constexpr int PR = panel_rows<D>(), PT = PR / 16;   // panel rows and tiles
     constexpr int KS = D / 32;   // k steps of a score tile
     constexpr int ET = D / 16;   // 16-wide output tiles
-    __shared__ float part[kFusedWaves][16][D + 4];
+    __shared__ __align__(16) float part[kFusedWaves][PR][D + 4];
     __shared__ double lred[kFusedWaves];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int li = lane & 15, q = lane >> 4;
-    const uint32_t npb = a.P / 16;
-    const uint32_t panels = npb + a.M / 16;
+    const uint32_t npb = a.P / PR;
+    const uint32_t panels = npb + a.M / PR;
     const uint32_t sp = blockIdx.x / panels, panel = blockIdx.x - sp * panels;
     const bool isC = panel < npb;
-    const uint32_t x0 = (isC ? panel : panel - npb) * 16;
+    const uint32_t x0 = (isC ? panel : panel - npb) * PR;
     const uint16_t* X = isC ? a.C : a.N;
     const uint16_t* Y = isC ? a.N : a.C;
     const uint16_t* Yt = isC ? a.Nt : a.Ct;
@@ -299,13 +309,18 @@ __global__ __launch_bounds__(64 * kFusedWaves, D == 256 ? 2 : 4) void bf16_fused
     // ids: a pair's centre (-1 past the chunk's end), a negative's node; a
     // term is kept when both are real and differ
     const int32_t* yid = isC ? a.ids + 2 * a.P : a.ids + a.P;
-    const int32_t pv = isC ? a.ids[a.P + x0 + li] : a.ids[2 * a.P + x0 + li];
-    bf16x8 xf[KS];
+    int32_t pv[PT];
+    bf16x8 xf[PT][KS];
+    f32x4 acc[PT][ET];
 #pragma unroll
-    for (int s = 0; s < KS; ++s) xf[s] = load8(X + (int64_t)(x0 + li) * D + 32 * s + 8 * q);
-    f32x4 acc[ET];
+    for (int r = 0; r < PT; ++r) {
+        pv[r] = a.ids[(isC ? a.P : 2 * a.P) + x0 + 16 * r + li];
 #pragma unroll
-    for (int t = 0; t < ET; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int s = 0; s < KS; ++s)
+            xf[r][s] = load8(X + (int64_t)(x0 + 16 * r + li) * D + 32 * s + 8 * q);
+#pragma unroll
+        for (int t = 0; t < ET; ++t) acc[r][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
     const float wk = -a.lr * (float)a.K / (float)a.M;
     const double lw = (double)a.K / (double)a.M;
     double lacc = 0.0;
@@ -327,54 +342,64 @@ __global__ __launch_bounds__(64 * kFusedWaves, D == 256 ? 2 : 4) void bf16_fused
 #pragma unroll
         for (int h = 0; h < 2; ++h)
             ids2[h] = *reinterpret_cast<const int4*>(yid + y0 + 8 * q + 4 * h);
-        f32x4 sc[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            sc[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int s = 0; s < KS; ++s)
-                sc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yf[h][s], xf[s], sc[h], 0, 0, 0);
-        }
-        // B operands of the output contraction, asked for once the score operands
-        // are used up and in flight beside the sigmas (before the scores they
-        // would hold more than 128 VGPRs in all, which halves the resident
-        // blocks: measured slower)
+        // B operands of the output contraction, in flight beside the score
+        // operands where the registers hold both (at d = 256 beside the sigmas)
         bf16x8 bt[ET];
-        __builtin_amdgcn_sched_barrier(0);
+        auto load_bt = [&] {
 #pragma unroll
-        for (int t = 0; t < ET; ++t) bt[t] = load8(Yt + (int64_t)(16 * t + li) * ny + y0 + 8 * q);
-        __builtin_amdgcn_sched_barrier(0);
-        uint32_t gw[4];   // G as 8 BF16 values, streamed rows 8q .. 8q + 7
+            for (int t = 0; t < ET; ++t)
+                bt[t] = load8(Yt + (int64_t)(16 * t + li) * ny + y0 + 8 * q);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        if constexpr (D != 256) load_bt();
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int32_t iv[4] = {ids2[h].x, ids2[h].y, ids2[h].z, ids2[h].w};
-            uint32_t gb[4];
+        for (int r = 0; r < PT; ++r) {
+            f32x4 sc[2];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float x = sc[h][j];
-                const int32_t sv = iv[j];
-                // no branch: the terms that are dropped are few
-                const bool on = (pv >= 0) & (sv >= 0) & (pv != sv);
-                float sig, l1p;
-                sigma_fast(x, sig, l1p);
-                gb[j] = on ? bf16_rne(wk * sig) : 0u;
-                // -(K/M) log sigma(-s) = (K/M) (max(s, 0) + log(1 + exp(-|s|)))
-                if (isC) lacc += on ? (double)(fmaxf(x, 0.0f) + l1p) : 0.0;
+            for (int h = 0; h < 2; ++h) {
+                sc[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int s = 0; s < KS; ++s)
+                    sc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yf[h][s], xf[r][s], sc[h], 0, 0, 0);
             }
-            gw[2 * h] = gb[0] | (gb[1] << 16);
-            gw[2 * h + 1] = gb[2] | (gb[3] << 16);
-        }
-        const bf16x8 ga = __builtin_bit_cast(bf16x8, make_uint4(gw[0], gw[1], gw[2], gw[3]));
+            if constexpr (D == 256) {
+                __builtin_amdgcn_sched_barrier(0);
+                load_bt();
+            }
+            uint32_t gw[4];   // G as 8 BF16 values, streamed rows 8q .. 8q + 7
 #pragma unroll
-        for (int t = 0; t < ET; ++t)
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ga, bt[t], acc[t], 0, 0, 0);
+            for (int h = 0; h < 2; ++h) {
+                const int32_t iv[4] = {ids2[h].x, ids2[h].y, ids2[h].z, ids2[h].w};
+                uint32_t gb[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float x = sc[h][j];
+                    const int32_t sv = iv[j];
+                    // no branch: the terms that are dropped are few
+                    const bool on = (pv[r] >= 0) & (sv >= 0) & (pv[r] != sv);
+                    float sig, l1p;
+                    sigma_fast(x, sig, l1p);
+                    gb[j] = on ? bf16_rne(wk * sig) : 0u;
+                    // -(K/M) log sigma(-s) = (K/M) (max(s, 0) + log(1 + exp(-|s|)))
+                    if (isC) lacc += on ? (double)(fmaxf(x, 0.0f) + l1p) : 0.0;
+                }
+                gw[2 * h] = gb[0] | (gb[1] << 16);
+                gw[2 * h + 1] = gb[2] | (gb[3] << 16);
+            }
+            const bf16x8 ga = __builtin_bit_cast(bf16x8, make_uint4(gw[0], gw[1], gw[2], gw[3]));
+#pragma unroll
+            for (int t = 0; t < ET; ++t)
+                acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ga, bt[t], acc[r][t], 0, 0, 0);
+        }
     }
     lacc *= lw;
-    // acc[t][j] is element (4q + j, 16 t + li) of the block's 16 x D output
+    // acc[r][t][j] is element (16 r + 4q + j, 16 t + li) of the block's PR x D output
 #pragma unroll
-    for (int t = 0; t < ET; ++t)
+    for (int r = 0; r < PT; ++r)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) part[wv][4 * q + j][16 * t + li] = acc[t][j];
+        for (int t = 0; t < ET; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) part[wv][16 * r + 4 * q + j][16 * t + li] = acc[r][t][j];
     if (isC) {
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) lacc += __shfl_xor(lacc, off);
@@ -388,7 +413,7 @@ __global__ __launch_bounds__(64 * kFusedWaves, D == 256 ? 2 : 4) void bf16_fused
     }
     float* const dpart = a.delta + (size_t)sp * (2 * a.P + a.M) * D;
     // four elements per thread
-    for (int i = threadIdx.x; i < 16 * D / 4; i += 64 * kFusedWaves) {
+    for (int i = threadIdx.x; i < PR * D / 4; i += 64 * kFusedWaves) {
         const int row = i / (D / 4), e = i % (D / 4) * 4;
         f32x4 v = *reinterpret_cast<const f32x4*>(&part[0][row][e]);
 #pragma unroll
@@ -628,10 +653,12 @@ void train_minibatches_bf16(Model& m, Walks& w, const felog_train_params& p,
         m.bf_vin.release();
         m.bf_sort_tmp.release();
     }
-    // blocks per panel of the fused launch: at least 512 blocks where 4 suffice
-    const uint32_t panels = P / 16 + M / 16;
+    // blocks per panel of the fused launch: at least one per compute unit
+    // (panels of 32 rows, one block resident each) or two, where 4 suffice
+    const uint32_t pr = d == 256 ? panel_rows<256>() : panel_rows<128>();
+    const uint32_t panels = P / pr + M / pr;
     uint32_t split = 1;
-    while (split < 4 && panels * split < 512) split *= 2;
+    while (split < 4 && panels * split < (pr == 32 ? 256u : 512u)) split *= 2;
     if (m.bf_delta.bytes < sizeof(float) * split * (size_t)nt * d)
         m.bf_delta.alloc(&c, sizeof(float) * split * (size_t)nt * d);
     if (!lds_plan && !m.bf_sort_tmp.ptr) {
@@ -644,7 +671,7 @@ void train_minibatches_bf16(Model& m, Walks& w, const felog_train_params& p,
                                             (uint32_t*)nullptr, (uint32_t)ct, 0u, 32u, c.stream));
         m.bf_sort_tmp.alloc(&c, std::max<size_t>(tmp, 256));
     }
-    const int64_t nslots = (int64_t)P + M + (int64_t)split * (P / 16);
+    const int64_t nslots = (int64_t)P + M + (int64_t)split * (P / pr);
     DevBuf loss_part;
     loss_part.alloc(&c, sizeof(double) * nslots);
     FELOG_HIP(hipMemsetAsync(loss_part.ptr, 0, sizeof(double) * nslots, c.stream));
