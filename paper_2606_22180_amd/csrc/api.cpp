@@ -209,6 +209,7 @@ felog_status felog_ctx_create(int device, void* hip_stream, uint64_t hbm_budget_
         noalloc_scratch_init(device);
         FELOG_HIP(hipEventCreate(&c->ev0));
         FELOG_HIP(hipEventCreate(&c->ev1));
+        host_copies_attach();
         *out = c.release();
     });
 }
@@ -226,6 +227,7 @@ void felog_ctx_destroy(felog_ctx* ctx)
     if (ctx->ev0) (void)hipEventDestroy(ctx->ev0);
     if (ctx->ev1) (void)hipEventDestroy(ctx->ev1);
     for (hipEvent_t e : ctx->timing_pool) (void)hipEventDestroy(e);
+    host_copies_detach();
     delete ctx;
 }
 
@@ -528,10 +530,8 @@ felog_status felog_walks_read_range(const felog_walks* w, int64_t first, int64_t
             for (int64_t c0 = 0; c0 < count; c0 += block) {
                 const int64_t nc = std::min(block, count - c0);
                 launch_walk_rows(*w, first + c0, nc, rows.as<int32_t>(), c->stream);
-                FELOG_HIP(hipMemcpyAsync(walks + c0 * w->L, rows.ptr, (size_t)(nc * row_bytes),
-                                         hipMemcpyDeviceToHost, c->stream));
+                copy_to_host(*c, walks + c0 * w->L, rows.ptr, (size_t)(nc * row_bytes));
             }
-            c->sync();
             return;
         }
         std::vector<int32_t> tmp(total);
@@ -623,9 +623,7 @@ felog_status felog_packed_read(const felog_packed* p, void* host, int64_t cap)
                       (long long)p->bytes);
         Ctx* c = p->g->ctx;
         c->make_current();
-        FELOG_HIP(hipMemcpyAsync(host, p->buf.ptr, (size_t)p->bytes, hipMemcpyDeviceToHost,
-                                 c->stream));
-        c->sync();
+        copy_to_host(*c, host, p->buf.ptr, (size_t)p->bytes);
     });
 }
 
@@ -902,9 +900,7 @@ felog_status felog_embeddings_read(const felog_model* m, int32_t which, float* h
         int64_t count = (int64_t)m->g->n * m->dim;
         FELOG_REQUIRE(cap >= count, "buffer holds %lld floats, need %lld", (long long)cap,
                       (long long)count);
-        FELOG_HIP(hipMemcpyAsync(host, t.ptr, sizeof(float) * count, hipMemcpyDeviceToHost,
-                                 m->ctx->stream));
-        m->ctx->sync();
+        copy_to_host(*m->ctx, host, t.ptr, sizeof(float) * count);
     });
 }
 
@@ -952,9 +948,8 @@ felog_status felog_embeddings_read_bf16(const felog_model* m, int32_t which, uin
         FELOG_REQUIRE(cap >= count, "buffer holds %lld values, need %lld", (long long)cap,
                       (long long)count);
         bf16_refresh_all(*const_cast<felog_model*>(m));   // round the masters as they stand
-        FELOG_HIP(hipMemcpyAsync(host, (which == FELOG_TABLE_IN ? m->bin : m->bout).ptr,
-                                 sizeof(uint16_t) * count, hipMemcpyDeviceToHost, m->ctx->stream));
-        m->ctx->sync();
+        copy_to_host(*m->ctx, host, (which == FELOG_TABLE_IN ? m->bin : m->bout).ptr,
+                     sizeof(uint16_t) * count);
     });
 }
 

@@ -343,6 +343,11 @@ void small_jobs_step(const std::vector<SmallJob*>& jobs, SmallBatchCtl& ctl, hip
 bool small_batch_aborted(SmallBatchCtl& ctl, hipStream_t s);   // waits for the stream
 void small_job_end(SmallJob& j, hipStream_t s, felog_train_stats* stats);   // waits too
 uint64_t small_path_bytes(int64_t P, int K, int d, int64_t B, int num_cus);
+// Device memory to the caller's, after the context's stream (hostcopy.cpp);
+// returns when the copy is complete.  Every context is counted in and out.
+void copy_to_host(const Ctx& c, void* dst, const void* src, size_t bytes);
+void host_copies_attach();
+void host_copies_detach();
 void feedback(Model& m, const felog_feedback_params& p, const Active* in, Active& out,
               double* psi_host, int64_t psi_cap);
 // The feedback step with no device allocation: Psi into the caller's psi[],

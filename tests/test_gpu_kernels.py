@@ -212,3 +212,36 @@ def test_launches_within_a_budget(fl, P, K):
         done += 1
         assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1])
     assert done >= 2
+
+
+def _one_edge(n):
+    return np.minimum(np.arange(n + 1, dtype=np.int64), 2), np.array([1, 0], np.int32)
+
+
+# Host reads of rows * 256 bytes: below and at the staged size (4 MiB), chunk
+# edges (2 MiB), the threaded size (16 MiB) and past one turn of the ring
+@pytest.mark.parametrize("rows", [16383, 16384, 24575, 24577, 65535, 65536, 65537, 163841])
+def test_large_reads(fl, ctx, rows):
+    G = fl.Graph.from_csr(ctx, *_one_edge(rows))
+    M = fl.Model.create(G, dim=64, seed=1)
+    want = np.arange(rows * 64, dtype=np.uint32).view(np.float32).reshape(rows, 64)
+    M.write(fl.TABLE_IN, want)
+    for _ in range(2):   # a new ring, one that waited
+        assert (M.read(fl.TABLE_IN).view(np.uint32) == want.view(np.uint32)).all()
+
+
+def test_large_reads_from_threads(fl):
+    """More readers than rings are kept, each with a context of its own."""
+    from concurrent.futures import ThreadPoolExecutor
+
+    def job(i):
+        c = fl.Context(0)
+        G = fl.Graph.from_csr(c, *_one_edge(90000 + i))
+        M = fl.Model.create(G, dim=64, seed=1)
+        want = np.full((90000 + i, 64), i + 1, np.float32)
+        want[:, 0] = np.arange(90000 + i)
+        M.write(fl.TABLE_IN, want)
+        return all((M.read(fl.TABLE_IN) == want).all() for _ in range(3))
+
+    with ThreadPoolExecutor(4) as ex:
+        assert all(ex.map(job, range(4)))
