@@ -37,51 +37,23 @@ constexpr int kMetaWords = 16;            // per minibatch parity
 // multiple of 2^(k-52); taking c off again is exact.
 __device__ __forceinline__ double on_grid(double t, double c) { return __dsub_rn(__dadd_rn(t, c), c); }
 
-// sigma(x), sigma(-x) (FP64) and log(1 + exp(-|x|)) (FP32, relative error
-// about 1e-7) from one exponential E = exp(-|x|): sigma of the argument with
-// the sign of x is 1 / (1 + E), the other E / (1 + E), both to full FP64
-// precision, and the logarithm is 2 atanh(E / (2 + E)).  Against exp, a
-// division, expf and log1pf of the math library (and 1 - sigma, which cancels)
-// this is a third of the vector instructions of the evaluation.
+// sigma(x) = 1 / (1 + exp(-x)) (FP64, without clipping, Eq. (2)) and
+// log(1 + exp(-|x|)) (FP32, relative error about 1e-7) from one exponential:
+// E = exp(-|x|) is that or its reciprocal, and the logarithm is
+// 2 atanh(E / (2 + E)).  expf and log1pf of the math library beside it were
+// half of the evaluation's vector instructions.
 struct SigmaTerms {
-    double pos, neg;   // sigma(x), sigma(-x)
+    double sigma;
     float l1p;
 };
 __device__ __forceinline__ SigmaTerms sigma_terms(double x)
 {
-    // E: argument -a = n log 2 + r, |r| <= log(2) / 2, Taylor series of exp(r) to
-    // r^13 / 13! (the next term is below 2^-57).  exp(-800) is 0 in FP64; NaN stays.
-    double a = fabs(x);
-    a = a > 800.0 ? 800.0 : a;
-    const double n = rint(a * -1.4426950408889634);
-    double r = fma(n, -0.6931471805599453, -a);
-    r = fma(n, -2.3190468138462996e-17, r);
-    double p = 1.6059043836821613e-10;
-    p = fma(p, r, 2.08767569878681e-9);
-    p = fma(p, r, 2.505210838544172e-8);
-    p = fma(p, r, 2.755731922398589e-7);
-    p = fma(p, r, 2.7557319223985893e-6);
-    p = fma(p, r, 2.48015873015873e-5);
-    p = fma(p, r, 1.984126984126984e-4);
-    p = fma(p, r, 1.388888888888889e-3);
-    p = fma(p, r, 8.333333333333333e-3);
-    p = fma(p, r, 4.1666666666666664e-2);
-    p = fma(p, r, 1.6666666666666666e-1);
-    p = fma(p, r, 0.5);
-    p = fma(p, r, 1.0);
-    p = fma(p, r, 1.0);
-    const double E = ldexp(p, (int)n);
-    // 1 / (1 + E), 1 + E in [1, 2]: two Newton steps on the hardware reciprocal
-    const double d = 1.0 + E;
-    double q = __builtin_amdgcn_rcp(d);
-    q = fma(q, fma(-d, q, 1.0), q);
-    q = fma(q, fma(-d, q, 1.0), q);
-    const double Eq = E * q;
+    const double en = exp(-x);
     SigmaTerms t;
-    t.pos = x < 0.0 ? Eq : q;
-    t.neg = x < 0.0 ? q : Eq;
+    t.sigma = 1.0 / (1.0 + en);
     // 2 atanh(s) = 2 s (1 + z / 3 + z^2 / 5 + ..), z = s^2 <= 1 / 9
-    const float e = (float)E, w = 2.0f + e;
+    const float ef = (float)en;
+    const float e = x < 0.0 ? __builtin_amdgcn_rcpf(ef) : ef, w = 2.0f + e;
     float u = __builtin_amdgcn_rcpf(w);
     u = fmaf(u, fmaf(-w, u, 1.0f), u);
     const float s = e * u, z = s * s;

@@ -11,9 +11,14 @@
 // same time, one FP64 exponential for the whole batch, and the coefficients
 // return to all lanes as scalars.
 //
-// Arithmetic of a dot (all paths): FP64; lane l multiplies its elements in
-// order (2 l, 2 l + 1, and at d = 256 also 128 + 2 l, 129 + 2 l), and the 64
-// (32) partial sums are added by the butterfly over distances 32, 16, .. 1.
+// Arithmetic of a dot (all paths): FP64, one fused chain over elements 4 j ..
+// 4 j + 3 (and at d = 256 on over 128 + 4 j .. 131 + 4 j) for each j, then the
+// butterfly over the 32 (16) chains.  A chain's elements lie in two lanes, so
+// it passes between them by DPP; each lane's own sum and one more butterfly
+// step would take four instructions less per dot, but the order is part of the
+// result: minibatches of summed updates can be unstable enough (16,384 pairs
+// on 20,000 nodes) to grow the last bit of one dot into the tables' leading
+// digits.
 #pragma once
 
 #include "sgns_device.h"
@@ -43,12 +48,21 @@ struct FwdShape {
     static constexpr int kT = K + 2;                  // touches per pair
 };
 
-// Sums of n values over L lanes, value by value: after the call v[0] of a lane
-// is the sum of value lane_value(lane).
+// Sums of n values over the odd ones of L lanes, value by value: after the call
+// v[0] of a lane is the sum of value lane_value(lane).
 template <int N, int X, int A>
 __device__ __forceinline__ void reduce_values(double (&v)[A])
 {
-    if constexpr (X > 0) {
+    if constexpr (X == 1) {
+        // the sums are in the odd lanes: the even ones take their first half
+        constexpr int H = (N + 1) / 2;
+        const bool odd = (__lane_id() & 1) != 0;
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+            const double even = from_xor<1>(v[j]);
+            v[j] = odd ? v[j + H < N ? j + H : j] : even;
+        }
+    } else {
         constexpr int H = (N + 1) / 2;
 #pragma unroll
         for (int j = 0; j < H; ++j)
@@ -202,13 +216,16 @@ struct FwdBatch {
         for (int b = 0; b < S; ++b)
 #pragma unroll
             for (int k = 0; k <= K; ++k) {
-                double acc = (double)vin[b][0].x * (double)vo[b][k][0].x;
-                acc = fma((double)vin[b][0].y, (double)vo[b][k][0].y, acc);
+                // each chain: the even lane's elements, then the odd lane's
+                double acc = 0.0;
 #pragma unroll
-                for (int i = 1; i < V; ++i) {
-                    acc = fma((double)vin[b][i].x, (double)vo[b][k][i].x, acc);
-                    acc = fma((double)vin[b][i].y, (double)vo[b][k][i].y, acc);
-                }
+                for (int i = 0; i < V; ++i)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        if (i + h > 0) acc = from_xor<1>(acc);
+                        acc = fma((double)vin[b][i].x, (double)vo[b][k][i].x, acc);
+                        acc = fma((double)vin[b][i].y, (double)vo[b][k][i].y, acc);
+                    }
                 s[b * (K + 1) + k] = acc;
             }
         reduce_values<N, L / 2>(s);
@@ -231,7 +248,7 @@ struct FwdBatch {
         mine = one && ok;
         const double dk = s[0];
         const SigmaTerms t = sigma_terms(dk);
-        g = k == 0 ? lr * t.neg : -lr * t.pos;
+        g = k == 0 ? lr * (1.0 - t.sigma) : -lr * t.sigma;
         if (!ok) g = 0.0;
         if (mine) lacc += fmax(k == 0 ? -dk : dk, 0.0) + (double)t.l1p;
     }
