@@ -82,6 +82,19 @@ void DevBuf::alloc(Ctx* c, size_t nbytes)
     c->peak = std::max(c->peak, c->in_use);
 }
 
+bool try_alloc(DevBuf& b, Ctx* c, size_t bytes)
+{
+    try {
+        b.alloc(c, bytes);
+        return true;
+    } catch (const Error& e) {
+        if (e.code != FELOG_ENOMEM) throw;
+        (void)hipGetLastError();
+        clear_error();
+        return false;
+    }
+}
+
 void DevBuf::release()
 {
     if (ptr) {
@@ -487,20 +500,6 @@ felog_status felog_walks_info(const felog_walks* w, int64_t* n_walks, int32_t* l
 constexpr int64_t kTurnBytes = (int64_t)256 << 20;
 constexpr int64_t kTurnMinInts = 4096;
 constexpr int64_t kTurnMinWalks = 1024;
-
-// Allocates unless the card has no room (the budget is the caller's to check).
-static bool try_alloc(DevBuf& b, Ctx* c, size_t bytes)
-{
-    try {
-        b.alloc(c, bytes);
-        return true;
-    } catch (const Error& e) {
-        if (e.code != FELOG_ENOMEM) throw;
-        (void)hipGetLastError();
-        clear_error();
-        return false;
-    }
-}
 
 felog_status felog_walks_read_range(const felog_walks* w, int64_t first, int64_t count,
                                     int32_t* walks, int64_t cap)

@@ -64,6 +64,9 @@ constexpr int kIdSets = 3;   // fewest minibatch id buffer sets a model holds
 constexpr int kScanSpanMin = 512;   // fewest touches a block of the SGNS scan passes takes
 constexpr int kTimingEvents = 6;   // events per timed minibatch
 
+// b.alloc, but false when device memory or the budget is short.
+bool try_alloc(DevBuf& b, Ctx* c, size_t nbytes);
+
 struct Ctx {
     int device = 0;
     hipStream_t stream = nullptr;
@@ -281,6 +284,8 @@ void build_noise_from_counts(Model& m, const uint32_t* d_counts);   // counts in
 void set_noise_cdf(Model& m, const uint64_t* host_cdf);   // a saved table, checked
 void launch_degree_counts(Graph& g, uint32_t* d_counts);
 void launch_corpus_counts(const Walks& w, uint32_t* d_counts);
+void launch_symbol_counts(const Walks& w, unsigned long long* d_counts,
+                          unsigned long long* d_pads);   // d_pads: the padded positions
 void train_minibatches(Model& m, const Walks& w, const felog_train_params& p, int64_t first_mb,
                        int64_t n_mb, bool apply, felog_train_stats* stats,
                        int32_t* rows_in, float* d_in, int64_t cap_in, int64_t* n_in,

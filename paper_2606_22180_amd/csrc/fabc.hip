@@ -7,7 +7,7 @@
 // (the padding after an isolated start's only node), so padded positions are
 // profiled and compressed like nodes.
 //
-// Profile: symbol counts (node atomics; padding counted per block), the top
+// Profile: symbol counts (nodes and padding), the top
 // kFabcMax symbols by (count descending, symbol ascending) through rounds of
 // block-local bitonic sorts, then Eq. (8) in one thread: grow k while
 // p(k+1) >= c + 0.1 g(k), c = 1/L + 1/32, g(k) = (1 - F_k) + k c, in FP64 with
@@ -50,28 +50,6 @@ __device__ __forceinline__ bool better(const Cand& a, const Cand& b)
 }
 
 // ------------------------------------------------------------------ profile
-__global__ __launch_bounds__(256) void fabc_count_kernel(const int32_t* __restrict__ data,
-                                                         int64_t total,
-                                                         unsigned long long* counts,
-                                                         unsigned long long* pads)
-{
-    __shared__ unsigned long long lds[256];
-    unsigned long long mine = 0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total;
-         i += (int64_t)gridDim.x * 256) {
-        const int32_t v = data[i];
-        if (v >= 0) atomicAdd(&counts[v], 1ull);
-        else ++mine;
-    }
-    lds[threadIdx.x] = mine;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (threadIdx.x < s) lds[threadIdx.x] += lds[threadIdx.x + s];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0 && lds[0]) atomicAdd(pads, lds[0]);
-}
-
 // One round of the top selection: each block sorts kTopSpan candidates and
 // keeps its best kFabcMax.  The first round reads the counts (candidate i is
 // symbol i - 1, the padding first), later rounds the previous round's output.
@@ -470,14 +448,7 @@ void fabc_profile(const Walks& w, int32_t k_max, int32_t* k, int32_t* symbols,
     DevBuf cnt, pads, top_a, top_b, kbuf;
     cnt.alloc(&c, sizeof(unsigned long long) * std::max<int64_t>(n, 1));
     pads.alloc(&c, sizeof(unsigned long long));
-    FELOG_HIP(hipMemsetAsync(cnt.ptr, 0, cnt.bytes, c.stream));
-    FELOG_HIP(hipMemsetAsync(pads.ptr, 0, pads.bytes, c.stream));
-    if (positions > 0) {
-        const int64_t blocks = std::min<int64_t>((positions + 255) / 256, (int64_t)c.num_cus * 16);
-        hipLaunchKernelGGL(fabc_count_kernel, dim3(blocks), dim3(256), 0, c.stream,
-                           w.data.as<int32_t>(), positions, cnt.as<unsigned long long>(),
-                           pads.as<unsigned long long>());
-    }
+    launch_symbol_counts(w, cnt.as<unsigned long long>(), pads.as<unsigned long long>());
     int64_t n_cand = n + 1;
     int64_t nb = (n_cand + kTopSpan - 1) / kTopSpan;
     top_a.alloc(&c, sizeof(Cand) * nb * kFabcMax);

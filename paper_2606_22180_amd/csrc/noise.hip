@@ -9,6 +9,8 @@
 // holds u.  A guide table (Chen & Asau's indexed search) over the top bits of
 // x gives a starting node no larger than the answer, from which a short
 // forward scan finds it: O(1) expected reads per draw.
+#include <algorithm>
+
 #include "common.h"
 #include "noise.h"
 
@@ -56,28 +58,138 @@ void launch_degree_counts(Graph& g, uint32_t* d_counts)
     FELOG_HIP(hipGetLastError());
 }
 
-// Occurrences of each node in a walk corpus (integer atomics: order-free).
-__global__ void corpus_counts_kernel(const int32_t* __restrict__ walks, int64_t total,
-                                     uint32_t* counts)
+// Occurrences of each node in a walk corpus, and of the padding (integer sums:
+// order-free).
+//
+// Device-scope atomics meet beyond the XCDs' L2s and stop at about 18 G/s
+// whatever their addresses, a fiftieth of the rate at which the corpus can be
+// read.  A workgroup therefore counts one range of nodes over one part of the
+// corpus in LDS: the corpus is read once per range (the ranges of a part are
+// on one XCD and share its L2), and the parts' counts are stored and summed
+// without atomics.  41.9 M positions over 2^17 nodes: 2.36 ms -> 64 us,
+// and 17 us for the sum.
+constexpr int kCountRange = 40960;        // counters of a workgroup: all of a CU's LDS
+constexpr int kCountThreads = 1024;
+constexpr int kCountInFlight = 4;         // 16-byte loads of a thread
+// Beyond 32 ranges (1.3 M nodes) a part would be less than an eighth of the
+// corpus and the workgroups too few; below 2^20 positions the atomics take
+// less time (60 us) than clearing, storing and summing the counters.
+constexpr int kCountRangesMax = 32;
+constexpr int64_t kCountPositionsMin = (int64_t)1 << 20;
+
+template <class T>
+__global__ __launch_bounds__(256) void node_counts_kernel(const int32_t* __restrict__ data,
+                                                          int64_t total, T* counts,
+                                                          unsigned long long* pads)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < total; i += stride) {
-        int32_t v = walks[i];
-        if (v >= 0) atomicAdd(&counts[v], 1u);
+    unsigned long long mine = 0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total;
+         i += (int64_t)gridDim.x * 256) {
+        const int32_t v = data[i];
+        if (v >= 0) atomicAdd(&counts[v], (T)1);
+        else ++mine;
     }
+    if (pads && mine) atomicAdd(pads, mine);
+}
+
+// Block r * parts + p: the nodes [r * range, (r + 1) * range) over positions
+// [p * span, (p + 1) * span), span a multiple of 4; data is 16-byte aligned.
+__global__ __launch_bounds__(kCountThreads) void node_count_parts_kernel(
+    const int32_t* __restrict__ data, int64_t total, int64_t span, int32_t parts, int32_t n,
+    int32_t range, uint32_t* __restrict__ out, unsigned long long* pads)
+{
+    __shared__ uint32_t cnt[kCountRange];
+    const int32_t part = (int32_t)(blockIdx.x % (uint32_t)parts);
+    const int32_t lo = (int32_t)(blockIdx.x / (uint32_t)parts) * range;
+    const uint32_t width = (uint32_t)min(range, n - lo);
+    for (uint32_t i = threadIdx.x; i < width; i += kCountThreads) cnt[i] = 0;
+    __syncthreads();
+    const int64_t begin = (int64_t)part * span, end = min(begin + span, total);
+    uint32_t mine = 0;
+    auto count = [&](int32_t v) {
+        const uint32_t at = (uint32_t)v - (uint32_t)lo;   // a padding -1 is beyond every width
+        if (at < width) atomicAdd(&cnt[at], 1u);
+        mine += v < 0 ? 1u : 0u;
+    };
+    const int64_t quads = end > begin ? (end - begin) >> 2 : 0;
+    const int4* rows = reinterpret_cast<const int4*>(data + begin);
+    for (int64_t q0 = threadIdx.x; q0 < quads; q0 += kCountInFlight * kCountThreads) {
+        int4 v[kCountInFlight];
+#pragma unroll
+        for (int u = 0; u < kCountInFlight; ++u)
+            v[u] = rows[min(q0 + u * kCountThreads, quads - 1)];
+#pragma unroll
+        for (int u = 0; u < kCountInFlight; ++u)
+            if (q0 + u * kCountThreads < quads) {
+                count(v[u].x);
+                count(v[u].y);
+                count(v[u].z);
+                count(v[u].w);
+            }
+    }
+    for (int64_t i = begin + 4 * quads + threadIdx.x; i < end; i += kCountThreads) count(data[i]);
+    if (pads && lo == 0 && mine) atomicAdd(pads, (unsigned long long)mine);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < width; i += kCountThreads)
+        out[(int64_t)part * n + lo + i] = cnt[i];
+}
+
+template <class T>
+__global__ __launch_bounds__(256) void node_count_sum_kernel(const uint32_t* __restrict__ in,
+                                                             int32_t parts, int32_t n, T* counts)
+{
+    const int32_t v = blockIdx.x * 256 + threadIdx.x;
+    if (v >= n) return;
+    T s = 0;
+    for (int32_t p = 0; p < parts; ++p) s += in[(int64_t)p * n + v];
+    counts[v] = s;
+}
+
+template <class T>
+void launch_node_counts(const Walks& w, T* counts, unsigned long long* pads)
+{
+    Ctx& c = *w.g->ctx;
+    const int32_t n = w.g->n;
+    const int64_t total = w.W * (int64_t)w.L;
+    const int32_t* data = w.data.as<int32_t>();
+    if (pads) FELOG_HIP(hipMemsetAsync(pads, 0, sizeof *pads, c.stream));
+    const int64_t ranges = (n + kCountRange - 1) / (int64_t)kCountRange;
+    if (total >= kCountPositionsMin && ranges <= kCountRangesMax) {
+        // one workgroup per CU; a multiple of 8 parts puts a part's ranges on
+        // one XCD; the parts' counts take at most a quarter of the corpus
+        int64_t parts = std::min<int64_t>(c.num_cus / ranges, total / (4 * (int64_t)n));
+        parts = parts >= 8 ? parts / 8 * 8 : parts;
+        DevBuf buf;
+        if (parts > 0 && try_alloc(buf, &c, sizeof(uint32_t) * (size_t)(parts * n))) {
+            const int32_t range = (int32_t)((n + ranges - 1) / ranges);
+            const int64_t span = ((total + parts - 1) / parts + 3) / 4 * 4;
+            hipLaunchKernelGGL(node_count_parts_kernel, dim3((uint32_t)(ranges * parts)),
+                               dim3(kCountThreads), 0, c.stream, data, total, span, (int32_t)parts,
+                               n, range, buf.as<uint32_t>(), pads);
+            hipLaunchKernelGGL(node_count_sum_kernel<T>, dim3((n + 255) / 256), dim3(256), 0,
+                               c.stream, buf.as<uint32_t>(), (int32_t)parts, n, counts);
+            FELOG_HIP(hipGetLastError());
+            c.sync();   // before buf is given back
+            return;
+        }
+    }
+    FELOG_HIP(hipMemsetAsync(counts, 0, sizeof(T) * n, c.stream));
+    if (total == 0) return;
+    const int64_t blocks = std::min<int64_t>((total + 255) / 256, (int64_t)c.num_cus * 16);
+    hipLaunchKernelGGL(node_counts_kernel<T>, dim3(blocks), dim3(256), 0, c.stream, data, total,
+                       counts, pads);
+    FELOG_HIP(hipGetLastError());
 }
 
 void launch_corpus_counts(const Walks& w, uint32_t* d_counts)
 {
-    Ctx& c = *w.g->ctx;
-    FELOG_HIP(hipMemsetAsync(d_counts, 0, sizeof(uint32_t) * w.g->n, c.stream));
-    int64_t total = w.W * w.L;
-    if (total == 0) return;
-    int64_t blocks = std::min<int64_t>((total + 255) / 256, 65536);
-    hipLaunchKernelGGL(corpus_counts_kernel, dim3(blocks), dim3(256), 0, c.stream,
-                       w.data.as<int32_t>(), total, d_counts);
-    FELOG_HIP(hipGetLastError());
+    launch_node_counts<uint32_t>(w, d_counts, nullptr);
+}
+
+void launch_symbol_counts(const Walks& w, unsigned long long* d_counts,
+                          unsigned long long* d_pads)
+{
+    launch_node_counts<unsigned long long>(w, d_counts, d_pads);
 }
 
 // W_u = floor(2^16 * sqrt(c) * sqrt(sqrt(c))).

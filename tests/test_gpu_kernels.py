@@ -245,3 +245,42 @@ def test_large_reads_from_threads(fl):
 
     with ThreadPoolExecutor(4) as ex:
         assert all(ex.map(job, range(4)))
+
+
+# Counted in LDS: one range of nodes filled exactly, one node more (two
+# ranges), fewer than eight parts, a remainder of 1 to 3 positions in a part;
+# by atomics: too few positions, too many nodes, no room for the parts' counts
+@pytest.mark.parametrize("n,r,L,spare", [
+    (40960, 1, 103, None), (40961, 1, 103, None), (100001, 1, 13, None), (300, 700, 5, None),
+    (1203, 875, 1, None), (65536, 1, 15, None), (1400000, 1, 2, None), (40961, 1, 103, 400000)])
+def test_corpus_counts(fl, orc, n, r, L, spare):
+    """The unigram counts and the codec's profile against a host count; a
+    quarter of the nodes are isolated (padded walks), node 0 is a hub."""
+    m = n - n // 4
+    v = np.arange(1, m, dtype=np.int64)
+    e = np.unique(np.sort(np.concatenate([np.stack([0 * v, v], 1), np.stack([v[:-1], v[1:]], 1)]),
+                          axis=1), axis=0)
+    g = synth.csr_from_edges(n, e)
+
+    def run(budget):
+        c = fl.Context(0, hbm_budget=budget)
+        G = fl.Graph.from_csr(c, g.indptr, g.indices)
+        M = fl.Model.create(G, dim=64, seed=1)
+        W = fl.Walks.generate(G, r=r, L=L, seed=5)
+        held = c.bytes_in_use()
+        M.set_unigram(W)
+        return M.read_cdf(), W, held
+
+    cdf, W, held = run(0)
+    if spare is not None:
+        # room for the counts, the weights and the table, not for parts of them
+        cdf, W, _ = run(held + 20 * n + spare)
+    x = W.read().ravel()
+    counts = np.bincount(x[x >= 0], minlength=n)
+    assert np.array_equal(cdf, orc.neg_cdf(counts.astype(np.uint32)))
+    if spare is None:
+        _, sym, cnt, total = W.fabc_profile()
+        assert total == x.size
+        all_counts = np.concatenate([[np.count_nonzero(x < 0)], counts]).astype(np.uint64)
+        order = np.lexsort((np.arange(-1, n), -all_counts.astype(np.int64)))[:len(sym)]
+        assert np.array_equal(sym, order - 1) and np.array_equal(cnt, all_counts[order])
