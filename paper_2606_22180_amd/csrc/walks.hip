@@ -167,18 +167,22 @@ __global__ __launch_bounds__(256) void walk_uniform_kernel(
 // by the extreme alpha values alone (same result).
 //
 // The transition takes the first accepted attempt in attempt order, or after
-// max_attempts rejections the last proposal.  Attempts are evaluated S at a
-// time: their record reads are issued together, the searches of the
-// undecided ones run in lockstep, and the first accepted attempt of the group
-// (in order) is taken.  Every attempt keeps its own counter, so the walk is
-// the one that evaluating attempt by attempt gives; with most proposals
-// rejected (p = 0.5, q = 2, weights in (0, 1]), pairs of attempts save round
-// trips to memory (S = 2 keeps 8 waves per SIMD; S = 4 drops to 5 and was
-// slower).
+// max_attempts rejections the last proposal.
+//
+// Bound by chains of dependent random reads of very different lengths: one to
+// tens of attempts per transition, each with none to 20 rounds of search.  A
+// lane therefore goes its own way through its walk: every pass of the loop
+// gives the searching lanes kN2vRounds rounds and, once kN2vProposers lanes are
+// between attempts (or none is searching), those their next attempt (a Philox
+// block, most of a pass's instructions).  A wave then takes as many passes as
+// the longest of its 64 walks' sums needs; with all lanes at the same
+// transition, two attempts at a time, it was the sum of the longest, and idle
+// searches read along: 300,007 walks of 80 (deg 29, p = 0.5, q = 2, weighted)
+// 5.5 -> 4.0 ms, now about 300 M random reads at 75 G/s.
 // --------------------------------------------------------------------------
-constexpr int kN2vAttempts = 2;   // attempts evaluated per round trip
+constexpr int kN2vRounds = 2;      // 1 to 4 are within 6 %
+constexpr int kN2vProposers = 16;  // 8 to 48 are within 9 %
 
-template <int S>
 __global__ __launch_bounds__(256) void walk_node2vec_kernel(
     const int64_t* __restrict__ indptr, const int32_t* __restrict__ indices,
     const int2* __restrict__ edges, const float* __restrict__ wmax,
@@ -187,117 +191,103 @@ __global__ __launch_bounds__(256) void walk_node2vec_kernel(
     uint64_t seed, int64_t id_base, int32_t* __restrict__ walks,
     unsigned long long* __restrict__ capped)
 {
-    int64_t col = col0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t col = col0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (col >= col_end) return;
-    int64_t si = col % n_starts;
+    const int64_t si = col % n_starts;
     int32_t v = starts ? starts[si] : (int32_t)si;
-    int32_t prev = -1;
-    int64_t wid = id_base + col;
+    const int64_t wid = id_base + col;
     walks[col] = v;
     uint32_t my_capped = 0;
     const float a_hi = fmaxf(1.0f, inv_q), a_lo = fminf(1.0f, inv_q);
-    int32_t t = 0;
-    for (; t + 1 < L; ++t) {
-        const int64_t lo = indptr[v];
-        const int64_t deg = indptr[v + 1] - lo;
-        if (deg == 0) break;
-        const float bound = t == 0 ? wmax[v] : __fmul_rn(wmax[v], amax);
-        int64_t plo = 0, phi = 0;
-        if (t > 0) {
-            plo = indptr[prev];
-            phi = indptr[prev + 1];
+    // the transition from v (row lo, deg; previous node's row plo, pdeg), and its
+    // attempt
+    int32_t t = 0, prev = -1;
+    int64_t lo = indptr[v], plo = 0;
+    uint32_t deg = (uint32_t)(indptr[v + 1] - lo), pdeg = 0;
+    float bound = wmax[v];
+    uint32_t attempt = 0;
+    // the proposal, its row and largest weight
+    int32_t x = -1;
+    int64_t xlo = 0;
+    uint32_t xdeg = 0;
+    float wx = 0.0f, w = 0.0f, lhs = 0.0f;
+    // the search: target in indices[base + l, base + h)
+    int64_t base = 0;
+    uint32_t l = 0, h = 0;
+    int32_t target = 0;
+    enum { kPropose, kSearch, kDone };
+    int mode = L > 1 && deg > 0 ? kPropose : kDone;
+
+    // the attempt's end: the next transition, or the next attempt
+    auto settle = [&](bool accept) {
+        if (!accept && ++attempt < max_attempts) {
+            mode = kPropose;
+            return;
         }
-        int32_t x = -1;
-        bool done = false;
-        for (uint32_t a0 = 0; a0 < max_attempts && !done; a0 += S) {
-            int32_t xs[S];     // proposals
-            float ws[S], lhs[S];
-            int st[S];         // 0 rejected, 1 accepted, 2 decided by adjacency to prev
-#pragma unroll
-            for (int k = 0; k < S; ++k) {
-                const Rand4 r = philox4x32((uint32_t)wid, (uint32_t)(wid >> 32), (uint32_t)t,
-                                           kTagN2V | (a0 + (uint32_t)k), seed);
-                const int64_t e = lo + scale32(r.v[0], (uint32_t)deg);
-                if (edges) {
-                    const int2 rec = edges[e];
-                    xs[k] = rec.x;
-                    ws[k] = __int_as_float(rec.y);
-                } else {
-                    xs[k] = indices[e];
-                    ws[k] = 1.0f;
-                }
-                lhs[k] = __fmul_rn((float)(r.v[1] >> 8) * (1.0f / 16777216.0f), bound);
-            }
-            bool any_adj = false;
-#pragma unroll
-            for (int k = 0; k < S; ++k) {
-                if (t == 0) st[k] = lhs[k] < ws[k] ? 1 : 0;
-                else if (xs[k] == prev) st[k] = lhs[k] < __fmul_rn(ws[k], inv_p) ? 1 : 0;
-                else if (!(lhs[k] < __fmul_rn(ws[k], a_hi))) st[k] = 0;
-                else if (lhs[k] < __fmul_rn(ws[k], a_lo)) st[k] = 1;
-                else st[k] = 2;
-                any_adj = any_adj || st[k] == 2;
-            }
-            if (any_adj) {
-                // lower-bound searches of the undecided proposals, each in the
-                // shorter of the rows of prev and x for the other node, in
-                // lockstep: every round reads one index per search (inactive
-                // searches re-read prev's first entry)
-                int64_t l[S], h[S], en[S];
-                int32_t tg[S];
-#pragma unroll
-                for (int k = 0; k < S; ++k) {
-                    l[k] = plo;
-                    h[k] = plo;
-                    tg[k] = 0;
-                    if (st[k] == 2) {
-                        const int64_t xlo = indptr[xs[k]], xhi = indptr[xs[k] + 1];
-                        const bool in_x = xhi - xlo < phi - plo;
-                        l[k] = in_x ? xlo : plo;
-                        h[k] = in_x ? xhi : phi;
-                        tg[k] = in_x ? prev : xs[k];
-                    }
-                    en[k] = h[k];
-                }
-                for (;;) {
-                    bool active = false;
-                    int32_t val[S];
-                    int64_t mid[S];
-#pragma unroll
-                    for (int k = 0; k < S; ++k) {
-                        mid[k] = l[k] + ((h[k] - l[k]) >> 1);
-                        val[k] = indices[l[k] < h[k] ? mid[k] : plo];
-                    }
-#pragma unroll
-                    for (int k = 0; k < S; ++k) {
-                        if (l[k] < h[k]) {
-                            active = true;
-                            if (val[k] < tg[k]) l[k] = mid[k] + 1;
-                            else h[k] = mid[k];
-                        }
-                    }
-                    if (!active) break;
-                }
-#pragma unroll
-                for (int k = 0; k < S; ++k) {
-                    if (st[k] == 2) {
-                        const bool adj = l[k] < en[k] && indices[l[k] < en[k] ? l[k] : plo] == tg[k];
-                        st[k] = lhs[k] < __fmul_rn(ws[k], adj ? 1.0f : inv_q) ? 1 : 0;
-                    }
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < S; ++k) {
-                if (!done && a0 + (uint32_t)k < max_attempts) {
-                    x = xs[k];
-                    done = st[k] == 1;
-                }
-            }
-        }
-        if (!done) ++my_capped;
+        if (!accept) ++my_capped;
+        walks[(int64_t)(t + 1) * W + col] = x;
         prev = v;
+        plo = lo;
+        pdeg = deg;
         v = x;
-        walks[(int64_t)(t + 1) * W + col] = v;
+        lo = xlo;
+        deg = xdeg;
+        bound = __fmul_rn(wx, amax);
+        attempt = 0;
+        ++t;
+        mode = t + 1 < L && deg > 0 ? kPropose : kDone;
+    };
+
+    for (;;) {
+        const int searching = __popcll(__ballot(mode == kSearch));
+        const int proposing = __popcll(__ballot(mode == kPropose));
+        if (searching + proposing == 0) break;
+        if (mode == kPropose && (proposing >= kN2vProposers || searching == 0)) {
+            const Rand4 r = philox4x32((uint32_t)wid, (uint32_t)(wid >> 32), (uint32_t)t,
+                                       kTagN2V | attempt, seed);
+            const int64_t e = lo + scale32(r.v[0], deg);
+            if (edges) {
+                const int2 rec = edges[e];
+                x = rec.x;
+                w = __int_as_float(rec.y);
+            } else {
+                x = indices[e];
+                w = 1.0f;
+            }
+            lhs = __fmul_rn((float)(r.v[1] >> 8) * (1.0f / 16777216.0f), bound);
+            bool accept = false, undecided = false;
+            if (t == 0) accept = lhs < w;
+            else if (x == prev) accept = lhs < __fmul_rn(w, inv_p);
+            else if (lhs < __fmul_rn(w, a_hi)) {
+                accept = lhs < __fmul_rn(w, a_lo);
+                undecided = !accept;
+            }
+            if (accept || undecided || attempt + 1 == max_attempts) {
+                xlo = indptr[x];
+                xdeg = (uint32_t)(indptr[x + 1] - xlo);
+                wx = wmax[x];
+            }
+            if (undecided) {
+                const bool in_x = xdeg < pdeg;
+                base = in_x ? xlo : plo;
+                h = in_x ? xdeg : pdeg;
+                l = 0;
+                target = in_x ? prev : x;
+                mode = kSearch;
+            } else {
+                settle(accept);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kN2vRounds; ++k)
+            if (mode == kSearch) {
+                const uint32_t mid = l + ((h - l) >> 1);
+                const int32_t val = indices[base + mid];
+                if (val < target) l = mid + 1;
+                else h = mid;
+                const bool adj = val == target;
+                if (adj || l >= h) settle(lhs < __fmul_rn(w, adj ? 1.0f : inv_q));
+            }
     }
     for (int32_t s = t + 1; s < L; ++s) walks[(int64_t)s * W + col] = -1;
     if (my_capped) atomicAdd(capped, (unsigned long long)my_capped);
@@ -320,7 +310,7 @@ void launch_walk_columns(Walks& w, const felog_walk_params& p, const Active* sta
         FELOG_REQUIRE(d_capped, "node2vec walks need a device counter for capped proposals");
         float inv_p = 1.0f / p.p, inv_q = 1.0f / p.q;
         float amax = fmaxf(1.0f, fmaxf(inv_p, inv_q));
-        hipLaunchKernelGGL(walk_node2vec_kernel<kN2vAttempts>, dim3(blocks), dim3(256), 0, s,
+        hipLaunchKernelGGL(walk_node2vec_kernel, dim3(blocks), dim3(256), 0, s,
                            g.indptr.as<int64_t>(), g.indices.as<int32_t>(),
                            g.weighted ? g.edges.as<int2>() : nullptr, g.wmax.as<float>(), st,
                            n_starts, w.W, col0, col0 + ncols, w.L, inv_p, inv_q, amax, 1u << 16,
