@@ -77,19 +77,34 @@ constexpr int kCountInFlight = 4;         // 16-byte loads of a thread
 constexpr int kCountRangesMax = 32;
 constexpr int64_t kCountPositionsMin = (int64_t)1 << 20;
 
+// Adds a workgroup's paddings: one atomic, for they all meet at one address
+// (4 ns each).  s: a word per wave; below 2^32 paddings in a workgroup.
+__device__ __forceinline__ void add_pads(unsigned long long* pads, uint32_t mine, uint32_t* s)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off);
+    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = mine;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (uint32_t i = 1; i < blockDim.x / 64; ++i) mine += s[i];
+        if (mine) atomicAdd(pads, (unsigned long long)mine);
+    }
+}
+
 template <class T>
 __global__ __launch_bounds__(256) void node_counts_kernel(const int32_t* __restrict__ data,
                                                           int64_t total, T* counts,
                                                           unsigned long long* pads)
 {
-    unsigned long long mine = 0;
+    __shared__ uint32_t waves[4];
+    uint32_t mine = 0;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total;
          i += (int64_t)gridDim.x * 256) {
         const int32_t v = data[i];
         if (v >= 0) atomicAdd(&counts[v], (T)1);
         else ++mine;
     }
-    if (pads && mine) atomicAdd(pads, mine);
+    if (pads) add_pads(pads, mine, waves);
 }
 
 // Block r * parts + p: the nodes [r * range, (r + 1) * range) over positions
@@ -128,10 +143,13 @@ __global__ __launch_bounds__(kCountThreads) void node_count_parts_kernel(
             }
     }
     for (int64_t i = begin + 4 * quads + threadIdx.x; i < end; i += kCountThreads) count(data[i]);
-    if (pads && lo == 0 && mine) atomicAdd(pads, (unsigned long long)mine);
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < width; i += kCountThreads)
         out[(int64_t)part * n + lo + i] = cnt[i];
+    if (pads && lo == 0) {
+        __syncthreads();
+        add_pads(pads, mine, cnt);
+    }
 }
 
 template <class T>
@@ -160,7 +178,9 @@ void launch_node_counts(const Walks& w, T* counts, unsigned long long* pads)
         int64_t parts = std::min<int64_t>(c.num_cus / ranges, total / (4 * (int64_t)n));
         parts = parts >= 8 ? parts / 8 * 8 : parts;
         DevBuf buf;
-        if (parts > 0 && try_alloc(buf, &c, sizeof(uint32_t) * (size_t)(parts * n))) {
+        // a part's counts fit 32 bits
+        if (parts > 0 && total / parts < ((int64_t)1 << 32) - 4 &&
+            try_alloc(buf, &c, sizeof(uint32_t) * (size_t)(parts * n))) {
             const int32_t range = (int32_t)((n + ranges - 1) / ranges);
             const int64_t span = ((total + parts - 1) / parts + 3) / 4 * 4;
             hipLaunchKernelGGL(node_count_parts_kernel, dim3((uint32_t)(ranges * parts)),

@@ -284,3 +284,24 @@ def test_corpus_counts(fl, orc, n, r, L, spare):
         all_counts = np.concatenate([[np.count_nonzero(x < 0)], counts]).astype(np.uint64)
         order = np.lexsort((np.arange(-1, n), -all_counts.astype(np.int64)))[:len(sym)]
         assert np.array_equal(sym, order - 1) and np.array_equal(cnt, all_counts[order])
+
+
+# Every lane at its own transition: one step and none, few lanes of a wave,
+# walks that end at once beside long ones, and transitions that only end at the
+# cap (leaving a leaf needs the return to prev, accepted once in 10^6 attempts)
+@pytest.mark.parametrize("n,r,L,p,q,weighted", [
+    (5, 1, 1, 0.5, 2.0, False), (63, 1, 2, 0.5, 2.0, True), (65, 3, 33, 8.0, 0.125, True),
+    (200, 2, 50, 0.05, 20.0, False), (67, 1, 4, 1e6, 1.0, True)])
+def test_node2vec_lanes(fl, ctx, orc, n, r, L, p, q, weighted):
+    rng = np.random.default_rng(n)
+    m = n - n // 5                       # the last fifth is isolated
+    v = np.arange(1, m, dtype=np.int64)
+    e = np.concatenate([np.stack([0 * v, v], 1), rng.integers(0, max(m // 2, 2), (2 * n, 2))])
+    e = np.sort(e[e[:, 0] != e[:, 1]], axis=1)
+    e = np.unique(e, axis=0)
+    g = synth.csr_from_edges(n, e, *([synth.edge_weights(e.shape[0], 3)] if weighted else []))
+    G = fl.Graph.from_csr(ctx, g.indptr, g.indices, *([g.weights] if weighted else []))
+    W = fl.Walks.generate(G, r=r, L=L, seed=11, id_base=3, kind=fl.WALK_NODE2VEC, p=p, q=q)
+    want, capped = orc.walks_node2vec(g, np.arange(n), r, L, p, q, 11, 3)
+    assert np.array_equal(W.read(), want)
+    assert W.capped() == capped and (capped > 0) == (p == 1e6)
