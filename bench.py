@@ -596,8 +596,9 @@ def sgns_roofline(sts, d: int, K: int, pairs: int):
 # --------------------------------------------------------------- counters
 COUNTER_SUMMARY = os.path.join(ROOT, "profiles", "sgns_small_update_rmat23w_counters.md")
 COUNTER_SOURCES = ("paper_2606_22180_amd/csrc/sgns_small.hip",
-                   "paper_2606_22180_amd/csrc/sgns_device.h", "paper_2606_22180_amd/csrc/noise.h",
-                   "paper_2606_22180_amd/csrc/common.h")
+                   "paper_2606_22180_amd/csrc/sgns_device.h",
+                   "paper_2606_22180_amd/csrc/sgns_forward.h", "paper_2606_22180_amd/csrc/wave.h",
+                   "paper_2606_22180_amd/csrc/noise.h", "paper_2606_22180_amd/csrc/common.h")
 
 
 def kernel_sources_digest() -> str:

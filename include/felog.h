@@ -81,8 +81,9 @@ felog_status felog_ctx_set_timing(felog_ctx* ctx, int32_t every);
  * P (K + 2) <= 8192 touches (and K <= 14 at d = 64) run as plan launches (ids and a sort of each
  * minibatch's touches by row, many minibatches per launch) and one persistent
  * cooperative update launch per group of minibatches; larger ones run
- * per-minibatch launches.  path 1: per-minibatch launches always.  Both give
- * bit-identical tables.  blocks: workgroups of the persistent launch (0 = the
+ * per-minibatch launches.  path 1: per-minibatch launches always (with plans
+ * up to 16384 touches where they fit, else with the ids of a group of
+ * minibatches in launches of their own).  All give bit-identical tables.  blocks: workgroups of the persistent launch (0 = the
  * default, 64; capped at what can be resident at once).  With timing on
  * (felog_ctx_set_timing), every plan and update launch of path 0 is timed.
  * Errors: path not 0 or 1, blocks outside [0, 65536]. */
@@ -346,8 +347,8 @@ typedef struct felog_train_stats {
     int64_t timed_launches;   /* forward (and apply) launches timed with events    */
     double ms_forward;        /* summed duration of the timed forward launches     */
     double ms_apply;          /* summed duration of the timed apply launches       */
-    double ms_prep;           /* summed duration of the timed id / rank / offset   */
-                              /* launches that precede each timed forward          */
+    double ms_prep;           /* duration of the id / rank / offset or plan launches
+                                 of the timed minibatches (their share of a group's) */
     double ms_apply_first;    /* summed duration of the first of the timed apply
                                  launches (out rows, chunks of split rows)         */
     int64_t rows_out_single;  /* of rows_out, the rows touched once in their

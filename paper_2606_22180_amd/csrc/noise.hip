@@ -61,9 +61,8 @@ void launch_degree_counts(Graph& g, uint32_t* d_counts)
 // Occurrences of each node in a walk corpus, and of the padding (integer sums:
 // order-free).
 //
-// Device-scope atomics meet beyond the XCDs' L2s and stop at about 18 G/s
-// whatever their addresses, a fiftieth of the rate at which the corpus can be
-// read.  A workgroup therefore counts one range of nodes over one part of the
+// Device-scope atomics meet beyond the XCDs' L2s and run at 10 to 45 G/s, a
+// fiftieth of the rate at which the corpus can be read.  A workgroup therefore counts one range of nodes over one part of the
 // corpus in LDS: the corpus is read once per range (the ranges of a part are
 // on one XCD and share its L2), and the parts' counts are stored and summed
 // without atomics.  41.9 M positions over 2^17 nodes: 2.36 ms -> 64 us,
@@ -71,9 +70,10 @@ void launch_degree_counts(Graph& g, uint32_t* d_counts)
 constexpr int kCountRange = 40960;        // counters of a workgroup: all of a CU's LDS
 constexpr int kCountThreads = 1024;
 constexpr int kCountInFlight = 4;         // 16-byte loads of a thread
-// Beyond 32 ranges (1.3 M nodes) a part would be less than an eighth of the
-// corpus and the workgroups too few; below 2^20 positions the atomics take
-// less time (60 us) than clearing, storing and summing the counters.
+// The time grows with the ranges (104 M positions over 1.3 M nodes, 32 ranges,
+// where a part is an eighth of the corpus: 0.99 ms against 3.03 by atomics);
+// beyond 32 the parts no longer fill the XCDs.  At 2^20 positions the atomics
+// take 118 us and the parts 16 plus the allocation of their counts.
 constexpr int kCountRangesMax = 32;
 constexpr int64_t kCountPositionsMin = (int64_t)1 << 20;
 
