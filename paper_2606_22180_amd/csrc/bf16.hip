@@ -25,9 +25,9 @@
 // both a centre and a negative; summing its terms in a fixed order instead of
 // with atomics makes the tables bit-reproducible.  The touches' order comes
 // from a plan that sorts them by (table, row, touch): in LDS, one workgroup
-// per minibatch for up to 64 minibatches per launch, when 2P + M <= 8192,
+// per minibatch for up to 256 minibatches per launch, when 2P + M <= 8192,
 // else a radix sort per minibatch (stable, so equal rows keep touch order).
-// The ids (ctx, ctr, neg) of up to 64 minibatches come from one launch
+// The ids (ctx, ctr, neg) of up to 256 minibatches come from one launch
 // before them.
 // MFMA: v_mfma_f32_16x16x32_bf16.  Lane l holds 8 consecutive k of row
 // (l mod 16) of A and of column (l mod 16) of B, k chunk l / 16; it receives
@@ -129,6 +129,10 @@ __device__ __forceinline__ void sigma_fast(float x, float& sig, float& l1p)
 // They read only the walks and the noise table, so one launch draws them for
 // many minibatches and the per-minibatch launches start from the ids.
 constexpr int kIdBatch = 64;
+// The same with LDS plans where the context has no budget (7 MB more at P = M =
+// 1,024): a plan workgroup on every compute unit takes the 80 us that 64 of them
+// take, on the training stream (minibatch 24.2 -> 23.2 us).
+constexpr int kIdBatchWide = 256;
 
 __global__ __launch_bounds__(256) void bf16_ids_kernel(Bf16Args a, uint32_t mb0, uint32_t nmb,
                                                        uint32_t first0, uint64_t chunk_pairs,
@@ -454,7 +458,7 @@ __device__ __forceinline__ uint32_t touch_key(int32_t row, uint32_t t, uint32_t 
     return ((t >= P ? 1u : 0u) << rb) | (uint32_t)row;
 }
 
-// Plan of up to 64 minibatches with 2P + M <= kBfPlanMax, one workgroup per
+// Plan of up to 256 minibatches with 2P + M <= kBfPlanMax, one workgroup per
 // minibatch: keys (key << 16 | t) in LDS, bitonic sort ascending, then the
 // sorted keys and touches.
 constexpr int kBfPlanThreads = 512;
@@ -671,6 +675,18 @@ void train_minibatches_bf16(Model& m, Walks& w, const felog_train_params& p,
                                             (uint32_t*)nullptr, (uint32_t)ct, 0u, 32u, c.stream));
         m.bf_sort_tmp.alloc(&c, std::max<size_t>(tmp, 256));
     }
+    // wide id batches: a few MB more, not taken from a budget
+    int64_t id_batch = kIdBatch;
+    if (lds_plan && end - first_mb > kIdBatch && c.budget == 0) {
+        const size_t wide = sizeof(int32_t) * (size_t)kIdBatchWide * nt;
+        id_batch = kIdBatchWide;
+        for (DevBuf* x : {&m.bf_ids, &m.bf_skey, &m.bf_stouch}) {
+            DevBuf grown;
+            if (x->bytes >= wide) continue;
+            if (try_alloc(grown, &c, wide)) *x = std::move(grown);
+            else id_batch = kIdBatch;
+        }
+    }
     const int64_t nslots = (int64_t)P + M + (int64_t)split * (P / pr);
     DevBuf loss_part;
     loss_part.alloc(&c, sizeof(double) * nslots);
@@ -727,10 +743,10 @@ void train_minibatches_bf16(Model& m, Walks& w, const felog_train_params& p,
         a.mb = (uint32_t)b;
         if (b == batch_end) {
             // ids (and, when they fit in LDS, plans) of the next minibatches,
-            // up to kIdBatch and the chunk's end
+            // up to id_batch and the chunk's end
             while (gated <= chunk && gated < w.chunk_ready.size())
                 FELOG_HIP(hipStreamWaitEvent(c.stream, w.chunk_ready[gated++], 0));
-            int64_t lim = std::min<int64_t>(end, b + kIdBatch);
+            int64_t lim = std::min<int64_t>(end, b + id_batch);
             if (chunk + 1 < sch.chunk_first_mb.size())
                 lim = std::min<int64_t>(lim, sch.chunk_first_mb[chunk + 1]);
             batch0 = b;

@@ -305,3 +305,28 @@ def test_node2vec_lanes(fl, ctx, orc, n, r, L, p, q, weighted):
     want, capped = orc.walks_node2vec(g, np.arange(n), r, L, p, q, 11, 3)
     assert np.array_equal(W.read(), want)
     assert W.capped() == capped and (capped > 0) == (p == 1e6)
+
+
+# Id batches of the BF16 form: just past the narrow batch, at and past the wide
+# one, and cut by the chunks' ends; a context with a budget keeps the narrow one
+@pytest.mark.parametrize("n_mb,chunk", [(65, 0), (256, 0), (257, 0), (600, 90)])
+def test_bf16_id_batches(fl, n_mb, chunk):
+    n = 400
+    rng = np.random.default_rng(2)
+    e = np.sort(rng.integers(0, n, (2500, 2)), 1)
+    g = synth.csr_from_edges(n, np.unique(e[e[:, 0] != e[:, 1]], axis=0))
+
+    def train(budget):
+        c = fl.Context(0, hbm_budget=budget)
+        G = fl.Graph.from_csr(c, g.indptr, g.indices)
+        W = fl.Walks.generate(G, r=4, L=20, seed=4)
+        M = fl.Model.create(G, dim=64, seed=6, precision=fl.PREC_BF16)
+        prm = fl.train_params(window=3, negatives=5, minibatch_pairs=64, seed=9,
+                              shared_negatives=64, chunk_walks=chunk)
+        st = M.train_steps(W, prm, 0, n_mb)
+        assert st.minibatches == n_mb
+        return M.read(fl.TABLE_IN), M.read(fl.TABLE_OUT), st.loss
+
+    wide, narrow = train(0), train(1 << 30)
+    assert np.array_equal(wide[0], narrow[0]) and np.array_equal(wide[1], narrow[1])
+    assert wide[2] == narrow[2]
