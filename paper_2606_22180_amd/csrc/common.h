@@ -189,6 +189,7 @@ struct Model {
     int32_t cap_K = 0;
     int id_sets = 0;              // id sets with counters and offsets (at least kIdSets)
     int id_sets_cap = 0;          // id sets of the other arrays, for cap_pairs and cap_K
+    bool few_id_sets = false;     // memory was short: no more than kIdSets id sets
     MinibatchBufs mb;
     DevBuf ent_out;               // int4 [P(K+1)]: (FP64 g, ctx, pair-order key) of each
                                   // out-touch, by row segment

@@ -1136,13 +1136,41 @@ static uint64_t id_set_bytes(const SetStrides& st)
 }
 static uint64_t id_counter_bytes(int64_t n) { return 16 * (uint64_t)n + 4 * kMetaWords; }
 
+// Id sets beyond kIdSets are optional, and each holds 16 bytes per node: all of
+// a model's take at most an eighth of its two tables or 256 MiB, whichever is
+// more (at 65,536 pairs on 2^20 nodes eight sets take 0.15 GB beside 1.07 GB of
+// tables at d = 128; sixteen on 2^27 nodes would take 28 GB at any d).
+static int id_sets_wanted(const Model& m, const SetStrides& st, int want)
+{
+    const int64_t tables = 2 * (int64_t)sizeof(float) * m.g->n * m.dim;
+    const int64_t room = std::max<int64_t>(tables / 8, (int64_t)256 << 20);
+    const int64_t cost = (int64_t)(id_set_bytes(st) + id_counter_bytes(m.g->n));
+    return (int)std::max<int64_t>(kIdSets, std::min<int64_t>(want, kIdSets + room / cost));
+}
+
+// Gives the id sets beyond kIdSets back (with the others, which are allocated
+// again on use); the model takes no more than kIdSets from then on.
+static bool give_back_id_sets(Model& m)
+{
+    if (std::max(m.id_sets, m.id_sets_cap) <= kIdSets) return false;
+    MinibatchBufs& b = m.mb;
+    for (DevBuf* x : {&b.cnt_in, &b.cnt_out, &b.off_in, &b.off_out, &m.meta, &b.touch_row,
+                      &b.touch_pos, &b.list_in, &b.list_out, &b.chunks_in, &b.chunks_out,
+                      &b.split_in, &b.split_out, &b.mrows_in, &b.mrows_out, &b.partials})
+        x->release();
+    m.id_sets = m.id_sets_cap = 0;
+    m.few_id_sets = true;
+    return true;
+}
+
 // The model's scratch for minibatches of P pairs and K negatives with at least
-// kIdSets id sets, and as many as `want` when the budget and the card have
-// room; returns the id sets there are.
+// kIdSets id sets, and up to `want` (id_sets_wanted) where the budget and the
+// card have room; returns the id sets there are.
 static int ensure_id_buffers(Model& m, int64_t P, int K, int want)
 {
     Ctx& c = *m.ctx;
     const int64_t n = m.g->n;
+    const bool grows = m.cap_pairs < P || m.cap_K < K;
     const int64_t cp = std::max<int64_t>(m.cap_pairs, P);
     const int ck = std::max(m.cap_K, K);
     const SetStrides st = set_strides(n, cp, ck);
@@ -1150,7 +1178,29 @@ static int ensure_id_buffers(Model& m, int64_t P, int K, int want)
     DevBuf* const per_set[] = {&b.touch_row, &b.touch_pos, &b.list_in,  &b.list_out, &b.chunks_in,
                                &b.chunks_out, &b.split_in, &b.split_out, &b.mrows_in, &b.mrows_out,
                                &b.partials};
-    auto alloc_sets = [&](int sets) {
+    want = m.few_id_sets ? kIdSets : id_sets_wanted(m, st, want);
+    const int have = std::min(m.id_sets, m.id_sets_cap);
+    if (!grows && have >= want) return have;
+    if (grows) {
+        m.cap_pairs = 0;   // an allocation that fails leaves no stale capacity
+        m.cap_K = 0;
+        m.id_sets_cap = 0;
+        for (DevBuf* x : per_set) x->release();
+        for (DevBuf* x : {&m.ent_out, &m.dinp, &m.key_in, &m.partial}) x->release();
+    }
+    auto alloc_all = [&](int sets) {
+        // (sets of a smaller minibatch beyond those wanted now are given back)
+        if (m.id_sets < sets || (grows && m.id_sets > sets)) alloc_id_counters(m, sets);
+        if (m.cap_pairs < cp || m.cap_K < ck) {
+            m.ent_out.alloc(&c, sizeof(int4) * cp * (ck + 1));
+            m.dinp.alloc(&c, sizeof(float) * cp * m.dim);
+            m.key_in.alloc(&c, sizeof(uint32_t) * cp);
+            m.split_rows_in = st.split_in;
+            m.partial.alloc(&c, sizeof(double) * (st.split_in + st.split_out) * m.dim);
+            m.cap_pairs = cp;
+            m.cap_K = ck;
+        }
+        if (m.id_sets_cap >= sets) return;
         m.id_sets_cap = 0;
         for (DevBuf* x : per_set) x->release();
         const int64_t k = sets;
@@ -1167,41 +1217,29 @@ static int ensure_id_buffers(Model& m, int64_t P, int K, int want)
         b.partials.alloc(&c, (sizeof(uint4) + sizeof(unsigned long long)) * k * st.scan_blocks);
         m.id_sets_cap = sets;
     };
-    if (m.cap_pairs < P || m.cap_K < K) {
-        const int64_t touches_out = cp * (ck + 1);
-        m.cap_pairs = 0;   // an allocation that fails leaves no stale capacity
-        m.cap_K = 0;
-        m.id_sets_cap = 0;
-        for (DevBuf* x : per_set) x->release();
-        m.ent_out.alloc(&c, sizeof(int4) * touches_out);
-        m.dinp.alloc(&c, sizeof(float) * cp * m.dim);
-        m.key_in.alloc(&c, sizeof(uint32_t) * cp);
-        m.split_rows_in = st.split_in;
-        m.partial.alloc(&c, sizeof(double) * (st.split_in + st.split_out) * m.dim);
-        m.cap_pairs = cp;
-        m.cap_K = ck;
-    }
-    const int have = std::min(m.id_sets, m.id_sets_cap);
-    if (have >= std::max(want, (int)kIdSets)) return have;
-    int sets = std::max(want, (int)kIdSets);
-    if (c.budget) {
-        uint64_t held = 0;
+    int sets = want;
+    if (c.budget && sets > kIdSets) {
+        // more than fit the budget are not tried
+        uint64_t held = 0, need = (id_set_bytes(st) + id_counter_bytes(n)) * (uint64_t)sets;
         for (DevBuf* x : per_set) held += x->bytes;
         for (DevBuf* x : {&b.cnt_in, &b.cnt_out, &b.off_in, &b.off_out, &m.meta}) held += x->bytes;
+        if (grows)
+            need += 16 * (uint64_t)cp * (ck + 1) + 4 * (uint64_t)cp * (m.dim + 1) +
+                    8 * (uint64_t)(st.split_in + st.split_out) * m.dim;
         const uint64_t room = c.budget + held - std::min(c.budget + held, c.in_use);
-        if ((id_set_bytes(st) + id_counter_bytes(n)) * (uint64_t)sets > room)
-            sets = std::max(kIdSets, m.id_sets_cap);
+        if (need > room) sets = std::max(kIdSets, m.id_sets_cap);
     }
     try {
-        if (m.id_sets < sets) alloc_id_counters(m, sets);
-        if (m.id_sets_cap < sets) alloc_sets(sets);
+        alloc_all(sets);
     } catch (const Error& e) {
-        if (e.code != FELOG_ENOMEM || sets == kIdSets) throw;
+        // once more with kIdSets, after giving back what is more than those;
+        // the model does not try again
+        const bool more = give_back_id_sets(m) || sets > kIdSets;
+        if (e.code != FELOG_ENOMEM || !more) throw;
         (void)hipGetLastError();
         clear_error();
-        for (DevBuf* x : per_set) x->release();
-        if (m.id_sets != kIdSets) alloc_id_counters(m, kIdSets);
-        alloc_sets(kIdSets);
+        m.few_id_sets = true;
+        alloc_all(kIdSets);
     }
     return std::min(m.id_sets, m.id_sets_cap);
 }
@@ -1301,10 +1339,6 @@ void train_minibatches(Model& m, const Walks& wc, const felog_train_params& p, i
     if (apply && !one_stream)
         G = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)kIdGroupMax, end - first_mb,
                                                          kIdGroupTouches / (P * (K + 2))}));
-    const int id_sets = ensure_id_buffers(m, P, K, G > 1 ? 2 * G : kIdSets);
-    if (G > 1 && id_sets < 2 * G) G = std::max(1, id_sets / 2);
-    const int rings = G > 1 ? 2 : kIdSets;
-    const SetStrides st = set_strides(m.g->n, m.cap_pairs, m.cap_K);
     // pairs per forward wave: two steps (at 65,536 pairs, d = 128, K = 5 one
     // step ran 71 us, two to four 63; at 5,000 pairs, d = 256, K = 7 one step
     // 18.1, two 17.4, four 20.2), one where two would leave fewer than eight
@@ -1313,14 +1347,21 @@ void train_minibatches(Model& m, const Walks& wc, const felog_train_params& p, i
     const int ppw = P >= (int64_t)2 * side * c.num_cus * 8 ? std::min(64 / (K + 2), 2 * side) : side;
     const int64_t waves = (P + ppw - 1) / ppw;
     const int64_t blocks = (waves + 3) / 4;
-    DevBuf loss_part;
+    // the call's own buffers come before the id sets, which take what is left
+    DevBuf loss_part, slices, vin, vout;
     loss_part.alloc(&c, sizeof(double) * blocks * 4);
+    std::vector<int32_t> sl = make_slices(w.L, p.window);
+    slices.alloc(&c, sizeof(int32_t) * std::max<size_t>(sl.size(), 1));
+    if (!apply) {
+        vin.alloc(&c, sizeof(float) * (size_t)P * m.dim);
+        vout.alloc(&c, sizeof(float) * (size_t)P * (K + 1) * m.dim);
+    }
+    const int id_sets = ensure_id_buffers(m, P, K, G > 1 ? 2 * G : kIdSets);
+    if (G > 1 && id_sets < 2 * G) G = std::max(1, id_sets / 2);
+    const int rings = G > 1 ? 2 : kIdSets;
+    const SetStrides st = set_strides(m.g->n, m.cap_pairs, m.cap_K);
     FELOG_HIP(hipMemsetAsync(loss_part.ptr, 0, sizeof(double) * blocks * 4, c.stream));
     FELOG_HIP(hipMemsetAsync(m.row_totals.ptr, 0, sizeof(uint64_t) * 3, c.stream));
-
-    std::vector<int32_t> sl = make_slices(w.L, p.window);
-    DevBuf slices;
-    slices.alloc(&c, sizeof(int32_t) * std::max<size_t>(sl.size(), 1));
     if (!sl.empty())
         FELOG_HIP(hipMemcpyAsync(slices.ptr, sl.data(), sizeof(int32_t) * sl.size(),
                                  hipMemcpyHostToDevice, c.stream));
@@ -1524,9 +1565,6 @@ void train_minibatches(Model& m, const Walks& wc, const felog_train_params& p, i
         IdGroup ig{};
         finish_group(ig, a, 0, 1);
         gate(c.stream, chunk);
-        DevBuf vin, vout;
-        vin.alloc(&c, sizeof(float) * (size_t)P * m.dim);
-        vout.alloc(&c, sizeof(float) * (size_t)P * (K + 1) * m.dim);
         FELOG_HIP(hipMemsetAsync(vin.ptr, 0, vin.bytes, c.stream));
         FELOG_HIP(hipMemsetAsync(vout.ptr, 0, vout.bytes, c.stream));
         launch_ids(m, a, ig, c.stream);

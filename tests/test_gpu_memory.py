@@ -1,0 +1,77 @@
+"""Device memory that training takes beyond what it needs: bounded, and not in
+the way of anything that fits without it.  Results do not depend on it."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fl():
+    from paper_2606_22180_amd import build, felog
+    import os
+    if not os.path.exists(build.LIB):
+        build.build()
+    felog.load()
+    return felog
+
+
+def _ring(n):
+    """The cycle 0, 1, .., n - 1."""
+    v = np.arange(n, dtype=np.int64)
+    nbr = np.sort(np.stack([(v - 1) % n, (v + 1) % n], 1), 1)
+    return np.arange(0, 2 * n + 1, 2, dtype=np.int64), nbr.ravel().astype(np.int32)
+
+
+def _model(fl, ctx, n, *, dim=64, starts=3000, L=12, precision=0):
+    G = fl.Graph.from_csr(ctx, *_ring(n))
+    A = fl.Active.from_host(G, np.arange(min(starts, n), dtype=np.int32))
+    W = fl.Walks.generate(G, r=2, L=L, seed=3, starts=A)
+    M = fl.Model.create(G, dim=dim, seed=5, precision=precision)
+    return G, A, W, M
+
+
+def _prm(fl, P, K=5):
+    return fl.train_params(window=4, negatives=K, minibatch_pairs=P, seed=9)
+
+
+def test_id_sets_are_bounded(fl):
+    """2,500 pairs on 2^22 nodes: id sets of 67 MB, of which sixteen would let
+    eight minibatches' ids share a launch.  Beyond the three of a model, an
+    eighth of its tables (268 MB), and the same tables as three sets give."""
+    n, prm = 1 << 22, _prm(fl, 2500)
+    c = fl.Context(0)
+    objs = _model(fl, c, n)
+    held = c.bytes_in_use()
+    objs[3].train_steps(objs[2], prm, 0, 20)
+    grown = c.bytes_in_use() - held
+    print("[gpu] grown by", grown, flush=True)
+    assert grown <= 2 * 4 * n * 64 // 8 + (32 << 20)
+    rows = [objs[3].read(t)[:4096] for t in (0, 1)]
+    for o in reversed(objs):
+        o.close()
+    c2 = fl.Context(0, hbm_budget=held + (60 << 20))   # three sets only
+    objs = _model(fl, c2, n)
+    objs[3].train_steps(objs[2], prm, 0, 20)
+    assert all(np.array_equal(a, objs[3].read(t)[:4096]) for t, a in enumerate(rows))
+
+
+def test_larger_minibatches_after_groups(fl):
+    """A budget that one minibatch of 60,000 pairs fits still does after groups
+    of smaller minibatches took id sets from it."""
+    n = 1 << 16
+
+    def steps(budget, small_first):
+        c = fl.Context(0, hbm_budget=budget)
+        objs = _model(fl, c, n)
+        if small_first:
+            objs[3].train_steps(objs[2], _prm(fl, 2500), 0, 20)
+        else:
+            objs[3].train_delta(objs[2], _prm(fl, 64), 0)    # (the corpus's column list)
+        objs[3].train_steps(objs[2], _prm(fl, 60000), 0, 1)
+        return c.bytes_in_use()
+
+    need = steps(0, False)
+    print("[gpu] needed", need, flush=True)
+    steps(need + (2 << 20), False)
+    steps(need + (2 << 20), True)
