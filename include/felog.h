@@ -62,7 +62,9 @@ typedef struct felog_model felog_model;
 /* Bind a context to HIP device `device` and stream `hip_stream` (a hipStream_t,
  * or NULL for the null stream).  `hbm_budget_bytes` caps the device memory the
  * context may hold at once (0 = no cap); an allocation beyond it fails with
- * FELOG_ENOMEM. */
+ * FELOG_ENOMEM.  Memory that the context's models took beyond what training
+ * needs (at most an eighth of a model's tables or 256 MiB, whichever is more,
+ * and some tens of MB of plans) is given back first. */
 felog_status felog_ctx_create(int device, void* hip_stream, uint64_t hbm_budget_bytes,
                               felog_ctx** out);
 /* Every object created on the context (graphs and what is made from them)

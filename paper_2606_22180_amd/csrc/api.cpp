@@ -61,10 +61,11 @@ DevBuf& DevBuf::operator=(DevBuf&& o) noexcept
     return *this;
 }
 
-void DevBuf::alloc(Ctx* c, size_t nbytes)
+void DevBuf::alloc(Ctx* c, size_t nbytes, bool spare)
 {
     release();
     if (nbytes == 0) nbytes = 16;
+    if (c->budget && c->in_use + nbytes > c->budget && !spare) c->give_back();
     if (c->budget && c->in_use + nbytes > c->budget)
         fail(FELOG_ENOMEM, "HBM budget exceeded: %llu bytes held, %llu requested, budget %llu",
              (unsigned long long)c->in_use, (unsigned long long)nbytes,
@@ -72,6 +73,10 @@ void DevBuf::alloc(Ctx* c, size_t nbytes)
     c->make_current();
     void* p = nullptr;
     hipError_t e = hipMalloc(&p, nbytes);
+    if (e == hipErrorOutOfMemory && !spare && c->give_back()) {
+        (void)hipGetLastError();
+        e = hipMalloc(&p, nbytes);
+    }
     if (e != hipSuccess)
         fail(FELOG_ENOMEM, "hipMalloc(%llu) failed: %s", (unsigned long long)nbytes,
              hipGetErrorString(e));
@@ -85,7 +90,7 @@ void DevBuf::alloc(Ctx* c, size_t nbytes)
 bool try_alloc(DevBuf& b, Ctx* c, size_t bytes)
 {
     try {
-        b.alloc(c, bytes);
+        b.alloc(c, bytes, true);
         return true;
     } catch (const Error& e) {
         if (e.code != FELOG_ENOMEM) throw;
@@ -105,6 +110,31 @@ void DevBuf::release()
     ptr = nullptr;
     bytes = 0;
     ctx = nullptr;
+}
+
+bool Ctx::give_back()
+{
+    bool freed = false;
+    for (Model* m : models) freed = m->give_back() || freed;
+    return freed;
+}
+
+bool Model::give_back()
+{
+    if (held) return false;
+    const HoldScratch hold(*this);   // (what it keeps is allocated anew)
+    const uint64_t before = ctx->in_use;
+    shrink_id_sets(*this);
+    shrink_plans(*this);
+    shrink_id_batches(*this);
+    return ctx->in_use < before;
+}
+
+Model::~Model()
+{
+    if (!ctx) return;
+    auto it = std::find(ctx->models.begin(), ctx->models.end(), this);
+    if (it != ctx->models.end()) ctx->models.erase(it);
 }
 
 void Ctx::make_current() const { (void)hipSetDevice(device); }
@@ -173,6 +203,7 @@ static std::unique_ptr<felog_model> new_model(felog_graph* g, const felog_model_
     Ctx* c = g->ctx;
     auto m = std::make_unique<felog_model>();
     m->ctx = c;
+    c->models.push_back(m.get());
     m->g = g;
     m->dim = p->dim;
     m->neg_dist = p->neg_dist;

@@ -627,6 +627,29 @@ __global__ void loss_sum_kernel(const double* part, int64_t n, double* out)
     if (threadIdx.x == 0) out[0] = lds[0];
 }
 
+// Bytes of the ids, and of the sorted keys or touches, for minibatches of up to P
+// pairs and M negatives: a narrow id batch, or one large minibatch's sort.
+static size_t id_bytes(size_t P, size_t M) { return sizeof(int32_t) * (2 * P + M) * kIdBatch; }
+static size_t sorted_bytes(size_t P, size_t M)
+{
+    const size_t ct = 2 * P + M;
+    return sizeof(uint32_t) * std::max(ct, (size_t)kIdBatch * std::min<size_t>(ct, kBfPlanMax));
+}
+
+// Leaves the model narrow id batches if it has wide ones; it takes no more from then on.
+void shrink_id_batches(Model& m)
+{
+    const size_t ids = id_bytes(m.bf_P, m.bf_M), sorted = sorted_bytes(m.bf_P, m.bf_M);
+    if (m.bf_ids.bytes <= ids && m.bf_skey.bytes <= sorted && m.bf_stouch.bytes <= sorted) return;
+    m.bf_narrow = true;
+    m.bf_ids.release();
+    m.bf_skey.release();
+    m.bf_stouch.release();
+    if (!try_alloc(m.bf_ids, m.ctx, ids) || !try_alloc(m.bf_skey, m.ctx, sorted) ||
+        !try_alloc(m.bf_stouch, m.ctx, sorted))
+        m.bf_P = m.bf_M = 0;   // (they are taken on the next use)
+}
+
 void train_minibatches_bf16(Model& m, Walks& w, const felog_train_params& p,
                             const TrainSchedule& sch, const int32_t* d_slices, int64_t first_mb,
                             int64_t end, float* cap_in, float* cap_out, felog_train_stats* stats)
@@ -638,11 +661,22 @@ void train_minibatches_bf16(Model& m, Walks& w, const felog_train_params& p,
     const int d = m.dim;
     uint32_t rb = 1;
     while (((int64_t)1 << rb) <= m.g->n) ++rb;   // n < 2^rb
+    // blocks per panel of the fused launch: at least one per compute unit
+    // (panels of 32 rows, one block resident each) or two, where 4 suffice
+    const uint32_t pr = d == 256 ? panel_rows<256>() : panel_rows<128>();
+    const uint32_t panels = P / pr + M / pr;
+    uint32_t split = 1;
+    while (split < 4 && panels * split < (pr == 32 ? 256u : 512u)) split *= 2;
+    const int64_t nslots = (int64_t)P + M + (int64_t)split * (P / pr);
+    DevBuf loss_part;
+    loss_part.alloc(&c, sizeof(double) * nslots);
+    FELOG_HIP(hipMemsetAsync(loss_part.ptr, 0, sizeof(double) * nslots, c.stream));
+    const HoldScratch hold(m);
     if (m.bf_P < P || m.bf_M < M) {
         m.bf_P = std::max(m.bf_P, P);
         m.bf_M = std::max(m.bf_M, M);
-        const size_t cp = m.bf_P, cm = m.bf_M, ct = 2 * cp + cm;
-        m.bf_ids.alloc(&c, sizeof(int32_t) * ct * kIdBatch);
+        const size_t cp = m.bf_P, cm = m.bf_M;
+        m.bf_ids.alloc(&c, id_bytes(cp, cm));
         m.bf_C.alloc(&c, sizeof(uint16_t) * cp * d);
         m.bf_O.alloc(&c, sizeof(uint16_t) * cp * d);
         m.bf_N.alloc(&c, sizeof(uint16_t) * cm * d);
@@ -650,19 +684,12 @@ void train_minibatches_bf16(Model& m, Walks& w, const felog_train_params& p,
         m.bf_Nt.alloc(&c, sizeof(uint16_t) * cm * d);
         m.bf_g0.alloc(&c, sizeof(float) * cp);
         // a launch group's LDS plans or one large minibatch's sorted touches
-        const size_t sorted = std::max(ct, (size_t)kIdBatch * std::min<size_t>(ct, kBfPlanMax));
-        m.bf_skey.alloc(&c, sizeof(uint32_t) * sorted);
-        m.bf_stouch.alloc(&c, sizeof(uint32_t) * sorted);
+        m.bf_skey.alloc(&c, sorted_bytes(cp, cm));
+        m.bf_stouch.alloc(&c, sorted_bytes(cp, cm));
         m.bf_kin.release();
         m.bf_vin.release();
         m.bf_sort_tmp.release();
     }
-    // blocks per panel of the fused launch: at least one per compute unit
-    // (panels of 32 rows, one block resident each) or two, where 4 suffice
-    const uint32_t pr = d == 256 ? panel_rows<256>() : panel_rows<128>();
-    const uint32_t panels = P / pr + M / pr;
-    uint32_t split = 1;
-    while (split < 4 && panels * split < (pr == 32 ? 256u : 512u)) split *= 2;
     if (m.bf_delta.bytes < sizeof(float) * split * (size_t)nt * d)
         m.bf_delta.alloc(&c, sizeof(float) * split * (size_t)nt * d);
     if (!lds_plan && !m.bf_sort_tmp.ptr) {
@@ -677,21 +704,17 @@ void train_minibatches_bf16(Model& m, Walks& w, const felog_train_params& p,
     }
     // wide id batches: a few MB more, not taken from a budget
     int64_t id_batch = kIdBatch;
-    if (lds_plan && end - first_mb > kIdBatch && c.budget == 0) {
+    if (lds_plan && end - first_mb > kIdBatch && c.budget == 0 && !m.bf_narrow) {
         const size_t wide = sizeof(int32_t) * (size_t)kIdBatchWide * nt;
         id_batch = kIdBatchWide;
         for (DevBuf* x : {&m.bf_ids, &m.bf_skey, &m.bf_stouch}) {
             DevBuf grown;
             if (x->bytes >= wide) continue;
             if (try_alloc(grown, &c, wide)) *x = std::move(grown);
-            else id_batch = kIdBatch;
+            else m.bf_narrow = true;   // not tried again
         }
+        if (m.bf_narrow) id_batch = kIdBatch;
     }
-    const int64_t nslots = (int64_t)P + M + (int64_t)split * (P / pr);
-    DevBuf loss_part;
-    loss_part.alloc(&c, sizeof(double) * nslots);
-    FELOG_HIP(hipMemsetAsync(loss_part.ptr, 0, sizeof(double) * nslots, c.stream));
-
     Bf16Args a{};
     a.tin = m.tin.as<float>();
     a.tout = m.tout.as<float>();

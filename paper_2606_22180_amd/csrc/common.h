@@ -55,7 +55,10 @@ struct DevBuf {
     DevBuf(DevBuf&& o) noexcept { *this = std::move(o); }
     DevBuf& operator=(DevBuf&& o) noexcept;
     ~DevBuf() { release(); }
-    void alloc(Ctx* c, size_t nbytes);
+    // Where the budget or the card is short, the context's idle models first
+    // give back what they can take again (Model::give_back); not for `spare`
+    // memory, which its user can do without.
+    void alloc(Ctx* c, size_t nbytes, bool spare = false);
     void release();
     template <class T> T* as() const { return static_cast<T*>(ptr); }
 };
@@ -64,8 +67,10 @@ constexpr int kIdSets = 3;   // fewest minibatch id buffer sets a model holds
 constexpr int kScanSpanMin = 512;   // fewest touches a block of the SGNS scan passes takes
 constexpr int kTimingEvents = 6;   // events per timed minibatch
 
-// b.alloc, but false when device memory or the budget is short.
+// b.alloc of spare memory; false when device memory or the budget is short.
 bool try_alloc(DevBuf& b, Ctx* c, size_t nbytes);
+
+struct Model;
 
 struct Ctx {
     int device = 0;
@@ -91,6 +96,8 @@ struct Ctx {
     int32_t sgns_blocks = 0;
     // every launch on `stream`: the second and third streams are `stream` itself
     bool single_stream = false;
+    std::vector<Model*> models;   // those that give_back asks
+    bool give_back();             // true when memory came free
     void make_current() const;
     void sync() const;
     void ensure_aux();
@@ -206,6 +213,7 @@ struct Model {
     // minibatch's touch info, segments, position pairs and counts; per
     // minibatch, the out-touch coefficients, in-row deltas and context copies
     int64_t sm_tmax = 0, sm_G = 0, sm_pairs = 0;
+    int64_t sm_keep_tmax = 0, sm_keep_G = 0;   // plans that shrink_plans leaves
     int32_t sm_dim = 0;
     DevBuf sm_tinfo, sm_segs, sm_spair, sm_meta, sm_gpos, sm_dinp, sm_ctxc;
     // shared-negative (BF16) minibatch scratch
@@ -215,6 +223,27 @@ struct Model {
     // a launch group (small minibatches) or one minibatch with its sort input
     // and radix-sort storage (large ones)
     DevBuf bf_delta, bf_skey, bf_stouch, bf_kin, bf_vin, bf_sort_tmp;
+    bool bf_narrow = false;       // memory was short: no wide id batches
+
+    bool held = false;            // a training call is using the scratch (HoldScratch)
+    // Frees the scratch that makes launches cheaper and that training does
+    // without: id sets beyond kIdSets, plans of more minibatches than a launch
+    // needs, wide BF16 id batches.  True when memory came free.
+    bool give_back();
+    Model() = default;
+    Model(const Model&) = delete;
+    Model& operator=(const Model&) = delete;
+    ~Model();
+};
+
+// Keeps the model's scratch where it is until the end of a training call.  The
+// call's other allocations come before it.
+struct HoldScratch {
+    Model& m;
+    explicit HoldScratch(Model& model) : m(model) { m.held = true; }
+    ~HoldScratch() { m.held = false; }
+    HoldScratch(const HoldScratch&) = delete;
+    HoldScratch& operator=(const HoldScratch&) = delete;
 };
 
 // Minibatch schedule of one training call over a corpus.
@@ -292,6 +321,11 @@ void train_minibatches(Model& m, const Walks& w, const felog_train_params& p, in
                        int32_t* rows_in, float* d_in, int64_t cap_in, int64_t* n_in,
                        int32_t* rows_out, float* d_out, int64_t cap_out, int64_t* n_out);
 int64_t count_minibatches(Walks& w, const felog_train_params& p, int64_t* total_pairs);
+// the parts of Model::give_back
+void shrink_id_sets(Model& m);
+void shrink_plans(Model& m);
+void shrink_id_batches(Model& m);
+void drop_plans(Model& m);   // all of them
 void model_alloc_update_state(Model& m);   // row counters, offsets, minibatch counters
 void fabc_profile(const Walks& w, int32_t k_max, int32_t* k, int32_t* symbols,
                   uint64_t* counts, int32_t* n_ranked, uint64_t* total);

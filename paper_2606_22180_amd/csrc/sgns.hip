@@ -873,13 +873,14 @@ int64_t count_minibatches(Walks& w, const felog_train_params& p, int64_t* total_
 static void alloc_id_counters(Model& m, int sets)
 {
     Ctx& c = *m.ctx;
+    const bool spare = sets > kIdSets;
     const int64_t n = m.g->n;
     MinibatchBufs& b = m.mb;
     m.id_sets = 0;
     for (DevBuf* x : {&b.cnt_in, &b.cnt_out, &b.off_in, &b.off_out, &m.meta}) x->release();
     for (DevBuf* x : {&b.cnt_in, &b.cnt_out, &b.off_in, &b.off_out})
-        x->alloc(&c, sizeof(uint32_t) * n * sets);
-    m.meta.alloc(&c, sizeof(uint32_t) * sets * kMetaWords);
+        x->alloc(&c, sizeof(uint32_t) * n * sets, spare);
+    m.meta.alloc(&c, sizeof(uint32_t) * sets * kMetaWords, spare);
     m.id_sets = sets;
     m.counters_dirty = true;
 }
@@ -1148,19 +1149,47 @@ static int id_sets_wanted(const Model& m, const SetStrides& st, int want)
     return (int)std::max<int64_t>(kIdSets, std::min<int64_t>(want, kIdSets + room / cost));
 }
 
-// Gives the id sets beyond kIdSets back (with the others, which are allocated
-// again on use); the model takes no more than kIdSets from then on.
-static bool give_back_id_sets(Model& m)
+// (Re)allocates the arrays of `sets` id sets other than the counters.
+static void alloc_id_sets(Model& m, int sets, const SetStrides& st)
 {
-    if (std::max(m.id_sets, m.id_sets_cap) <= kIdSets) return false;
+    Ctx& c = *m.ctx;
     MinibatchBufs& b = m.mb;
-    for (DevBuf* x : {&b.cnt_in, &b.cnt_out, &b.off_in, &b.off_out, &m.meta, &b.touch_row,
-                      &b.touch_pos, &b.list_in, &b.list_out, &b.chunks_in, &b.chunks_out,
-                      &b.split_in, &b.split_out, &b.mrows_in, &b.mrows_out, &b.partials})
-        x->release();
-    m.id_sets = m.id_sets_cap = 0;
+    const bool spare = sets > kIdSets;
+    struct {
+        DevBuf& buf;
+        size_t bytes;
+    } const arrays[] = {
+        {b.touch_row, sizeof(int32_t) * st.touches},
+        {b.touch_pos, sizeof(uint32_t) * st.touches},
+        {b.list_in, sizeof(int32_t) * st.in},
+        {b.list_out, sizeof(int32_t) * st.out},
+        {b.chunks_in, sizeof(int4) * st.in},
+        {b.chunks_out, sizeof(int4) * st.out},
+        {b.split_in, sizeof(int4) * st.split_in},
+        {b.split_out, sizeof(int4) * st.split_out},
+        {b.mrows_in, sizeof(int4) * st.mrows_in},
+        {b.mrows_out, sizeof(int4) * st.mrows_out},
+        {b.partials, (sizeof(uint4) + sizeof(unsigned long long)) * st.scan_blocks}};
+    m.id_sets_cap = 0;
+    for (const auto& x : arrays) x.buf.release();
+    for (const auto& x : arrays) x.buf.alloc(&c, sets * x.bytes, spare);
+    m.id_sets_cap = sets;
+}
+
+// Leaves the model kIdSets id sets if it has more; it takes no more from then on.
+void shrink_id_sets(Model& m)
+{
+    if (std::max(m.id_sets, m.id_sets_cap) <= kIdSets) return;
     m.few_id_sets = true;
-    return true;
+    try {
+        if (m.id_sets > kIdSets) alloc_id_counters(m, kIdSets);
+        if (m.id_sets_cap > kIdSets)
+            alloc_id_sets(m, kIdSets, set_strides(m.g->n, m.cap_pairs, m.cap_K));
+    } catch (const Error& e) {
+        if (e.code != FELOG_ENOMEM) throw;   // (they are taken on the next use)
+        (void)hipGetLastError();
+        clear_error();
+    }
 }
 
 // The model's scratch for minibatches of P pairs and K negatives with at least
@@ -1175,9 +1204,10 @@ static int ensure_id_buffers(Model& m, int64_t P, int K, int want)
     const int ck = std::max(m.cap_K, K);
     const SetStrides st = set_strides(n, cp, ck);
     MinibatchBufs& b = m.mb;
-    DevBuf* const per_set[] = {&b.touch_row, &b.touch_pos, &b.list_in,  &b.list_out, &b.chunks_in,
-                               &b.chunks_out, &b.split_in, &b.split_out, &b.mrows_in, &b.mrows_out,
-                               &b.partials};
+    DevBuf* const sets_bufs[] = {&b.cnt_in, &b.cnt_out, &b.off_in, &b.off_out, &m.meta,
+                                 &b.touch_row, &b.touch_pos, &b.list_in, &b.list_out,
+                                 &b.chunks_in, &b.chunks_out, &b.split_in, &b.split_out,
+                                 &b.mrows_in, &b.mrows_out, &b.partials};
     want = m.few_id_sets ? kIdSets : id_sets_wanted(m, st, want);
     const int have = std::min(m.id_sets, m.id_sets_cap);
     if (!grows && have >= want) return have;
@@ -1185,7 +1215,7 @@ static int ensure_id_buffers(Model& m, int64_t P, int K, int want)
         m.cap_pairs = 0;   // an allocation that fails leaves no stale capacity
         m.cap_K = 0;
         m.id_sets_cap = 0;
-        for (DevBuf* x : per_set) x->release();
+        for (int i = 5; i < 16; ++i) sets_bufs[i]->release();
         for (DevBuf* x : {&m.ent_out, &m.dinp, &m.key_in, &m.partial}) x->release();
     }
     auto alloc_all = [&](int sets) {
@@ -1200,46 +1230,38 @@ static int ensure_id_buffers(Model& m, int64_t P, int K, int want)
             m.cap_pairs = cp;
             m.cap_K = ck;
         }
-        if (m.id_sets_cap >= sets) return;
-        m.id_sets_cap = 0;
-        for (DevBuf* x : per_set) x->release();
-        const int64_t k = sets;
-        b.touch_row.alloc(&c, sizeof(int32_t) * k * st.touches);
-        b.touch_pos.alloc(&c, sizeof(uint32_t) * k * st.touches);
-        b.list_in.alloc(&c, sizeof(int32_t) * k * st.in);
-        b.list_out.alloc(&c, sizeof(int32_t) * k * st.out);
-        b.chunks_in.alloc(&c, sizeof(int4) * k * st.in);
-        b.chunks_out.alloc(&c, sizeof(int4) * k * st.out);
-        b.split_in.alloc(&c, sizeof(int4) * k * st.split_in);
-        b.split_out.alloc(&c, sizeof(int4) * k * st.split_out);
-        b.mrows_in.alloc(&c, sizeof(int4) * k * st.mrows_in);
-        b.mrows_out.alloc(&c, sizeof(int4) * k * st.mrows_out);
-        b.partials.alloc(&c, (sizeof(uint4) + sizeof(unsigned long long)) * k * st.scan_blocks);
-        m.id_sets_cap = sets;
+        if (m.id_sets_cap < sets) alloc_id_sets(m, sets, st);
     };
     int sets = want;
     if (c.budget && sets > kIdSets) {
         // more than fit the budget are not tried
         uint64_t held = 0, need = (id_set_bytes(st) + id_counter_bytes(n)) * (uint64_t)sets;
-        for (DevBuf* x : per_set) held += x->bytes;
-        for (DevBuf* x : {&b.cnt_in, &b.cnt_out, &b.off_in, &b.off_out, &m.meta}) held += x->bytes;
+        for (DevBuf* x : sets_bufs) held += x->bytes;
         if (grows)
             need += 16 * (uint64_t)cp * (ck + 1) + 4 * (uint64_t)cp * (m.dim + 1) +
                     8 * (uint64_t)(st.split_in + st.split_out) * m.dim;
         const uint64_t room = c.budget + held - std::min(c.budget + held, c.in_use);
         if (need > room) sets = std::max(kIdSets, m.id_sets_cap);
     }
-    try {
-        alloc_all(sets);
-    } catch (const Error& e) {
-        // once more with kIdSets, after giving back what is more than those;
-        // the model does not try again
-        const bool more = give_back_id_sets(m) || sets > kIdSets;
-        if (e.code != FELOG_ENOMEM || !more) throw;
-        (void)hipGetLastError();
-        clear_error();
-        m.few_id_sets = true;
-        alloc_all(kIdSets);
+    // where memory is short: with kIdSets, then without the plans of smaller
+    // minibatches too
+    for (int attempt = 0;; ++attempt) {
+        try {
+            alloc_all(sets);
+            break;
+        } catch (const Error& e) {
+            if (e.code != FELOG_ENOMEM || attempt == 2) throw;
+            (void)hipGetLastError();
+            clear_error();
+            if (attempt == 0) {
+                if (std::max(sets, m.id_sets) > kIdSets) m.few_id_sets = true;   // not tried again
+                for (DevBuf* x : sets_bufs) x->release();
+                m.id_sets = m.id_sets_cap = 0;
+                sets = kIdSets;
+            } else {
+                drop_plans(m);
+            }
+        }
     }
     return std::min(m.id_sets, m.id_sets_cap);
 }
@@ -1356,6 +1378,7 @@ void train_minibatches(Model& m, const Walks& wc, const felog_train_params& p, i
         vin.alloc(&c, sizeof(float) * (size_t)P * m.dim);
         vout.alloc(&c, sizeof(float) * (size_t)P * (K + 1) * m.dim);
     }
+    const HoldScratch hold(m);
     const int id_sets = ensure_id_buffers(m, P, K, G > 1 ? 2 * G : kIdSets);
     if (G > 1 && id_sets < 2 * G) G = std::max(1, id_sets / 2);
     const int rings = G > 1 ? 2 : kIdSets;

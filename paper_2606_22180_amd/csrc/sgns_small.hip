@@ -967,7 +967,7 @@ static void launch_plan(int K, int nblocks, const PlanBatch& pb, hipStream_t s)
 // minibatches (two sets of a launch group: the plans of group i + 1 are
 // written while the update of group i reads set i mod 2), the out-touch
 // coefficients, and each pair's in-row delta and context copy.
-static void small_buffers(Model& m, int64_t P, int32_t tmax, int64_t plans)
+static void take_small_buffers(Model& m, int64_t P, int32_t tmax, int64_t plans)
 {
     Ctx& c = *m.ctx;
     const int D = m.dim;
@@ -992,12 +992,45 @@ static void small_buffers(Model& m, int64_t P, int32_t tmax, int64_t plans)
     }
 }
 
-static void release_small_buffers(Model& m)
+void drop_plans(Model& m)
 {
     for (DevBuf* b : {&m.sm_tinfo, &m.sm_segs, &m.sm_meta, &m.sm_spair, &m.sm_gpos, &m.sm_dinp,
                       &m.sm_ctxc})
         b->release();
     m.sm_tmax = m.sm_G = m.sm_pairs = 0;
+}
+
+// Leaves the plans that the persistent update needs, or one for each of a
+// planned launch's two sets.
+void shrink_plans(Model& m)
+{
+    const int64_t t = m.sm_keep_tmax, g = m.sm_keep_G;
+    if (m.sm_tmax * m.sm_G <= t * g) return;
+    m.sm_tmax = m.sm_G = 0;
+    for (DevBuf* b : {&m.sm_tinfo, &m.sm_segs, &m.sm_meta, &m.sm_spair, &m.sm_gpos}) b->release();
+    try {
+        take_small_buffers(m, m.sm_pairs, (int32_t)t, g);
+    } catch (const Error& e) {
+        if (e.code != FELOG_ENOMEM) throw;   // (they are taken on the next use)
+        (void)hipGetLastError();
+        clear_error();
+    }
+}
+
+static void small_buffers(Model& m, int64_t P, int32_t tmax, int64_t plans)
+{
+    try {
+        take_small_buffers(m, P, tmax, plans);
+    } catch (const Error& e) {
+        if (e.code != FELOG_ENOMEM) throw;
+        // once more, for this call's sizes only and with the id sets of larger
+        // minibatches given back
+        (void)hipGetLastError();
+        clear_error();
+        shrink_id_sets(m);
+        drop_plans(m);
+        take_small_buffers(m, P, tmax, plans);
+    }
 }
 
 // Bytes of one minibatch's plan, and of what a call holds beside its plans.
@@ -1302,7 +1335,6 @@ void train_minibatches_small(Model& m, Walks& w, const felog_train_params& p,
     const int nblocks = small_update_blocks(c, D, K);
     const int nwaves = nblocks * (kUpdThreads / 64);
 
-    small_buffers(m, P, tmax, 2 * G);
     // control words: barrier flags (an unused line, then one per workgroup,
     // each on its own 128-byte line), the abort flag on the next line, then
     // the loss partials, one per wave, and the four phase-clock sums
@@ -1318,8 +1350,6 @@ void train_minibatches_small(Model& m, Walks& w, const felog_train_params& p,
                        (int32_t)(ctl.bytes / sizeof(uint32_t)));
     FELOG_HIP(hipMemsetAsync(m.row_totals.ptr, 0, sizeof(uint64_t) * 3, c.stream));
 
-    const PlanArgs pa = plan_args(m, w, p, d_slices, tmax);
-
     // every minibatch's descriptor, uploaded once for the call
     std::vector<size_t> last_chunk;   // chunk of the last minibatch of each launch
     int64_t pairs = 0;
@@ -1329,6 +1359,11 @@ void train_minibatches_small(Model& m, Walks& w, const felog_train_params& p,
     FELOG_HIP(hipMemcpyAsync(ddesc.ptr, desc.data(), sizeof(MbDesc) * desc.size(),
                              hipMemcpyHostToDevice, c.stream));
 
+    const HoldScratch hold(m);
+    small_buffers(m, P, tmax, 2 * G);
+    m.sm_keep_tmax = m.sm_keep_G == 2 * G ? std::max<int64_t>(m.sm_keep_tmax, tmax) : tmax;
+    m.sm_keep_G = 2 * G;
+    const PlanArgs pa = plan_args(m, w, p, d_slices, tmax);
     UpdJob uj{};
     uj.tin = m.tin.as<float>();
     uj.tout = m.tout.as<float>();
@@ -1512,19 +1547,24 @@ bool train_minibatches_planned(Model& m, Walks& w, const felog_train_params& p,
         const uint64_t fixed = planned_fixed_bytes(P, K, D) + 4096;
         if (room < fixed + sets * plan_bytes(tmax)) return false;
         G = std::min<int64_t>(G, (int64_t)((room - fixed) / (sets * plan_bytes(tmax))));
-        if (m.sm_tmax < tmax || m.sm_G < sets * G || m.sm_pairs < P) release_small_buffers(m);
+        if (m.sm_tmax < tmax || m.sm_G < sets * G || m.sm_pairs < P) drop_plans(m);
     }
     const int64_t side = D == 64 ? 2 : 1;
     const int64_t nwaves = (P + side - 1) / side;
     DevBuf loss_part;
+    const HoldScratch hold(m);
     try {
-        small_buffers(m, P, tmax, sets * G);
         loss_part.alloc(&c, sizeof(double) * nwaves);
+        small_buffers(m, P, tmax, sets * G);
+        if (m.sm_keep_G <= 2) {
+            m.sm_keep_tmax = std::max<int64_t>(m.sm_keep_tmax, tmax);
+            m.sm_keep_G = 2;
+        }
     } catch (const Error& e) {
         if (e.code != FELOG_ENOMEM) throw;
         (void)hipGetLastError();
         clear_error();
-        release_small_buffers(m);
+        drop_plans(m);
         return false;
     }
     int64_t pairs = 0;

@@ -75,3 +75,56 @@ def test_larger_minibatches_after_groups(fl):
     print("[gpu] needed", need, flush=True)
     steps(need + (2 << 20), False)
     steps(need + (2 << 20), True)
+
+
+# what comes after the groups: a second corpus, or a minibatch's captured deltas
+@pytest.mark.parametrize("then", ["corpus", "deltas"])
+def test_id_sets_make_room(fl, then):
+    """Groups of minibatches take id sets from a budget; an allocation that
+    fits beside three sets gets their memory, and training goes on."""
+    n, prm = 1 << 18, _prm(fl, 2500, K=20)
+
+    def steps(budget, spare):
+        c = fl.Context(0, hbm_budget=budget)
+        objs = _model(fl, c, n)
+        held = c.bytes_in_use()
+        objs[3].train_steps(objs[2], prm, 0, 20)
+        used = c.bytes_in_use()
+        if spare and then == "corpus":
+            W = fl.Walks.generate(objs[0], r=1, L=spare // (4 * n), seed=4)
+            assert np.array_equal(W.read_range(0, 5)[:, 0], np.arange(5))
+            W.close()
+        elif spare:
+            objs[3].train_delta(objs[2], prm, 3)
+        objs[3].train_steps(objs[2], prm, 20, 20)
+        return held, used, [objs[3].read(t) for t in (0, 1)]
+
+    held, many, rows = steps(0, 0)
+    _, few, rows3 = steps(held + (40 << 20), 0)
+    print("[gpu] %d bytes held with many id sets, %d with three" % (many, few), flush=True)
+    assert many - few > 60 << 20 and all(np.array_equal(a, b) for a, b in zip(rows, rows3))
+    # room for the many sets, but not for them and what follows
+    budget = many + (5 << 20)
+    _, used, got = steps(budget, budget - few - (4 << 20))
+    assert used == many and all(np.array_equal(a, b) for a, b in zip(rows, got))
+
+
+def test_plans_make_room(fl):
+    """The same of the plans of a group of minibatches (update path 1)."""
+    n, prm = 1 << 12, _prm(fl, 1024)
+
+    def steps(budget, spare):
+        c = fl.Context(0, hbm_budget=budget)
+        c.set_sgns_path(1)
+        objs = _model(fl, c, n)
+        objs[3].train_steps(objs[2], prm, 0, 130)
+        used = c.bytes_in_use()
+        if spare:
+            fl.Walks.generate(objs[0], r=1, L=spare // (4 * n), seed=4).close()
+        objs[3].train_steps(objs[2], prm, 130, 130)
+        return used, [objs[3].read(t) for t in (0, 1)]
+
+    used, rows = steps(0, 0)
+    for extra in (1 << 16, 1 << 20):
+        got = steps(used + extra, extra + (8 << 20))
+        assert got[0] == used and all(np.array_equal(a, b) for a, b in zip(rows, got[1]))
