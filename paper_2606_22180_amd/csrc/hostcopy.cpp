@@ -151,6 +151,7 @@ void host_copies_detach()
 
 void copy_to_host(const Ctx& c, void* dst, const void* src, size_t bytes)
 {
+    c.make_current();   // a ring's events are of the device that is current when it is made
     std::unique_ptr<Ring> ring;
     if (bytes >= kStagedMin && !pinned(dst)) ring = take_ring(c.device);
     if (!ring) {
