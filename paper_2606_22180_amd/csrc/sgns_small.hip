@@ -901,13 +901,21 @@ bool small_path_applies(const Model& m, const felog_train_params& p)
 // over 64 minibatches are under 1% of their time, and the plans stay small.
 int64_t small_minibatches_per_launch() { return 64; }
 
+// Bytes of one minibatch's plan (take_small_buffers), and of the buffers beside
+// the plans.
+static uint64_t plan_bytes(int64_t T) { return (uint64_t)(8 + 4 + 2) * T + 16; }
+static uint64_t pair_buffer_bytes(int64_t P, int K, int d)
+{
+    return 8 * (uint64_t)(P * (K + 2)) + 2 * 4 * (uint64_t)P * d;
+}
+
 // Device bytes the small-minibatch update holds for minibatches of P pairs
 // and K negatives at dimension d, over a call of B minibatches.
 uint64_t small_path_bytes(int64_t P, int K, int d, int64_t B, int num_cus)
 {
-    const uint64_t T = (uint64_t)(P * (K + 2)), G = (uint64_t)small_minibatches_per_launch();
+    const uint64_t G = (uint64_t)small_minibatches_per_launch();
     const uint64_t blocks = (uint64_t)std::max(kDefaultUpdBlocks, num_cus);
-    return 2 * (8 * T * G + 16 * T * G + 4 * T * G + 16 * G) + 8 * T + 2 * 4 * (uint64_t)P * d +
+    return 2 * G * plan_bytes(P * (K + 2)) + pair_buffer_bytes(P, K, d) +
            32 * (uint64_t)std::max<int64_t>(B, 1) + 4 * kFlagStride * (blocks + 2) +
            8 * blocks * (kUpdThreads / 64) + 64;
 }
@@ -1031,13 +1039,6 @@ static void small_buffers(Model& m, int64_t P, int32_t tmax, int64_t plans)
         drop_plans(m);
         take_small_buffers(m, P, tmax, plans);
     }
-}
-
-// Bytes of one minibatch's plan, and of what a call holds beside its plans.
-static uint64_t plan_bytes(int64_t T) { return (uint64_t)(8 + 4 + 2) * T + 16; }
-static uint64_t planned_fixed_bytes(int64_t P, int K, int d)
-{
-    return 8 * (uint64_t)(P * (K + 2)) + 2 * 4 * (uint64_t)P * d + 8 * ((uint64_t)P + 1);
 }
 
 // Plan arguments of a training call (plan set 0; the caller offsets them).
@@ -1544,7 +1545,7 @@ bool train_minibatches_planned(Model& m, Walks& w, const felog_train_params& p,
                                 &m.sm_dinp, &m.sm_ctxc})
             held += b->bytes;
         const uint64_t room = c.budget + held - std::min(c.budget + held, c.in_use);
-        const uint64_t fixed = planned_fixed_bytes(P, K, D) + 4096;
+        const uint64_t fixed = pair_buffer_bytes(P, K, D) + 8 * ((uint64_t)P + 1) + 4096;
         if (room < fixed + sets * plan_bytes(tmax)) return false;
         G = std::min<int64_t>(G, (int64_t)((room - fixed) / (sets * plan_bytes(tmax))));
         if (m.sm_tmax < tmax || m.sm_G < sets * G || m.sm_pairs < P) drop_plans(m);

@@ -128,3 +128,24 @@ def test_plans_make_room(fl):
     for extra in (1 << 16, 1 << 20):
         got = steps(used + extra, extra + (8 << 20))
         assert got[0] == used and all(np.array_equal(a, b) for a, b in zip(rows, got[1]))
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+def test_serving_estimate_of_plans(fl, mode):
+    """A persistent or shared job reserves its plans (14 bytes per touch of 128
+    minibatches) beside what a job of launches does, and holds no more."""
+    n, P, K, dim = 1500, 1024, 5, 64
+    est, peak = {}, {}
+    for m in (0, mode):
+        S = fl.Server(0, 0, slots=1, minibatch_pairs=P, negatives=K, update_mode=m)
+        jid = S.submit(*_ring(n), dim=dim, r=8, L=20, window=3, seed=2)
+        st = S.wait(jid, 60.0)
+        S.close()
+        assert st.state == fl.JOB_DONE
+        est[m], peak[m] = st.device_bytes, st.peak_bytes
+    print("[gpu] estimates %s, peaks %s" % (est, peak), flush=True)
+    plans = 128 * (14 * P * (K + 2) + 16)
+    pairs = 8 * P * (K + 2) + 8 * P * dim
+    # descriptors, slices, control words and loss slots: below 256 KiB here
+    assert 0 < est[mode] - est[0] <= (plans + pairs + (256 << 10)) * 17 // 16
+    assert peak[mode] <= est[mode] and peak[0] <= est[0]
