@@ -198,3 +198,43 @@ def test_bf16_bit_reproducible(fl, ctx, sbm, P, M):
          % (P, M, di, do, l0, l1))
     assert di == 0 and do == 0
     assert l0 == l1
+
+
+@pytest.mark.parametrize("dim,P,M", [(64, 4096, 4096), (128, 4096, 4096), (256, 4096, 4096),
+                                     (64, 2048, 2048), (256, 2048, 2048), (128, 2048, 6144)])
+def test_bf16_step_by_parts(fl, ctx, orc, sbm, dim, P, M):
+    """P + M of 8,192 and more: a panel's output is one block's, with no parts
+    for the apply to add; half of that: two parts (the smaller shapes above have
+    four).  The minibatch's definition in FP64 matrix products, to the same
+    bound; the oracle draws the pairs and negatives."""
+    g, K = sbm.train, 5
+    G, W, Mo, prm = _setup(fl, ctx, g, dim=dim, P=P, M=M, K=K)
+    walks = orc.walks_uniform(g, np.arange(g.n), 10, 40, 11)
+    cdf = orc.neg_cdf(g.degrees().astype(np.uint64))
+    B, _ = orc.count_minibatches(walks, 5, P)
+    rng = np.random.default_rng(dim)
+    tin, tout = (rng.normal(0, 0.2, (g.n, dim)).astype(np.float32) for _ in range(2))
+    Mo.write(fl.TABLE_IN, tin)
+    Mo.write(fl.TABLE_OUT, tout)
+    for b in (20, B - 1):                                   # the last has fewer pairs
+        ri, di, ro, do, _ = Mo.train_delta(W, prm, b)
+        mb = orc.minibatch_pairs(walks, 5, P, b)
+        neg = orc.shared_negatives(b, 0, M, prm.seed, cdf)
+        lr = orc.lr_at(b, B, prm.lr_start, prm.lr_end)
+        C, O, N = (orc.bf16_round(t).astype(np.float64)
+                   for t in (tin[mb.ctx], tout[mb.ctr], tout[neg]))
+        Gm = lr * K / M / (1 + np.exp(-(C @ N.T))) * (neg[None, :] != mb.ctr[:, None])
+        Gr = orc.bf16_round(Gm.astype(np.float32)).astype(np.float64)
+        g0 = (lr / (1 + np.exp((C * O).sum(1))))[:, None]
+        for rows, got, ref, mass in (
+                (ri, di, _agg(g.n, dim, mb.ctx, g0 * O - Gr @ N),
+                 _agg(g.n, dim, mb.ctx, g0 * np.abs(O) + Gm @ np.abs(N))),
+                (ro, do, _agg(g.n, dim, mb.ctr, g0 * C) - _agg(g.n, dim, neg, Gr.T @ C),
+                 _agg(g.n, dim, mb.ctr, g0 * np.abs(C)) + _agg(g.n, dim, neg, Gm.T @ np.abs(C)))):
+            full = np.zeros((g.n, dim))
+            full[rows] = got
+            err = np.linalg.norm(full - ref, axis=1)
+            tol = 2.0 ** -8 * np.linalg.norm(mass, axis=1) + 1e-5 * np.linalg.norm(ref, axis=1)
+            _say("d=%d P=%d M=%d mb %d: max err/tol %.3f" %
+                 (dim, P, M, b, (err / np.maximum(tol, 1e-30)).max()))
+            assert (err <= tol + 1e-30).all()
