@@ -673,22 +673,20 @@ void train_minibatches_bf16(Model& m, Walks& w, const felog_train_params& p,
     FELOG_HIP(hipMemsetAsync(loss_part.ptr, 0, sizeof(double) * nslots, c.stream));
     const HoldScratch hold(m);
     if (m.bf_P < P || m.bf_M < M) {
-        m.bf_P = std::max(m.bf_P, P);
-        m.bf_M = std::max(m.bf_M, M);
-        const size_t cp = m.bf_P, cm = m.bf_M;
+        const uint32_t cp = std::max(m.bf_P, P), cm = std::max(m.bf_M, M);
+        m.bf_P = m.bf_M = 0;   // an allocation that fails leaves no stale capacity
+        for (DevBuf* x : {&m.bf_ids, &m.bf_C, &m.bf_O, &m.bf_N, &m.bf_Ct, &m.bf_Nt, &m.bf_g0,
+                          &m.bf_skey, &m.bf_stouch, &m.bf_kin, &m.bf_vin, &m.bf_sort_tmp})
+            x->release();
         m.bf_ids.alloc(&c, id_bytes(cp, cm));
-        m.bf_C.alloc(&c, sizeof(uint16_t) * cp * d);
-        m.bf_O.alloc(&c, sizeof(uint16_t) * cp * d);
-        m.bf_N.alloc(&c, sizeof(uint16_t) * cm * d);
-        m.bf_Ct.alloc(&c, sizeof(uint16_t) * cp * d);
-        m.bf_Nt.alloc(&c, sizeof(uint16_t) * cm * d);
+        for (DevBuf* x : {&m.bf_C, &m.bf_O, &m.bf_Ct}) x->alloc(&c, sizeof(uint16_t) * cp * d);
+        for (DevBuf* x : {&m.bf_N, &m.bf_Nt}) x->alloc(&c, sizeof(uint16_t) * cm * d);
         m.bf_g0.alloc(&c, sizeof(float) * cp);
         // a launch group's LDS plans or one large minibatch's sorted touches
         m.bf_skey.alloc(&c, sorted_bytes(cp, cm));
         m.bf_stouch.alloc(&c, sorted_bytes(cp, cm));
-        m.bf_kin.release();
-        m.bf_vin.release();
-        m.bf_sort_tmp.release();
+        m.bf_P = cp;
+        m.bf_M = cm;
     }
     if (m.bf_delta.bytes < sizeof(float) * split * (size_t)nt * d)
         m.bf_delta.alloc(&c, sizeof(float) * split * (size_t)nt * d);

@@ -149,3 +149,43 @@ def test_serving_estimate_of_plans(fl, mode):
     # descriptors, slices, control words and loss slots: below 256 KiB here
     assert 0 < est[mode] - est[0] <= (plans + pairs + (256 << 10)) * 17 // 16
     assert peak[mode] <= est[mode] and peak[0] <= est[0]
+
+
+@pytest.mark.parametrize("route,large,small", [("bf16", 512, 64), ("persistent", 1024, 64),
+                                               ("planned", 2048, 64), ("ids", 60000, 2500)])
+def test_after_a_refused_call(fl, route, large, small):
+    """Minibatches that do not fit a budget are refused by every call; smaller
+    ones after them are refused too (buffers of the refused size that did fit are
+    kept) or train as they do alone."""
+    def prm(P):
+        return fl.train_params(window=4, negatives=5, minibatch_pairs=P, seed=9,
+                               shared_negatives=P if route == "bf16" else 0)
+
+    def steps(budget, sizes):
+        c = fl.Context(0, hbm_budget=budget)
+        c.set_sgns_path(int(route == "planned"))
+        objs = _model(fl, c, 4096, precision=fl.PREC_BF16 if route == "bf16" else 0)
+        held, status = c.bytes_in_use(), []
+        for P in sizes:
+            try:
+                objs[3].train_steps(objs[2], prm(P), 0, 3)
+                status.append(0)
+            except fl.FelogError as err:
+                assert err.status == fl.FELOG_ENOMEM
+                status.append(err.status)
+        return held, c.bytes_in_use(), status, [objs[3].read(t) for t in (0, 1)]
+
+    held, _, _, rows = steps(0, [small])
+    _, all_held, _, both = steps(0, [large, large, small])
+    refused = trained = 0
+    for k in range(1, 36):                       # every buffer is the one too many
+        _, _, status, got = steps(held + (all_held - held + (2 << 20)) * k // 35,
+                                  [large, large, small])
+        assert status[0] == status[1] and (status[0] or not status[2])
+        refused += status[0] != 0
+        trained += status[0] != 0 and not status[2]
+        if not status[2]:
+            assert all(np.array_equal(a, b) for a, b in zip(rows if status[0] else both, got))
+    print("[gpu] %s: %d of 35 budgets refused, %d of them trained the smaller" %
+          (route, refused, trained), flush=True)
+    assert 0 < trained <= refused < 35
