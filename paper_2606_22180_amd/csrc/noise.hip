@@ -314,6 +314,13 @@ __global__ void guide_kernel(const uint64_t* cdf, int32_t n, int32_t bits, uint6
     guide[b] = lo;
 }
 
+// Room for a new table; training is refused until build_guide has ended.
+static void alloc_cdf(Model& m)
+{
+    m.have_noise = false;
+    m.cdf.alloc(m.ctx, sizeof(uint64_t) * ((size_t)m.g->n + 1));
+}
+
 // guide table of m.cdf (n + 1 entries, total > 0)
 static void build_guide(Model& m, uint64_t total)
 {
@@ -339,7 +346,7 @@ void set_noise_cdf(Model& m, const uint64_t* host_cdf)
     for (int32_t i = 0; i < n; ++i)
         FELOG_REQUIRE(host_cdf[i + 1] >= host_cdf[i], "the noise table decreases at node %d", i);
     FELOG_REQUIRE(host_cdf[n] > 0, "the noise distribution is empty (every weight is zero)");
-    m.cdf.alloc(&c, sizeof(uint64_t) * (n + 1));
+    alloc_cdf(m);
     FELOG_HIP(hipMemcpyAsync(m.cdf.ptr, host_cdf, sizeof(uint64_t) * (n + 1),
                              hipMemcpyHostToDevice, c.stream));
     build_guide(m, host_cdf[n]);
@@ -357,18 +364,20 @@ void build_noise_from_counts(Model& m, const uint32_t* d_counts)
     int64_t nb = (n + 2047) / 2048;
     DevBuf sums;
     sums.alloc(&c, sizeof(uint64_t) * (nb + 1));
-    m.cdf.alloc(&c, sizeof(uint64_t) * (n + 1));
     hipLaunchKernelGGL(block_sums_u64, dim3(nb), dim3(256), 0, c.stream, w.as<uint64_t>(), n,
                        sums.as<uint64_t>());
     hipLaunchKernelGGL(scan_sums_u64, dim3(1), dim3(256), 0, c.stream, sums.as<uint64_t>(), nb);
+    FELOG_HIP(hipGetLastError());
+    uint64_t total = 0;
+    FELOG_HIP(hipMemcpyAsync(&total, sums.as<uint64_t>() + nb, sizeof total,
+                             hipMemcpyDeviceToHost, c.stream));
+    c.sync();
+    // (the model keeps the table that it has)
+    FELOG_REQUIRE(total > 0, "the noise distribution is empty (every count is zero)");
+    alloc_cdf(m);
     hipLaunchKernelGGL(finish_cdf_u64, dim3(nb), dim3(256), 0, c.stream, w.as<uint64_t>(), n,
                        sums.as<uint64_t>(), m.cdf.as<uint64_t>());
     FELOG_HIP(hipGetLastError());
-    uint64_t total = 0;
-    FELOG_HIP(hipMemcpyAsync(&total, m.cdf.as<uint64_t>() + n, sizeof total,
-                             hipMemcpyDeviceToHost, c.stream));
-    c.sync();
-    FELOG_REQUIRE(total > 0, "the noise distribution is empty (every count is zero)");
     build_guide(m, total);
 }
 

@@ -330,3 +330,25 @@ def test_bf16_id_batches(fl, n_mb, chunk):
     wide, narrow = train(0), train(1 << 30)
     assert np.array_equal(wide[0], narrow[0]) and np.array_equal(wide[1], narrow[1])
     assert wide[2] == narrow[2]
+
+
+def test_empty_noise_table_is_refused(fl, ctx):
+    """Counts of a corpus without walks are refused, and the model goes on with
+    the table that it has."""
+    n = 200
+    rng = np.random.default_rng(5)
+    e = np.sort(rng.integers(0, n, (900, 2)), 1)
+    g = synth.csr_from_edges(n, np.unique(e[e[:, 0] != e[:, 1]], axis=0))
+    G = fl.Graph.from_csr(ctx, g.indptr, g.indices)
+    W = fl.Walks.generate(G, r=4, L=12, seed=4)
+    none = fl.Walks.generate(G, r=1, L=12, seed=4, starts=fl.Active.from_host(G, np.zeros(0, np.int32)))
+    M, R = (fl.Model.create(G, dim=64, seed=6) for _ in range(2))
+    with pytest.raises(fl.FelogError) as err:
+        M.set_unigram(none)
+    assert err.value.status == fl.FELOG_EINVAL
+    assert np.array_equal(M.read_cdf(), R.read_cdf())
+    prm = fl.train_params(window=3, negatives=5, minibatch_pairs=256, seed=9)
+    for m in (M, R):
+        m.train_steps(W, prm, 0, 4)
+    for which in (0, 1):
+        assert np.array_equal(M.read(which), R.read(which))
