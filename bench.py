@@ -548,7 +548,7 @@ def sgns_roofline(sts, d: int, K: int, pairs: int):
         per_mb_plan = (pairs * (8 + 8 * K) + touches * 8) / mbs
         for name, per, ms in (("sgns_small_update_kernel<%d, %d>" % (d, K), per_mb_update,
                                sum(s.ms_update for s in sts)),
-                              ("sgns_plan_kernel<%d>" % K, per_mb_plan,
+                              ("sgns_plan_kernel<%d, 8192>" % K, per_mb_plan,
                                sum(s.ms_prep for s in sts))):
             avg = ms / 1e3 / max(1, timed)
             byt = per * per_launch_mb
@@ -566,12 +566,12 @@ def sgns_roofline(sts, d: int, K: int, pairs: int):
     else:
         multi_out = rows_out - single
         out_touches = pairs * (K + 1)
-        per = {"sgns_forward_kernel<%d, %d>" % (d, K):
+        per = {"sgns_forward_kernel<%d, %d, false>" % (d, K):
                    (row_bytes + single * d * 4 + pairs * (8 + 8 * K)) / mbs,
                "sgns_apply_kernel<%d, 0>" % d:
                    (multi_out * d * 8 + rows_in * d * 4 + (out_touches - single) * 16) / mbs,
                "sgns_apply_kernel<%d, 1>" % d: (rows_in * d * 8 + pairs * d * 4) / mbs}
-        ms = {"sgns_forward_kernel<%d, %d>" % (d, K): sum(s.ms_forward for s in sts),
+        ms = {"sgns_forward_kernel<%d, %d, false>" % (d, K): sum(s.ms_forward for s in sts),
               "sgns_apply_kernel<%d, 0>" % d: sum(s.ms_apply_first for s in sts),
               "sgns_apply_kernel<%d, 1>" % d: sum(s.ms_apply - s.ms_apply_first for s in sts)}
         for name in per:

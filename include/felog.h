@@ -80,13 +80,15 @@ felog_status felog_ctx_bytes_in_use(const felog_ctx* ctx, uint64_t* bytes);
 felog_status felog_ctx_set_timing(felog_ctx* ctx, int32_t every);
 
 /* SGNS update path of the FP32 form.  path 0 (the default): minibatches of
- * P (K + 2) <= 8192 touches (and K <= 14 at d = 64) run as plan launches (ids and a sort of each
+ * P (K + 2) <= 8192 touches (at d = 64 with K <= 14, beyond which the launches
+ * of path 1 are faster) run as plan launches (ids and a sort of each
  * minibatch's touches by row, many minibatches per launch) and one persistent
  * cooperative update launch per group of minibatches; larger ones run
  * per-minibatch launches.  path 1: per-minibatch launches always (with plans
  * up to 16384 touches where they fit, else with the ids of a group of
- * minibatches in launches of their own).  All give bit-identical tables.  blocks: workgroups of the persistent launch (0 = the
- * default, 64; capped at what can be resident at once).  With timing on
+ * minibatches in launches of their own).  All give bit-identical tables.
+ * blocks: workgroups of the persistent launch (0 = the default, 64; capped at
+ * what can be resident at once).  With timing on
  * (felog_ctx_set_timing), every plan and update launch of path 0 is timed.
  * Errors: path not 0 or 1, blocks outside [0, 65536]. */
 felog_status felog_ctx_set_sgns_path(felog_ctx* ctx, int32_t path, int32_t blocks);
@@ -352,7 +354,8 @@ typedef struct felog_train_stats {
     double ms_prep;           /* duration of the id / rank / offset or plan launches
                                  of the timed minibatches (their share of a group's) */
     double ms_apply_first;    /* summed duration of the first of the timed apply
-                                 launches (out rows, chunks of split rows)         */
+                                 launches (out rows, chunks of split rows), or of the
+                                 only one, where the ids come from plans            */
     int64_t rows_out_single;  /* of rows_out, the rows touched once in their
                                  minibatch (updated by the forward launch)          */
     int32_t path;             /* update path the call took: 0 per-minibatch launches,

@@ -83,15 +83,14 @@ struct Ctx {
     int32_t timing_every = 0;             // time every n-th training launch (0 = off)
     std::vector<hipEvent_t> timing_pool;  // kTimingEvents events per timed minibatch
     // second stream for the table-independent part of later minibatches, and
-    // its events: [0] start, [1 + set] ids ready, [1 + kIdSets + set] buffers
-    // free, [1 + 2 kIdSets] forward done
+    // its events: [0] start, [1 + ring] ids ready, [1 + kIdSets + ring] buffers free
     hipStream_t aux = nullptr;
-    hipEvent_t pipe_ev[2 + 2 * kIdSets] = {};
+    hipEvent_t pipe_ev[1 + 2 * kIdSets] = {};
     // third stream: walk chunks of a round beside the training of earlier ones
     hipStream_t walk_stream = nullptr;
     // SGNS update path: 0 = the persistent small-minibatch update where it
     // applies, 1 = per-minibatch launches always; workgroups of the persistent
-    // launch (0 = one per compute unit)
+    // launch (0 = the default, 64)
     int32_t sgns_path = 0;
     int32_t sgns_blocks = 0;
     // every launch on `stream`: the second and third streams are `stream` itself

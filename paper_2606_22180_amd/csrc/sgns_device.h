@@ -12,14 +12,9 @@ namespace felog {
 // per minibatch.  (On the split rows' partial sums, which the next launch
 // reads, the hint made the minibatch slower.)
 typedef float nt_f4 __attribute__((ext_vector_type(4)));
-typedef int nt_i2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void store_nt(float4* p, const float4& v)
 {
     __builtin_nontemporal_store(nt_f4{v.x, v.y, v.z, v.w}, reinterpret_cast<nt_f4*>(p));
-}
-__device__ __forceinline__ void store_nt(int2* p, const int2& v)
-{
-    __builtin_nontemporal_store(nt_i2{v.x, v.y}, reinterpret_cast<nt_i2*>(p));
 }
 __device__ __forceinline__ void store_nt(uint32_t* p, uint32_t v) { __builtin_nontemporal_store(v, p); }
 __device__ __forceinline__ void store_nt(int4* p, const int4& v)

@@ -881,20 +881,18 @@ __global__ void zero_words_kernel(uint32_t* p, int32_t n)
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-// The forward of the update kernel holds the touches of a wave's pairs in one
-// lane each: (64 / lanes per pair) pairs of K + 2 touches must fit 64 lanes
-// (K <= 14 at d = 64, where 16 lanes take a pair).
-static bool small_touches_fit_wave(int d, int K)
-{
-    const int pairs_per_wave = d >= 128 ? 2 : 4;
-    return pairs_per_wave * (K + 2) <= 64;
-}
+// At d = 64 the persistent update is taken up to K = 14.  Beyond that planned
+// launches are as fast or faster: us per minibatch of the persistent update and
+// of planned launches, 8,192 touches, 1,000 nodes and R-MAT 2^18: K = 14 11.9 and
+// 12.1, 11.3 and 11.7; K = 15 12.1 and 12.0, 11.6 and 11.5; K = 17 12.5 and 12.2,
+// 12.1 and 11.5; K = 20 13.1 and 12.7, 12.9 and 12.2.
+static bool persistent_pays(int d, int K) { return d > 64 || K <= 14; }
 
 bool small_path_applies(const Model& m, const felog_train_params& p)
 {
     return m.precision == FELOG_PREC_FP32 && m.ctx->sgns_path == 0 &&
            p.minibatch_pairs * (p.negatives + 2) <= kSmallMaxTouches && p.negatives <= 20 &&
-           small_touches_fit_wave(m.dim, p.negatives);
+           persistent_pays(m.dim, p.negatives);
 }
 
 // Minibatches per plan / update launch pair: the launches' fixed costs spread
@@ -1178,7 +1176,7 @@ bool small_job_fits(const Model& m, const felog_train_params& p)
 {
     return m.precision == FELOG_PREC_FP32 && p.negatives <= 20 &&
            p.minibatch_pairs * (p.negatives + 2) <= kSmallMaxTouches &&
-           (m.dim == 64 || m.dim == 128 || m.dim == 256) && small_touches_fit_wave(m.dim, p.negatives);
+           (m.dim == 64 || m.dim == 128 || m.dim == 256) && persistent_pays(m.dim, p.negatives);
 }
 
 SmallJobPtr small_job_begin(Model& m, Walks& w, const felog_train_params& p, int nblocks)
