@@ -172,17 +172,25 @@ __global__ __launch_bounds__(256) void walk_uniform_kernel(
 // Bound by chains of dependent random reads of very different lengths: one to
 // tens of attempts per transition, each with none to 20 rounds of search.  A
 // lane therefore goes its own way through its walk: every pass of the loop
-// gives the searching lanes kN2vRounds rounds and, once kN2vProposers lanes are
+// gives the searching lanes ROUNDS rounds and, once kN2vProposers lanes are
 // between attempts (or none is searching), those their next attempt (a Philox
 // block, most of a pass's instructions).  A wave then takes as many passes as
 // the longest of its 64 walks' sums needs; with all lanes at the same
 // transition, two attempts at a time, it was the sum of the longest, and idle
-// searches read along: 300,007 walks of 80 (deg 29, p = 0.5, q = 2, weighted)
-// 5.5 -> 4.0 ms, now about 300 M random reads at 75 G/s.
+// searches read along.  Against that, 40 steps from every node, ms:
+//   deg 29, weighted, p = 0.5, q = 2: R-MAT 2^18 2.70 -> 1.73, 300,007 nodes of
+//   equal degree 2.46 -> 2.42 (their long stretches of the same length leave
+//   lockstep little to lose); p = 0.25, q = 4: 8.1 -> 4.9 and 6.1 -> 5.5;
+//   R-MAT 2^20, deg 16, unweighted, p = 1, q = 2 4.0 -> 3.6.
+// Rounds: five.  With two the 300,007 nodes took 2.68 ms and, p = 1, q = 2, 2.06
+// (lockstep 1.74, five 1.72).  Two where the L2s hold the entries and p < 1 < q:
+// 30,000 nodes of degree 33, weighted, p = 0.5, q = 2 0.90, five 0.96 and lockstep
+// 1.52; p = 0.25, q = 4 2.10, 2.37 and 3.71.
 // --------------------------------------------------------------------------
-constexpr int kN2vRounds = 2;      // 1 to 4 are within 6 %
-constexpr int kN2vProposers = 16;  // 8 to 48 are within 9 %
+constexpr int64_t kN2vCachedBytes = (int64_t)32 << 20;   // entries that the L2s hold
+constexpr int kN2vProposers = 16;  // 8 to 32 are within 7 %
 
+template <int ROUNDS>
 __global__ __launch_bounds__(256) void walk_node2vec_kernel(
     const int64_t* __restrict__ indptr, const int32_t* __restrict__ indices,
     const int2* __restrict__ edges, const float* __restrict__ wmax,
@@ -279,7 +287,7 @@ __global__ __launch_bounds__(256) void walk_node2vec_kernel(
             }
         }
 #pragma unroll
-        for (int k = 0; k < kN2vRounds; ++k)
+        for (int k = 0; k < ROUNDS; ++k)
             if (mode == kSearch) {
                 const uint32_t mid = l + ((h - l) >> 1);
                 const int32_t val = indices[base + mid];
@@ -293,6 +301,79 @@ __global__ __launch_bounds__(256) void walk_node2vec_kernel(
     if (my_capped) atomicAdd(capped, (unsigned long long)my_capped);
 }
 
+// The same walks where q = 1: alpha is 1/p at the previous node and 1 elsewhere,
+// so no attempt needs a search.  The lanes keep to the same transition, A
+// attempts in flight, and a step's walks are written as one row (lanes at
+// transitions of their own write a line each).  40 steps from every node, ms,
+// with the kernel above and this one: 300,007 nodes of degree 29, weighted,
+// p = 1 0.79 and 0.54, p = 0.25 1.86 and 1.08; R-MAT 2^20, deg 16, p = 0.25 2.81
+// and 2.17.
+template <int A>
+__global__ __launch_bounds__(256) void walk_node2vec_q1_kernel(
+    const int64_t* __restrict__ indptr, const int32_t* __restrict__ indices,
+    const int2* __restrict__ edges, const float* __restrict__ wmax,
+    const int32_t* __restrict__ starts, int64_t n_starts, int64_t W, int64_t col0,
+    int64_t col_end, int32_t L, float inv_p, float amax, uint32_t max_attempts, uint64_t seed,
+    int64_t id_base, int32_t* __restrict__ walks, unsigned long long* __restrict__ capped)
+{
+    const int64_t col = col0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (col >= col_end) return;
+    const int64_t si = col % n_starts;
+    int32_t v = starts ? starts[si] : (int32_t)si;
+    const int64_t wid = id_base + col;
+    walks[col] = v;
+    uint32_t my_capped = 0;
+    int32_t t = 0, prev = -1;
+    for (; t + 1 < L; ++t) {
+        const int64_t lo = indptr[v];
+        const uint32_t deg = (uint32_t)(indptr[v + 1] - lo);
+        if (deg == 0) break;
+        const float bound = t == 0 ? wmax[v] : __fmul_rn(wmax[v], amax);
+        int32_t x = -1;
+        for (uint32_t attempt = 0;; attempt += A) {   // max_attempts is a multiple of A
+            int32_t xs[A];
+            float ws[A], lhs[A];
+#pragma unroll
+            for (int k = 0; k < A; ++k) {
+                const Rand4 r = philox4x32((uint32_t)wid, (uint32_t)(wid >> 32), (uint32_t)t,
+                                           kTagN2V | (attempt + k), seed);
+                const int64_t e = lo + scale32(r.v[0], deg);
+                if (edges) {
+                    const int2 rec = edges[e];
+                    xs[k] = rec.x;
+                    ws[k] = __int_as_float(rec.y);
+                } else {
+                    xs[k] = indices[e];
+                    ws[k] = 1.0f;
+                }
+                lhs[k] = __fmul_rn((float)(r.v[1] >> 8) * (1.0f / 16777216.0f), bound);
+            }
+            bool accept = false;
+#pragma unroll
+            for (int k = 0; k < A; ++k)
+                if (!accept) {
+                    x = xs[k];
+                    accept = lhs[k] < (t > 0 && x == prev ? __fmul_rn(ws[k], inv_p) : ws[k]);
+                }
+            if (accept) break;
+            if (attempt + A >= max_attempts) {
+                ++my_capped;
+                break;
+            }
+        }
+        walks[(int64_t)(t + 1) * W + col] = x;
+        prev = v;
+        v = x;
+    }
+    for (int32_t s = t + 1; s < L; ++s) walks[(int64_t)s * W + col] = -1;
+    if (my_capped) atomicAdd(capped, (unsigned long long)my_capped);
+}
+
+// Attempts in flight.  Where the L2s hold the entries, a wasted read costs little and a round trip is most of the time: four (30,000 nodes of degree
+// 33, weighted, p = 0.25 0.36 ms, two 0.48; p = 1 0.16 and 0.19).  Beyond, the reads
+// count: two, or one where no weight and no 1/p > 1 rejects the most (300,007 nodes,
+// weighted, p = 0.25 1.08 with two and 1.08 with four, R-MAT 2^20 2.17 and 2.63;
+// p = 1 0.54 with one, 0.63 with two).  One where nothing but a return is rejected.
 void launch_walk_columns(Walks& w, const felog_walk_params& p, const Active* starts,
                          int64_t n_starts, int64_t col0, int64_t ncols, hipStream_t s,
                          unsigned long long* d_capped)
@@ -310,11 +391,25 @@ void launch_walk_columns(Walks& w, const felog_walk_params& p, const Active* sta
         FELOG_REQUIRE(d_capped, "node2vec walks need a device counter for capped proposals");
         float inv_p = 1.0f / p.p, inv_q = 1.0f / p.q;
         float amax = fmaxf(1.0f, fmaxf(inv_p, inv_q));
-        hipLaunchKernelGGL(walk_node2vec_kernel, dim3(blocks), dim3(256), 0, s,
-                           g.indptr.as<int64_t>(), g.indices.as<int32_t>(),
-                           g.weighted ? g.edges.as<int2>() : nullptr, g.wmax.as<float>(), st,
-                           n_starts, w.W, col0, col0 + ncols, w.L, inv_p, inv_q, amax, 1u << 16,
-                           p.seed, w.id_base, w.data.as<int32_t>(), d_capped);
+        constexpr uint32_t max_attempts = 1u << 16;
+        const bool cached = g.nnz * (g.weighted ? 8 : 4) <= kN2vCachedBytes;
+        auto launch = [&](auto kernel, auto... alphas) {
+            hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, g.indptr.as<int64_t>(),
+                               g.indices.as<int32_t>(), g.weighted ? g.edges.as<int2>() : nullptr,
+                               g.wmax.as<float>(), st, n_starts, w.W, col0, col0 + ncols, w.L,
+                               alphas..., amax, max_attempts, p.seed, w.id_base,
+                               w.data.as<int32_t>(), d_capped);
+        };
+        if (inv_q != 1.0f) {
+            if (cached && p.p < 1.0f && p.q > 1.0f) launch(walk_node2vec_kernel<2>, inv_p, inv_q);
+            else launch(walk_node2vec_kernel<5>, inv_p, inv_q);
+        } else if (amax == 1.0f && !(cached && g.weighted)) {
+            launch(walk_node2vec_q1_kernel<1>, inv_p);
+        } else if (!cached) {
+            launch(walk_node2vec_q1_kernel<2>, inv_p);
+        } else {
+            launch(walk_node2vec_q1_kernel<4>, inv_p);
+        }
     }
     FELOG_HIP(hipGetLastError());
 }

@@ -352,3 +352,24 @@ def test_empty_noise_table_is_refused(fl, ctx):
         m.train_steps(W, prm, 0, 4)
     for which in (0, 1):
         assert np.array_equal(M.read(which), R.read(which))
+
+
+# q = 1 (no searches): one, two and four attempts in flight, by weights, p and
+# whether the entries pass 32 MB; walks that end at once, leaves whose only
+# neighbour is the previous node, transitions that end at the cap
+@pytest.mark.parametrize("n,m,p,weighted", [
+    (65, 200, 0.25, False), (65, 200, 0.25, True), (500, 3000, 1.0, False),
+    (500, 3000, 2.0, True), (64, 80, 1e6, False), (200000, 4300000, 0.5, False),
+    (200000, 4300000, 1.0, True), (100000, 2200000, 0.25, True)])
+def test_node2vec_without_searches(fl, ctx, orc, n, m, p, weighted):
+    rng = np.random.default_rng(n)
+    e = rng.integers(0, n - n // 8, (m, 2))                  # the last eighth is isolated
+    e = np.unique(np.sort(e[e[:, 0] != e[:, 1]], axis=1), axis=0)
+    g = synth.csr_from_edges(n, e, *([synth.edge_weights(e.shape[0], 3)] if weighted else []))
+    G = fl.Graph.from_csr(ctx, g.indptr, g.indices, *([g.weights] if weighted else []))
+    starts = np.arange(0, n, max(1, n // 700), dtype=np.int32)
+    W = fl.Walks.generate(G, r=3, L=17, seed=11, id_base=5, kind=fl.WALK_NODE2VEC, p=p, q=1.0,
+                          starts=fl.Active.from_host(G, starts))
+    want, capped = orc.walks_node2vec(g, starts, 3, 17, p, 1.0, 11, 5)
+    assert np.array_equal(W.read(), want)
+    assert W.capped() == capped and (capped > 0) == (p == 1e6)
