@@ -85,8 +85,8 @@ felog_status felog_ctx_set_timing(felog_ctx* ctx, int32_t every);
  * minibatch's touches by row, many minibatches per launch) and one persistent
  * cooperative update launch per group of minibatches; larger ones run
  * per-minibatch launches.  path 1: per-minibatch launches always (with plans
- * up to 16384 touches where they fit, else with the ids of a group of
- * minibatches in launches of their own).  All give bit-identical tables.
+ * up to 16384 touches where they fit and the call has three or four minibatches
+ * at least, else with the ids of a group of minibatches in launches of their own).  All give bit-identical tables.
  * blocks: workgroups of the persistent launch (0 = the default, 64; capped at
  * what can be resident at once).  With timing on
  * (felog_ctx_set_timing), every plan and update launch of path 0 is timed.

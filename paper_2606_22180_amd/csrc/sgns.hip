@@ -47,6 +47,7 @@
 // access is a coalesced 256-byte transaction per i.
 #include <algorithm>
 #include <cmath>
+#include <optional>
 
 #include "common.h"
 #include "noise.h"
@@ -1176,6 +1177,19 @@ static void alloc_id_sets(Model& m, int sets, const SetStrides& st)
     m.id_sets_cap = sets;
 }
 
+// Frees the id sets, but for their counters, and the buffers of one minibatch.
+static void drop_id_buffers(Model& m)
+{
+    MinibatchBufs& b = m.mb;
+    m.cap_pairs = 0;
+    m.cap_K = 0;
+    m.id_sets_cap = 0;
+    for (DevBuf* x : {&b.touch_row, &b.touch_pos, &b.list_in, &b.list_out, &b.chunks_in,
+                      &b.chunks_out, &b.split_in, &b.split_out, &b.mrows_in, &b.mrows_out,
+                      &b.partials, &m.ent_out, &m.dinp, &m.key_in, &m.partial})
+        x->release();
+}
+
 // Leaves the model kIdSets id sets if it has more; it takes no more from then on.
 void shrink_id_sets(Model& m)
 {
@@ -1211,13 +1225,7 @@ static int ensure_id_buffers(Model& m, int64_t P, int K, int want)
     want = m.few_id_sets ? kIdSets : id_sets_wanted(m, st, want);
     const int have = std::min(m.id_sets, m.id_sets_cap);
     if (!grows && have >= want) return have;
-    if (grows) {
-        m.cap_pairs = 0;   // an allocation that fails leaves no stale capacity
-        m.cap_K = 0;
-        m.id_sets_cap = 0;
-        for (int i = 5; i < 16; ++i) sets_bufs[i]->release();
-        for (DevBuf* x : {&m.ent_out, &m.dinp, &m.key_in, &m.partial}) x->release();
-    }
+    if (grows) drop_id_buffers(m);   // an allocation that fails leaves no stale capacity
     auto alloc_all = [&](int sets) {
         // (sets of a smaller minibatch beyond those wanted now are given back)
         if (m.id_sets < sets || (grows && m.id_sets > sets)) alloc_id_counters(m, sets);
@@ -1264,6 +1272,18 @@ static int ensure_id_buffers(Model& m, int64_t P, int K, int want)
         }
     }
     return std::min(m.id_sets, m.id_sets_cap);
+}
+
+// Fewest minibatches of a call that planned launches serve.  They start with the
+// plans of the first ones, a workgroup each, which take 30 us and more however
+// few there are; the launches of ids and scans are 28 us per minibatch.  us of
+// a call (ids / planned), 100,000 nodes, d = 128, K = 5: 1,024 pairs 124 / 134 for one
+// minibatch, 152 / 166 two, 178 / 176 three; 2,048 pairs 123 / 170, 157 / 212, 192 /
+// 231, 224 / 240 and 265 / 251 for one to five (on 1,000 nodes 133 / 149, 169 / 171,
+// 203 / 184, 241 / 197); 256 pairs 118 / 118, 144 / 145.
+static int64_t planned_fewest(int64_t touches)
+{
+    return touches <= kSmallMaxTouches / 4 ? 1 : touches <= kSmallMaxTouches ? 3 : 4;
 }
 
 void train_minibatches(Model& m, const Walks& wc, const felog_train_params& p, int64_t first_mb,
@@ -1338,20 +1358,25 @@ void train_minibatches(Model& m, const Walks& wc, const felog_train_params& p, i
         return;
     }
 
-    if (apply && P * (K + 2) <= 2 * kSmallMaxTouches) {
-        std::vector<int32_t> sl = make_slices(w.L, p.window);
-        DevBuf slices;
-        slices.alloc(&c, sizeof(int32_t) * std::max<size_t>(sl.size(), 1));
-        if (!sl.empty())
-            FELOG_HIP(hipMemcpyAsync(slices.ptr, sl.data(), sizeof(int32_t) * sl.size(),
-                                     hipMemcpyHostToDevice, c.stream));
-        if (small_path_applies(m, p)) {
-            train_minibatches_small(m, w, p, sch, slices.as<int32_t>(), first_mb, end, stats);
-            return;
-        }
-        if (train_minibatches_planned(m, w, p, sch, slices.as<int32_t>(), first_mb, end, stats))
-            return;
+    const std::vector<int32_t> sl = make_slices(w.L, p.window);
+    DevBuf slices;
+    slices.alloc(&c, sizeof(int32_t) * std::max<size_t>(sl.size(), 1));
+    if (!sl.empty())
+        FELOG_HIP(hipMemcpyAsync(slices.ptr, sl.data(), sizeof(int32_t) * sl.size(),
+                                 hipMemcpyHostToDevice, c.stream));
+    const int64_t touches = P * (K + 2);
+    if (apply && touches <= kSmallMaxTouches && small_path_applies(m, p)) {
+        train_minibatches_small(m, w, p, sch, slices.as<int32_t>(), first_mb, end, stats);
+        return;
     }
+    // planned launches where they apply, for calls of a few minibatches only
+    // where the ids' buffers find no room
+    const bool few = end - first_mb < planned_fewest(touches);
+    auto planned = [&] {
+        return apply && touches <= 2 * kSmallMaxTouches &&
+               train_minibatches_planned(m, w, p, sch, slices.as<int32_t>(), first_mb, end, stats);
+    };
+    if (!few && planned()) return;
 
     // Launch groups: the ids of up to eight minibatches together, about 2^21
     // touches, in two rings of id sets; without the memory for them (or for a
@@ -1370,24 +1395,31 @@ void train_minibatches(Model& m, const Walks& wc, const felog_train_params& p, i
     const int64_t waves = (P + ppw - 1) / ppw;
     const int64_t blocks = (waves + 3) / 4;
     // the call's own buffers come before the id sets, which take what is left
-    DevBuf loss_part, slices, vin, vout;
-    loss_part.alloc(&c, sizeof(double) * blocks * 4);
-    std::vector<int32_t> sl = make_slices(w.L, p.window);
-    slices.alloc(&c, sizeof(int32_t) * std::max<size_t>(sl.size(), 1));
-    if (!apply) {
-        vin.alloc(&c, sizeof(float) * (size_t)P * m.dim);
-        vout.alloc(&c, sizeof(float) * (size_t)P * (K + 1) * m.dim);
+    DevBuf loss_part, vin, vout;
+    std::optional<HoldScratch> hold;
+    int id_sets = 0;
+    try {
+        loss_part.alloc(&c, sizeof(double) * blocks * 4);
+        if (!apply) {
+            vin.alloc(&c, sizeof(float) * (size_t)P * m.dim);
+            vout.alloc(&c, sizeof(float) * (size_t)P * (K + 1) * m.dim);
+        }
+        hold.emplace(m);
+        id_sets = ensure_id_buffers(m, P, K, G > 1 ? 2 * G : kIdSets);
+    } catch (const Error& e) {
+        if (e.code != FELOG_ENOMEM || !few) throw;
+        const std::string what = felog_last_error();
+        loss_part.release();
+        if (apply) drop_id_buffers(m);
+        if (planned()) return;
+        set_error("%s", what.c_str());
+        throw;
     }
-    const HoldScratch hold(m);
-    const int id_sets = ensure_id_buffers(m, P, K, G > 1 ? 2 * G : kIdSets);
     if (G > 1 && id_sets < 2 * G) G = std::max(1, id_sets / 2);
     const int rings = G > 1 ? 2 : kIdSets;
     const SetStrides st = set_strides(m.g->n, m.cap_pairs, m.cap_K);
     FELOG_HIP(hipMemsetAsync(loss_part.ptr, 0, sizeof(double) * blocks * 4, c.stream));
     FELOG_HIP(hipMemsetAsync(m.row_totals.ptr, 0, sizeof(uint64_t) * 3, c.stream));
-    if (!sl.empty())
-        FELOG_HIP(hipMemcpyAsync(slices.ptr, sl.data(), sizeof(int32_t) * sl.size(),
-                                 hipMemcpyHostToDevice, c.stream));
 
     PrepArgs pa{};
     pa.walks = w.data.as<int32_t>();

@@ -168,7 +168,7 @@ def test_after_a_refused_call(fl, route, large, small):
         held, status = c.bytes_in_use(), []
         for P in sizes:
             try:
-                objs[3].train_steps(objs[2], prm(P), 0, 3)
+                objs[3].train_steps(objs[2], prm(P), 0, 6)
                 status.append(0)
             except fl.FelogError as err:
                 assert err.status == fl.FELOG_ENOMEM

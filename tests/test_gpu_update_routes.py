@@ -114,7 +114,7 @@ def test_one_hub(fl, orc, dim):
     n, P, K, r, L = 64, 1024, 5, 20, 12
     g = _star(n)
     prm = fl.train_params(window=3, negatives=K, minibatch_pairs=P, seed=9)
-    res = [_train(fl, g, prm, 0, 2, route=x, dim=dim, r=r) for x in ("ids", "planned", "persistent")]
+    res = [_train(fl, g, prm, 0, 6, route=x, dim=dim, r=r) for x in ("ids", "planned", "persistent")]
     for x in res[1:]:
         assert np.array_equal(x[0], res[0][0]) and np.array_equal(x[1], res[0][1])
         assert x[3] == res[0][3]
@@ -190,3 +190,38 @@ def test_id_groups(fl, orc, n, dim, K, P, chunk, count):
     for got, ref, mv in zip(res[0], tab, moved):
         err = np.abs(got.astype(np.float64) - ref)
         assert (err <= 1e-5 * mv[:, None] + count * np.spacing(np.abs(ref)) + 1e-12).all()
+
+
+# calls below, at and above the fewest minibatches that planned launches serve,
+# by touches; a budget that has room for plans but not for the ids' buffers
+@pytest.mark.parametrize("P,K,counts", [(292, 5, (1, 2)), (293, 5, (1, 2, 3, 4)),
+                                        (1171, 5, (1, 3, 4, 5)), (2340, 5, (1, 3, 4, 5))])
+def test_few_minibatches(fl, P, K, counts):
+    n, dim = 900, 64
+    g = _random_graph(n)
+    prm = fl.train_params(window=3, negatives=K, minibatch_pairs=P, seed=9)
+    fewest = 1 if P * (K + 2) <= 2048 else 3 if P * (K + 2) <= 8192 else 4
+    for count in counts:
+        res = []
+        for budget in (0, 1, 2):
+            if budget == 2:
+                budget = tight
+            c = fl.Context(0, hbm_budget=0 if budget == 1 else budget)
+            c.set_sgns_path(1)
+            c.set_timing(1)
+            G, W, M = _build(fl, c, g, dim=dim, r=6, L=12)
+            held = c.bytes_in_use()
+            if budget == 1:                              # one call per minibatch: the ids
+                for b in range(count):
+                    st = M.train_steps(W, prm, b, 1)
+            else:
+                st = M.train_steps(W, prm, 0, count)
+            res.append((M.read(fl.TABLE_IN), M.read(fl.TABLE_OUT)))
+            if budget == 0:
+                assert (st.ms_apply_first == st.ms_apply) == (count >= fewest)
+                # half of what the ids' buffers of these minibatches take
+                tight = held + (8 + 16 + 20) * P * (K + 2) + 12 * P * dim + 20000
+            elif budget > 1:
+                assert st.ms_apply_first == st.ms_apply  # plans
+        for r in res[1:]:
+            assert np.array_equal(r[0], res[0][0]) and np.array_equal(r[1], res[0][1])
