@@ -218,10 +218,10 @@ static std::unique_ptr<felog_model> new_model(felog_graph* g, const felog_model_
     }
     launch_init_tables(*m, p->seed);
     if (p->neg_dist == FELOG_NEG_DEGREE) {
-        DevBuf counts;
+        DevBuf counts, work;
         counts.alloc(c, sizeof(uint32_t) * g->n);
         launch_degree_counts(*g, counts.as<uint32_t>());
-        build_noise_from_counts(*m, counts.as<uint32_t>());
+        build_noise_from_counts(*m, counts.as<uint32_t>(), work);
         c->sync();
     }
     c->sync();
@@ -893,10 +893,10 @@ felog_status felog_model_set_unigram(felog_model* m, const felog_walks* corpus)
         NEED(corpus);
         FELOG_REQUIRE(corpus->g == m->g, "corpus belongs to another graph");
         Ctx* c = m->ctx;
-        DevBuf counts;
+        DevBuf counts, work;
         counts.alloc(c, sizeof(uint32_t) * m->g->n);
-        launch_corpus_counts(*corpus, counts.as<uint32_t>());
-        build_noise_from_counts(*m, counts.as<uint32_t>());
+        launch_corpus_counts(*corpus, counts.as<uint32_t>(), work);
+        build_noise_from_counts(*m, counts.as<uint32_t>(), work);
         c->sync();
     });
 }
@@ -1249,10 +1249,10 @@ felog_status felog_run(felog_model* m, const felog_run_params* p, felog_run_stat
                 float ms = 0;
                 FELOG_HIP(hipEventElapsedTime(&ms, c->ev0, c->ev1));
                 st.ms_walk[r] = ms;
-                DevBuf counts;
+                DevBuf counts, work;
                 counts.alloc(c, sizeof(uint32_t) * m->g->n);
-                launch_corpus_counts(*w, counts.as<uint32_t>());
-                build_noise_from_counts(*m, counts.as<uint32_t>());
+                launch_corpus_counts(*w, counts.as<uint32_t>(), work);
+                build_noise_from_counts(*m, counts.as<uint32_t>(), work);
                 c->sync();
                 check_train_params(m, w.get(), &p->train);
                 train_minibatches(*m, *w, p->train, 0, -1, true, &ts, nullptr, nullptr, 0,

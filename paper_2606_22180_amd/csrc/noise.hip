@@ -62,11 +62,11 @@ void launch_degree_counts(Graph& g, uint32_t* d_counts)
 // order-free).
 //
 // Device-scope atomics meet beyond the XCDs' L2s and run at 10 to 45 G/s, a
-// fiftieth of the rate at which the corpus can be read.  A workgroup therefore counts one range of nodes over one part of the
-// corpus in LDS: the corpus is read once per range (the ranges of a part are
-// on one XCD and share its L2), and the parts' counts are stored and summed
-// without atomics.  41.9 M positions over 2^17 nodes: 2.36 ms -> 64 us,
-// and 17 us for the sum.
+// fiftieth of the rate at which the corpus can be read.  A workgroup therefore
+// counts one range of nodes over one part of the corpus in LDS: the corpus is
+// read once per range (the ranges of a part are on one XCD and share its L2),
+// and the parts' counts are stored and summed without atomics.  41.9 M positions
+// over 2^17 nodes: 2.36 ms -> 64 us, and 17 us for the sum.
 constexpr int kCountRange = 40960;        // counters of a workgroup: all of a CU's LDS
 constexpr int kCountThreads = 1024;
 constexpr int kCountInFlight = 4;         // 16-byte loads of a thread
@@ -76,6 +76,12 @@ constexpr int kCountInFlight = 4;         // 16-byte loads of a thread
 // take 118 us and the parts 16 plus the allocation of their counts.
 constexpr int kCountRangesMax = 32;
 constexpr int64_t kCountPositionsMin = (int64_t)1 << 20;
+// Fewest parts: with 26 ranges of 2^20 nodes and one part of 4.2 M positions, 26
+// workgroups take 250 us; 32-bit atomics take 50, 160 for twice the positions and
+// 390 for four times, where four parts take 250 (the codec's 64-bit atomics 240,
+// 380 and 650).
+template <class T>
+constexpr int64_t count_parts_min() { return sizeof(T) == 8 ? 2 : 4; }
 
 // Adds a workgroup's paddings: one atomic, for they all meet at one address
 // (4 ns each).  s: a word per wave; below 2^32 paddings in a workgroup.
@@ -164,7 +170,7 @@ __global__ __launch_bounds__(256) void node_count_sum_kernel(const uint32_t* __r
 }
 
 template <class T>
-void launch_node_counts(const Walks& w, T* counts, unsigned long long* pads)
+void launch_node_counts(const Walks& w, T* counts, unsigned long long* pads, DevBuf& buf)
 {
     Ctx& c = *w.g->ctx;
     const int32_t n = w.g->n;
@@ -177,9 +183,8 @@ void launch_node_counts(const Walks& w, T* counts, unsigned long long* pads)
         // one XCD; the parts' counts take at most a quarter of the corpus
         int64_t parts = std::min<int64_t>(c.num_cus / ranges, total / (4 * (int64_t)n));
         parts = parts >= 8 ? parts / 8 * 8 : parts;
-        DevBuf buf;
         // a part's counts fit 32 bits
-        if (parts > 0 && total / parts < ((int64_t)1 << 32) - 4 &&
+        if (parts >= count_parts_min<T>() && total / parts < ((int64_t)1 << 32) - 4 &&
             try_alloc(buf, &c, sizeof(uint32_t) * (size_t)(parts * n))) {
             const int32_t range = (int32_t)((n + ranges - 1) / ranges);
             const int64_t span = ((total + parts - 1) / parts + 3) / 4 * 4;
@@ -189,7 +194,6 @@ void launch_node_counts(const Walks& w, T* counts, unsigned long long* pads)
             hipLaunchKernelGGL(node_count_sum_kernel<T>, dim3((n + 255) / 256), dim3(256), 0,
                                c.stream, buf.as<uint32_t>(), (int32_t)parts, n, counts);
             FELOG_HIP(hipGetLastError());
-            c.sync();   // before buf is given back
             return;
         }
     }
@@ -201,15 +205,17 @@ void launch_node_counts(const Walks& w, T* counts, unsigned long long* pads)
     FELOG_HIP(hipGetLastError());
 }
 
-void launch_corpus_counts(const Walks& w, uint32_t* d_counts)
+void launch_corpus_counts(const Walks& w, uint32_t* d_counts, DevBuf& work)
 {
-    launch_node_counts<uint32_t>(w, d_counts, nullptr);
+    launch_node_counts<uint32_t>(w, d_counts, nullptr, work);
 }
 
 void launch_symbol_counts(const Walks& w, unsigned long long* d_counts,
                           unsigned long long* d_pads)
 {
-    launch_node_counts<unsigned long long>(w, d_counts, d_pads);
+    DevBuf work;
+    launch_node_counts<unsigned long long>(w, d_counts, d_pads, work);
+    if (work.ptr) w.g->ctx->sync();   // before it is given back
 }
 
 // W_u = floor(2^16 * sqrt(c) * sqrt(sqrt(c))).
@@ -318,7 +324,8 @@ __global__ void guide_kernel(const uint64_t* cdf, int32_t n, int32_t bits, uint6
 static void alloc_cdf(Model& m)
 {
     m.have_noise = false;
-    m.cdf.alloc(m.ctx, sizeof(uint64_t) * ((size_t)m.g->n + 1));
+    const size_t bytes = sizeof(uint64_t) * ((size_t)m.g->n + 1);
+    if (m.cdf.bytes != bytes) m.cdf.alloc(m.ctx, bytes);
 }
 
 // guide table of m.cdf (n + 1 entries, total > 0)
@@ -330,7 +337,8 @@ static void build_guide(Model& m, uint64_t total)
     while (bits < 31 && ((int64_t)1 << bits) < n) ++bits;
     m.guide_bits = bits;
     m.total_weight = total;
-    m.guide.alloc(&c, sizeof(int32_t) * ((size_t)1 << bits));
+    const size_t bytes = sizeof(int32_t) * ((size_t)1 << bits);
+    if (m.guide.bytes != bytes) m.guide.alloc(&c, bytes);
     hipLaunchKernelGGL(guide_kernel, dim3((((int64_t)1 << bits) + 255) / 256), dim3(256), 0,
                        c.stream, m.cdf.as<uint64_t>(), n, bits, total, m.guide.as<int32_t>());
     FELOG_HIP(hipGetLastError());
@@ -352,12 +360,16 @@ void set_noise_cdf(Model& m, const uint64_t* host_cdf)
     build_guide(m, host_cdf[n]);
 }
 
-void build_noise_from_counts(Model& m, const uint32_t* d_counts)
+void build_noise_from_counts(Model& m, const uint32_t* d_counts, DevBuf& w)
 {
     Ctx& c = *m.ctx;
     int32_t n = m.g->n;
-    DevBuf w;
-    w.alloc(&c, sizeof(uint64_t) * n);
+    // the weights go where the counts of parts were (a large block given back and
+    // another taken can cost 300 us), but no budget pays for more than they need
+    if (w.bytes < sizeof(uint64_t) * n || c.budget) {
+        if (w.ptr) c.sync();
+        w.alloc(&c, sizeof(uint64_t) * n);
+    }
     hipLaunchKernelGGL(noise_weights_kernel, dim3((n + 255) / 256), dim3(256), 0, c.stream,
                        d_counts, n, w.as<uint64_t>());
     FELOG_HIP(hipGetLastError());

@@ -201,10 +201,10 @@ static void run_job(Server& s, Job& job)
         model_alloc_update_state(m);
         launch_init_tables(m, d.seed);
         {
-            DevBuf counts;
+            DevBuf counts, work;
             counts.alloc(&ctx, sizeof(uint32_t) * g.n);
             launch_degree_counts(g, counts.as<uint32_t>());
-            build_noise_from_counts(m, counts.as<uint32_t>());
+            build_noise_from_counts(m, counts.as<uint32_t>(), work);
         }
         Walks w;
         w.g = &g;

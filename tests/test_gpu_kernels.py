@@ -373,3 +373,11 @@ def test_node2vec_without_searches(fl, ctx, orc, n, m, p, weighted):
     want, capped = orc.walks_node2vec(g, starts, 3, 17, p, 1.0, 11, 5)
     assert np.array_equal(W.read(), want)
     assert W.capped() == capped and (capped > 0) == (p == 1e6)
+
+
+# the fewest parts that counts are split over: four for the noise table, two for
+# the codec's profile, and one less of each
+@pytest.mark.parametrize("n,r,L", [(70000, 1, 17), (70000, 1, 15), (140000, 1, 9), (140000, 1, 7),
+                                   (262144, 1, 7)])
+def test_corpus_counts_of_few_parts(fl, orc, n, r, L):
+    test_corpus_counts(fl, orc, n, r, L, None)
