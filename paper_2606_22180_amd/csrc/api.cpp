@@ -524,13 +524,15 @@ felog_status felog_walks_info(const felog_walks* w, int64_t* n_walks, int32_t* l
     });
 }
 
-// Device block a corpus is turned through when read, and the smallest read
-// (ints) and block (walks) for which that is used: below 16 KB the block's
-// allocation costs more than turning on the host, and blocks of few walks
-// would make many small copies.
+// Device block a corpus is turned through when read, and its fewest walks
+// (blocks of few would make many small copies).
 constexpr int64_t kTurnBytes = (int64_t)256 << 20;
-constexpr int64_t kTurnMinInts = 4096;
 constexpr int64_t kTurnMinWalks = 1024;
+// Turning on the device costs 28 us (allocation, launch, one copy) and 0.24 ns per
+// int; turning on the host a copy of 7 us per step, 6 us and 0.46 ns per int.  us
+// on the host and on the device: 10,000 walks of 1 18 and 29, 100,000 59 and 51;
+// 3,000 of 2 22 and 28, 30,000 48 and 39; 1,000 of 8 65 and 28; 1 of 80 540 and 28.
+static bool turn_on_device(int64_t L, int64_t total) { return 7 * L + total / 4096 > 22; }
 
 felog_status felog_walks_read_range(const felog_walks* w, int64_t first, int64_t count,
                                     int32_t* walks, int64_t cap)
@@ -555,7 +557,7 @@ felog_status felog_walks_read_range(const felog_walks* w, int64_t first, int64_t
         if (c->budget) room = std::min<int64_t>(room, (int64_t)(c->budget - std::min(c->budget, c->in_use)));
         const int64_t block = std::min<int64_t>(count, room / row_bytes);
         DevBuf rows;
-        if (total > kTurnMinInts && block >= std::min<int64_t>(count, kTurnMinWalks) &&
+        if (turn_on_device(w->L, total) && block >= std::min<int64_t>(count, kTurnMinWalks) &&
             try_alloc(rows, c, (size_t)(block * row_bytes))) {
             for (int64_t c0 = 0; c0 < count; c0 += block) {
                 const int64_t nc = std::min(block, count - c0);

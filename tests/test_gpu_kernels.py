@@ -381,3 +381,11 @@ def test_node2vec_without_searches(fl, ctx, orc, n, m, p, weighted):
                                    (262144, 1, 7)])
 def test_corpus_counts_of_few_parts(fl, orc, n, r, L):
     test_corpus_counts(fl, orc, n, r, L, None)
+
+
+# around the sizes above which walks of one, two and three steps are turned on
+# the device (62k, 34k and 5k ints), and a single walk of four
+@pytest.mark.parametrize("n,L", [(61439, 1), (65536, 1), (16383, 2), (18432, 2), (1365, 3),
+                                 (1366, 3), (2731, 3), (5, 4)])
+def test_read_short_walks(fl, ctx, orc, n, L):
+    test_read_walk_rows(fl, ctx, orc, n, L)
