@@ -335,10 +335,11 @@ felog_status felog_graph_load_csr(felog_ctx* ctx, int32_t n_nodes, int64_t nnz,
         FELOG_REQUIRE(indptr[0] == 0, "indptr[0] must be 0 (got %lld)", (long long)indptr[0]);
         FELOG_REQUIRE(indptr[n_nodes] == nnz, "indptr[n] = %lld differs from nnz = %lld",
                       (long long)indptr[n_nodes], (long long)nnz);
-        int64_t isolated = 0;
+        int64_t isolated = 0, longest = 0;
         for (int32_t v = 0; v < n_nodes; ++v) {
             FELOG_REQUIRE(indptr[v + 1] >= indptr[v], "indptr decreases at row %d", v);
             isolated += indptr[v + 1] == indptr[v];
+            longest = std::max(longest, indptr[v + 1] - indptr[v]);
         }
         ctx->make_current();
         auto g = std::make_unique<felog_graph>();
@@ -347,6 +348,7 @@ felog_status felog_graph_load_csr(felog_ctx* ctx, int32_t n_nodes, int64_t nnz,
         g->nnz = nnz;
         g->weighted = weights != nullptr;
         g->isolated = isolated;
+        g->max_degree = longest;
         g->indptr.alloc(ctx, sizeof(int64_t) * (n_nodes + 1));
         g->indices.alloc(ctx, sizeof(int32_t) * std::max<int64_t>(nnz, 1));
         FELOG_HIP(hipMemcpyAsync(g->indptr.ptr, indptr, sizeof(int64_t) * (n_nodes + 1),

@@ -115,6 +115,7 @@ struct Graph {
                       // that a node2vec proposal reads one 8-byte record, not two arrays
     DevBuf wmax;      // float [n]     (max weight of each row; 1 when unweighted)
     int64_t isolated = 0;                // nodes without neighbours
+    int64_t max_degree = 0;              // 0: not known
 };
 
 struct Active {

@@ -182,12 +182,12 @@ __global__ __launch_bounds__(256) void walk_uniform_kernel(
 //   equal degree 2.46 -> 2.42 (their long stretches of the same length leave
 //   lockstep little to lose); p = 0.25, q = 4: 8.1 -> 4.9 and 6.1 -> 5.5;
 //   R-MAT 2^20, deg 16, unweighted, p = 1, q = 2 4.0 -> 3.6.
-// Rounds: five.  With two the 300,007 nodes took 2.68 ms and, p = 1, q = 2, 2.06
-// (lockstep 1.74, five 1.72).  Two where the L2s hold the entries and p < 1 < q:
-// 30,000 nodes of degree 33, weighted, p = 0.5, q = 2 0.90, five 0.96 and lockstep
-// 1.52; p = 0.25, q = 4 2.10, 2.37 and 3.71.
+// Rounds: five beyond the caches (300,007 nodes of equal degree 2.42 ms, two 2.68;
+// R-MAT 2^20, deg 16, p = 1, q = 2 7 % faster than two); two where the indices are
+// small, as the lanes' searches then end together less often than a round trip is
+// long: R-MAT of 59,716 nodes, weighted, p = 0.25 five rounds 18 % (q = 0.5) and 20 %
+// (q = 2) slower, 150,000 nodes of equal degree, 17 MB of indices, up to 20 %.
 // --------------------------------------------------------------------------
-constexpr int64_t kN2vCachedBytes = (int64_t)32 << 20;   // entries that the L2s hold
 constexpr int kN2vProposers = 16;  // 8 to 32 are within 7 %
 
 template <int ROUNDS>
@@ -301,20 +301,24 @@ __global__ __launch_bounds__(256) void walk_node2vec_kernel(
     if (my_capped) atomicAdd(capped, (unsigned long long)my_capped);
 }
 
-// The same walks where q = 1: alpha is 1/p at the previous node and 1 elsewhere,
-// so no attempt needs a search.  The lanes keep to the same transition, A
-// attempts in flight, and a step's walks are written as one row (lanes at
-// transitions of their own write a line each).  40 steps from every node, ms,
-// with the kernel above and this one: 300,007 nodes of degree 29, weighted,
-// p = 1 0.79 and 0.54, p = 0.25 1.86 and 1.08; R-MAT 2^20, deg 16, p = 0.25 2.81
-// and 2.17.
-template <int A>
-__global__ __launch_bounds__(256) void walk_node2vec_q1_kernel(
+// The same walks with the lanes of a wave at the same transition, so that a step's
+// walks are written as one row (lanes at transitions of their own write a line
+// each), with A attempts in flight.  Without SEARCH, for q = 1: alpha is 1/p at the
+// previous node and 1 elsewhere, and no attempt is undecided.  With SEARCH, for rows
+// of like length far beyond the caches, where few searches outlast the others and
+// the lines that are written in parts cost the most.  40 steps from every node, ms,
+// with the kernel above and this one: q = 1, 300,007 nodes of degree 29, weighted,
+// p = 1 0.74 and 0.48, p = 0.25 1.80 and 0.96; R-MAT 2^20, deg 16, p = 0.25 2.49 and
+// 1.83.  10^6 nodes of equal degree 16, p = 1, q = 4 11.0 and 6.5, weighted 11.5 and
+// 7.7.
+template <int A, bool SEARCH>
+__global__ __launch_bounds__(256) void walk_node2vec_rows_kernel(
     const int64_t* __restrict__ indptr, const int32_t* __restrict__ indices,
     const int2* __restrict__ edges, const float* __restrict__ wmax,
     const int32_t* __restrict__ starts, int64_t n_starts, int64_t W, int64_t col0,
-    int64_t col_end, int32_t L, float inv_p, float amax, uint32_t max_attempts, uint64_t seed,
-    int64_t id_base, int32_t* __restrict__ walks, unsigned long long* __restrict__ capped)
+    int64_t col_end, int32_t L, float inv_p, float inv_q, float amax, uint32_t max_attempts,
+    uint64_t seed, int64_t id_base, int32_t* __restrict__ walks,
+    unsigned long long* __restrict__ capped)
 {
     const int64_t col = col0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (col >= col_end) return;
@@ -323,7 +327,10 @@ __global__ __launch_bounds__(256) void walk_node2vec_q1_kernel(
     const int64_t wid = id_base + col;
     walks[col] = v;
     uint32_t my_capped = 0;
+    const float a_hi = fmaxf(1.0f, inv_q), a_lo = fminf(1.0f, inv_q);
     int32_t t = 0, prev = -1;
+    int64_t plo = 0;                  // the previous node's row
+    uint32_t pdeg = 0;
     for (; t + 1 < L; ++t) {
         const int64_t lo = indptr[v];
         const uint32_t deg = (uint32_t)(indptr[v + 1] - lo);
@@ -348,12 +355,37 @@ __global__ __launch_bounds__(256) void walk_node2vec_q1_kernel(
                 }
                 lhs[k] = __fmul_rn((float)(r.v[1] >> 8) * (1.0f / 16777216.0f), bound);
             }
+            bool undecided = false, found = false;   // an undecided attempt, and its end
+            if constexpr (SEARCH) {
+                static_assert(A == 1, "one search at a time");
+                undecided = t > 0 && xs[0] != prev && lhs[0] < __fmul_rn(ws[0], a_hi) &&
+                            !(lhs[0] < __fmul_rn(ws[0], a_lo));
+                if (undecided) {
+                    const int64_t xlo = indptr[xs[0]];
+                    const uint32_t xdeg = (uint32_t)(indptr[xs[0] + 1] - xlo);
+                    const bool in_x = xdeg < pdeg;
+                    const int64_t base = in_x ? xlo : plo;
+                    const int32_t target = in_x ? prev : xs[0];
+                    uint32_t l = 0, h = in_x ? xdeg : pdeg;
+                    bool adj = false;
+                    while (l < h) {
+                        const uint32_t mid = l + ((h - l) >> 1);
+                        const int32_t val = indices[base + mid];
+                        if (val < target) l = mid + 1;
+                        else h = mid;
+                        adj = val == target;
+                        if (adj) break;
+                    }
+                    found = lhs[0] < __fmul_rn(ws[0], adj ? 1.0f : inv_q);
+                }
+            }
             bool accept = false;
 #pragma unroll
             for (int k = 0; k < A; ++k)
                 if (!accept) {
                     x = xs[k];
-                    accept = lhs[k] < (t > 0 && x == prev ? __fmul_rn(ws[k], inv_p) : ws[k]);
+                    const float alpha = t > 0 && x == prev ? inv_p : t > 0 && SEARCH ? a_lo : 1.0f;
+                    accept = undecided ? found : lhs[k] < __fmul_rn(ws[k], alpha);
                 }
             if (accept) break;
             if (attempt + A >= max_attempts) {
@@ -362,6 +394,10 @@ __global__ __launch_bounds__(256) void walk_node2vec_q1_kernel(
             }
         }
         walks[(int64_t)(t + 1) * W + col] = x;
+        if constexpr (SEARCH) {
+            plo = lo;
+            pdeg = deg;
+        }
         prev = v;
         v = x;
     }
@@ -369,11 +405,23 @@ __global__ __launch_bounds__(256) void walk_node2vec_q1_kernel(
     if (my_capped) atomicAdd(capped, (unsigned long long)my_capped);
 }
 
-// Attempts in flight.  Where the L2s hold the entries, a wasted read costs little and a round trip is most of the time: four (30,000 nodes of degree
-// 33, weighted, p = 0.25 0.36 ms, two 0.48; p = 1 0.16 and 0.19).  Beyond, the reads
-// count: two, or one where no weight and no 1/p > 1 rejects the most (300,007 nodes,
-// weighted, p = 0.25 1.08 with two and 1.08 with four, R-MAT 2^20 2.17 and 2.63;
-// p = 1 0.54 with one, 0.63 with two).  One where nothing but a return is rejected.
+// Which kernel, by the indices' (the searches') and the entries' (the proposals')
+// bytes; times relative to the other choice, 40 steps from every node, five p by
+// five q.
+// q = 1: one attempt at a time beyond 16 MB of entries, where wasted reads cost the
+// most (15 to 128 MB, R-MAT and equal degrees: two 0.93 to 1.22 times the time of
+// one).  Below, a round trip is most of the time: four where a weight or p < 0.5
+// rejects many (12 MB, weighted: two 1.21 to 1.48 times the time of four), else two
+// (6 MB, p >= 0.5: four 1.05 to 1.84 times the time of two).
+// Else lanes at their own transitions, except on rows of like length (none longer
+// than eight times the mean) of more than 48 MB of indices, or 24 MB where neither
+// weights nor p < 1 reject: 61 to 66 MB five rounds 0.91 to 1.66 times the time of
+// rows; 33 MB 1.04 to 1.29 there, q > 1 and weights or p < 1 0.82 to 1.00; R-MAT 2^20
+// (rows of every length), q > 1 and weights or p < 1 0.72 to 0.99.
+// Rounds above: 24 MB lies between 17 MB, where five lose, and 33 MB, where two do.
+constexpr int64_t kN2vEntryBytes = (int64_t)16 << 20, kN2vIndexBytes = (int64_t)24 << 20;
+constexpr int64_t kN2vRowsBytes = (int64_t)48 << 20;
+
 void launch_walk_columns(Walks& w, const felog_walk_params& p, const Active* starts,
                          int64_t n_starts, int64_t col0, int64_t ncols, hipStream_t s,
                          unsigned long long* d_capped)
@@ -392,23 +440,28 @@ void launch_walk_columns(Walks& w, const felog_walk_params& p, const Active* sta
         float inv_p = 1.0f / p.p, inv_q = 1.0f / p.q;
         float amax = fmaxf(1.0f, fmaxf(inv_p, inv_q));
         constexpr uint32_t max_attempts = 1u << 16;
-        const bool cached = g.nnz * (g.weighted ? 8 : 4) <= kN2vCachedBytes;
-        auto launch = [&](auto kernel, auto... alphas) {
+        const int64_t index_bytes = g.nnz * 4, entry_bytes = g.nnz * (g.weighted ? 8 : 4);
+        const bool like_rows = g.max_degree > 0 && g.max_degree <= 8 * (g.nnz / g.n + 1);
+        const bool few_rejected = !g.weighted && p.p >= 1.0f;
+        auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, g.indptr.as<int64_t>(),
                                g.indices.as<int32_t>(), g.weighted ? g.edges.as<int2>() : nullptr,
                                g.wmax.as<float>(), st, n_starts, w.W, col0, col0 + ncols, w.L,
-                               alphas..., amax, max_attempts, p.seed, w.id_base,
+                               inv_p, inv_q, amax, max_attempts, p.seed, w.id_base,
                                w.data.as<int32_t>(), d_capped);
         };
-        if (inv_q != 1.0f) {
-            if (cached && p.p < 1.0f && p.q > 1.0f) launch(walk_node2vec_kernel<2>, inv_p, inv_q);
-            else launch(walk_node2vec_kernel<5>, inv_p, inv_q);
-        } else if (amax == 1.0f && !(cached && g.weighted)) {
-            launch(walk_node2vec_q1_kernel<1>, inv_p);
-        } else if (!cached) {
-            launch(walk_node2vec_q1_kernel<2>, inv_p);
+        if (inv_q == 1.0f) {
+            if (entry_bytes > kN2vEntryBytes)
+                launch(walk_node2vec_rows_kernel<1, false>);
+            else if (g.weighted || amax > 2.0f)
+                launch(walk_node2vec_rows_kernel<4, false>);
+            else launch(walk_node2vec_rows_kernel<2, false>);
+        } else if (index_bytes <= kN2vIndexBytes) {
+            launch(walk_node2vec_kernel<2>);
+        } else if (like_rows && (index_bytes > kN2vRowsBytes || few_rejected)) {
+            launch(walk_node2vec_rows_kernel<1, true>);
         } else {
-            launch(walk_node2vec_q1_kernel<4>, inv_p);
+            launch(walk_node2vec_kernel<5>);
         }
     }
     FELOG_HIP(hipGetLastError());

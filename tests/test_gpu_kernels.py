@@ -355,7 +355,7 @@ def test_empty_noise_table_is_refused(fl, ctx):
 
 
 # q = 1 (no searches): one, two and four attempts in flight, by weights, p and
-# whether the entries pass 32 MB; walks that end at once, leaves whose only
+# whether the entries pass 16 MB; walks that end at once, leaves whose only
 # neighbour is the previous node, transitions that end at the cap
 @pytest.mark.parametrize("n,m,p,weighted", [
     (65, 200, 0.25, False), (65, 200, 0.25, True), (500, 3000, 1.0, False),
@@ -371,6 +371,35 @@ def test_node2vec_without_searches(fl, ctx, orc, n, m, p, weighted):
     W = fl.Walks.generate(G, r=3, L=17, seed=11, id_base=5, kind=fl.WALK_NODE2VEC, p=p, q=1.0,
                           starts=fl.Active.from_host(G, starts))
     want, capped = orc.walks_node2vec(g, starts, 3, 17, p, 1.0, 11, 5)
+    assert np.array_equal(W.read(), want)
+    assert W.capped() == capped and (capped > 0) == (p == 1e6)
+
+
+# q other than 1 beyond 24 MB of indices: rows of like length walked in step (above
+# 48 MB, or without weights and p >= 1), a hub or p < 1 that keep lanes at their own
+# transitions; leaves, where a transition ends at the cap
+@pytest.mark.parametrize("n,m,p,q,weighted,hub", [
+    (200000, 3300000, 1.0, 2.0, False, False), (200000, 3300000, 2.0, 1.5, False, True),
+    (200000, 3300000, 0.5, 4.0, False, False), (200000, 3300000, 1.0, 0.5, False, False),
+    (400000, 6600000, 0.5, 4.0, True, False), (400000, 6600000, 1e6, 2.0, False, False)])
+def test_node2vec_beyond_the_caches(fl, ctx, orc, n, m, p, q, weighted, hub):
+    rng = np.random.default_rng(m)
+    k = n - n // 8                       # the last eighth: leaves, every other one isolated
+    e = np.sort(rng.integers(0, k, (m, 2)), axis=1)
+    e = e[e[:, 0] != e[:, 1]]
+    if hub:
+        e = np.concatenate([e, np.stack([np.zeros(400, np.int64), np.arange(1, 401)], 1)])
+    leaf = np.arange(k, n, 2, dtype=np.int64)
+    e = np.concatenate([e, np.stack([leaf - k, leaf], 1)])
+    key = np.unique(e[:, 0] * n + e[:, 1])
+    e = np.stack([key // n, key % n], 1)
+    g = synth.csr_from_edges(n, e, *([synth.edge_weights(e.shape[0], 3)] if weighted else []))
+    assert g.indices.shape[0] * 4 > (24 if n == 200000 else 48) << 20
+    G = fl.Graph.from_csr(ctx, g.indptr, g.indices, *([g.weights] if weighted else []))
+    starts = np.arange(0, n, n // 700, dtype=np.int32)
+    W = fl.Walks.generate(G, r=2, L=21, seed=11, id_base=5, kind=fl.WALK_NODE2VEC, p=p, q=q,
+                          starts=fl.Active.from_host(G, starts))
+    want, capped = orc.walks_node2vec(g, starts, 2, 21, p, q, 11, 5)
     assert np.array_equal(W.read(), want)
     assert W.capped() == capped and (capped > 0) == (p == 1e6)
 
